@@ -22,8 +22,7 @@
 //     workgroup), so that an iteration reads one descriptor instead of walking tiles in scalar code.
 //   Tiles not in the block index are never touched, key quarters of a tile without a kept entry are
 //     never loaded, and full tiles skip the element mask.
-// fp32 kernel (the 1e-4 variant): plain ALU code, one query row per group of head_dim/4 lanes,
-// iterating only over the set bits of the row's tile words.
+// fp32 kernel (the 1e-4 variant): v_mfma_f32_16x16x4_f32, 16 query rows per workgroup, blocks of 16 keys.
 #include <hip/hip_bf16.h>
 #include <math.h>
 
@@ -49,111 +48,268 @@ struct AttnArgs {
   int64_t q_sb, q_sh, q_ss, k_sb, k_sh, k_ss, v_sb, v_sh, v_ss, o_sb, o_sh, o_ss;
 };
 
-// Work numbering shared by both kernels. Block n runs on XCD n % 8. All query heads of one
-// (batch, KV head) pair get ids on one XCD so that they share that XCD's L2 copy of K / V;
-// within a pair the query tiles go last-first (the longest rows of the causal triangle first).
-struct WorkItem {
-  int b, hq, hkv, qt;
-  bool valid;
-};
-
-__device__ __forceinline__ WorkItem decode_work(const AttnArgs &a, int n) {
-  const int G = a.Hq / a.Hkv;
-  const int per_pair = G * a.nQt;
-  const int xcd = n % kXcd, slot = n / kXcd;
-  const int pair = (slot / per_pair) * kXcd + xcd;
-  const int within = slot % per_pair;
-  WorkItem w;
-  w.valid = pair < a.B * a.Hkv;
-  w.b = pair / a.Hkv;
-  w.hkv = pair % a.Hkv;
-  w.qt = a.nQt - 1 - within / G;
-  w.hq = w.hkv * G + within % G;
-  return w;
-}
-
-inline int work_blocks(const AttnArgs &a) {
-  const int n_pairs = a.B * a.Hkv;
-  return (n_pairs + kXcd - 1) / kXcd * kXcd * (a.Hq / a.Hkv) * a.nQt;
-}
-
 // ================================================================================================
-// fp32 variant
-template <int D>
-__global__ __launch_bounds__(256) void k_prefill_f32(AttnArgs a, const float *__restrict__ q,
-                                                     const float *__restrict__ k,
-                                                     const float *__restrict__ v,
-                                                     const int *__restrict__ row_ptr,
-                                                     const int *__restrict__ blk_col,
-                                                     const uint8_t *__restrict__ blk_kind,
-                                                     const uint64_t *__restrict__ tile_bits,
-                                                     const int *__restrict__ gather_idx,
-                                                     float *__restrict__ out, float *__restrict__ lse) {
-  constexpr int N = 4, LPR = D / N, GROUPS = 256 / LPR;
-  // a workgroup takes GROUPS rows of a query tile at a time; blockIdx.y spreads a tile's passes over workgroups
-  // (a row's keys are folded in one after the other: the more rows in flight, the better)
-  const WorkItem w = decode_work(a, blockIdx.x);
-  if (!w.valid) return;
-  const int group = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-  const int t0 = row_ptr[(int64_t)w.hq * (a.nQt + 1) + w.qt];
-  const int t1 = row_ptr[(int64_t)w.hq * (a.nQt + 1) + w.qt + 1];
-  const float *kb = k + w.b * a.k_sb + w.hkv * a.k_sh + sub * N;
-  const float *vb = v + w.b * a.v_sb + w.hkv * a.v_sh + sub * N;
-  for (int rl = blockIdx.y * GROUPS + group; rl < a.tile_m; rl += GROUPS * gridDim.y) {
-    const int i = w.qt * a.tile_m + rl;
-    if (i >= a.S) break;
-    const float4 qv = *reinterpret_cast<const float4 *>(q + w.b * a.q_sb + w.hq * a.q_sh + i * a.q_ss + sub * N);
-    float m = -INFINITY, l = 0.0f;
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int t = t0; t < t1; ++t) {
-      // (a column or a key outside its range, from a list that was never filled, is pulled inside it)
-      const int col = min(max(blk_col[t], 0), a.nKt + (gather_idx ? a.gather_stride / a.tile_n : 0) - 1);
-      // a gathered tile (index >= nKt): slot s of the tile stands for the head's matched column gcols[s]
-      const int *gcols = col >= a.nKt ? gather_idx + (int64_t)w.hq * a.gather_stride + (col - a.nKt) * a.tile_n : nullptr;
-      const int j0 = col * a.tile_n;
-      const bool full = blk_kind[t] & 1;  // every entry kept: the tile's words are not read (they may be unwritten)
-      for (int wd = 0; wd < a.wpr; ++wd) {
-        uint64_t bits = full ? ~0ull : tile_bits[((int64_t)t * a.tile_m + rl) * a.wpr + wd];
-        while (bits) {
-          // the rows of up to four kept keys are fetched together (their addresses depend on the bits, so nothing
-          // else hides the latency), then folded into the running softmax one after the other, in key order
-          constexpr int U = 4;
-          float4 kv[U], vv[U];
-          bool have[U];
+// fp32 variant, on v_mfma_f32_16x16x4_f32 (fp32 products and sums: the matrix instruction rounds like a chain of
+// fused multiply-adds).
+//
+// A workgroup takes 16 query rows of a query tile; its four waves share the rows' occupied blocks of 16 keys and are
+// merged through LDS at the end. Sixteen rows, not the whole tile, because a row's keys form one dependent chain and
+// the fp32 problems are small: 16-row groups times four waves are what fills 256 CUs (2 x 8 heads of 1500 rows are
+// 1504 groups), and a 16 x 16 block is the finest square the mask can be skipped at.
+// Both products keep a lane on one query (lane % 16): S^T = K Q^T leaves key 4 (lane / 16) + r in accumulator r, and
+// that is the B operand of step r of O^T += V^T P^T when the lanes of group g fetch V row 4 g + r, so P stays in
+// registers. The dims are dealt out so that every operand is a 16-byte load straight from memory in the product's
+// layout: K and Q lane (row, g) holds dims 16 c + 4 g .. + 3 of chunk c, V lane m dims 64 h + 4 m .. + 3. The V rows of
+// a block are fetched before its Q K products, the K rows of the next one too.
+// Bound by the fp32 matrix rate (64 flop per cycle and SIMD) on the occupied blocks and, for short rows, by the
+// latency of the first loads. 2 sequences x 8 heads x 1500 keys, d 128: 415 -> 74 us against a row per d / 4 plain lanes
+// (Q in LDS for a third workgroup per CU spilled: 154 us).
+constexpr int kF32Seg = 64;  // listed tiles expanded at a time
+
+// GATHER: the block index may hold gathered column tiles, whose key rows are looked up in gather_idx. (A template
+// argument, because the look-up in front of every row's address makes the loads of a block wait for each other.)
+template <int D, bool GATHER>
+__global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float *__restrict__ q, const float *__restrict__ k,
+                                                        const float *__restrict__ v, const int *__restrict__ row_ptr,
+                                                        const int *__restrict__ blk_col, const uint8_t *__restrict__ blk_kind,
+                                                        const uint64_t *__restrict__ tile_bits,
+                                                        const int *__restrict__ gather_idx, float *__restrict__ out,
+                                                        float *__restrict__ lse) {
+  constexpr int CK = D / 16, HV = D / 64, kPad = D + 4;  // (rows of the merge area padded: 16 rows, 16 different banks)
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  // one LDS area, two lives: mask words, columns and block list of a segment of tiles; then the waves' partial results
+  struct Lists {
+    unsigned words[kF32Seg][64];  // [tile][32-key word g * 16 + row]
+    int col[kF32Seg];
+    unsigned char occ[kF32Seg];   // bit kb: block kb of the tile holds a kept entry of these rows
+    unsigned short blk[kF32Seg * 8];
+  };
+  struct Parts {
+    float o[4][16 * kPad];
+    float m[4][16], l[4][16];
+  };
+  constexpr size_t kLds = sizeof(Lists) > sizeof(Parts) ? sizeof(Lists) : sizeof(Parts);
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  Lists &L = *reinterpret_cast<Lists *>(lds);
+  Parts &P = *reinterpret_cast<Parts *>(lds);
+
+  // Numbering: workgroup n runs on XCD n % 8, and the longest rows of the causal triangle go first. Where the
+  // (sequence, KV head) pairs divide evenly among the XCDs, the row groups of a pair stay on one of them and share
+  // its L2 copy of K and V; otherwise (two heads: 6 of 8 XCDs would stay empty) they go round robin.
+  const int G = a.Hq / a.Hkv, n_pairs = a.B * a.Hkv, RG = a.tile_m / 16, per_pair = G * a.nQt * RG;
+  const bool even = n_pairs % kXcd == 0;
+  const int within = even ? blockIdx.x / kXcd % per_pair : blockIdx.x / n_pairs;
+  const int pair = even ? blockIdx.x / kXcd / per_pair * kXcd + blockIdx.x % kXcd : blockIdx.x % n_pairs;
+  const int wb = pair / a.Hkv, whkv = pair % a.Hkv, whq = whkv * G + within % G;
+  const int wqt = a.nQt - 1 - within / (G * RG), rg = RG - 1 - within / G % RG, row0 = wqt * a.tile_m + rg * 16;
+  if (row0 >= a.S) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int i = row0 + r16;
+  const bool live = i < a.S;
+  const int t0 = row_ptr[(int64_t)whq * (a.nQt + 1) + wqt];
+  const int t1 = row_ptr[(int64_t)whq * (a.nQt + 1) + wqt + 1];
+  const float *kb = k + wb * a.k_sb + whkv * a.k_sh + 4 * g;
+  const float *vb = v + wb * a.v_sb + whkv * a.v_sh;
+
+  float4 qf[CK];
+  {
+    const float *qp = q + wb * a.q_sb + whq * a.q_sh + (int64_t)min(i, a.S - 1) * a.q_ss + 4 * g;
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            have[u] = bits != 0;
-            const int slot = wd * 64 + (have[u] ? __ffsll((unsigned long long)bits) - 1 : 0);
-            const int j = min(max(gcols ? gcols[slot] : j0 + slot, 0), a.S - 1);
-            bits &= bits - 1;  // (0 stays 0)
-            kv[u] = *reinterpret_cast<const float4 *>(kb + j * a.k_ss);
-            vv[u] = *reinterpret_cast<const float4 *>(vb + j * a.v_ss);
-          }
+    for (int c = 0; c < CK; ++c) qf[c] = *reinterpret_cast<const float4 *>(qp + 16 * c);
+  }
+  f32x4 o[HV * 4];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (!have[u]) break;  // uniform over the lanes of a row
-            float d = qv.x * kv[u].x + qv.y * kv[u].y + qv.z * kv[u].z + qv.w * kv[u].w;
+  for (int x = 0; x < HV * 4; ++x) o[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.0f;  // of the lane's row; l is this lane's part
+
+  for (int seg = t0; seg < t1; seg += kF32Seg) {
+    const int n_seg = min(kF32Seg, t1 - seg);
+    if (seg > t0) __syncthreads();  // every wave is done with the previous segment's lists
+    // ---- the rows' mask words of every listed tile, and which blocks of 16 keys they occupy
+    const int kinds = lane < n_seg ? blk_kind[seg + lane] : 0;
+    // (a column outside its range, from a list that was never filled, is pulled inside it)
+    if (wave == 0 && lane < n_seg)
+      L.col[lane] = min(max(blk_col[seg + lane], 0), a.nKt + (GATHER ? a.gather_stride / a.tile_n : 0) - 1);
+    for (int x0 = wave; x0 < n_seg; x0 += 16) {  // four tiles' words in flight per wave
+      unsigned word[4];
 #pragma unroll
-            for (int off = LPR / 2; off; off >>= 1) d += __shfl_xor(d, off);
-            const float s = d * a.scale;
-            const float mn = fmaxf(m, s);
-            const float corr = expf(m - mn), p = expf(s - mn);
-            l = l * corr + p;
-            o.x = o.x * corr + p * vv[u].x;
-            o.y = o.y * corr + p * vv[u].y;
-            o.z = o.z * corr + p * vv[u].z;
-            o.w = o.w * corr + p * vv[u].w;
-            m = mn;
-          }
+      for (int u = 0; u < 4; ++u) {
+        const int t = seg + min(x0 + 4 * u, n_seg - 1);
+        word[u] = reinterpret_cast<const unsigned *>(tile_bits)[((int64_t)t * a.tile_m + rg * 16 + r16) * (2 * a.wpr) +
+                                                                min(g, 2 * a.wpr - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int x = x0 + 4 * u;
+        if (x >= n_seg) break;
+        if (__builtin_amdgcn_readlane(kinds, x) & 1)  // every entry kept: the words do not count (they may be unwritten)
+          word[u] = ~0u;
+        if (!live || g >= 2 * a.wpr) word[u] = 0u;
+        L.words[x][lane] = word[u];
+        const uint64_t lo = __ballot((word[u] & 0xFFFFu) != 0), hi = __ballot((word[u] >> 16) != 0);
+        if (lane == 0) {
+          unsigned occ = 0;
+          for (int y = 0; y < 4; ++y)
+            occ |= ((lo >> (16 * y)) & 0xFFFF ? 1u << (2 * y) : 0u) | ((hi >> (16 * y)) & 0xFFFF ? 2u << (2 * y) : 0u);
+          L.occ[x] = (unsigned char)occ;
         }
       }
     }
-    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    *reinterpret_cast<float4 *>(out + w.b * a.o_sb + w.hq * a.o_sh + i * a.o_ss + sub * N) =
-        make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
-    if (lse && sub == 0)
-      lse[((int64_t)w.b * a.Hq + w.hq) * a.S + i] = l > 0.0f ? m + logf(l) : -INFINITY;
+    __syncthreads();
+    // ---- the block list: every wave adds up the same prefix, wave 0 writes
+    unsigned occ = lane < n_seg ? L.occ[lane] : 0u;
+    int at = __popc(occ);
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(at, off);
+      if (lane >= off) at += up;
+    }
+    const int n_blk = __builtin_amdgcn_readlane(at, 63);
+    if (wave == 0)
+      for (at -= __popc(occ); occ; occ &= occ - 1) L.blk[at++] = (unsigned short)(lane * 8 + __builtin_ctz(occ));
+    __syncthreads();
+
+    // row of K and V that slot s of tile x stands for
+    auto key_row = [&](int x, int s) -> int64_t {
+      const int col = __builtin_amdgcn_readfirstlane(L.col[x]);
+      int j = col * a.tile_n + s;
+      if (GATHER) {  // a gathered tile (index >= nKt): its slots are the head's matched columns
+        const int c = gather_idx[(int64_t)whq * a.gather_stride + max(col - a.nKt, 0) * a.tile_n + s];
+        if (col >= a.nKt) j = c;
+      }
+      return min(max(j, 0), a.S - 1);
+    };
+    auto load_k = [&](float4 (&kf)[CK], int e) {  // lane's row of the block: r16, dims 16 c + 4 g
+      const int blk = __builtin_amdgcn_readfirstlane(L.blk[e]);
+      const float *kp = kb + key_row(blk >> 3, (blk & 7) * 16 + r16) * a.k_ss;
+#pragma unroll
+      for (int c = 0; c < CK; ++c) kf[c] = *reinterpret_cast<const float4 *>(kp + 16 * c);
+    };
+    auto compute = [&](const float4 (&kf)[CK], float4 (&k_next)[CK], int e) {
+      const int blk = __builtin_amdgcn_readfirstlane(L.blk[e]), x = blk >> 3, b16 = blk & 7;
+      float4 vf[4][HV];  // V row 4 g + s, dims 64 h + 4 r16
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float *vp = vb + key_row(x, b16 * 16 + 4 * g + s) * a.v_ss + 4 * r16;
+#pragma unroll
+        for (int h = 0; h < HV; ++h) vf[s][h] = *reinterpret_cast<const float4 *>(vp + 64 * h);
+      }
+      if (e + 4 < n_blk) load_k(k_next, e + 4);
+      const unsigned kept = L.words[x][(b16 >> 1) * 16 + r16] >> (16 * (b16 & 1));  // low 16 bits: the block's keys
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: a product's result is ready only after the next has started
+#pragma unroll
+      for (int c = 0; c < CK; ++c) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].x, qf[c].x, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].y, qf[c].y, s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].z, qf[c].z, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].w, qf[c].w, s1, 0, 0, 0);
+      }
+      float p[4], mx = m, odd = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[r] = (kept >> (4 * g + r)) & 1 ? (s0[r] + s1[r]) * a.scale : -INFINITY;
+        mx = fmaxf(mx, p[r]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      if (__ballot(mx > m)) {
+        const float corr = mx > m ? expf(m - mx) : 1.0f;  // m = -inf: 0
+        l *= corr;
+#pragma unroll
+        for (int y = 0; y < HV * 4; ++y) o[y] *= corr;
+        m = fmaxf(m, mx);
+      }
+      const float ref = m == -INFINITY ? 0.0f : m;  // (no key of the row so far)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[r] = expf(p[r] - ref);
+        l += p[r];
+#pragma unroll
+        for (int h = 0; h < HV; ++h) {  // 0, or NaN where a V entry is infinite or NaN
+          odd = fmaf(vf[r][h].x, 0.0f, fmaf(vf[r][h].y, 0.0f, odd));
+          odd = fmaf(vf[r][h].z, 0.0f, fmaf(vf[r][h].w, 0.0f, odd));
+        }
+      }
+      if (__ballot(odd != 0.0f) == 0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int h = 0; h < HV; ++h) {
+            o[4 * h + 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].x, p[s], o[4 * h + 0], 0, 0, 0);
+            o[4 * h + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].y, p[s], o[4 * h + 1], 0, 0, 0);
+            o[4 * h + 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].z, p[s], o[4 * h + 2], 0, 0, 0);
+            o[4 * h + 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].w, p[s], o[4 * h + 3], 0, 0, 0);
+          }
+      } else {
+        // a V row of the block holds an infinity or a NaN: it must reach the rows that keep that key and no others
+        // (a product would multiply it with the others' zero weights), so the kept entries are added one by one
+#pragma unroll 1
+        for (int key = 0; key < 16; ++key) {
+          const float pk = __shfl(key & 2 ? (key & 1 ? p[3] : p[2]) : (key & 1 ? p[1] : p[0]), r16 + 16 * (key >> 2));
+          const float *vp = vb + key_row(x, b16 * 16 + key) * a.v_ss + 16 * g;
+          if (!((kept >> key) & 1)) continue;
+#pragma unroll
+          for (int h = 0; h < HV; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float4 vv = *reinterpret_cast<const float4 *>(vp + 64 * h + 4 * r);
+              o[4 * h + 0][r] = fmaf(pk, vv.x, o[4 * h + 0][r]);
+              o[4 * h + 1][r] = fmaf(pk, vv.y, o[4 * h + 1][r]);
+              o[4 * h + 2][r] = fmaf(pk, vv.z, o[4 * h + 2][r]);
+              o[4 * h + 3][r] = fmaf(pk, vv.w, o[4 * h + 3][r]);
+            }
+        }
+      }
+    };
+    float4 ka[CK], kc[CK];
+    int e = wave;
+    if (e < n_blk) load_k(ka, e);
+    for (; e < n_blk; e += 8) {
+      compute(ka, kc, e);
+      if (e + 4 >= n_blk) break;
+      compute(kc, ka, e + 4);
+    }
   }
+
+  // ---- merge the four waves. Accumulator r of o[4 h + x] is dim 64 h + 16 g + 4 r + x of the lane's row.
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  __syncthreads();  // the lists are done with
+  if (g == 0) {
+    P.m[wave][r16] = m;
+    P.l[wave][r16] = l;
+  }
+#pragma unroll
+  for (int h = 0; h < HV; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *reinterpret_cast<float4 *>(&P.o[wave][r16 * kPad + 64 * h + 16 * g + 4 * r]) =
+          make_float4(o[4 * h][r], o[4 * h + 1][r], o[4 * h + 2][r], o[4 * h + 3][r]);
+  __syncthreads();
+  const int row = threadIdx.x >> 4, part = threadIdx.x & 15;
+  if (row0 + row >= a.S) return;
+  float M = fmaxf(fmaxf(P.m[0][row], P.m[1][row]), fmaxf(P.m[2][row], P.m[3][row])), sum = 0.0f, wt[4];
+#pragma unroll
+  for (int y = 0; y < 4; ++y) {
+    wt[y] = P.m[y][row] > -INFINITY ? expf(P.m[y][row] - M) : 0.0f;  // (a wave that met no key of the row)
+    sum += wt[y] * P.l[y][row];
+  }
+  const float inv = sum > 0.0f ? 1.0f / sum : sum * 0.0f;  // (no key: 0; NaN stays NaN)
+#pragma unroll
+  for (int h = 0; h < HV; ++h) {
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const float4 x = *reinterpret_cast<const float4 *>(&P.o[y][row * kPad + 64 * h + 4 * part]);
+      acc.x = fmaf(wt[y], x.x, acc.x);
+      acc.y = fmaf(wt[y], x.y, acc.y);
+      acc.z = fmaf(wt[y], x.z, acc.z);
+      acc.w = fmaf(wt[y], x.w, acc.w);
+    }
+    *reinterpret_cast<float4 *>(out + wb * a.o_sb + whq * a.o_sh + (int64_t)(row0 + row) * a.o_ss + 64 * h + 4 * part) =
+        make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+  }
+  if (lse && part == 0) lse[((int64_t)wb * a.Hq + whq) * a.S + row0 + row] = sum > 0.0f ? M + logf(sum) : -INFINITY;
 }
 
 // ================================================================================================
@@ -910,19 +1066,14 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
     a.gather_rows = p->gather_rows;
     a.gather_stride = mk->gather_stride;
   }
-  const int blocks = work_blocks(a);
   if (p->dtype == DAM_F32) {
-    // (passes of a query tile as separate workgroups while the launch stays small)
-    const int rows_per_pass = 256 / (p->head_dim / 4), passes = (p->tile_m + rows_per_pass - 1) / rows_per_pass;
-    const int spread = blocks * passes <= 16384 ? passes : 1;
-    if (p->head_dim == 64)
-      k_prefill_f32<64><<<dim3(blocks, spread), 256, 0, st>>>(a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr,
-                                               mk->blk_col, mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
-    else
-      k_prefill_f32<128><<<dim3(blocks, spread), 256, 0, st>>>(a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr,
-                                                mk->blk_col, mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
+    auto kern = mk->gather_idx ? (p->head_dim == 64 ? k_prefill_f32<64, true> : k_prefill_f32<128, true>)
+                               : (p->head_dim == 64 ? k_prefill_f32<64, false> : k_prefill_f32<128, false>);
+    kern<<<p->batch * p->hq * a.nQt * (p->tile_m / 16), 256, 0, st>>>(a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr, mk->blk_col,
+                                                    mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
     return launch_status();
   }
+  const int blocks = (p->batch * p->hkv + kXcd - 1) / kXcd * kXcd * (p->hq / p->hkv) * a.nQt;  // an upper bound of the work items
   // (queried per call: the library keeps no state, and the device may differ from call to call)
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||

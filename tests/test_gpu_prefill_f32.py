@@ -1,0 +1,57 @@
+"""The fp32 prefill kernel at the sizes where its tiling can go wrong: 16-row groups, blocks of 16 keys shared by four
+waves, 64 listed tiles per segment, work numbering with and without a whole number of heads per XCD.
+Tolerance: sums of at most S products of O(1) values in fp32 against the fp64 oracle, S 2^-24 times a few: 2e-5."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_11104_amd import binding as B
+from test_gpu_prefill import gpu_mask_from_art
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-5
+
+
+def inputs(Hq, Hkv, S, d, seed):
+    rng = np.random.default_rng(seed)
+    Q, K, V = (rng.standard_normal((h, S, d)).astype(np.float32) for h in (Hq, Hkv, Hkv))
+    dflag, vflag = np.zeros((Hq, S), np.uint8), np.zeros((Hq, S), np.uint8)
+    dflag[0] = 1                                    # dense causal
+    for h in range(1, Hq):
+        dflag[h, : 1 + 7 * h % max(1, S)] = 1
+        vflag[h, :: 19 + h] = 1
+    return Q, K, V, oracle.from_patterns(dflag, vflag)
+
+
+def run(Q, K, V, mask):
+    t = lambda x: torch.from_numpy(x)[None].cuda()
+    out, lse = B.dam_sparse_attn_prefill(t(Q), t(K), t(V), mask, want_lse=True)
+    return out[0].cpu().numpy(), lse[0].cpu().numpy()
+
+
+@pytest.mark.parametrize("Hq,Hkv,S,d,tile,flags", [
+    (2, 1, 1, 64, 64, 0), (2, 2, 15, 128, 128, 0), (4, 2, 17, 64, 128, 0), (2, 1, 65, 128, 64, 0),
+    (8, 8, 130, 64, 64, 0), (16, 8, 259, 128, 128, B.DAM_MASK_GATHER_COLUMNS), (3, 3, 640, 64, 64, B.DAM_MASK_GATHER_COLUMNS),
+    (1, 1, 64 * 66 + 5, 64, 64, 0),                 # more listed tiles in a row than one segment holds
+])
+def test_edges_of_groups_blocks_and_segments(Hq, Hkv, S, d, tile, flags):
+    Q, K, V, art = inputs(Hq, Hkv, S, d, 7 + S)
+    mask = gpu_mask_from_art(art, S, tile, tile, flags=flags | B.DAM_MASK_SKIP_FULL_TILE_BITS)
+    out, lse = run(Q, K, V, mask)
+    O, LSE = oracle.attend_prefill(Q, K, V, art)
+    assert np.abs(out - O).max() <= TOL
+    assert np.abs(lse - LSE).max() <= TOL
+
+
+def test_a_row_does_not_see_what_it_does_not_keep():
+    """A NaN and an infinity in V rows reach exactly the query rows that keep those keys."""
+    S, d = 200, 128
+    Q, K, V, art = inputs(2, 1, S, d, 5)
+    V[0, 37, 3], V[0, 101, 70] = np.nan, np.inf
+    out, _ = run(Q, K, V, gpu_mask_from_art(art, S, 64, 64))
+    i = np.arange(S)
+    for h, keeps in ((0, lambda j: i >= j), (1, lambda j: (i >= j) & ((i - j < 8) | (j % 20 == 0)))):
+        assert np.array_equal(np.isnan(out[h, :, 3]), keeps(37))
+        assert np.array_equal(np.isinf(out[h, :, 70]), keeps(101))
+        assert np.isfinite(out[h, :, 5]).all()
