@@ -1,8 +1,9 @@
-"""ctypes binding of libdam.so (the C ABI declared in include/dam.h).
+"""Python binding of libdam.so (the C ABI declared in include/dam.h).
 
 Argument marshalling only: torch supplies device memory and the current HIP stream, every step of
-the path runs in the library's kernels. There is no CPU fallback: if the library has not been
-built, loading raises.
+the path runs in the library's kernels. The calls of a program's inner loops (mask build, prefill,
+decode, capture) go through the extension module _dam_native, the rest through ctypes. There is no
+CPU fallback: if the library or the extension has not been built, loading raises.
 """
 from __future__ import annotations
 
@@ -164,6 +165,23 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The extension module (csrc/py_native.cpp); raises if it has not been built."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _dam_native
+        except ImportError as e:
+            raise RuntimeError("_dam_native is missing: build it with `python paper_2506_11104_amd/build.py` "
+                               "(there is no fallback path)") from e
+        _native = _dam_native
+    return _native
+
+
 def _p(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -173,8 +191,12 @@ def _stream() -> int:
 
 
 def _check(fn: str, st: int):
-    if st != DAM_OK:
-        raise DamError(fn, st)
+    if st == DAM_OK:
+        return
+    if st == -1000:                # codes of _dam_native for what is no status of the library
+        raise DamError("dtype", DAM_ERR_UNSUPPORTED)
+    assert st != -1001, f"{fn}: shapes or strides of the tensors do not fit together"
+    raise DamError(fn, st)
 
 
 # ---------------------------------------------------------------------------------------------
@@ -220,9 +242,9 @@ def mask_workspace(params: MaskParams, device) -> torch.Tensor:
 
 def dam_mask_build(params: MaskParams, attn_sum, attn_cnt, diag_in, vert_in, out: MaskOut, ws: torch.Tensor) -> None:
     """Raw call: enqueues on torch's current stream; raises DamError on a non-zero status."""
-    st = lib().dam_mask_build(ctypes.byref(params), _p(attn_sum), _p(attn_cnt), _p(diag_in), _p(vert_in),
-                              ctypes.byref(out), _p(ws), ws.numel(), _stream())
-    _check("dam_mask_build", st)
+    st = (_native or native()).mask_build(params, attn_sum, attn_cnt, diag_in, vert_in, out, ws)
+    if st:
+        _check("dam_mask_build", st)
 
 
 def capture_params(q: torch.Tensor, k: torch.Tensor, L: int, scale: float = 0.0) -> CaptureParams:
@@ -244,12 +266,12 @@ def capture_workspace(p: CaptureParams, device) -> torch.Tensor:
 def dam_capture_accumulate(q, k, attn_sum, attn_cnt=None, scale: float = 0.0, ws=None) -> None:
     """attn_sum (and attn_cnt) [Hq][L][L] f32 += the causal attention probabilities (the valid pairs)
     of the captured sequence q [Hq][n][d], k [Hkv][n][d]."""
-    p = capture_params(q, k, attn_sum.shape[1], scale)
+    L = attn_sum.shape[1]
     if ws is None:
-        ws = capture_workspace(p, q.device)
-    st = lib().dam_capture_accumulate(ctypes.byref(p), _p(q), _p(k), _p(attn_sum), _p(attn_cnt), _p(ws), ws.numel(),
-                                      _stream())
-    _check("dam_capture_accumulate", st)
+        ws = capture_workspace(capture_params(q, k, L, scale), q.device)
+    st = (_native or native()).capture_accumulate(q, k, attn_sum, attn_cnt, L, scale, ws)
+    if st:
+        _check("dam_capture_accumulate", st)
 
 
 def mask_from_qk_workspace(params: MaskParams, cp: CaptureParams, device) -> torch.Tensor:
@@ -258,9 +280,9 @@ def mask_from_qk_workspace(params: MaskParams, cp: CaptureParams, device) -> tor
 
 
 def dam_mask_build_from_qk(params: MaskParams, cp: CaptureParams, q, k, out: MaskOut, ws: torch.Tensor) -> None:
-    st = lib().dam_mask_build_from_qk(ctypes.byref(params), ctypes.byref(cp), _p(q), _p(k), ctypes.byref(out), _p(ws),
-                                      ws.numel(), _stream())
-    _check("dam_mask_build_from_qk", st)
+    st = (_native or native()).mask_build_from_qk(params, cp, q, k, out, ws)
+    if st:
+        _check("dam_mask_build_from_qk", st)
 
 
 def build_mask(*, mode: int, H: int, L: int, S: int, tile_m: int = 128, tile_n: int = 128, lam: float = 0.5,
@@ -396,13 +418,12 @@ def dam_sparse_attn_prefill(q, k, v, mask: Mask, out=None, lse=None, scale: floa
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
-    p = attn_params(q, k, v, out, mask.tile_m, mask.tile_n, scale, mask.gather_rows, flags)
     if ws is None:
-        ws = prefill_workspace(p, q.device)
-    mv = mask.view()
-    st = lib().dam_sparse_attn_prefill(ctypes.byref(p), _p(q), _p(k), _p(v), ctypes.byref(mv), _p(out), _p(lse),
-                                       _p(ws), ws.numel(), _stream())
-    _check("dam_sparse_attn_prefill", st)
+        ws = prefill_workspace(attn_params(q, k, v, out, mask.tile_m, mask.tile_n, scale, mask.gather_rows, flags), q.device)
+    st = (_native or native()).prefill(q, k, v, mask.blk_row_ptr, mask.blk_col, mask.blk_kind, mask.tile_bits, mask.gather_idx,
+                                       mask.gather_cnt, mask.tile_m, mask.tile_n, mask.gather_rows, flags, scale, out, lse, ws)
+    if st:
+        _check("dam_sparse_attn_prefill", st)
     return (out, lse) if (want_lse or lse is not None) else out
 
 
@@ -432,13 +453,11 @@ def dam_sparse_attn_decode(q, kcache, vcache, kept_ptr, kept_idx, max_kept: int,
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    assert kcache.stride() == vcache.stride()
-    p = decode_params(q, kcache, out, scale, shared_lists)
     if ws is None:
-        ws = decode_workspace(p, max_kept, q.device)
-    st = lib().dam_sparse_attn_decode(ctypes.byref(p), _p(q), _p(kcache), _p(vcache), _p(kept_ptr), _p(kept_idx),
-                                      max_kept, _p(out), _p(lse), _p(ws), ws.numel(), _stream())
-    _check("dam_sparse_attn_decode", st)
+        ws = decode_workspace(decode_params(q, kcache, out, scale, shared_lists), max_kept, q.device)
+    st = (_native or native()).decode(q, kcache, vcache, kept_ptr, kept_idx, None, max_kept, out, lse, scale, shared_lists, ws, 0)
+    if st:
+        _check("dam_sparse_attn_decode", st)
     return (out, lse) if (want_lse or lse is not None) else out
 
 
@@ -456,14 +475,12 @@ def dam_sparse_attn_decode_grouped(q, kcache, vcache, kept_ptr, kept_idx, kept_m
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    assert kcache.stride() == vcache.stride()
-    p = decode_params(q, kcache, out, scale, shared_lists)
     if ws is None:
-        ws = decode_grouped_workspace(p, max_kept, q.device)
-    st = lib().dam_sparse_attn_decode_grouped(ctypes.byref(p), _p(q), _p(kcache), _p(vcache), _p(kept_ptr),
-                                              _p(kept_idx), _p(kept_member), max_kept, _p(out), _p(lse), _p(ws),
-                                              ws.numel(), _stream())
-    _check("dam_sparse_attn_decode_grouped", st)
+        ws = decode_grouped_workspace(decode_params(q, kcache, out, scale, shared_lists), max_kept, q.device)
+    st = (_native or native()).decode(q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out, lse, scale, shared_lists,
+                                      ws, 1)
+    if st:
+        _check("dam_sparse_attn_decode_grouped", st)
     return (out, lse) if (want_lse or lse is not None) else out
 
 
@@ -474,15 +491,12 @@ def dam_sparse_attn_decode_patterns(q, kcache, vcache, plan: "Mask", pos: int, m
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    assert kcache.stride() == vcache.stride()
-    p = decode_params(q, kcache, out, scale, True)
     if ws is None:
-        ws = decode_grouped_workspace(p, max_entries, q.device)
-    st = lib().dam_sparse_attn_decode_patterns(ctypes.byref(p), _p(q), _p(kcache), _p(vcache), _p(plan.kept_ptr),
-                                               _p(plan.kept_idx), _p(plan.kept_member), _p(plan.plan_table),
-                                               plan.plan_table.shape[1], pos, max_entries, _p(out), _p(lse), _p(ws),
-                                               ws.numel(), _stream())
-    _check("dam_sparse_attn_decode_patterns", st)
+        ws = decode_grouped_workspace(decode_params(q, kcache, out, scale, True), max_entries, q.device)
+    st = (_native or native()).decode_patterns(q, kcache, vcache, plan.kept_ptr, plan.kept_idx, plan.kept_member, plan.plan_table,
+                                               pos, max_entries, out, lse, scale, ws)
+    if st:
+        _check("dam_sparse_attn_decode_patterns", st)
     return (out, lse) if (want_lse or lse is not None) else out
 
 
@@ -490,11 +504,10 @@ def dam_sparse_attn_decode_grouped_static(q, kcache, vcache, kept_ptr, kept_idx,
                                           lse=None, scale: float = 0.0, shared_lists: bool = False) -> None:
     """dam_sparse_attn_decode_grouped without a workspace: the library's fixed scratch array holds the partial
     results. The caller passes every buffer (out, lse): this wrapper allocates nothing either."""
-    assert kcache.stride() == vcache.stride()
-    p = decode_params(q, kcache, out, scale, shared_lists)
-    st = lib().dam_sparse_attn_decode_grouped_static(ctypes.byref(p), _p(q), _p(kcache), _p(vcache), _p(kept_ptr),
-                                                     _p(kept_idx), _p(kept_member), max_kept, _p(out), _p(lse), _stream())
-    _check("dam_sparse_attn_decode_grouped_static", st)
+    st = (_native or native()).decode(q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out, lse, scale, shared_lists,
+                                      None, 2)
+    if st:
+        _check("dam_sparse_attn_decode_grouped_static", st)
 
 
 # ---------------------------------------------------------------------------------------------

@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ into paper_2506_11104_amd/libdam.so for gfx950.
+"""Compile the HIP sources under csrc/ into paper_2506_11104_amd/libdam.so for gfx950, and the Python
+extension csrc/py_native.cpp (host code on torch's headers) into paper_2506_11104_amd/_dam_native.so.
 
 hipcc cross-compiles without a GPU. Packed-fp32 code generation is switched off for the device
 pass (the host pass does not know the feature and says so; that warning is harmless).
@@ -24,14 +25,35 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.j
 EXTRA = {"dam_capture.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
+NATIVE = os.path.join(HERE, "_dam_native.so")
+
+
+def build_native():
+    """The extension links against libdam.so beside it and against the torch that will import it."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+           "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(t, "include"), "-isystem",
+           os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           os.path.join(CSRC, "py_native.cpp"), "-o", NATIVE, "-L" + HERE, "-ldam", "-L" + os.path.join(t, "lib"), "-lc10",
+           "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for py_native.cpp:\n" + r.stderr)
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
     srcs = sources()
-    deps = srcs + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
-    if not force and os.path.exists(OUT) and os.path.getmtime(OUT) >= max(os.path.getmtime(f) for f in deps):
+    deps = srcs + [os.path.join(CSRC, "py_native.cpp")] + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
+    newest = max(os.path.getmtime(f) for f in deps)
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= newest for f in (OUT, NATIVE)):
         return OUT
     os.makedirs(OBJ, exist_ok=True)
 
@@ -52,6 +74,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    build_native()
     return OUT
 
 
