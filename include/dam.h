@@ -21,8 +21,8 @@
  *   - Plain C. "device" pointers are HIP device addresses, "host" pointers are ordinary host memory.
  *     Parameter structs are host memory and are read before the call returns.
  *   - Ownership: every buffer (inputs, outputs, workspace) is allocated and freed by the caller.
- *     The library keeps no state between calls and allocates nothing (one stated exception:
- *     dam_sparse_attn_decode_grouped_static and its fixed scratch array).
+ *     The library allocates nothing and keeps no state between calls but a counter that numbers them
+ *     (one stated exception: dam_sparse_attn_decode_grouped_static and its fixed scratch array).
  *   - Asynchrony: all device work is enqueued on `stream` (a hipStream_t passed as void*; NULL is the
  *     default stream). No entry point synchronises the host. Device scalars written by a call
  *     (bmin, blk_total, kept_total) are valid once the caller has synchronised the stream.

@@ -6,16 +6,18 @@
 // HBM-bound gather of 2 * head_dim * sizeof(T) bytes per kept key. A K or V row is read by LPR
 // adjacent lanes with one 16-byte load each (a whole row per load instruction group, fully
 // coalesced); every lane keeps 4 keys in flight. The kept list is split over several workgroups
-// per head so that all 256 CUs stream; partial (max, sum, O) triples are merged by log-sum-exp.
+// per head so that all 256 CUs stream; partial (max, sum, O) triples are merged by log-sum-exp, by
+// the last workgroup of a list to finish.
 // Workgroups are numbered so that all query heads sharing a KV head run on the same XCD and hit
 // the same L2 for the rows their lists have in common. The grouped-query form (one merged list per
 // KV head) takes the matrix-core kernel of dam_decode_mfma.hip for bf16 and head_dim 128, and the
-// plain-ALU kernel here otherwise; both feed the same merge pass.
+// plain-ALU kernel here otherwise.
 #include <hip/hip_bf16.h>
 #include <math.h>
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 
 #include "dam_internal.h"
 
@@ -27,6 +29,7 @@ constexpr int kUnroll = 4;  // keys in flight per lane (K and V fragment each); 
 
 struct DecodeArgs {
   int B, Hq, Hkv, cap, splits, shared_lists;
+  uint64_t flag;  // of this call (arrive_last)
   float scale;
   int64_t q_sb, q_sh, kv_sb, kv_sh, kv_ss, o_sb, o_sh;
 };
@@ -109,7 +112,66 @@ __device__ __forceinline__ int in_cache(int row, int cap) { return min(max(row, 
 __device__ __forceinline__ void store_out(float *p, float v) { *p = v; }
 __device__ __forceinline__ void store_out(__hip_bfloat16 *p, float v) { *p = __float2bfloat16(v); }
 
-// Partial result of one split: running max m, sum l (relative to m) and un-normalised O.
+// The end of a split: acc (of dim threadIdx.x < D), M and Lsum are the workgroup's result for one query head. A single
+// split normalises and stores it; otherwise it goes to the workspace.
+template <typename T, int D>
+__device__ __forceinline__ void store_split(const DecodeArgs &a, int b, int hq, int split, float acc, float M, float Lsum,
+                                            float *part_o, float *part_ml, T *out, float *lse) {
+  const int item = b * a.Hq + hq;
+  if (a.splits == 1) {
+    store_out(out + b * a.o_sb + hq * a.o_sh + threadIdx.x, Lsum > 0.0f ? acc / Lsum : 0.0f);
+    if (lse && threadIdx.x == 0) lse[item] = Lsum > 0.0f ? (M + log2f(Lsum)) * 0.6931471805599453f : -INFINITY;
+    return;
+  }
+  const int64_t at = (int64_t)item * a.splits + split;
+  store_through(part_o + at * D + threadIdx.x, acc);
+  if (threadIdx.x == 0) {
+    store_through(part_ml + at * 2, M);
+    store_through(part_ml + at * 2 + 1, Lsum);
+  }
+}
+
+// The last workgroup of a list (whole workgroups of 256 call this): the splits of `heads` query heads from hq0 on,
+// merged by log-sum-exp and stored. flags: the list's own.
+template <typename T, int D>
+__device__ __forceinline__ void merge_splits(const DecodeArgs &a, int b, int hq0, int heads, int split, uint64_t *flags,
+                                             const float *part_o, const float *part_ml, T *out, float *lse) {
+  __shared__ int s_last;
+  constexpr int kShares = 256 / D;  // threads that share a dim and take the splits in turn
+  __shared__ float s_acc[kShares][D];
+  stores_done();
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const bool last = arrive_last(flags, a.splits, split, a.flag);
+    if (threadIdx.x == 0) s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  const int t = threadIdx.x % D, share = threadIdx.x / D;
+  for (int x = 0; x < heads; ++x) {
+    const int hq = hq0 + x;
+    const int64_t at = ((int64_t)b * a.Hq + hq) * a.splits;
+    float M = -INFINITY, L = 0.0f, acc = 0.0f;
+    for (int s = 0; s < a.splits; ++s) M = fmaxf(M, part_ml[(at + s) * 2]);
+    if (M > -INFINITY)
+      for (int s = 0; s < a.splits; ++s) {
+        const float w = exp2f(part_ml[(at + s) * 2] - M);
+        L += w * part_ml[(at + s) * 2 + 1];
+        if (s % kShares == share) acc += w * part_o[(at + s) * D + t];
+      }
+    __syncthreads();  // (s_acc of the head before)
+    s_acc[share][t] = acc;
+    __syncthreads();
+    if (share == 0) {
+#pragma unroll
+      for (int y = 1; y < kShares; ++y) acc += s_acc[y][t];
+      store_out(out + b * a.o_sb + hq * a.o_sh + t, L > 0.0f ? acc / L : 0.0f);
+      if (lse && t == 0) lse[(int64_t)b * a.Hq + hq] = L > 0.0f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+    }
+  }
+}
+
+// One split of one list.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_decode_partial(DecodeArgs a, const T *__restrict__ q,
                                                         const T *__restrict__ kc,
@@ -117,8 +179,8 @@ __global__ __launch_bounds__(256) void k_decode_partial(DecodeArgs a, const T *_
                                                         const int *__restrict__ kept_ptr,
                                                         const int *__restrict__ kept_idx,
                                                         float *__restrict__ part_o,
-                                                        float *__restrict__ part_ml, T *__restrict__ out,
-                                                        float *__restrict__ lse) {
+                                                        float *__restrict__ part_ml, uint64_t *__restrict__ flags,
+                                                        T *__restrict__ out, float *__restrict__ lse) {
   constexpr int N = Frag<T>::N;        // elements per lane
   constexpr int LPR = D / N;           // lanes per row
   constexpr int GROUPS = 256 / LPR;    // rows in flight per pass of the block
@@ -215,19 +277,9 @@ __global__ __launch_bounds__(256) void k_decode_partial(DecodeArgs a, const T *_
         Lsum += w * s_l[g];
         acc += w * s_o[g][threadIdx.x];
       }
-    if (a.splits == 1) {  // the whole list was handled here: normalise and store, no merge pass
-      store_out(out + b * a.o_sb + hq * a.o_sh + threadIdx.x, Lsum > 0.0f ? acc / Lsum : 0.0f);
-      if (lse && threadIdx.x == 0)
-        lse[item] = Lsum > 0.0f ? (M + log2f(Lsum)) * 0.6931471805599453f : -INFINITY;
-    } else {
-      const int64_t slot_out = (int64_t)item * a.splits + split;
-      part_o[slot_out * D + threadIdx.x] = acc;
-      if (threadIdx.x == 0) {
-        part_ml[slot_out * 2] = M;
-        part_ml[slot_out * 2 + 1] = Lsum;
-      }
-    }
+    store_split<T, D>(a, b, hq, split, acc, M, Lsum, part_o, part_ml, out, lse);
   }
+  if (a.splits > 1) merge_splits<T, D>(a, b, hq, 1, split, flags + (int64_t)item * a.splits, part_o, part_ml, out, lse);
 }
 
 // Grouped-query form: one workgroup per (sequence, KV head, split) walks the merged list of the KV
@@ -242,7 +294,8 @@ __global__ __launch_bounds__(256) void k_decode_group(DecodeArgs a, const T *__r
                                                       const int *__restrict__ kept_idx,
                                                       const uint8_t *__restrict__ kept_member,
                                                       float *__restrict__ part_o, float *__restrict__ part_ml,
-                                                      T *__restrict__ out, float *__restrict__ lse) {
+                                                      uint64_t *__restrict__ flags, T *__restrict__ out,
+                                                      float *__restrict__ lse) {
   constexpr int N = Frag<T>::N;
   constexpr int LPR = D / N;
   constexpr int GROUPS = 256 / LPR;
@@ -347,8 +400,6 @@ __global__ __launch_bounds__(256) void k_decode_group(DecodeArgs a, const T *__r
       for (int e = 0; e < N; ++e) s_o[group][sub * N + e] = o[x][e];
       __syncthreads();
       if (threadIdx.x < D) {
-        const int hq = hkv * G + x;
-        const int item = b * a.Hq + hq;
         float M = -INFINITY;
         for (int gI = 0; gI < GROUPS; ++gI) M = fmaxf(M, s_m[gI]);
         float Lsum = 0.0f, acc = 0.0f;
@@ -358,44 +409,11 @@ __global__ __launch_bounds__(256) void k_decode_group(DecodeArgs a, const T *__r
             Lsum += w * s_l[gI];
             acc += w * s_o[gI][threadIdx.x];
           }
-        if (a.splits == 1) {
-          store_out(out + b * a.o_sb + hq * a.o_sh + threadIdx.x, Lsum > 0.0f ? acc / Lsum : 0.0f);
-          if (lse && threadIdx.x == 0)
-            lse[item] = Lsum > 0.0f ? (M + log2f(Lsum)) * 0.6931471805599453f : -INFINITY;
-        } else {
-          const int64_t slot_out = (int64_t)item * a.splits + split;
-          part_o[slot_out * D + threadIdx.x] = acc;
-          if (threadIdx.x == 0) {
-            part_ml[slot_out * 2] = M;
-            part_ml[slot_out * 2 + 1] = Lsum;
-          }
-        }
+        store_split<T, D>(a, b, hkv * G + x, split, acc, M, Lsum, part_o, part_ml, out, lse);
       }
     }
   }
-}
-
-template <typename T, int D>
-__global__ void k_decode_merge(DecodeArgs a, const float *__restrict__ part_o,
-                               const float *__restrict__ part_ml, T *__restrict__ out,
-                               float *__restrict__ lse) {
-  const int item = blockIdx.x;
-  const int b = item / a.Hq, hq = item % a.Hq;
-  const int t = threadIdx.x;
-  float M = -INFINITY;
-  for (int s = 0; s < a.splits; ++s) M = fmaxf(M, part_ml[((int64_t)item * a.splits + s) * 2]);
-  float L = 0.0f, acc = 0.0f;
-  if (M > -INFINITY)
-    for (int s = 0; s < a.splits; ++s) {
-      const int64_t at = (int64_t)item * a.splits + s;
-      const float w = exp2f(part_ml[at * 2] - M);
-      L += w * part_ml[at * 2 + 1];
-      acc += w * part_o[at * D + t];
-    }
-  const float res = L > 0.0f ? acc / L : 0.0f;
-  store_out(out + b * a.o_sb + hq * a.o_sh + t, res);
-  if (lse && t == 0)
-    lse[item] = L > 0.0f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+  if (a.splits > 1) merge_splits<T, D>(a, b, hkv * G, G, split, flags + (int64_t)pair * a.splits, part_o, part_ml, out, lse);
 }
 
 int pick_splits(int64_t items, int64_t max_kept) {
@@ -406,16 +424,36 @@ int pick_splits(int64_t items, int64_t max_kept) {
   return (int)std::min<int64_t>(std::max<int64_t>(s, 1), 64);
 }
 
-// Splits of the grouped form, and whether the call takes the matrix-core kernel (one wave per
-// workgroup: four per CU, each with at least two blocks of 32 entries).
-int group_splits(const dam_decode_params *p, int64_t max_kept, bool *mfma) {
+// Splits of the grouped form, and whether the call takes the matrix-core kernel (.groups workgroups per list of .waves
+// waves, four waves per CU, each with at least one block of 32 entries, since a block's products and softmax are one
+// chain of about 1.2 us; the plain kernel: .groups workgroups per list).
+// Up to four splits are the waves of one workgroup; beyond, workgroups of four waves, of which one fits a CU, as many
+// as fit the chip at once: one more would run alone after the others.
+GroupSplit group_splits(const dam_decode_params *p, int64_t max_kept, bool *mfma) {
   const int64_t items = (int64_t)p->batch * p->hkv;
   *mfma = decode_group_mfma_fits(p);
-  if (!*mfma) return pick_splits(items, max_kept);
-  int64_t s = (1024 + items - 1) / items;
-  s = std::min<int64_t>(s, std::max<int64_t>(1, max_kept / 64));
-  return (int)std::min<int64_t>(std::max<int64_t>(s, 1), 64);
+  if (!*mfma) return {1, pick_splits(items, max_kept)};
+  const int64_t s = std::min<int64_t>((1024 + items - 1) / items, std::max<int64_t>(1, max_kept / 32));
+  if (s <= 4) return {(int)s, 1};
+  const int64_t groups = std::min<int64_t>(256 / items, max_kept / 128);
+  return {4, (int)std::min<int64_t>(std::max<int64_t>(groups, 1), 16)};
 }
+
+// Workspace of a call whose lists are split over `splits` workgroups: partial O, (reference, sum), flags.
+struct Partials {
+  float *o, *ml;
+  uint64_t *flags;
+  size_t bytes, flag_bytes;
+  Partials(void *ws, const dam_decode_params *p, int splits, int64_t lists) {
+    Carver c(ws);
+    o = c.take<float>((size_t)p->batch * p->hq * splits * p->head_dim);
+    ml = c.take<float>((size_t)p->batch * p->hq * splits * 2);
+    const size_t before = c.off;
+    flags = splits > 1 ? c.take<uint64_t>((size_t)lists * splits) : nullptr;
+    bytes = c.off;
+    flag_bytes = c.off - before;
+  }
+};
 
 int validate(const dam_decode_params *p, const void *q, const void *kc, const void *vc,
              const int32_t *kept_ptr, const int32_t *kept_idx, int64_t max_kept, const void *out) {
@@ -435,26 +473,33 @@ int validate(const dam_decode_params *p, const void *q, const void *kc, const vo
 
 template <typename T, int D>
 void launch(const DecodeArgs &a, const void *q, const void *kc, const void *vc, const int32_t *kept_ptr,
-            const int32_t *kept_idx, void *out, float *lse, float *part_o, float *part_ml, hipStream_t st) {
+            const int32_t *kept_idx, void *out, float *lse, const Partials &part, hipStream_t st) {
   const int G = a.Hq / a.Hkv;
   const int n_pairs = a.B * a.Hkv;
   const int rounds = (n_pairs + kXcd - 1) / kXcd;
   const int blocks = rounds * kXcd * G * a.splits;
   k_decode_partial<T, D><<<blocks, 256, 0, st>>>(a, static_cast<const T *>(q), static_cast<const T *>(kc),
-                                                static_cast<const T *>(vc), kept_ptr, kept_idx, part_o, part_ml,
+                                                static_cast<const T *>(vc), kept_ptr, kept_idx, part.o, part.ml, part.flags,
                                                 static_cast<T *>(out), lse);
-  if (a.splits > 1) k_decode_merge<T, D><<<a.B * a.Hq, D, 0, st>>>(a, part_o, part_ml, static_cast<T *>(out), lse);
 }
 
 }  // namespace
 
+// Numbers in an order that no data follows (the splitmix64 mixing of a counter), from a start that differs from
+// process to process.
+uint64_t dam::fresh_flag() {
+  static std::atomic<uint64_t> count{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+  uint64_t x = count.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+  x ^= x >> 31;
+  return x ? x : 1;
+}
+
 extern "C" size_t dam_sparse_attn_decode_workspace(const dam_decode_params *p, int64_t max_kept) {
   if (!p || p->batch < 1 || p->hq < 1 || p->head_dim < 1 || max_kept < 0) return 0;
   const int splits = pick_splits((int64_t)p->batch * p->hq, max_kept);
-  Carver c(nullptr);
-  c.take<float>((size_t)p->batch * p->hq * splits * p->head_dim);
-  c.take<float>((size_t)p->batch * p->hq * splits * 2);
-  return c.off;
+  return Partials(nullptr, p, splits, (int64_t)p->batch * p->hq).bytes;
 }
 
 extern "C" int dam_sparse_attn_decode(const dam_decode_params *p, const void *q, const void *kcache,
@@ -472,16 +517,15 @@ extern "C" int dam_sparse_attn_decode(const dam_decode_params *p, const void *q,
   a.q_sb = p->q_stride[0]; a.q_sh = p->q_stride[1];
   a.kv_sb = p->kv_stride[0]; a.kv_sh = p->kv_stride[1]; a.kv_ss = p->kv_stride[2];
   a.o_sb = p->o_stride[0]; a.o_sh = p->o_stride[1];
-  Carver c(ws);
-  float *part_o = c.take<float>((size_t)a.B * a.Hq * a.splits * p->head_dim);
-  float *part_ml = c.take<float>((size_t)a.B * a.Hq * a.splits * 2);
+  a.flag = a.splits > 1 ? fresh_flag() : 0;
+  const Partials part(ws, p, a.splits, (int64_t)a.B * a.Hq);
   hipStream_t st = static_cast<hipStream_t>(stream_v);
   if (p->dtype == DAM_BF16) {
-    if (p->head_dim == 128) launch<__hip_bfloat16, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part_o, part_ml, st);
-    else launch<__hip_bfloat16, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part_o, part_ml, st);
+    if (p->head_dim == 128) launch<__hip_bfloat16, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part, st);
+    else launch<__hip_bfloat16, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part, st);
   } else {
-    if (p->head_dim == 128) launch<float, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part_o, part_ml, st);
-    else launch<float, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part_o, part_ml, st);
+    if (p->head_dim == 128) launch<float, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part, st);
+    else launch<float, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part, st);
   }
   return launch_status();
 }
@@ -490,18 +534,17 @@ namespace {
 
 template <typename T, int D>
 void launch_group(const DecodeArgs &a, const void *q, const void *kc, const void *vc, const int32_t *kept_ptr,
-                  const int32_t *kept_idx, const uint8_t *kept_member, void *out, float *lse, float *part_o,
-                  float *part_ml, hipStream_t st) {
+                  const int32_t *kept_idx, const uint8_t *kept_member, void *out, float *lse, const Partials &part,
+                  hipStream_t st) {
   const int blocks = a.B * a.Hkv * a.splits;
   if (a.Hq / a.Hkv <= 4)
     k_decode_group<T, D, 4><<<blocks, 256, 0, st>>>(a, static_cast<const T *>(q), static_cast<const T *>(kc),
-                                                    static_cast<const T *>(vc), kept_ptr, kept_idx, kept_member, part_o,
-                                                    part_ml, static_cast<T *>(out), lse);
+                                                    static_cast<const T *>(vc), kept_ptr, kept_idx, kept_member, part.o,
+                                                    part.ml, part.flags, static_cast<T *>(out), lse);
   else
     k_decode_group<T, D, 8><<<blocks, 256, 0, st>>>(a, static_cast<const T *>(q), static_cast<const T *>(kc),
-                                                    static_cast<const T *>(vc), kept_ptr, kept_idx, kept_member, part_o,
-                                                    part_ml, static_cast<T *>(out), lse);
-  if (a.splits > 1) k_decode_merge<T, D><<<a.B * a.Hq, D, 0, st>>>(a, part_o, part_ml, static_cast<T *>(out), lse);
+                                                    static_cast<const T *>(vc), kept_ptr, kept_idx, kept_member, part.o,
+                                                    part.ml, part.flags, static_cast<T *>(out), lse);
 }
 
 }  // namespace
@@ -510,11 +553,7 @@ extern "C" size_t dam_sparse_attn_decode_grouped_workspace(const dam_decode_para
   if (!p || p->batch < 1 || p->hq < 1 || p->hkv < 1 || p->head_dim < 1 || max_kept < 0) return 0;
   if (p->hq % p->hkv) return 0;
   bool mfma;
-  const int splits = group_splits(p, max_kept, &mfma);
-  Carver c(nullptr);
-  c.take<float>((size_t)p->batch * p->hq * splits * p->head_dim);
-  c.take<float>((size_t)p->batch * p->hq * splits * 2);
-  return c.off;
+  return Partials(nullptr, p, group_splits(p, max_kept, &mfma).groups, (int64_t)p->batch * p->hkv).bytes;
 }
 
 namespace {
@@ -527,30 +566,29 @@ int decode_grouped_run(const dam_decode_params *p, const void *q, const void *kc
   DecodeArgs a;
   a.B = p->batch; a.Hq = p->hq; a.Hkv = p->hkv; a.cap = p->kv_capacity;
   bool mfma;
-  a.splits = group_splits(p, max_kept, &mfma);
+  const GroupSplit split = group_splits(p, max_kept, &mfma);
+  a.splits = split.groups;
   a.shared_lists = p->shared_lists != 0;
   a.scale = p->scale > 0.0f ? p->scale : 1.0f / sqrtf((float)p->head_dim);
   a.q_sb = p->q_stride[0]; a.q_sh = p->q_stride[1];
   a.kv_sb = p->kv_stride[0]; a.kv_sh = p->kv_stride[1]; a.kv_ss = p->kv_stride[2];
   a.o_sb = p->o_stride[0]; a.o_sh = p->o_stride[1];
-  Carver c(ws);
-  float *part_o = c.take<float>((size_t)a.B * a.Hq * a.splits * p->head_dim);
-  float *part_ml = c.take<float>((size_t)a.B * a.Hq * a.splits * 2);
+  const Partials part(ws, p, split.groups, (int64_t)a.B * a.Hkv);
   if (mfma) {
-    // matrix-core pass; with more than four splits its partial results go through the merge pass
-    const int rc = launch_decode_group_mfma(p, a.splits, a.scale, q, kcache, vcache, kept_ptr, kept_idx, kept_member, part_o,
-                                            part_ml, out, lse, st, plan_table, n_flags, pos);
+    const int rc = launch_decode_group_mfma(p, split, a.scale, q, kcache, vcache, kept_ptr, kept_idx, kept_member, part.o,
+                                            part.ml, part.flags, out, lse, st, plan_table, n_flags, pos);
     if (rc != DAM_OK) return rc;
-    if (!decode_group_mfma_merges(a.splits))
-      k_decode_merge<__hip_bfloat16, 128><<<a.B * a.Hq, 128, 0, st>>>(a, part_o, part_ml, static_cast<__hip_bfloat16 *>(out), lse);
-  } else if (plan_table) {
+    return launch_status();
+  }
+  a.flag = a.splits > 1 ? fresh_flag() : 0;
+  if (plan_table) {
     return DAM_ERR_UNSUPPORTED;  // plans are decoded by the matrix-core kernel only
   } else if (p->dtype == DAM_BF16) {
-    if (p->head_dim == 128) launch_group<__hip_bfloat16, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part_o, part_ml, st);
-    else launch_group<__hip_bfloat16, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part_o, part_ml, st);
+    if (p->head_dim == 128) launch_group<__hip_bfloat16, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part, st);
+    else launch_group<__hip_bfloat16, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part, st);
   } else {
-    if (p->head_dim == 128) launch_group<float, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part_o, part_ml, st);
-    else launch_group<float, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part_o, part_ml, st);
+    if (p->head_dim == 128) launch_group<float, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part, st);
+    else launch_group<float, 64>(a, q, kcache, vcache, kept_ptr, kept_idx, kept_member, out, lse, part, st);
   }
   return launch_status();
 }
@@ -599,7 +637,10 @@ extern "C" int dam_sparse_attn_decode_patterns(const dam_decode_params *p, const
 // dam_sparse_attn_decode_grouped for callers that cannot allocate: the partial results of the splits live in
 // a fixed array in device memory that belongs to the library instead of a caller's workspace.
 constexpr size_t kStaticScratchBytes = DAM_DECODE_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// (beside the partial results the flags of a call's splits: at most 1024 of them, lists that are split at all being
+// fewer than 512 in at most 512 + lists workgroups)
+constexpr size_t kStaticFlagBytes = 1024 * sizeof(uint64_t);
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticFlagBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -628,12 +669,14 @@ extern "C" int dam_sparse_attn_decode_grouped_static(const dam_decode_params *p,
                                                      int64_t max_kept, void *out, float *lse, void *stream_v) {
   const int bad = validate_grouped(p, q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out);
   if (bad != DAM_OK) return bad;
-  const size_t need = dam_sparse_attn_decode_grouped_workspace(p, max_kept);
-  if (need == 0 || need > kStaticScratchBytes) return DAM_ERR_WORKSPACE;  // the call does not fit the fixed array
+  bool mfma;
+  const Partials need(nullptr, p, group_splits(p, max_kept, &mfma).groups, (int64_t)p->batch * p->hkv);
+  // the call does not fit the fixed array
+  if (need.bytes - need.flag_bytes > kStaticScratchBytes || need.flag_bytes > kStaticFlagBytes) return DAM_ERR_WORKSPACE;
   void *ws = nullptr;
   const int st = scratch_address(&ws);
   if (st != DAM_OK) return st;
-  // nothing to clear: every split writes its partial result before the merge pass reads it
+  // nothing to clear: every split writes its partial result and its flag before they are read
   return decode_grouped_run(p, q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out, lse, ws,
                             static_cast<hipStream_t>(stream_v));
 }

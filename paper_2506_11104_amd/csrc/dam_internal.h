@@ -28,6 +28,43 @@ struct Carver {
   }
 };
 
+// ------------------------------------------------------------------------------------------------
+// The last of several workgroups that share an item, without a launch of its own and without anything that has to
+// start at zero: every workgroup writes its partial result with stores that go through to memory (store_through),
+// then its flag, a 64-bit number drawn anew by the host for every call; the one that then finds the flags of all is
+// the last (two that finish together may both be: they then do the same work on the same values), does what is left,
+// and clears the flags, so that a replay of the same launch from a HIP graph does not find them set. A memory that was
+// never written, or by another call, holds the number with a probability of 2^-64 per flag.
+// (An atomic counter would need clearing by a launch, and a release fence writes back the XCD's whole L2: a merge
+// kernel of its own costs about 5 us behind a dependent launch, this about 2.)
+uint64_t fresh_flag();  // dam_decode.hip; never 0
+
+#ifdef __HIPCC__
+// 16 bytes to memory past this XCD's L2, for readers on other XCDs; not complete before stores_done()
+__device__ __forceinline__ void store_through(void *p, float x, float y, float z, float w) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  const f32x4_t v = {x, y, z, w};
+  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void store_through(float *p, float x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// To be called by one whole wave after the stores of its workgroup are done; n <= 64 flags, this workgroup's is `self`.
+// True in the last workgroup, which may then read what the others stored.
+__device__ __forceinline__ bool arrive_last(uint64_t *flags, int n, int self, uint64_t flag) {
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) __hip_atomic_store(&flags[self], flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  stores_done();
+  const uint64_t seen = lane < n ? __hip_atomic_load(&flags[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : flag;
+  if (__ballot(seen != flag) != 0) return false;
+  if (lane < n) __hip_atomic_store(&flags[lane], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return true;
+}
+#endif
+
 // dam_capture.hip: argument check of a capture, bytes of its row log-sum-exp buffer, and the fused
 // form that writes the true mask of one captured sequence (bit = probability >= threshold, the
 // threshold given as the ordered fp32 key the mask builder uses).
@@ -38,15 +75,17 @@ void launch_capture_true_bits(const dam_capture_params *p, const void *q, const 
 
 // dam_decode_mfma.hip: the partial pass of the grouped-query decode on the matrix cores. `fits` says
 // whether a call can take it (bf16, head_dim 128, at most 8 query heads per KV head, a head's cache rows
-// within 4 GiB); the launch writes one (reference, sum, un-normalised O) triple per (sequence, query
-// head, split) in the layout the merge pass of dam_decode.hip reads. plan_table != nullptr: the lists are a
-// position-independent plan (DAM_MASK_PATTERN_PLAN) decoded at position pos; n_flags is the table's row length.
+// within 4 GiB). A list is shared by `waves` waves of each of `groups` workgroups; with more than one group the partial
+// results go through part_o [pair][group][128 G], part_ml [pair][group][G][2] and flags [pair][group].
+// plan_table != nullptr: the lists are a position-independent plan (DAM_MASK_PATTERN_PLAN) decoded at position pos;
+// n_flags is the table's row length.
+struct GroupSplit {
+  int waves, groups;
+};
 bool decode_group_mfma_fits(const dam_decode_params *p);
-// true: the kernel merges the splits itself and stores the output (no merge pass, part_o / part_ml unused)
-bool decode_group_mfma_merges(int splits);
-int launch_decode_group_mfma(const dam_decode_params *p, int splits, float scale, const void *q, const void *kc,
+int launch_decode_group_mfma(const dam_decode_params *p, GroupSplit split, float scale, const void *q, const void *kc,
                              const void *vc, const int32_t *kept_ptr, const int32_t *kept_idx,
-                             const uint8_t *kept_member, float *part_o, float *part_ml, void *out, float *lse,
-                             hipStream_t st, const uint8_t *plan_table = nullptr, int n_flags = 0, int pos = 0);
+                             const uint8_t *kept_member, float *part_o, float *part_ml, uint64_t *flags, void *out,
+                             float *lse, hipStream_t st, const uint8_t *plan_table = nullptr, int n_flags = 0, int pos = 0);
 
 }  // namespace dam
