@@ -1704,38 +1704,66 @@ __global__ __launch_bounds__(256) void k_row_fill(Geom g, const uint64_t *__rest
 }
 
 // ------------------------------------------------------------------------------------------------
-// Kept lists of one row for grouped-query decoding (DAM_MASK_GROUP_LISTS): one list per group of G
-// consecutive maps, holding each key some map of the group keeps once, in G + 1 runs (kept by two or
-// more maps; by map 0 alone; by map 1 alone; ...), each ascending, with a byte of member bits per
-// entry. A lane owns kPieceBits consecutive keys, a wave a chunk of 64 such pieces; the work is spread
-// thin on purpose: the lists are short, so the time is the latency of the longest chain of dependent
-// steps in one wave (its fullest piece), not throughput. Count per (group, run, chunk), exclusive
-// scan in that order (which is the order of the output), fill.
+// Kept lists of one row, as a decode step needs them: one list per group of G consecutive maps (DAM_MASK_GROUP_LISTS;
+// a list per map is groups of one), holding each key some map of the group keeps once, in G + 1 runs (kept by two or
+// more maps; by map 0 alone; by map 1 alone; ...), each ascending, with a byte of member bits per entry. A lane owns
+// kPieceBits consecutive keys, a workgroup kListSpan; the work is spread thin on purpose: the lists are short, so the
+// time is launches and the latency of the longest chain of dependent steps, not throughput.
+//
+// Two launches, count per (group, run, span) and fill, both straight from the flags (from the true bits for a row above
+// pcl): a piece is eight flag bytes of the columns and eight of the diagonals, and turning whole flag rows into
+// bitsets first is a launch of its own for twice the reading. The fill kernel adds up the counts before its own
+// itself, so there is no scan launch either (at most a few thousand counts). 8 KV heads of 4 maps at row 20000: 21 us
+// in four launches (bitsets, count, scan, fill) -> 13 us; 16 maps at row 4095: 13 -> 8 us.
 constexpr int kMaxGroup = 8;
 constexpr int kPieceBits = 8;
 constexpr int kPiecesPerWord = 64 / kPieceBits;
 constexpr int kChunkWords = 64 / kPiecesPerWord;  // mask words per wave
+constexpr int kListSpan = 256 * kPieceBits;       // keys per workgroup
 
-// This lane's piece of row i for the maps of group kv (m[x], zero for x >= G and beyond the row), and
-// the bits set in at least two of them. Lane l: piece l % kPiecesPerWord of word chunk * kChunkWords +
-// l / kPiecesPerWord.
-__device__ __forceinline__ void group_pieces(const Geom &g, const uint64_t *__restrict__ true_bits,
-                                             const uint64_t *__restrict__ cbits, const uint64_t *__restrict__ rrev,
-                                             int kv, int G, int i, int chunk, int lane, unsigned (&m)[kMaxGroup],
-                                             unsigned &shared) {
-  const int w = chunk * kChunkWords + lane / kPiecesPerWord;
-  const int shift = (lane % kPiecesPerWord) * kPieceBits;
+// Eight flag bytes from p on as eight bits (p of any alignment).
+__device__ __forceinline__ unsigned flags8(const uint8_t *p) {
+  uint64_t v;
+  __builtin_memcpy(&v, p, 8);
+  const uint64_t nz = ((((v & 0x7F7F7F7F7F7F7F7Full) + 0x7F7F7F7F7F7F7F7Full) | v) & 0x8080808080808080ull) >> 7;
+  return (unsigned)((nz * 0x0102040810204080ull) >> 56);  // byte k's bit to bit k
+}
+
+// The mask bits of row i, keys [key0, key0 + 8) of one map; key0 a multiple of 8.
+__device__ __forceinline__ unsigned row_piece(const Geom &g, const uint64_t *__restrict__ true_bits,
+                                              const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int h, int i,
+                                              int key0) {
+  if (key0 > i) return 0;
+  unsigned bits;
+  if (i < g.L) {
+    bits = (unsigned)(true_bits[((int64_t)h * g.L + i) * g.tbw + (key0 >> 6)] >> (key0 & 63)) & 0xFFu;
+    if (key0 + 8 > g.L) bits &= (1u << (g.L - key0)) - 1;
+  } else {
+    const uint8_t *d = dflag + (int64_t)h * g.P, *v = vflag + (int64_t)h * g.P;
+    const int u = i - key0;  // offset of the first key; key k of the piece has offset u - k
+    if (key0 + 8 <= g.P && u >= 7 && u < g.P) {
+      bits = flags8(v + key0) | __brev(flags8(d + u - 7)) >> 24;
+    } else {
+      bits = 0;
+      for (int k = 0; k < 8; ++k) {
+        const bool col = key0 + k < g.P && v[key0 + k] != 0;
+        const bool off = u - k >= 0 && u - k < g.P && d[u - k] != 0;
+        bits |= (col || off ? 1u : 0u) << k;
+      }
+    }
+  }
+  return i - key0 >= 7 ? bits : bits & ((2u << (i - key0)) - 1);  // keys up to the row's own
+}
+
+// This lane's pieces for the maps of group kv (m[x], zero for x >= G), and the bits set in at least two of them.
+__device__ __forceinline__ void row_pieces(const Geom &g, const uint64_t *__restrict__ true_bits,
+                                           const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int kv, int G, int i,
+                                           int key0, unsigned (&m)[kMaxGroup], unsigned &shared) {
   unsigned any = 0;
   shared = 0;
 #pragma unroll
   for (int x = 0; x < kMaxGroup; ++x) {
-    m[x] = 0;
-    if (x < G && w <= (i >> 6)) {
-      const int h = kv * G + x;
-      const uint64_t word = mask_word(g, true_bits ? true_bits + (int64_t)h * g.L * g.tbw : nullptr,
-                                      cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, i, w);
-      m[x] = (unsigned)(word >> shift) & ((1u << kPieceBits) - 1);
-    }
+    m[x] = x < G ? row_piece(g, true_bits, dflag, vflag, kv * G + x, i, key0) : 0u;
     shared |= any & m[x];
     any |= m[x];
   }
@@ -1746,57 +1774,81 @@ __device__ __forceinline__ int wave_total(int v) {
   return v;
 }
 
-// cnt[(kv * (G + 1) + run) * nchunks + chunk]
-__global__ __launch_bounds__(256) void k_group_count(Geom g, const uint64_t *__restrict__ true_bits,
-                                                     const uint64_t *__restrict__ cbits,
-                                                     const uint64_t *__restrict__ rrev, int row, int G,
-                                                     int nchunks, int *__restrict__ cnt) {
-  const int lane = threadIdx.x & 63, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), kv = blockIdx.y;
-  if (chunk >= nchunks) return;  // whole waves
+// cnt[(kv * (G + 1) + run) * spans + span]
+__global__ __launch_bounds__(256) void k_list_count(Geom g, const uint64_t *__restrict__ true_bits,
+                                                    const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int row,
+                                                    int G, int *__restrict__ cnt) {
+  __shared__ int part[4][kMaxGroup + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kv = blockIdx.y, spans = gridDim.x;
   unsigned m[kMaxGroup], shared;
-  group_pieces(g, true_bits, cbits, rrev, kv, G, row, chunk, lane, m, shared);
-  int *out = cnt + (int64_t)kv * (G + 1) * nchunks + chunk;
-  const int c0 = wave_total(__popc(shared));
-  if (lane == 0) out[0] = c0;
+  row_pieces(g, true_bits, dflag, vflag, kv, G, row, (blockIdx.x * 256 + threadIdx.x) * kPieceBits, m, shared);
 #pragma unroll
-  for (int x = 0; x < kMaxGroup; ++x) {
-    if (x < G) {
-      const int c = wave_total(__popc(m[x] & ~shared));
-      if (lane == 0) out[(int64_t)(1 + x) * nchunks] = c;
+  for (int r = 0; r <= kMaxGroup; ++r)
+    if (r <= G) {
+      const int c = wave_total(__popc(r == 0 ? shared : m[r - 1] & ~shared));
+      if (lane == 0) part[wave][r] = c;
     }
-  }
+  __syncthreads();
+  if (threadIdx.x <= G)
+    cnt[((int64_t)kv * (G + 1) + threadIdx.x) * spans + blockIdx.x] =
+        part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
 }
 
-// first[e]: exclusive scan of cnt (n_groups * (G + 1) * nchunks + 1 entries)
-__global__ __launch_bounds__(256) void k_group_fill(Geom g, const uint64_t *__restrict__ true_bits,
-                                                    const uint64_t *__restrict__ cbits,
-                                                    const uint64_t *__restrict__ rrev, int row, int G,
-                                                    int nchunks, int n_groups, const int *__restrict__ first,
-                                                    int *__restrict__ kept_ptr, int *__restrict__ kept_idx,
-                                                    uint8_t *__restrict__ kept_member, int64_t capacity) {
-  const int lane = threadIdx.x & 63, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), kv = blockIdx.y;
-  if (chunk >= nchunks) return;  // whole waves
-  const int *mine_first = first + (int64_t)kv * (G + 1) * nchunks + chunk;
-  if (chunk == 0 && lane == 0) {  // (offsets past the capacity of the list buffers are cut to it, like the block index')
-    const int64_t clamp = kept_idx ? capacity : INT64_MAX;
-    kept_ptr[kv] = (int)min((int64_t)mine_first[0], clamp);
-    if (kv == n_groups - 1) kept_ptr[n_groups] = (int)min((int64_t)first[(int64_t)n_groups * (G + 1) * nchunks], clamp);
+__global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__restrict__ true_bits,
+                                                   const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int row,
+                                                   int G, const int *__restrict__ cnt, int *__restrict__ kept_ptr,
+                                                   int64_t *__restrict__ kept_total, int *__restrict__ kept_idx,
+                                                   uint8_t *__restrict__ kept_member, int64_t capacity) {
+  // [r <= G]: entries before run r of this span, counted from the end of what lies before run r - 1's; [G + 1]: the rest
+  __shared__ unsigned long long before[kMaxGroup + 2];
+  __shared__ int part[4][kMaxGroup + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kv = blockIdx.y, n_groups = gridDim.y, span = blockIdx.x, spans = gridDim.x;
+  if (threadIdx.x < kMaxGroup + 2) before[threadIdx.x] = 0;
+  const int key0 = (span * 256 + (int)threadIdx.x) * kPieceBits;
+  unsigned m[kMaxGroup], shared;
+  row_pieces(g, true_bits, dflag, vflag, kv, G, row, key0, m, shared);
+  __syncthreads();
+  const int64_t at0 = (int64_t)kv * (G + 1) * spans + span, last = (int64_t)n_groups * (G + 1) * spans;
+  unsigned long long sum = 0;
+  for (int64_t e = threadIdx.x; e < at0; e += 256) sum += cnt[e];
+  for (int off = 32; off; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0 && sum) atomicAdd(&before[0], sum);
+  for (int e = threadIdx.x; e < G * spans; e += 256) atomicAdd(&before[1 + e / spans], (unsigned long long)cnt[at0 + e]);
+  if (kv == n_groups - 1 && span == 0)  // the workgroup that reports the total adds up the counts from its last run on
+    for (int64_t e = at0 + (int64_t)G * spans + threadIdx.x; e < last; e += 256)
+      atomicAdd(&before[G + 1], (unsigned long long)cnt[e]);
+  int incl[kMaxGroup + 1];
+#pragma unroll
+  for (int r = 0; r <= kMaxGroup; ++r)
+    if (r <= G) {
+      incl[r] = __popc(r == 0 ? shared : m[r - 1] & ~shared);
+      for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl[r], off);
+        if (lane >= off) incl[r] += up;
+      }
+      if (lane == 63) part[wave][r] = incl[r];
+    }
+  __syncthreads();
+  if (threadIdx.x == 0 && span == 0) {  // (offsets past the capacity of the list buffers are cut to it, like the block index')
+    const unsigned long long clamp = kept_idx ? (unsigned long long)capacity : (unsigned long long)INT64_MAX;
+    kept_ptr[kv] = (int)min(before[0], clamp);
+    if (kv == n_groups - 1) {
+      unsigned long long total = 0;
+      for (int r = 0; r <= G + 1; ++r) total += before[r];
+      kept_ptr[n_groups] = (int)min(total, clamp);
+      if (kept_total) *kept_total = (int64_t)total;
+    }
   }
   if (!kept_idx) return;
-  unsigned m[kMaxGroup], shared;
-  group_pieces(g, true_bits, cbits, rrev, kv, G, row, chunk, lane, m, shared);
-  const int key0 = (chunk * kChunkWords + lane / kPiecesPerWord) * 64 + (lane % kPiecesPerWord) * kPieceBits;
+  int64_t base = 0;
 #pragma unroll
   for (int r = 0; r <= kMaxGroup; ++r) {
     if (r <= G) {
       unsigned left = r == 0 ? shared : m[r - 1] & ~shared;  // lane's piece of run r
-      const int v = __popc(left);
-      int incl = v;
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
-      int64_t at = (int64_t)mine_first[(int64_t)r * nchunks] + incl - v;
+      base += (int64_t)before[r];
+      int64_t at = base + incl[r] - __popc(left);
+      for (int x = 0; x < wave; ++x) at += part[x][r];
       while (left) {
         const int bit = __ffs(left) - 1;
         left &= left - 1;
@@ -1821,7 +1873,7 @@ __global__ __launch_bounds__(256) void k_group_fill(Geom g, const uint64_t *__re
 // part in G + 1 runs (patterns of two or more maps; of map 0 alone; ...), each run ascending in the key it
 // stands for. A diagonal r is stored as -1 - r (key p - r at position p), a column c as c. The diagonal part
 // is the kept list of the last row of a P x P mask that has the group's diagonals and no columns (key j of
-// that row is offset P - 1 - j), so the chunked count / scan / fill of the merged lists serves unchanged; the
+// that row is offset P - 1 - j), counted, scanned and filled in chunks of a wave's 64 pieces; the
 // column part reads the column bitset itself. cnt / first: [((kv * 2 + part) * (G + 1) + run) * nchunks + chunk].
 __device__ __forceinline__ void plan_pieces(const Geom &gp, const uint64_t *__restrict__ cbits,
                                             const uint64_t *__restrict__ rrev, int kv, int G, int part, int n_cols, int chunk,
@@ -1985,7 +2037,7 @@ int list_group(const dam_mask_params *p) {
   return (p->flags & DAM_MASK_GROUP_LISTS) && p->group >= 1 && p->group <= kMaxGroup ? p->group : 1;
 }
 
-// Chunks of kChunkWords mask words covering keys 0..row (one wave each in the group-list kernels).
+// Chunks of kChunkWords mask words covering keys 0..row (one wave each in the plan kernels).
 int group_chunks(int row) { return ((row >> 6) + 1 + kChunkWords - 1) / kChunkWords; }
 
 Geom geometry(const dam_mask_params *p) {
@@ -2037,10 +2089,9 @@ Workspace carve(const dam_mask_params *p, void *ws) {
   const int nrows = p->row_end > p->row_begin ? p->row_end - p->row_begin : 0;
   size_t n_cnt = (size_t)g.H * (size_t)(nrows > 0 ? nrows : 1);
   size_t n_first = 1;
-  if (nrows == 1 && p->row_begin >= 0) {  // a single row goes through the group-list kernels: run sizes per chunk, and their scan
+  if (nrows == 1 && p->row_begin >= 0) {  // a single row: the run sizes per span
     const int group = list_group(p);
-    n_first = (size_t)(g.H / group) * (size_t)group_chunks(p->row_begin) * (size_t)(group + 1) + 1;
-    n_cnt = std::max(n_cnt, n_first);
+    n_cnt = std::max(n_cnt, (size_t)(g.H / group) * (size_t)(p->row_begin / kListSpan + 1) * (size_t)(group + 1));
   }
   if (p->flags & DAM_MASK_PATTERN_PLAN) {  // two parts (diagonals, columns) over the P pattern positions
     const int group = list_group(p);
@@ -2135,7 +2186,9 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const bool gather = want_blocks && (p->flags & DAM_MASK_GATHER_COLUMNS) != 0;
   const int gstride = dam_gather_stride(p);
   const int *gidx = gather ? o->gather_idx : nullptr, *gcnt = gather ? o->gather_cnt : nullptr;
-  if (want_blocks || want_lists || o->dense_bits) {
+  const int nrows = p->row_end - p->row_begin;
+  const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
+  if (want_blocks || (want_lists && (plan || nrows > 1)) || o->dense_bits) {  // (a single row is listed from the flags)
     const size_t prep_lds = want_blocks && (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0;
     k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
                                                    w.off_all, gstride, gather ? o->gather_idx : nullptr,
@@ -2169,7 +2222,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
     const int sw = (g.S + 63) / 64;
     k_dense_bits<<<dim3((sw + 255) / 256, g.S, g.H), 256, 0, stream>>>(g, true_bits, w.cbits, w.rrev, sw, o->dense_bits);
   }
-  if (want_lists && (p->flags & DAM_MASK_PATTERN_PLAN)) {
+  if (want_lists && plan) {
     Geom gp = g;  // the P x P pattern-only mask whose last row lists the diagonals
     gp.L = 0;
     gp.S = g.P;
@@ -2182,18 +2235,12 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
                                           o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member, o->kept_capacity);
     k_plan_table<<<dim3((g.P + 255) / 256, n_groups), 256, 0, stream>>>(dflag, g.P, G, o->plan_table);
   } else if (want_lists) {
-    const int nrows = p->row_end - p->row_begin;
     if (nrows == 1) {
-      // one row (a decode step): the chunked kernels below, whose longest dependent chain is eight steps; lists per
-      // map are groups of one
-      const int G = list_group(p), n_groups = g.H / G, nchunks = group_chunks(p->row_begin);
-      const dim3 grid((nchunks + 3) / 4, n_groups);
-      k_group_count<<<grid, 256, 0, stream>>>(g, true_bits, w.cbits, w.rrev, p->row_begin, G, nchunks, w.row_cnt);
-      k_exclusive_scan<<<1, 1024, 0, stream>>>(w.row_cnt, (int64_t)n_groups * (G + 1) * nchunks, 0, w.group_first, o->kept_total,
-                                               INT64_MAX);
-      k_group_fill<<<grid, 256, 0, stream>>>(g, true_bits, w.cbits, w.rrev, p->row_begin, G, nchunks, n_groups, w.group_first,
-                                             o->kept_ptr, o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member,
-                                             o->kept_capacity);
+      const int G = list_group(p);
+      const dim3 grid(p->row_begin / kListSpan + 1, g.H / G);
+      k_list_count<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, w.row_cnt);
+      k_list_fill<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, w.row_cnt, o->kept_ptr, o->kept_total,
+                                            o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member, o->kept_capacity);
     } else if (nrows > 0) {
       k_row_count<<<dim3(nrows, g.H), 256, 0, stream>>>(g, true_bits, w.cbits, w.rrev, p->row_begin, nrows, w.row_cnt);
       const bool fill_lists = o->kept_idx && o->kept_capacity > 0;
