@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dam_internal.h"
 
@@ -27,6 +28,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 struct CapArgs {
   int Hq, Hkv, n, L, d, tbw;
+  int parts, chunk;  // matrix-core path: a row tile's stages of keys are shared by `parts` workgroups, `chunk` stages each
+  unsigned theta_key;          // fused form: the threshold as an ordered key,
+  float bmin, *out_bmin;       // and the minimum it was found against, stored by the second pass when wanted
   float c2;  // scale * log2(e): logits in log2 units
   int64_t q_sh, q_ss, k_sh, k_ss;
 };
@@ -81,7 +85,6 @@ __device__ __forceinline__ float to_f32(__hip_bfloat16 x) { return __bfloat162fl
 
 template <typename T, int MODE>
 __global__ __launch_bounds__(256) void k_capture_rows(CapArgs a, const T *__restrict__ q, const T *__restrict__ k,
-                                                      const unsigned *__restrict__ theta_key,
                                                       uint64_t *__restrict__ true_bits, float *__restrict__ attn_sum,
                                                       float *__restrict__ attn_cnt) {
   extern __shared__ float smem[];  // [d] query, then [i + 1] logits
@@ -112,7 +115,8 @@ __global__ __launch_bounds__(256) void k_capture_rows(CapArgs a, const T *__rest
   sum = (red[0] + red[1]) + (red[2] + red[3]);
   const float lse2 = mx + __builtin_amdgcn_logf(sum);  // v_log_f32 is the base-2 logarithm
   if (MODE == kEmitBits) {
-    const unsigned theta = *theta_key;
+    const unsigned theta = a.theta_key;
+    if (a.out_bmin && blockIdx.x == 0 && h == 0 && threadIdx.x == 0) *a.out_bmin = a.bmin;
     uint64_t *out = true_bits + ((int64_t)h * a.L + i) * a.tbw;
     for (int w = wave; w < a.tbw; w += 4) {
       const int j = w * 64 + lane;
@@ -131,8 +135,8 @@ __global__ __launch_bounds__(256) void k_capture_rows(CapArgs a, const T *__rest
 }
 
 // ================================================================================================
-// Matrix-core kernels (bf16, head_dim 128). One workgroup of 4 waves per (head, tile of 128 query
-// rows), each wave owning 32 rows; K moves through LDS in stages of 64 keys (16 KiB), double
+// Matrix-core kernels (bf16, head_dim 128). The two reducing passes: one workgroup of 4 waves per (head, tile of
+// 128 query rows), each wave owning 32 rows; K moves through LDS in stages of 64 keys (16 KiB), double
 // buffered, one barrier per stage. A K row is 16 chunks of 16 bytes; chunk c of row r is stored at
 // position c ^ (r & 15), so that the 16-byte operand reads of 16 consecutive rows cover all banks.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -142,40 +146,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int kRows = 128, kBlk = 32, kBlkBytes = kBlk * 256;
 constexpr int kXcd = 8;
 constexpr int kStageKeys = 64, kStageBytes = kStageKeys * 256;
-constexpr int kPadRow = 36;  // floats per row of a wave's 32 x 32 transposition tile (16-byte aligned, conflict-free)
-
-struct KStage {
-  uint4 r[4];
-};
-
-// This thread's four 16-byte pieces of the 64 keys starting at key0. `kp` points at this thread's
-// piece of key `threadIdx.x >> 4`; rows past the sequence end are redirected to the last row (such
-// keys are masked by causality anyway), which only a sequence's last stage has to look at.
-__device__ __forceinline__ KStage k_fetch(const __hip_bfloat16 *__restrict__ kp, int64_t k_ss, int key0, int n_keys) {
-  KStage st;
-  const __hip_bfloat16 *base = kp + (int64_t)key0 * k_ss;
-  if (key0 + kStageKeys <= n_keys) {  // workgroup-uniform
-#pragma unroll
-    for (int it = 0; it < 4; ++it) st.r[it] = *reinterpret_cast<const uint4 *>(base + (int64_t)(16 * it) * k_ss);
-  } else {
-    const int row = threadIdx.x >> 4;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int over = max(key0 + row + 16 * it - (n_keys - 1), 0);
-      st.r[it] = *reinterpret_cast<const uint4 *>(base + (int64_t)(16 * it - over) * k_ss);
-    }
-  }
-  return st;
-}
-
-__device__ __forceinline__ void k_stash(unsigned char *buf, const KStage &st) {
-  const int row = threadIdx.x >> 4, chunk = threadIdx.x & 15;
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    const int r = row + 16 * it;
-    *reinterpret_cast<uint4 *>(buf + r * 256 + ((chunk ^ (r & 15)) << 4)) = st.r[it];
-  }
-}
+constexpr int kMaxParts = 4;
 
 // One wave's quarter of a stage as four load-to-LDS copies (lane L of the wave fetches 16 bytes from
 // gbase + voff[it] and writes them to LDS byte lds_at + 4096 it + 16 L): rows wave * 4 + L / 16 + 16 it
@@ -193,22 +164,6 @@ __device__ __forceinline__ void k_copy_stage(unsigned lds_at, const void *gbase,
   DAM_CAP_COPY(2);
   DAM_CAP_COPY(3);
 #undef DAM_CAP_COPY
-}
-
-// S^T block of 32 keys: accumulator e of lane (n = lane & 31, hf = lane >> 5) is the raw logit
-// (before the scale) of query row n of the wave with key 8 (e / 4) + 4 hf + e % 4 of the block,
-// added to the start value `s`. kaddr[c] is this lane's operand c in the block at LDS offset 0; OFF
-// (a constant: buffer and half) lands in the instruction's offset field. All eight operand reads
-// are issued before the first product: the chain then waits for one LDS round trip, not for eight.
-template <int OFF>
-__device__ __forceinline__ f32x16 s_block(const unsigned char *const (&kaddr)[8], const bf16x8 (&qf)[8], f32x16 s) {
-  bf16x8 kf[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) kf[c] = *reinterpret_cast<const bf16x8 *>(kaddr[c] + OFF);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int c = 0; c < 8; ++c) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c], qf[c], s, 0, 0, 0);
-  return s;
 }
 
 // Bits 0 .. 31 of a 32-key block starting at key0 that are causal for row i (key <= i).
@@ -236,124 +191,129 @@ struct IntC {
   static constexpr int value = V;
 };
 
+// Which (query head, item) a workgroup takes: workgroup g runs on XCD g % 8. Where the KV heads divide evenly among the
+// XCDs, all query heads and items of one KV head stay on one of them, whose L2 then holds that head's K; otherwise (four
+// KV heads: half the chip would stay empty) they go round robin. Items of a KV head are handed out in ascending order.
+__device__ __forceinline__ void cap_numbering(const CapArgs &a, int items, int &h, int &item) {
+  const int G = a.Hq / a.Hkv, per_kv = G * items;
+  const bool even = a.Hkv % kXcd == 0;
+  const int within = even ? blockIdx.x / kXcd % per_kv : blockIdx.x / a.Hkv;
+  const int kv = even ? blockIdx.x / kXcd / per_kv * kXcd + blockIdx.x % kXcd : blockIdx.x % a.Hkv;
+  h = kv * G + within % G;
+  item = within / G;
+}
+
+// The log2-sum-exp of row i of head h from the parts the first pass left: lse2[part][head][L], -inf where a part held no
+// key of the row.
+__device__ __forceinline__ float row_lse(const CapArgs &a, const float *__restrict__ lse2, int h, int i) {
+  const float *at = lse2 + (int64_t)h * a.L + i;
+  if (a.parts == 1) return *at;
+  float v[kMaxParts], M = -INFINITY, sum = 0.0f;
+#pragma unroll
+  for (int x = 0; x < kMaxParts; ++x) v[x] = x < a.parts ? at[(int64_t)x * a.Hq * a.L] : -INFINITY;
+#pragma unroll
+  for (int x = 0; x < kMaxParts; ++x) M = fmaxf(M, v[x]);  // finite: part 0 holds key 0
+#pragma unroll
+  for (int x = 0; x < kMaxParts; ++x) sum += __builtin_amdgcn_exp2f(v[x] - M);
+  return M + __builtin_amdgcn_logf(sum);
+}
+
 // Emission of the summed form: probabilities p = exp2(logit * c2 - lse) of every causal pair, added to
-// A (and 1 to C). The kernel is bound by the read-modify-write of A and C, so K simply moves global
-// -> registers -> LDS one stage ahead, and a block's probabilities are transposed through LDS so that
-// a row's 32 keys are read and written as one 128-byte line.
-__global__ __launch_bounds__(256) void k_capture_sum(CapArgs a, const __hip_bfloat16 *__restrict__ q,
-                                                     const __hip_bfloat16 *__restrict__ k,
-                                                     const float *__restrict__ lse2, float *__restrict__ attn_sum,
-                                                     float *__restrict__ attn_cnt) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kStageBytes + 4 * 32 * kPadRow * 4];
-  // Workgroup numbering: workgroup g runs on XCD g % 8; all query heads and query tiles of one KV head
-  // get ids with the same g % 8, so that one XCD's L2 holds that head's K; within a KV head the long
-  // rows come first.
-  const int nQt = (a.n + kRows - 1) / kRows;
-  const int G = a.Hq / a.Hkv, per_kv = G * nQt;
-  const int xcd = blockIdx.x % kXcd, slot = blockIdx.x / kXcd;
-  const int kv = (slot / per_kv) * kXcd + xcd, within = slot % per_kv;
-  if (kv >= a.Hkv) return;
-  const int qt = nQt - 1 - within / G, h = kv * G + within % G;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// A (and 1 to C).
+// Bound by the read-modify-write of A and C (16 bytes per pair against 256 flop), so the kernel is laid out for bytes in
+// flight: a wave owns 32 rows x 64 keys and nothing else, fetches its part of A and C up front (16 KiB) behind the Q and K
+// operands, which come from L2 straight in the products' layout (no LDS, no barrier), and stores when its products are
+// done. The workgroup's waves lie side by side along the rows, 1 KiB of each (128 bytes per row and wave, spread over
+// 128 rows, took twice the time). In the product S = Q K^T a lane holds one key of 16 rows, so a row's 32 keys are one
+// 128-byte line across the lanes, whatever the row length. A row tile per workgroup with K staged through LDS had one
+// block of A and C in flight and as many workgroups as row tiles (256 at 32 heads x 1000 tokens): 208 -> 81 us there
+// with its first pass (3.8 TB/s of A and C without it), 64 heads x 4096 tokens 2150 -> 1740 us (5.3 TB/s).
+constexpr int kSumKeys = 64;
+constexpr int kSumSpan = 4 * kSumKeys;  // keys of a workgroup's waves side by side: 1 KiB of every row
+// Workgroups of a head: rows come in groups of 32, and the 8 groups of block R of kSumSpan rows need R + 1 of them each.
+__host__ __device__ constexpr int sum_items_before(int R) { return 4 * R * (R + 1); }
+// STREAM: non-temporal loads and stores. 5 to 10 % faster where a wave's 256 bytes of a row are whole 128-byte lines (A and
+// C pass through once), twice as slow where they are not (the neighbour's half of a line then does not meet it in L2).
+template <bool STREAM>
+__global__ __launch_bounds__(256, 2) void k_capture_sum(CapArgs a, const __hip_bfloat16 *__restrict__ q,
+                                                        const __hip_bfloat16 *__restrict__ k,
+                                                        const float *__restrict__ lse2, float *__restrict__ attn_sum,
+                                                        float *__restrict__ attn_cnt) {
+  const int blocks = (a.n + kSumSpan - 1) / kSumSpan;
+  int h, t;
+  cap_numbering(a, sum_items_before(blocks), h, t);
+  int R = (int)((sqrtf((float)t + 1.0f) - 1.0f) * 0.5f);  // sum_items_before(R) <= t
+  while (sum_items_before(R) > t) --R;
+  while (sum_items_before(R + 1) <= t) ++R;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hf = lane >> 5;
-  const int wave_first = qt * kRows + wave * 32;
-  const int i = wave_first + n;  // this lane's query row
-  const bool live = i < a.n;
-  const int kbase = n * 256 + ((hf ^ (n & 15)) << 4);
-  const unsigned char *kaddr[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) kaddr[c] = lds + (kbase ^ (c << 5));
-  const __hip_bfloat16 *kp = k + (int64_t)kv * a.k_sh + (int64_t)(threadIdx.x >> 4) * a.k_ss + (threadIdx.x & 15) * 8;
+  const int within = t - sum_items_before(R);
+  const int row0 = R * kSumSpan + within / (R + 1) * 32, key0 = within % (R + 1) * kSumSpan + wave * kSumKeys;
+  if (row0 >= a.n || key0 > row0 + 31) return;  // (whole waves) no row, or every key above the diagonal
+  const int n_blk = key0 + 32 <= row0 + 31 ? 2 : 1;  // blocks of 32 keys that reach below the diagonal
 
-  bf16x8 qf[8];
-  {
-    const __hip_bfloat16 *qp = q + (int64_t)h * a.q_sh + (int64_t)i * a.q_ss + 8 * hf;
+  bf16x8 qf[8], kf[2][8];
+  const __hip_bfloat16 *qp = q + (int64_t)h * a.q_sh + (int64_t)min(row0 + n, a.n - 1) * a.q_ss + 8 * hf;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      u32x4 raw = {0u, 0u, 0u, 0u};
-      if (live) raw = *reinterpret_cast<const u32x4 *>(qp + 16 * c);
-      qf[c] = __builtin_bit_cast(bf16x8, raw);
+  for (int c = 0; c < 8; ++c) qf[c] = *reinterpret_cast<const bf16x8 *>(qp + 16 * c);
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const __hip_bfloat16 *kp =
+        k + (int64_t)(h / (a.Hq / a.Hkv)) * a.k_sh + (int64_t)min(key0 + 32 * b + n, a.n - 1) * a.k_ss + 8 * hf;
+    if (b < n_blk) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) kf[b][c] = *reinterpret_cast<const bf16x8 *>(kp + 16 * c);
     }
   }
-  // stages that hold a key <= the tile's last live row
-  const int last_row = min(qt * kRows + kRows - 1, a.n - 1);
-  const int n_stage = last_row / kStageKeys + 1;
-  const float my_lse = live ? lse2[(int64_t)h * a.L + i] : 0.0f;
-  float *tile = reinterpret_cast<float *>(lds + 2 * kStageBytes) + wave * 32 * kPadRow;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  // One block of 32 keys: buffer BUF (= st & 1), half HALF of its stage.
-  auto block = [&](auto bufc, auto halfc, int st) {
-    constexpr int BUF = decltype(bufc)::value, HALF = decltype(halfc)::value;
-    constexpr int OFF = BUF * kStageBytes + HALF * kBlkBytes;
-    const int key0 = st * kStageKeys + HALF * kBlk;
-    if (key0 > wave_first + 31) return;  // wave-uniform: the block lies above all rows of this wave
-    const f32x16 s = s_block<OFF>(kaddr, qf, zero);
+  // accumulator e is row 8 (e / 4) + 4 hf + e % 4 of the wave with key n of the block
+  auto row_of = [&](int e) { return 8 * (e >> 2) + 4 * hf + (e & 3); };
+  float lse[16];
+  const float lse_n = row_lse(a, lse2, h, min(row0 + n, a.n - 1));
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float4 pv;
-      pv.x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * g], a.c2, -my_lse));
-      pv.y = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * g + 1], a.c2, -my_lse));
-      pv.z = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * g + 2], a.c2, -my_lse));
-      pv.w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * g + 3], a.c2, -my_lse));
-      *reinterpret_cast<float4 *>(tile + n * kPadRow + 8 * g + 4 * hf) = pv;
-    }
-    // the tile is private to the wave, whose LDS operations complete in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int col = (lane & 7) * 4, j0 = key0 + col;
+  for (int e = 0; e < 16; ++e) lse[e] = __shfl(lse_n, row_of(e));
+  const int64_t at0 = ((int64_t)h * a.L + row0) * a.L + key0;  // of row row0, key key0
+  // (one lane offset for every element: the row of an element differs by a wave-uniform step)
+  const int lane_at = 4 * hf * a.L + n;
+  auto take = [](const float *p) { return STREAM ? __builtin_nontemporal_load(p) : *p; };
+  auto put = [](float v, float *p) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
+  // (inside: every pair of the tile is causal and exists, so nothing is tested)
+  auto body = [&](auto inside) {
+    float av[2][16], cv[2][16];
+    auto wanted = [&](int b, int e) {
+      return decltype(inside)::value || (row0 + row_of(e) < a.n && key0 + 32 * b + n <= row0 + row_of(e));
+    };
+    auto each = [&](auto f) {
 #pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-      const int r = (lane >> 3) + 8 * pass, row = wave_first + r;
-      const float4 pv = *reinterpret_cast<const float4 *>(tile + r * kPadRow + col);
-      if (row < a.n && j0 <= row) {
-        float *ap = attn_sum + ((int64_t)h * a.L + row) * a.L + j0;
-        float *cp = attn_cnt ? attn_cnt + ((int64_t)h * a.L + row) * a.L + j0 : nullptr;
-        if (j0 + 3 <= row && (a.L & 3) == 0) {
-          float4 av = *reinterpret_cast<float4 *>(ap);
-          av.x += pv.x; av.y += pv.y; av.z += pv.z; av.w += pv.w;
-          *reinterpret_cast<float4 *>(ap) = av;
-          if (cp) {
-            float4 cv = *reinterpret_cast<float4 *>(cp);
-            cv.x += 1.0f; cv.y += 1.0f; cv.z += 1.0f; cv.w += 1.0f;
-            *reinterpret_cast<float4 *>(cp) = cv;
-          }
-        } else {
-          const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
+      for (int b = 0; b < 2; ++b)
+        if (b < n_blk) {
 #pragma unroll
-          for (int x = 0; x < 4; ++x)
-            if (j0 + x <= row) {
-              ap[x] += pe[x];
-              if (cp) cp[x] += 1.0f;
-            }
+          for (int e = 0; e < 16; ++e) f(b, e, at0 + (int64_t)(8 * (e >> 2) + (e & 3)) * a.L + 32 * b);
         }
+    };
+    each([&](int b, int e, int64_t at) { av[b][e] = wanted(b, e) ? take(attn_sum + at + lane_at) : 0.0f; });
+    if (attn_cnt) each([&](int b, int e, int64_t at) { cv[b][e] = wanted(b, e) ? take(attn_cnt + at + lane_at) : 0.0f; });
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      if (b < n_blk) {
+        f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[c], kf[b][c], s, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) av[b][e] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], a.c2, -lse[e]));
       }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    each([&](int b, int e, int64_t at) {
+      if (wanted(b, e)) put(av[b][e], attn_sum + at + lane_at);
+    });
+    if (attn_cnt)
+      each([&](int b, int e, int64_t at) {
+        if (wanted(b, e)) put(cv[b][e] + 1.0f, attn_cnt + at + lane_at);
+      });
   };
-
-  // One stage of 64 keys out of buffer BUF (= st & 1); the next stage's rows travel through registers
-  // meanwhile and are written to the other buffer behind the blocks.
-  auto stage = [&](auto bufc, int st) {
-    constexpr int BUF = decltype(bufc)::value;
-    KStage next;
-    const bool more = st + 1 < n_stage;
-    if (more) next = k_fetch(kp, a.k_ss, (st + 1) * kStageKeys, a.n);
-    block(bufc, IntC<0>{}, st);
-    block(bufc, IntC<1>{}, st);
-    if (more) k_stash(lds + (BUF ^ 1) * kStageBytes, next);
-    __syncthreads();
-  };
-
-  k_stash(lds, k_fetch(kp, a.k_ss, 0, a.n));
-  __syncthreads();
-  for (int st = 0; st < n_stage; st += 2) {
-    stage(IntC<0>{}, st);
-    if (st + 1 < n_stage) stage(IntC<1>{}, st + 1);  // workgroup-uniform
-  }
+  if (row0 + 31 < a.n && key0 + kSumKeys - 1 <= row0) body(std::true_type{});
+  else body(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -373,16 +333,12 @@ __global__ __launch_bounds__(256) void k_capture_sum(CapArgs a, const __hip_bflo
 template <int PASS>
 __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfloat16 *__restrict__ q,
                                                       const __hip_bfloat16 *__restrict__ k, float *__restrict__ lse2,
-                                                      const unsigned *__restrict__ theta_key,
                                                       uint64_t *__restrict__ true_bits) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kStageBytes];
-  // workgroup numbering as in k_capture_sum
   const int nQt = (a.n + kRows - 1) / kRows;
-  const int G = a.Hq / a.Hkv, per_kv = G * nQt;
-  const int xcd = blockIdx.x % kXcd, slot = blockIdx.x / kXcd;
-  const int kv = (slot / per_kv) * kXcd + xcd, within = slot % per_kv;
-  if (kv >= a.Hkv) return;
-  const int qt = nQt - 1 - within / G, h = kv * G + within % G;
+  int h, item;
+  cap_numbering(a, nQt * a.parts, h, item);
+  const int qt = nQt - 1 - item / a.parts, part = item % a.parts, kv = h / (a.Hq / a.Hkv);  // the long rows first
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 31, hf = lane >> 5;
   const int wave_first = qt * kRows + wave * 32;
@@ -395,7 +351,9 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
   // K rows reach LDS by load-to-LDS copies: thread t brings piece (t & 15) ^ (row & 15) of row
   // t >> 4 (+ 16 per copy) of a stage to position t & 15 of that row. Rows past the sequence end are
   // redirected to the last row (such keys are masked by causality anyway).
-  const char *kh = reinterpret_cast<const char *>(k + (int64_t)kv * a.k_sh);
+  // (everything below counts stages, blocks and keys from this part's first stage, an even one)
+  const int key_first = part * a.chunk * kStageKeys, n_keys = a.n - key_first, i_rel = i - key_first;
+  const char *kh = reinterpret_cast<const char *>(k + (int64_t)kv * a.k_sh + (int64_t)key_first * a.k_ss);
   const int64_t row_bytes = a.k_ss * 2;
   const int srow = threadIdx.x >> 4;
   const unsigned piece = (((threadIdx.x & 15) ^ (srow & 15)) << 4);
@@ -407,12 +365,12 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
   auto copy_stage = [&](int st, int buf) {
     const int key0 = st * kStageKeys;
     const char *gbase = kh + (int64_t)key0 * row_bytes;
-    if (key0 + kStageKeys <= a.n) {  // workgroup-uniform
+    if (key0 + kStageKeys <= n_keys) {  // workgroup-uniform
       k_copy_stage(lds_mine + buf * kStageBytes, gbase, voff_full);
     } else {
       unsigned voff[4];
 #pragma unroll
-      for (int it = 0; it < 4; ++it) voff[it] = (unsigned)(min(srow + 16 * it, a.n - 1 - key0) * row_bytes) + piece;
+      for (int it = 0; it < 4; ++it) voff[it] = (unsigned)(min(srow + 16 * it, n_keys - 1 - key0) * row_bytes) + piece;
       k_copy_stage(lds_mine + buf * kStageBytes, gbase, voff);
     }
   };
@@ -428,9 +386,37 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
     }
   }
   const int last_row = min(qt * kRows + kRows - 1, a.n - 1);
-  const int n_stage = last_row / kStageKeys + 1;        // stages that hold a key <= the tile's last live row
-  const int diag_g = qt * 4 + wave;                     // the wave's last block: the one the diagonal crosses
-  const int n_blocks = min(diag_g + 1, 2 * n_stage);    // blocks 0 .. n_blocks - 1 hold a key <= a row of the wave
+  const int word_first = 2 * part * a.chunk;
+  // the words up to the next part's, or to the end of the row
+  const int nw32 = part == a.parts - 1 ? a.tbw * 2 - word_first : min(a.tbw * 2 - word_first, 2 * a.chunk);
+  // the tile's words of this part from word w_done on (keys above the diagonal): all zero; written by the whole
+  // workgroup, 16 bytes per thread along a row
+  auto clear_words = [&](int w_done) {
+    const int rest = nw32 - w_done;
+    if (rest <= 0) return;
+    const int rows = min(kRows, a.n - qt * kRows), per_row = (rest + 3) / 4;
+    unsigned *tile_out = reinterpret_cast<unsigned *>(true_bits + ((int64_t)h * a.L + qt * kRows) * a.tbw) + word_first;
+    for (int x = threadIdx.x; x < rows * per_row; x += 256) {
+      const int r = x / per_row, w = w_done + 4 * (x % per_row);
+      unsigned *dst = tile_out + (int64_t)r * (2 * a.tbw) + w;
+      if (w + 3 < nw32 && (a.tbw & 1) == 0) {
+        *reinterpret_cast<uint4 *>(dst) = make_uint4(0u, 0u, 0u, 0u);
+      } else {
+        for (int y = 0; y < 4 && w + y < nw32; ++y) dst[y] = 0u;
+      }
+    }
+  };
+  if (key_first > last_row) {  // no key of this part lies below the tile's diagonal
+    if (PASS == 1) clear_words(0);
+    else if (live && hf == 0) lse2[((int64_t)part * a.Hq + h) * a.L + i] = -INFINITY;
+    return;
+  }
+  // this part's stages, of those that hold a key <= the tile's last live row. (In this form, quotient plus one: with the
+  // equal min(stages - first, chunk) the compiler takes 202 registers instead of 142, and a wave per SIMD less fits.)
+  const int n_stage = (unsigned)min(last_row - key_first, a.chunk * kStageKeys - 1) / kStageKeys + 1;
+  const int diag_g = qt * 4 + wave - 2 * part * a.chunk;  // the wave's last block: the one the diagonal crosses
+  // blocks 0 .. n_blocks - 1 hold a key <= a row of the wave (a wave with a live row needs no more than the stages hold)
+  const int n_blocks = min(diag_g + 1, 2 * a.chunk);
 
   // PASS 0 state: reference m_ref (log2 units; moves only when a maximum outgrows it by more than 8,
   // so that the sum rarely has to be rescaled) and the sum of exp2(t - m_ref) over this lane's keys
@@ -439,16 +425,16 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
   // ordered key: 0 keeps every causal entry, all ones keeps none; so do theta <= 0 and theta = +inf.
   float thr = 0.0f;
   if (PASS == 1) {
-    const float my_lse = live ? lse2[(int64_t)h * a.L + i] : 0.0f;
-    const unsigned tk = *theta_key;
+    const float my_lse = live ? row_lse(a, lse2, h, i) : 0.0f;
+    const unsigned tk = a.theta_key;
+    if (a.out_bmin && blockIdx.x == 0 && threadIdx.x == 0) *a.out_bmin = a.bmin;
     const float theta = __uint_as_float((tk & 0x80000000u) ? (tk & 0x7FFFFFFFu) : ~tk);
     if (tk == 0u || theta <= 0.0f) thr = -INFINITY;
     else if (tk == 0xFFFFFFFFu || !(theta < INFINITY)) thr = INFINITY;
     else thr = (my_lse + __builtin_amdgcn_logf(theta)) / a.c2;
   }
   unsigned words[4] = {0u, 0u, 0u, 0u};  // bits of the current 128-key group of this lane's row
-  unsigned *out32 = reinterpret_cast<unsigned *>(true_bits + ((int64_t)h * a.L + (live ? i : 0)) * a.tbw);
-  const int nw32 = a.tbw * 2;
+  unsigned *out32 = reinterpret_cast<unsigned *>(true_bits + ((int64_t)h * a.L + (live ? i : 0)) * a.tbw) + word_first;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   f32x16 S0 = zero, S1 = zero;  // logits of the even / odd blocks
   bf16x8 kf[8];                 // operands of the next chain
@@ -501,7 +487,7 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
       v = (v | (v << 4)) & 0x0F0F0F0Fu;
       unsigned mine = (v ^ 0x0F0F0F0Fu) << (4 * hf);
       mine |= (unsigned)__shfl_xor((int)mine, 32);
-      if (g == diag_g) mine &= causal_bits(i, g * kBlk);  // wave-uniform
+      if (g == diag_g) mine &= causal_bits(i_rel, g * kBlk);  // wave-uniform
       words[G4] = mine;
     }
   };
@@ -551,7 +537,7 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
     if (do_chain) {
       // entries above the diagonal start from -inf, so that the products leave them there
       f32x16 acc = zero;
-      if (PASS == 0 && g + 1 == diag_g) acc = causal_start(causal_bits(i, (g + 1) * kBlk) >> (4 * hf));
+      if (PASS == 0 && g + 1 == diag_g) acc = causal_start(causal_bits(i_rel, (g + 1) * kBlk) >> (4 * hf));
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c], qf[c], acc, 0, 0, 0);
@@ -607,26 +593,12 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
   }
   if (PASS == 0) {
     const float m_o = __shfl_xor(m_ref, 32), l_o = __shfl_xor(l_run, 32);
-    const float M = fmaxf(m_ref, m_o);  // finite: every live row holds key 0
+    const float M = fmaxf(m_ref, m_o);  // (-inf: no key of the row in this part)
     const float tot = l_run * __builtin_amdgcn_exp2f(m_ref - M) + l_o * __builtin_amdgcn_exp2f(m_o - M);
-    if (live && hf == 0) lse2[(int64_t)h * a.L + i] = M + __builtin_amdgcn_logf(tot);
+    if (live && hf == 0)
+      lse2[((int64_t)part * a.Hq + h) * a.L + i] = M == -INFINITY ? -INFINITY : M + __builtin_amdgcn_logf(tot);
   } else {
-    // words of the tile's rows past its last 128-key group: all zero (keys above the diagonal);
-    // written by the whole workgroup, 16 bytes per thread along a row
-    const int w_done = ((n_stage + 1) / 2) * 4, rest = nw32 - w_done;
-    if (rest > 0) {
-      const int rows = min(kRows, a.n - qt * kRows), per_row = (rest + 3) / 4;
-      unsigned *tile_out = reinterpret_cast<unsigned *>(true_bits + ((int64_t)h * a.L + qt * kRows) * a.tbw);
-      for (int x = threadIdx.x; x < rows * per_row; x += 256) {
-        const int r = x / per_row, w = w_done + 4 * (x % per_row);
-        unsigned *dst = tile_out + (int64_t)r * nw32 + w;
-        if (w + 3 < nw32 && (a.tbw & 1) == 0) {
-          *reinterpret_cast<uint4 *>(dst) = make_uint4(0u, 0u, 0u, 0u);
-        } else {
-          for (int y = 0; y < 4 && w + y < nw32; ++y) dst[y] = 0u;
-        }
-      }
-    }
+    clear_words(((n_stage + 1) / 2) * 4);
   }
 }
 
@@ -639,31 +611,48 @@ CapArgs make_args(const dam_capture_params *p) {
   a.c2 = (p->scale > 0.0f ? p->scale : 1.0f / sqrtf((float)p->head_dim)) * kLog2e;
   a.q_sh = p->q_stride[0]; a.q_ss = p->q_stride[1];
   a.k_sh = p->k_stride[0]; a.k_ss = p->k_stride[1];
+  a.theta_key = 0;
+  a.bmin = 0.0f;
+  a.out_bmin = nullptr;
+  a.parts = 1;
+  a.chunk = 0;
+  if (mfma_path(p)) {
+    // A workgroup walks its row tile's stages one after the other, about a microsecond each: while the row tiles alone
+    // leave the chip (three workgroups per CU) with room, up to four workgroups share a tile's stages, an even number
+    // each. 32 heads x 1000 tokens, first pass: 18 -> 12 us.
+    const int n_stage = (p->len + kStageKeys - 1) / kStageKeys, tiles = p->hq * ((p->len + kRows - 1) / kRows);
+    const int parts = std::max(1, std::min(kMaxParts, 1024 / tiles));
+    a.chunk = ((n_stage + parts - 1) / parts + 1) / 2 * 2;
+    a.parts = (n_stage + a.chunk - 1) / a.chunk;
+  }
   return a;
 }
 
 template <int MODE>
-void launch(const dam_capture_params *p, const void *q, const void *k, float *lse2, const unsigned *theta_key,
-            uint64_t *true_bits, float *attn_sum, float *attn_cnt, hipStream_t st) {
-  const CapArgs a = make_args(p);
+void launch(const dam_capture_params *p, const CapArgs &a, const void *q, const void *k, float *lse2, uint64_t *true_bits,
+            float *attn_sum, float *attn_cnt, hipStream_t st) {
   if (mfma_path(p)) {
     const int nQt = (a.n + kRows - 1) / kRows;
-    const dim3 grid((a.Hkv + kXcd - 1) / kXcd * kXcd * (a.Hq / a.Hkv) * nQt);
+    const int grid = a.Hq * nQt * a.parts;
     const __hip_bfloat16 *qb = static_cast<const __hip_bfloat16 *>(q), *kb = static_cast<const __hip_bfloat16 *>(k);
-    k_capture_pipe<0><<<grid, 256, 0, st>>>(a, qb, kb, lse2, theta_key, true_bits);
-    if (MODE == kEmitBits) k_capture_pipe<1><<<grid, 256, 0, st>>>(a, qb, kb, lse2, theta_key, true_bits);
-    else k_capture_sum<<<grid, 256, 0, st>>>(a, qb, kb, lse2, attn_sum, attn_cnt);
+    k_capture_pipe<0><<<grid, 256, 0, st>>>(a, qb, kb, lse2, true_bits);
+    if (MODE == kEmitBits) k_capture_pipe<1><<<grid, 256, 0, st>>>(a, qb, kb, lse2, true_bits);
+    else {
+      const bool whole_lines = ((a.L * 4) | (int)(reinterpret_cast<uintptr_t>(attn_sum) | reinterpret_cast<uintptr_t>(attn_cnt))) % 128 == 0;
+      auto kern = whole_lines ? k_capture_sum<true> : k_capture_sum<false>;
+      kern<<<a.Hq * sum_items_before((a.n + kSumSpan - 1) / kSumSpan), 256, 0, st>>>(a, qb, kb, lse2, attn_sum, attn_cnt);
+    }
     return;
   }
   const dim3 grid(a.n, a.Hq);
   const size_t lds = (size_t)(a.d + a.n) * sizeof(float);
   if (p->dtype == DAM_BF16)
     k_capture_rows<__hip_bfloat16, MODE><<<grid, 256, lds, st>>>(a, static_cast<const __hip_bfloat16 *>(q),
-                                                                static_cast<const __hip_bfloat16 *>(k), theta_key, true_bits,
+                                                                static_cast<const __hip_bfloat16 *>(k), true_bits,
                                                                 attn_sum, attn_cnt);
   else
     k_capture_rows<float, MODE><<<grid, 256, lds, st>>>(a, static_cast<const float *>(q), static_cast<const float *>(k),
-                                                       theta_key, true_bits, attn_sum, attn_cnt);
+                                                       true_bits, attn_sum, attn_cnt);
 }
 
 }  // namespace
@@ -686,18 +675,22 @@ int capture_validate(const dam_capture_params *p, const void *q, const void *k) 
 }
 
 size_t capture_lse_bytes(const dam_capture_params *p) {
-  return align_up((size_t)p->hq * (size_t)p->pcl * sizeof(float), 256);
+  return align_up((size_t)std::max(make_args(p).parts, 1) * p->hq * (size_t)p->pcl * sizeof(float), 256);
 }
 
 void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
-                              const unsigned *theta_key, uint64_t *true_bits, hipStream_t st) {
-  launch<kEmitBits>(p, q, k, lse2, theta_key, true_bits, nullptr, nullptr, st);
+                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, hipStream_t st) {
+  CapArgs a = make_args(p);
+  a.theta_key = theta_key;
+  a.bmin = bmin;
+  a.out_bmin = out_bmin;
+  launch<kEmitBits>(p, a, q, k, lse2, true_bits, nullptr, nullptr, st);
 }
 
 }  // namespace dam
 
 extern "C" size_t dam_capture_workspace(const dam_capture_params *p) {
-  if (!p || p->hq < 1 || p->pcl < 1) return 0;
+  if (!p || p->hq < 1 || p->pcl < 1 || p->len < 1) return 0;
   return dam::capture_lse_bytes(p);
 }
 
@@ -707,7 +700,7 @@ extern "C" int dam_capture_accumulate(const dam_capture_params *p, const void *q
   if (bad != DAM_OK) return bad;
   if (!attn_sum) return DAM_ERR_INVALID_ARG;
   if (!ws || ws_bytes < dam_capture_workspace(p)) return DAM_ERR_WORKSPACE;
-  launch<kEmitSum>(p, q, k, static_cast<float *>(ws), nullptr, nullptr, attn_sum, attn_cnt,
+  launch<kEmitSum>(p, make_args(p), q, k, static_cast<float *>(ws), nullptr, attn_sum, attn_cnt,
                    static_cast<hipStream_t>(stream_v));
   return dam::launch_status();
 }

@@ -71,7 +71,7 @@ __device__ __forceinline__ bool arrive_last(uint64_t *flags, int n, int self, ui
 int capture_validate(const dam_capture_params *p, const void *q, const void *k);
 size_t capture_lse_bytes(const dam_capture_params *p);
 void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
-                              const unsigned *theta_key, uint64_t *true_bits, hipStream_t stream);
+                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, hipStream_t stream);
 
 // dam_decode_mfma.hip: the partial pass of the grouped-query decode on the matrix cores. `fits` says
 // whether a call can take it (bf16, head_dim 128, at most 8 query heads per KV head, a head's cache rows

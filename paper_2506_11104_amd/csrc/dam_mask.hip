@@ -144,15 +144,6 @@ __global__ void k_threshold(float eps, float tau, const float *__restrict__ bmin
   *theta_key = threshold_key<LAMBDA2, FROM_A>(eps, tau, *bmin_p);
 }
 
-// minimum and key found on the host: into the workspace (and the caller's bmin) for the kernels that read them there
-__global__ void k_set_threshold(float bmin, unsigned key, float *__restrict__ ws_bmin, unsigned *__restrict__ ws_key,
-                                float *__restrict__ out_bmin) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  *ws_bmin = bmin;
-  *ws_key = key;
-  if (out_bmin) *out_bmin = bmin;
-}
-
 // ------------------------------------------------------------------------------------------------
 // App. B: the alternative transforms between the mean map and the threshold (dam_transform other
 // than Box-Cox). Every one of them is non-decreasing in the mean (raw sum: in the sum), so the same
@@ -2106,9 +2097,9 @@ Workspace carve(const dam_mask_params *p, void *ws) {
 
 // a1 and the threshold of a2. attn_sum / attn_cnt are only read in the general minimum. Returns how the
 // true-mask kernel gets the key: by value when the host could find it (then that kernel also writes out_bmin),
-// else from the workspace (in_workspace forces that form: the capture kernels read the key there).
+// else from the workspace.
 Threshold stage_threshold(const dam_mask_params *p, const Geom &g, const Workspace &w, const float *attn_sum,
-                          const float *attn_cnt, hipStream_t stream, float *out_bmin, bool in_workspace, bool *bmin_written) {
+                          const float *attn_cnt, hipStream_t stream, float *out_bmin, bool *bmin_written) {
   const Threshold from_ws{w.theta_key, 0u, 0.0f, nullptr};
   *bmin_written = false;
   if (p->transform != DAM_T_BOXCOX) {
@@ -2131,10 +2122,6 @@ Threshold stage_threshold(const dam_mask_params *p, const Geom &g, const Workspa
     if (half) key = attn_cnt ? threshold_key<1, false>(p->eps, p->tau, bmin) : threshold_key<1, true>(p->eps, p->tau, bmin);
     else key = attn_cnt ? threshold_key<2, false>(p->eps, p->tau, bmin) : threshold_key<2, true>(p->eps, p->tau, bmin);
     *bmin_written = true;
-    if (in_workspace) {
-      k_set_threshold<<<1, 64, 0, stream>>>(bmin, key, w.bmin, w.theta_key, out_bmin);
-      return from_ws;
-    }
     return Threshold{nullptr, key, bmin, out_bmin};
   }
   const int64_t n = (int64_t)g.H * g.L * g.L;
@@ -2285,7 +2272,7 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
 
   if (p->mode == DAM_FROM_ATTN_MAP) {
     bool bmin_written;
-    const Threshold thr = stage_threshold(p, g, w, attn_sum, attn_cnt, stream, o->bmin, false, &bmin_written);
+    const Threshold thr = stage_threshold(p, g, w, attn_sum, attn_cnt, stream, o->bmin, &bmin_written);
     // a2: true mask, one comparison per element
     dim3 grid((g.tbw + 3) / 4, (g.L + kTmRows - 1) / kTmRows, g.H);
     if (attn_cnt && p->transform == DAM_T_RAW_SUM)
@@ -2331,8 +2318,9 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
   float *lse2 = reinterpret_cast<float *>(static_cast<char *>(ws) + w.bytes);
   const uint8_t *dflag = nullptr, *vflag = nullptr;
   bool bmin_written;
-  stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, true, &bmin_written);
-  launch_capture_true_bits(cp, q, k, lse2, w.theta_key, o->true_bits, stream);
+  // (one causal capture of two tokens or more: the minimum, and so the threshold, is known on the host)
+  const Threshold thr = stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, &bmin_written);
+  launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits, stream);
   stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
   stage_extension(p, g, w, o, o->true_bits, dflag, vflag, stream);
   return launch_status();

@@ -1,0 +1,30 @@
+"""Captures whose row tiles are shared by up to four workgroups (stages of 64 keys, an even number per part), and the summed
+form around its tiles of 32 rows and 256 keys, with row lengths that are whole 128-byte lines and that are not."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from dam_testlib import dev
+from paper_2506_11104_amd import binding as B
+from paper_2506_11104_amd import workloads as wl
+from test_gpu_capture import ATOL, RTOL, fused_against_oracle, seq_pair
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,L,Hq,Hkv", [(255, 256, 2, 1), (257, 288, 8, 8), (385, 385, 3, 3), (513, 515, 2, 2), (600, 640, 16, 8),
+                                        (1025, 1026, 2, 1)])
+def test_parts_and_tiles(n, L, Hq, Hkv):
+    Q, K = seq_pair(700 + n, Hq, Hkv, n, 128, "bf16", std=1.2)
+    A, C = oracle.capture(Q, K, L)
+    a_dev, c_dev = (torch.zeros((Hq, L, L), dtype=torch.float32, device="cuda") for _ in range(2))
+    ws = torch.full((B.capture_workspace(B.capture_params(dev(Q, "bf16"), dev(K, "bf16"), L), "cuda").numel(),), 0xFF,
+                    dtype=torch.uint8, device="cuda")
+    B.dam_capture_accumulate(dev(Q, "bf16"), dev(K, "bf16"), a_dev, c_dev, ws=ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(c_dev.cpu().numpy(), C)
+    err = np.abs(a_dev.cpu().numpy() - A)
+    assert (err <= ATOL + RTOL * A).all(), err.max()
+    w = wl.scaled(wl.WORKLOADS["c2"], hq=Hq, hkv=Hkv, seq=n, pcl=n)
+    fused_against_oracle(Q, K, w, n, 128, 128, 0.05, 0.8, "bf16")
