@@ -920,8 +920,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const bool bad = qlive && (seen != 0u || seen_full) && !(l_tot >= 0x1p-100f && l_tot <= 0x1p100f);
       if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_bad = 1;  // read by thread 0 after the loop's barrier
     }
-    if (qlive) {
-      __hip_bfloat16 *op = out + wb * a.o_sb + whq * a.o_sh + (int64_t)qrow * a.o_ss;
+    // The rows go out as whole 256-byte lines: a lane holds eight bytes here and there of its query's row, so the wave
+    // turns its 32 rows around in 8 KiB of the K ring (16-byte chunk c of row r at c ^ (r & 15)) and every store
+    // instruction then covers four rows. (Eight bytes per lane and store straight from the accumulators: 2.6 us per item
+    // until the stores had drained, up to 20 us with every workgroup storing at once.) Not the V ring, which has to stay
+    // finite, and only when every wave's copies have landed; what the others still read of K belongs to no block.
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    {
+      int l = lane;  // (opaque, or the addresses below are computed once for all items and kept through the pipeline)
+      asm volatile("" : "+v"(l));
+      unsigned char *turn = lds + wave * 8192;
+      unsigned char *row_at = turn + (l & 31) * 256 + 8 * (l >> 5);
 #pragma unroll
       for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -929,12 +938,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           uint2 pr;
           pr.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
           pr.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
-          *reinterpret_cast<uint2 *>(op + 32 * db + 8 * g + 4 * hf) = pr;
+          *reinterpret_cast<uint2 *>(row_at + (((4 * db + g) ^ (l & 15)) << 4)) = pr;
         }
-      if (lse && hf == 0)
-        lse[((int64_t)wb * a.Hq + whq) * a.S + qrow] =
-            l_tot > 0.0f ? ((FAST ? 0.0f : m_run * c2) + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int row_first = wqt * kBM + wave * 32;
+      __hip_bfloat16 *op = out + wb * a.o_sb + whq * a.o_sh + (int64_t)row_first * a.o_ss + 8 * (l & 15);
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int r = 4 * it + (l >> 4);
+        const uint4 x = *reinterpret_cast<const uint4 *>(turn + r * 256 + (((l & 15) ^ (r & 15)) << 4));
+        if (row_first + r < a.S) *reinterpret_cast<uint4 *>(op + (int64_t)r * a.o_ss) = x;
+      }
     }
+    if (qlive && lse && hf == 0)
+      lse[((int64_t)wb * a.Hq + whq) * a.S + qrow] =
+          l_tot > 0.0f ? ((FAST ? 0.0f : m_run * c2) + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
   }  // next work item
 }
 
