@@ -630,8 +630,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float *__restrict__ lse, int *__restrict__ ctl, int2 *__restrict__ redo, const __hip_bfloat16 *__restrict__ kgath,
     const __hip_bfloat16 *__restrict__ vgath) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-  __shared__ int s_item[2];
-  __shared__ int s_wsum[4];
+  __shared__ int s_item[4];  // the next item: its number and queue, its listed tiles [t0, t1)
+  __shared__ int s_nblk;
   __shared__ int s_bad;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -665,38 +665,105 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   const int G = a.Hq / a.Hkv, n_pairs = a.B * a.Hkv, per_pair = G * a.nQt;
   const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcd - 1);  // XCC_ID, 4 bits
-  int hop = 0;
-  int prev_item = -1, prev_queue = 0;  // (thread 0 only) the item just finished
+  uint2 *blk_list = reinterpret_cast<uint2 *>(lds + kBlkList);
+  // The listed tiles [seg0, seg0 + n_seg) of an item that starts at t0 -> list of block descriptors in LDS (two words:
+  // first key, and mask offset | flags << 28), closed by a dummy entry that every read past the end returns. By wave 0
+  // alone, two tiles per lane: between two barriers, whatever the other waves do.
+  auto expand = [&](int t0, int seg0, int n_seg) {
+    int before = 0;
+#pragma unroll
+    for (int half = 0; half < kSegTiles / 64; ++half) {
+      const int x = half * 64 + lane;
+      int quarters = 0, col = 0, full = 0;
+      if (x < n_seg) {
+        const int kind = blk_kind[seg0 + x];
+        // a column outside the index's range (a list that was never filled) is pulled inside it: the result is
+        // then wrong, but every address formed from it stays within the head's rows
+        col = min(max(blk_col[seg0 + x], 0), a.nKt + (GATHER ? a.gather_rows / kBN : 0) - 1);
+        quarters = (kind >> 1) & 15;
+        full = kind & 1;
+      }
+      const int cnt = __popc(quarters);
+      int incl = cnt;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+      }
+      int at = before + incl - cnt;
+      before += __builtin_amdgcn_readlane(incl, 63);
+      while (quarters) {
+        const int qq = __builtin_ctz(quarters);
+        quarters &= quarters - 1;
+        const bool gth = GATHER && col >= a.nKt;  // gathered tile: rows of the head's gathered copy (flag 4)
+        const int key0 = gth ? min((col - a.nKt) * kBN + kBlkKeys * qq, a.gather_rows - kBlkKeys) : col * kBN + kBlkKeys * qq;
+        const unsigned off_bits = (unsigned)((seg0 + x - t0) * (kBM * 16) + 4 * qq);
+        blk_list[at++] = make_uint2((unsigned)key0, off_bits | (unsigned)(full | (gth ? 4 : 0)) << 28);
+      }
+      if (n_seg <= 64) break;
+    }
+    if (lane == 0) {
+      blk_list[before] = make_uint2(0u, 2u << 28);  // dummy: key 0, the item's first mask words, nothing kept
+      s_nblk = before;
+    }
+  };
+  // The queues. A workgroup's first item is its rank among those numbered for the same queue, without an atomic (all 512
+  // of them start at once, and atomics on one counter are served one after the other: up to 7 us); the counters hand out
+  // what follows.
+  auto queue_items = [&](int qu) { return (n_pairs - qu + kXcd - 1) / kXcd * per_pair; };  // of the pairs p with p % 8 == qu
+  auto queue_starts = [&](int qu) { return ((int)gridDim.x - qu + kXcd - 1) / kXcd; };
+  // (Each draws when its item is finished, not before: with the ticket's way laid under the stores of the item before, the 32k layer
+  // prefill of the 32k layer took 1170 instead of 1100 us.)
+  int hop = 0;  // (wave 0) queue of the next draw
+  int prev_item = -1, prev_queue = 0;  // (wave 0) the item just finished
+  bool first = true;
   while (true) {
     __syncthreads();  // previous item: every wave is done with the LDS rings, with s_item and with s_bad
-    if (tid == 0) {
+    if (wave == 0) {
       int item = -1, queue = 0;
       if (FAST) {
-        if (s_bad) {  // some row of the previous item needs the running reference: hand the item over
+        if (prev_item >= 0 && s_bad && lane == 0) {  // some row of the previous item needs the running reference: hand it over
           redo[atomicAdd(&ctl[kRedoCount], 1)] = make_int2(prev_item, prev_queue);
           s_bad = 0;
         }
-        for (; hop < kXcd; ++hop) {
+        if (first) {
+          queue = blockIdx.x % kXcd;
+          if ((int)blockIdx.x / kXcd < queue_items(queue)) item = blockIdx.x / kXcd;
+        }
+        while (item < 0 && hop < kXcd) {
           queue = (my_xcd + hop) & (kXcd - 1);
-          const int pairs_here = (n_pairs - queue + kXcd - 1) / kXcd;  // pairs p with p % 8 == queue
-          const int got = atomicAdd(&ctl[queue], 1);
-          if (got < pairs_here * per_pair) {
-            item = got;
-            break;
-          }
+          int got = 0;
+          if (lane == 0) got = atomicAdd(&ctl[queue], 1);
+          got = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
+          if (got < queue_items(queue)) item = got;
+          else ++hop;
         }
       } else {
-        const int got = atomicAdd(&ctl[kRedoNext], 1);
+        int got = 0;
+        if (lane == 0) got = atomicAdd(&ctl[kRedoNext], 1);
+        got = __builtin_amdgcn_readfirstlane(got);
         if (got < ctl[kRedoCount]) {  // (written by the kernel before this one)
           const int2 e = redo[got];
-          item = e.x;
-          queue = e.y;
+          item = __builtin_amdgcn_readfirstlane(e.x);
+          queue = __builtin_amdgcn_readfirstlane(e.y);
         }
       }
-      s_item[0] = item;
-      s_item[1] = queue;
+      first = false;
       prev_item = item;
       prev_queue = queue;
+      int t0 = 0, t1 = 0;
+      if (item >= 0) {
+        const int within = item % per_pair, hkv = ((item / per_pair) * kXcd + queue) % a.Hkv;
+        const int *rp = row_ptr + (int64_t)(hkv * G + within % G) * (a.nQt + 1) + (a.nQt - 1 - within / G);
+        t0 = __builtin_amdgcn_readfirstlane(rp[0]);
+        t1 = __builtin_amdgcn_readfirstlane(rp[1]);
+        expand(t0, t0, min(kSegTiles, t1 - t0));
+      }
+      if (lane == 0) {
+        s_item[0] = item;
+        s_item[1] = queue;
+        s_item[2] = t0;
+        s_item[3] = t1;
+      }
     }
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item[0]), queue = __builtin_amdgcn_readfirstlane(s_item[1]);
@@ -704,8 +771,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int pair = (item / per_pair) * kXcd + queue, within = item % per_pair;
     const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
     const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
-    const int t0 = __builtin_amdgcn_readfirstlane(row_ptr[(int64_t)whq * (a.nQt + 1) + wqt]);
-    const int t1 = __builtin_amdgcn_readfirstlane(row_ptr[(int64_t)whq * (a.nQt + 1) + wqt + 1]);
+    const int t0 = __builtin_amdgcn_readfirstlane(s_item[2]), t1 = __builtin_amdgcn_readfirstlane(s_item[3]);
     const int qrow_l = wave * 32 + n;  // this lane's query row inside the tile
     const int qrow = wqt * kBM + qrow_l;
     const bool qlive = qrow < a.S;
@@ -718,11 +784,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const unsigned char *vgg = reinterpret_cast<const unsigned char *>(vgath) + g_rows * vss2;
 
     // ---- the stream of occupied 32-key blocks of this query tile. The listed tiles are expanded, kSegTiles at
-    // a time, into a list of block descriptors in LDS (two words: first key, and mask offset | flags << 28),
-    // closed by a dummy entry that every read past the end returns. The pipeline then reads one descriptor per
+    // a time, into a list of block descriptors in LDS. The pipeline then reads one descriptor per
     // iteration (fetched before the previous iteration's barrier, so that nothing waits for it) instead of
     // walking tiles and quarters in scalar code, which cost a sixth of the instructions of an iteration.
-    uint2 *blk_list = reinterpret_cast<uint2 *>(lds + kBlkList);
     int n_blk = 0;      // entries of the current list before the dummy
     int cursor = 0;     // index of the descriptor held in pre_raw
     uint2 pre_raw = make_uint2(0u, 2u << 28);
@@ -731,39 +795,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const int key0 = __builtin_amdgcn_readfirstlane((int)raw.x);
       const unsigned meta = (unsigned)__builtin_amdgcn_readfirstlane((int)raw.y);
       return Blk{key0, (int)(meta & 0x0FFFFFFFu), (int)(meta >> 28)};
-    };
-    // tiles [seg0, seg0 + n_seg) -> list; called by the whole workgroup, ends with a barrier
-    auto expand = [&](int seg0, int n_seg) {
-      int quarters = 0, col = 0, full = 0;
-      if (tid < n_seg) {
-        const int kind = blk_kind[seg0 + tid];
-        // a column outside the index's range (a list that was never filled) is pulled inside it: the result is
-        // then wrong, but every address formed from it stays within the head's rows
-        col = min(max(blk_col[seg0 + tid], 0), a.nKt + (GATHER ? a.gather_rows / kBN : 0) - 1);
-        quarters = (kind >> 1) & 15;
-        full = kind & 1;
-      }
-      const int cnt = __popc(quarters);
-      int incl = cnt;
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
-      if (lane == 63) s_wsum[wave] = incl;  // kSegTiles = 128: only waves 0 and 1 hold tiles
-      __syncthreads();
-      int at = incl - cnt + (wave == 1 ? s_wsum[0] : 0);
-      while (quarters) {
-        const int qq = __builtin_ctz(quarters);
-        quarters &= quarters - 1;
-        const bool gth = GATHER && col >= a.nKt;  // gathered tile: rows of the head's gathered copy (flag 4)
-        const int key0 = gth ? min((col - a.nKt) * kBN + kBlkKeys * qq, a.gather_rows - kBlkKeys) : col * kBN + kBlkKeys * qq;
-        const unsigned off_bits = (unsigned)((seg0 + tid - t0) * (kBM * 16) + 4 * qq);
-        blk_list[at++] = make_uint2((unsigned)key0, off_bits | (unsigned)(full | (gth ? 4 : 0)) << 28);
-      }
-      const int total = s_wsum[0] + s_wsum[1];
-      if (tid == 0) blk_list[total] = make_uint2(0u, 2u << 28);  // dummy: key 0, the item's first mask words, nothing kept
-      __syncthreads();
-      n_blk = __builtin_amdgcn_readfirstlane(total);
     };
     // K or V block -> ring slot: two 1 KiB copies per wave; every address is the head's base plus a
     // 32-bit byte offset (the host checks that a head's rows span less than 4 GiB). In the ragged case
@@ -830,8 +861,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // one pass of the pipeline per segment of kSegTiles listed tiles (a query tile of c3 has at most 32;
       // the accumulators, the softmax state and the Q fragments carry over)
       for (int seg0 = t0; seg0 < t1; seg0 += kSegTiles) {
-        if (seg0 > t0) __syncthreads();  // every wave is done with the previous list and with the rings
-        expand(seg0, min(kSegTiles, t1 - seg0));
+        if (seg0 > t0) {
+          __syncthreads();  // every wave is done with the previous list and with the rings
+          if (wave == 0) expand(t0, seg0, min(kSegTiles, t1 - seg0));
+          __syncthreads();
+        }
+        n_blk = __builtin_amdgcn_readfirstlane(s_nblk);
         d[0] = decode(list_read(0));
         d[1] = decode(list_read(1));
         d[2] = decode(list_read(2));
