@@ -39,7 +39,10 @@ using namespace dam;
 constexpr int kXcd = 8;
 // control words at the start of the bf16 kernel's workspace: the eight queue counters, then the redo list's
 // length and its read cursor; the list itself (one int2 per work item at most) starts at byte kCtlBytes
-constexpr int kRedoCount = 8, kRedoNext = 9, kCtlWords = 10, kCtlBytes = 256;
+// The words lie 256 bytes apart: atomics on one line are served one after the other, and everything else that memory
+// channel holds waits behind them. (With the counters side by side and every finished workgroup trying all of them, the
+// workgroups still at work took up to 9 us for an iteration of 0.7: 2000 tokens, 32 heads.)
+constexpr int kCtlStep = 64, kRedoCount = 8 * kCtlStep, kRedoNext = 9 * kCtlStep, kCtlWords = 10, kCtlBytes = kCtlWords * kCtlStep * 4;
 
 struct AttnArgs {
   int B, Hq, Hkv, S, nQt, nKt, tile_m, tile_n, wpr;
@@ -709,7 +712,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // The queues. A workgroup's first item is its rank among those numbered for the same queue, without an atomic (all 512
   // of them start at once, and atomics on one counter are served one after the other: up to 7 us); the counters hand out
   // what follows.
-  auto queue_items = [&](int qu) { return (n_pairs - qu + kXcd - 1) / kXcd * per_pair; };  // of the pairs p with p % 8 == qu
+  // (Where the pairs do not divide evenly among the XCDs the queues hold every eighth item of all pairs instead: with
+  // four pairs half the chip would have nothing to start with.)
+  const bool even = n_pairs % kXcd == 0;
+  auto queue_items = [&](int qu) { return even ? n_pairs / kXcd * per_pair : (n_pairs * per_pair - qu + kXcd - 1) / kXcd; };
+  auto pair_of = [&](int item, int qu) { return even ? item / per_pair * kXcd + qu : (item * kXcd + qu) % n_pairs; };
+  auto within_of = [&](int item, int qu) { return even ? item % per_pair : (item * kXcd + qu) / n_pairs; };
   auto queue_starts = [&](int qu) { return ((int)gridDim.x - qu + kXcd - 1) / kXcd; };
   // (Each draws when its item is finished, not before: with the ticket's way laid under the stores of the item before, the 32k layer
   // prefill of the 32k layer took 1170 instead of 1100 us.)
@@ -732,7 +740,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         while (item < 0 && hop < kXcd) {
           queue = (my_xcd + hop) & (kXcd - 1);
           int got = 0;
-          if (lane == 0) got = atomicAdd(&ctl[queue], 1);
+          if (queue_items(queue) <= queue_starts(queue)) {  // all of them handed out as first items
+            ++hop;
+            continue;
+          }
+          if (lane == 0) got = atomicAdd(&ctl[queue * kCtlStep], 1);
           got = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
           if (got < queue_items(queue)) item = got;
           else ++hop;
@@ -752,7 +764,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       prev_queue = queue;
       int t0 = 0, t1 = 0;
       if (item >= 0) {
-        const int within = item % per_pair, hkv = ((item / per_pair) * kXcd + queue) % a.Hkv;
+        const int within = within_of(item, queue), hkv = pair_of(item, queue) % a.Hkv;
         const int *rp = row_ptr + (int64_t)(hkv * G + within % G) * (a.nQt + 1) + (a.nQt - 1 - within / G);
         t0 = __builtin_amdgcn_readfirstlane(rp[0]);
         t1 = __builtin_amdgcn_readfirstlane(rp[1]);
@@ -768,7 +780,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item[0]), queue = __builtin_amdgcn_readfirstlane(s_item[1]);
     if (item < 0) break;
-    const int pair = (item / per_pair) * kXcd + queue, within = item % per_pair;
+    const int pair = pair_of(item, queue), within = within_of(item, queue);
     const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
     const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
     const int t0 = __builtin_amdgcn_readfirstlane(s_item[2]), t1 = __builtin_amdgcn_readfirstlane(s_item[3]);
@@ -1000,7 +1012,7 @@ __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloa
                                                    __hip_bfloat16 *__restrict__ kgath, __hip_bfloat16 *__restrict__ vgath,
                                                    int *__restrict__ queue_next) {
   // (also resets the work queues of the attention kernel that follows: one launch less per call)
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kCtlWords) queue_next[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kCtlWords) queue_next[threadIdx.x * kCtlStep] = 0;
   const int bh = blockIdx.y, b = bh / a.Hq, hq = bh % a.Hq, hkv = hq / (a.Hq / a.Hkv);
   const int s = blockIdx.x * 16 + (threadIdx.x >> 4), chunk = threadIdx.x & 15;
   if (s >= a.gather_rows) return;
@@ -1016,26 +1028,16 @@ __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloa
 }
 
 __global__ void k_zero_queues(int *queue_next) {
-  if (threadIdx.x < kCtlWords) queue_next[threadIdx.x] = 0;
+  if (threadIdx.x < kCtlWords) queue_next[threadIdx.x * kCtlStep] = 0;
 }
 
 // Every work item onto the redo list, in the order the queues would hand them out (DAM_ATTN_RUNNING_REFERENCE:
 // the caller asks for the variant with a running reference from the start).
 __global__ void k_list_all_items(AttnArgs a, int *__restrict__ ctl, int2 *__restrict__ redo) {
-  const int n_pairs = a.B * a.Hkv, per_pair = (a.Hq / a.Hkv) * a.nQt;
-  const int rounds = (n_pairs + kXcd - 1) / kXcd * per_pair;
-  int n_q[kXcd], total = 0;
-  for (int x = 0; x < kXcd; ++x) {
-    n_q[x] = (n_pairs - x + kXcd - 1) / kXcd * per_pair;  // items of queue x
-    total += n_q[x];
-  }
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < rounds * kXcd; e += gridDim.x * blockDim.x) {
-    const int queue = e % kXcd, item = e / kXcd;
-    if (item >= n_q[queue]) continue;
-    int at = 0;  // valid entries before (item, queue) in round-robin order
-    for (int x = 0; x < kXcd; ++x) at += min(n_q[x], item + (x < queue ? 1 : 0));
-    redo[at] = make_int2(item, queue);
-  }
+  const int total = a.B * a.Hq * a.nQt;
+  // (queues of unequal length differ by one item: entry e is item e / 8 of queue e % 8 in both cases)
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x)
+    redo[e] = make_int2(e / kXcd, e % kXcd);
   if (blockIdx.x == 0 && threadIdx.x == 0) ctl[kRedoCount] = total;
 }
 
@@ -1128,7 +1130,7 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
                                                     mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
     return launch_status();
   }
-  const int blocks = (p->batch * p->hkv + kXcd - 1) / kXcd * kXcd * (p->hq / p->hkv) * a.nQt;  // an upper bound of the work items
+  const int blocks = p->batch * p->hq * a.nQt;  // work items
   // (queried per call: the library keeps no state, and the device may differ from call to call)
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
