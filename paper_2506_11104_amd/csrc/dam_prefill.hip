@@ -37,12 +37,11 @@ namespace {
 using namespace dam;
 
 constexpr int kXcd = 8;
-// control words at the start of the bf16 kernel's workspace: the eight queue counters, then the redo list's
-// length and its read cursor; the list itself (one int2 per work item at most) starts at byte kCtlBytes
+// control words at the start of the bf16 kernel's workspace: the eight queue counters
 // The words lie 256 bytes apart: atomics on one line are served one after the other, and everything else that memory
 // channel holds waits behind them. (With the counters side by side and every finished workgroup trying all of them, the
 // workgroups still at work took up to 9 us for an iteration of 0.7: 2000 tokens, 32 heads.)
-constexpr int kCtlStep = 64, kRedoCount = 8 * kCtlStep, kRedoNext = 9 * kCtlStep, kCtlWords = 10, kCtlBytes = kCtlWords * kCtlStep * 4;
+constexpr int kCtlStep = 64, kCtlWords = kXcd, kCtlBytes = kCtlWords * kCtlStep * 4;
 
 struct AttnArgs {
   int B, Hq, Hkv, S, nQt, nKt, tile_m, tile_n, wpr;
@@ -621,27 +620,39 @@ __device__ __forceinline__ void pipe_iter_seg(const unsigned char *__restrict__ 
 // may reach past the end of K and V.
 // GATHER: the block index may hold gathered column tiles (tile index >= nKt), whose K / V rows come from
 // the per-head gathered copies.
-// FAST: the softmax without a running maximum (see pipe_iter). Work items come from the eight queues; an item
-// in which some row's sum of weights left the safe range is appended to the redo list (ctl[kRedoCount], then
-// `redo`), and the FAST = false instantiation, launched behind this one, takes exactly those items and overwrites
-// their rows. With well-scaled inputs the list stays empty.
-template <bool RAGGED, bool GATHER, bool FAST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prefill_bf16_pipe(
-    AttnArgs a, const __hip_bfloat16 *__restrict__ q, const __hip_bfloat16 *__restrict__ k,
-    const __hip_bfloat16 *__restrict__ v, const int *__restrict__ row_ptr, const int *__restrict__ blk_col,
-    const uint8_t *__restrict__ blk_kind, const uint64_t *__restrict__ tile_bits, __hip_bfloat16 *__restrict__ out,
-    float *__restrict__ lse, int *__restrict__ ctl, int2 *__restrict__ redo, const __hip_bfloat16 *__restrict__ kgath,
-    const __hip_bfloat16 *__restrict__ vgath) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-  __shared__ int s_item[4];  // the next item: its number and queue, its listed tiles [t0, t1)
-  __shared__ int s_nblk;
-  __shared__ int s_bad;
+// FAST: the softmax without a running maximum (see pipe_iter). An item in which some row's sum of weights left the safe
+// range goes onto the workgroup's own list (Shared::redo, threaded through `next`, a word per item), and when the queues
+// are empty the FAST = false instantiation takes exactly those items and overwrites their rows. With well-scaled inputs
+// the lists stay empty. (Behind the items, not among them: both variants inside one loop over the items spilled registers
+// in its pipeline. As a launch of its own the second variant cost 4 to 5 us per call, almost always for nothing.)
+struct Shared {
+  int item[4];  // the next item: its number and queue, its listed tiles [t0, t1)
+  int nblk, bad;
+  int redo;     // first item of the workgroup's redo list (8 * item + queue), or -1
+};
+struct Operands {
+  const __hip_bfloat16 *q, *k, *v;
+  const int *row_ptr, *blk_col;
+  const uint8_t *blk_kind;
+  const uint64_t *tile_bits;
+  __hip_bfloat16 *out;
+  float *lse;
+  int *ctl, *next;
+  const __hip_bfloat16 *kgath, *vgath;
+};
 
+template <bool RAGGED, bool GATHER, bool FAST>
+__device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands &t, unsigned char *lds, Shared &sh, bool from_list) {
+  const __hip_bfloat16 *__restrict__ q = t.q, *__restrict__ k = t.k, *__restrict__ v = t.v;
+  const int *__restrict__ row_ptr = t.row_ptr, *__restrict__ blk_col = t.blk_col;
+  const uint8_t *__restrict__ blk_kind = t.blk_kind;
+  const uint64_t *__restrict__ tile_bits = t.tile_bits;
+  __hip_bfloat16 *__restrict__ out = t.out;
+  float *__restrict__ lse = t.lse;
+  const __hip_bfloat16 *__restrict__ kgath = t.kgath, *__restrict__ vgath = t.vgath;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, hf = lane >> 5;
   const float c2 = a.scale * 1.4426950408889634f;
-  if (!FAST && ctl[kRedoCount] == 0) return;  // nothing to redo (the usual case): leave before any set-up
-  if (FAST && tid == 0) s_bad = 0;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
 
   // LDS byte offsets of this lane's operand fragments inside a block (layout note above), chunk pair 0
@@ -659,12 +670,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int bits_addr = wave * 256 + lane * 4;             // where its copy lands inside a bits slot
   const unsigned lds_kv = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);              // this wave's part of a K/V slot
   const unsigned lds_bits = __builtin_amdgcn_readfirstlane(lds_base + kBitsRing + wave * 256);  // ... of a bits slot
-
-  // The first two iterations of an item multiply weights that are exactly zero (the leading dummy
-  // blocks) with whatever the V ring holds: it has to be finite. Later items find the previous item's
-  // V rows there; the first one would find what an earlier kernel left in LDS, so clear the ring once.
-  for (int at = tid * 16; at < kRing * kBlkBytes; at += 256 * 16)
-    *reinterpret_cast<uint4 *>(lds + kVRing + at) = make_uint4(0u, 0u, 0u, 0u);
 
   const int G = a.Hq / a.Hkv, n_pairs = a.B * a.Hkv, per_pair = G * a.nQt;
   const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcd - 1);  // XCC_ID, 4 bits
@@ -706,7 +711,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     if (lane == 0) {
       blk_list[before] = make_uint2(0u, 2u << 28);  // dummy: key 0, the item's first mask words, nothing kept
-      s_nblk = before;
+      sh.nblk = before;
     }
   };
   // The queues. A workgroup's first item is its rank among those numbered for the same queue, without an atomic (all 512
@@ -719,20 +724,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto pair_of = [&](int item, int qu) { return even ? item / per_pair * kXcd + qu : (item * kXcd + qu) % n_pairs; };
   auto within_of = [&](int item, int qu) { return even ? item % per_pair : (item * kXcd + qu) / n_pairs; };
   auto queue_starts = [&](int qu) { return ((int)gridDim.x - qu + kXcd - 1) / kXcd; };
-  // (Each draws when its item is finished, not before: with the ticket's way laid under the stores of the item before, the 32k layer
-  // prefill of the 32k layer took 1170 instead of 1100 us.)
+  // (Each draws when its item is finished: with the ticket's way laid under the stores of the item before, the prefill of
+  // the 32k layer took up to 5 % longer.)
   int hop = 0;  // (wave 0) queue of the next draw
   int prev_item = -1, prev_queue = 0;  // (wave 0) the item just finished
   bool first = true;
   while (true) {
-    __syncthreads();  // previous item: every wave is done with the LDS rings, with s_item and with s_bad
+    __syncthreads();  // previous item: every wave is done with the LDS rings, with s_item and with sh.bad
     if (wave == 0) {
       int item = -1, queue = 0;
-      if (FAST) {
-        if (prev_item >= 0 && s_bad && lane == 0) {  // some row of the previous item needs the running reference: hand it over
-          redo[atomicAdd(&ctl[kRedoCount], 1)] = make_int2(prev_item, prev_queue);
-          s_bad = 0;
+      if (FAST && prev_item >= 0 && sh.bad && lane == 0) {  // some row of the previous item needs the running reference
+        const int id = prev_item * kXcd + prev_queue;
+        t.next[id] = sh.redo;
+        sh.redo = id;
+        sh.bad = 0;
+      }
+      if (!FAST && from_list) {
+        const int id = __builtin_amdgcn_readfirstlane(sh.redo);
+        if (id >= 0) {
+          item = id / kXcd;
+          queue = id % kXcd;
+          if (lane == 0) sh.redo = t.next[id];
         }
+      } else {
         if (first) {
           queue = blockIdx.x % kXcd;
           if ((int)blockIdx.x / kXcd < queue_items(queue)) item = blockIdx.x / kXcd;
@@ -744,19 +758,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             ++hop;
             continue;
           }
-          if (lane == 0) got = atomicAdd(&ctl[queue * kCtlStep], 1);
+          if (lane == 0) got = atomicAdd(&t.ctl[queue * kCtlStep], 1);
           got = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
           if (got < queue_items(queue)) item = got;
           else ++hop;
-        }
-      } else {
-        int got = 0;
-        if (lane == 0) got = atomicAdd(&ctl[kRedoNext], 1);
-        got = __builtin_amdgcn_readfirstlane(got);
-        if (got < ctl[kRedoCount]) {  // (written by the kernel before this one)
-          const int2 e = redo[got];
-          item = __builtin_amdgcn_readfirstlane(e.x);
-          queue = __builtin_amdgcn_readfirstlane(e.y);
         }
       }
       first = false;
@@ -771,19 +776,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         expand(t0, t0, min(kSegTiles, t1 - t0));
       }
       if (lane == 0) {
-        s_item[0] = item;
-        s_item[1] = queue;
-        s_item[2] = t0;
-        s_item[3] = t1;
+        sh.item[0] = item;
+        sh.item[1] = queue;
+        sh.item[2] = t0;
+        sh.item[3] = t1;
       }
     }
     __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(s_item[0]), queue = __builtin_amdgcn_readfirstlane(s_item[1]);
+    const int item = __builtin_amdgcn_readfirstlane(sh.item[0]), queue = __builtin_amdgcn_readfirstlane(sh.item[1]);
     if (item < 0) break;
     const int pair = pair_of(item, queue), within = within_of(item, queue);
     const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
     const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
-    const int t0 = __builtin_amdgcn_readfirstlane(s_item[2]), t1 = __builtin_amdgcn_readfirstlane(s_item[3]);
+    const int t0 = __builtin_amdgcn_readfirstlane(sh.item[2]), t1 = __builtin_amdgcn_readfirstlane(sh.item[3]);
     const int qrow_l = wave * 32 + n;  // this lane's query row inside the tile
     const int qrow = wqt * kBM + qrow_l;
     const bool qlive = qrow < a.S;
@@ -878,7 +883,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           if (wave == 0) expand(t0, seg0, min(kSegTiles, t1 - seg0));
           __syncthreads();
         }
-        n_blk = __builtin_amdgcn_readfirstlane(s_nblk);
+        n_blk = __builtin_amdgcn_readfirstlane(sh.nblk);
         d[0] = decode(list_read(0));
         d[1] = decode(list_read(1));
         d[2] = decode(list_read(2));
@@ -965,7 +970,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // a row with a kept entry whose sum of weights is zero, tiny, huge, infinite or NaN: its logits lie outside
       // what exp2 without a reference can carry (|logit * log2 e| of the order of 100)
       const bool bad = qlive && (seen != 0u || seen_full) && !(l_tot >= 0x1p-100f && l_tot <= 0x1p100f);
-      if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_bad = 1;  // read by thread 0 after the loop's barrier
+      if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) sh.bad = 1;  // read by thread 0 after the loop's barrier
     }
     // The rows go out as whole 256-byte lines: a lane holds eight bytes here and there of its query's row, so the wave
     // turns its 32 rows around in 8 KiB of the K ring (16-byte chunk c of row r at c ^ (r & 15)) and every store
@@ -1005,6 +1010,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }  // next work item
 }
 
+// The second variant behind the first is a function of its own, called when there is something on the list: inlined, it
+// spilled registers of the first. It finds its arguments in LDS (every wave takes them back into scalar registers).
+struct Spilled {
+  AttnArgs a;
+  Operands t;
+};
+template <typename T>
+__device__ __forceinline__ T uniform_copy(const T &from) {
+  T to;
+  static_assert(sizeof(T) % 4 == 0, "copied by words");
+  const int *src = reinterpret_cast<const int *>(&from);
+  int *dst = reinterpret_cast<int *>(&to);
+#pragma unroll
+  for (unsigned x = 0; x < sizeof(T) / 4; ++x) dst[x] = __builtin_amdgcn_readfirstlane(src[x]);
+  return to;
+}
+template <bool RAGGED, bool GATHER>
+__device__ __attribute__((noinline)) void prefill_with_reference(
+    __attribute__((address_space(3))) const Spilled *args, __attribute__((address_space(3))) unsigned char *lds,
+    __attribute__((address_space(3))) Shared *sh) {
+  const Spilled s = uniform_copy(*(const Spilled *)args);
+  prefill_items<RAGGED, GATHER, false>(s.a, s.t, (unsigned char *)lds, *(Shared *)sh, true);
+}
+
+// FAST = false: every item with the running reference (DAM_ATTN_RUNNING_REFERENCE).
+template <bool RAGGED, bool GATHER, bool FAST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prefill_bf16_pipe(AttnArgs a, Operands t) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  __shared__ Shared sh;
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    sh.bad = 0;
+    sh.redo = -1;
+  }
+  // The first two iterations of an item multiply weights that are exactly zero (the leading dummy
+  // blocks) with whatever the V ring holds: it has to be finite. Later items find the previous item's
+  // V rows there; the first one would find what an earlier kernel left in LDS, so clear the ring once.
+  for (int at = tid * 16; at < kRing * kBlkBytes; at += 256 * 16)
+    *reinterpret_cast<uint4 *>(lds + kVRing + at) = make_uint4(0u, 0u, 0u, 0u);
+
+  prefill_items<RAGGED, GATHER, FAST>(a, t, lds, sh, false);
+  if constexpr (FAST) {
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(sh.redo) < 0) return;
+    __shared__ Spilled args;
+    if (tid == 0) args = Spilled{a, t};
+    __syncthreads();
+    prefill_with_reference<RAGGED, GATHER>((__attribute__((address_space(3))) const Spilled *)&args,
+                                           (__attribute__((address_space(3))) unsigned char *)lds,
+                                           (__attribute__((address_space(3))) Shared *)&sh);
+  }
+}
+
 // Copies of the K and V rows of every head's matched columns (gather_idx, -1 = empty slot -> zeros) as
 // [batch][hq][gather_rows] rows at the row stride of K (of V), so that a gathered tile is loaded like any other.
 __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloat16 *__restrict__ k,
@@ -1029,16 +1087,6 @@ __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloa
 
 __global__ void k_zero_queues(int *queue_next) {
   if (threadIdx.x < kCtlWords) queue_next[threadIdx.x * kCtlStep] = 0;
-}
-
-// Every work item onto the redo list, in the order the queues would hand them out (DAM_ATTN_RUNNING_REFERENCE:
-// the caller asks for the variant with a running reference from the start).
-__global__ void k_list_all_items(AttnArgs a, int *__restrict__ ctl, int2 *__restrict__ redo) {
-  const int total = a.B * a.Hq * a.nQt;
-  // (queues of unequal length differ by one item: entry e is item e / 8 of queue e % 8 in both cases)
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x)
-    redo[e] = make_int2(e / kXcd, e % kXcd);
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctl[kRedoCount] = total;
 }
 
 int validate(const dam_attn_params *p, const void *q, const void *k, const void *v, const dam_mask_view *mk,
@@ -1094,18 +1142,18 @@ AttnArgs make_args(const dam_attn_params *p) {
 
 }  // namespace
 
-// bytes of the redo list: an int2 per (batch, query head, query tile), rounded up to 256
+// bytes of the redo lists' links: a word per (batch, query head, query tile) and one per queue, rounded up to 256
 static size_t redo_bytes(const dam_attn_params *p) {
   const size_t items = (size_t)p->batch * p->hq * (size_t)((p->seq + p->tile_m - 1) / p->tile_m);
-  return (items * sizeof(int2) + 255) / 256 * 256;
+  return ((items + kXcd) * sizeof(int) + 255) / 256 * 256;
 }
 
 extern "C" size_t dam_sparse_attn_prefill_workspace(const dam_attn_params *p) {
   if (!p || p->batch < 1 || p->hkv < 1 || p->hq < 1 || p->seq < 1 || p->gather_rows < 0) return 0;
   if (p->dtype != DAM_BF16) return 0;
   if (p->hq % p->hkv || p->tile_m < 64) return 0;
-  // the control words of the bf16 kernel (queue counters, redo list length and cursor), the redo list (one entry per
-  // work item at most), then the gathered K and V copies (rows at the caches' strides)
+  // the control words of the bf16 kernel (queue counters), the links of the redo lists, then the gathered K and V copies
+  // (rows at the caches' strides)
   return kCtlBytes + redo_bytes(p) +
          (size_t)p->batch * p->hq * p->gather_rows * (size_t)(p->k_stride[2] + p->v_stride[2]) * sizeof(__hip_bfloat16);
 }
@@ -1137,43 +1185,30 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return DAM_ERR_DEVICE;
   int *ctl = static_cast<int *>(ws);
-  int2 *redo = reinterpret_cast<int2 *>(static_cast<char *>(ws) + kCtlBytes);
+  int *next = reinterpret_cast<int *>(static_cast<char *>(ws) + kCtlBytes);
   __hip_bfloat16 *kgath = reinterpret_cast<__hip_bfloat16 *>(static_cast<char *>(ws) + kCtlBytes + redo_bytes(p));
   __hip_bfloat16 *vgath = kgath + (size_t)p->batch * p->hq * a.gather_rows * (size_t)a.k_ss;
   if (a.gather_rows > 0)
     k_gather_kv<<<dim3((a.gather_rows + 15) / 16, p->batch * p->hq), 256, 0, st>>>(
         a, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->gather_idx,
         kgath, vgath, ctl);
-  else
+  else if (blocks > 2 * n_cu)  // (fewer items are all first items: no counter is asked)
     k_zero_queues<<<1, 64, 0, st>>>(ctl);
   const int persistent = std::min(blocks, 2 * n_cu);  // two workgroups fit a CU (registers and LDS)
   const bool ragged = p->seq % kBlkKeys != 0, gather = a.gather_rows > 0;
-  using Kernel = void (*)(AttnArgs, const __hip_bfloat16 *, const __hip_bfloat16 *, const __hip_bfloat16 *, const int *,
-                          const int *, const uint8_t *, const uint64_t *, __hip_bfloat16 *, float *, int *, int2 *,
-                          const __hip_bfloat16 *, const __hip_bfloat16 *);
+  using Kernel = void (*)(AttnArgs, Operands);
   static const Kernel kernels[2][4] = {
       {k_prefill_bf16_pipe<false, false, false>, k_prefill_bf16_pipe<true, false, false>,
        k_prefill_bf16_pipe<false, true, false>, k_prefill_bf16_pipe<true, true, false>},
       {k_prefill_bf16_pipe<false, false, true>, k_prefill_bf16_pipe<true, false, true>,
        k_prefill_bf16_pipe<false, true, true>, k_prefill_bf16_pipe<true, true, true>}};
-  const int which = (ragged ? 1 : 0) + (gather ? 2 : 0);
-  const bool reference_only = (p->flags & DAM_ATTN_RUNNING_REFERENCE) != 0;
-  // first the softmax without a running maximum over every work item; then the variant with one over the items
-  // the first pass put on the redo list (none for well-scaled inputs: its workgroups then leave at once)
-  for (int fast = 1; fast >= 0; --fast) {
-    // (idempotent; set on every call rather than remembered in a static)
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[fast][which]), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kPipeLds) != hipSuccess)
-      return DAM_ERR_DEVICE;
-    if (fast && reference_only) {
-      k_list_all_items<<<std::min((blocks + 255) / 256, 256), 256, 0, st>>>(a, ctl, redo);
-      continue;
-    }
-    kernels[fast][which]<<<persistent, 256, kPipeLds, st>>>(a, (const __hip_bfloat16 *)q, (const __hip_bfloat16 *)k,
-                                                            (const __hip_bfloat16 *)v, mk->blk_row_ptr, mk->blk_col,
-                                                            mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl,
-                                                            redo, kgath, vgath);
-  }
+  const Kernel kern = kernels[(p->flags & DAM_ATTN_RUNNING_REFERENCE) ? 0 : 1][(ragged ? 1 : 0) + (gather ? 2 : 0)];
+  // (idempotent; set on every call rather than remembered in a static)
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kPipeLds) != hipSuccess)
+    return DAM_ERR_DEVICE;
+  const Operands t{(const __hip_bfloat16 *)q, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->blk_row_ptr, mk->blk_col,
+                   mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl, next, kgath, vgath};
+  kern<<<persistent, 256, kPipeLds, st>>>(a, t);
   return launch_status();
 }
 
