@@ -238,3 +238,26 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "libdam.so"))
     with pytest.raises(RuntimeError, match="missing"):
         B.lib()
+
+
+def test_what_torch_throws_is_a_python_error_at_the_native_entries():
+    """A tensor without memory of its own (here one that vmap has wrapped) and, on a machine without a GPU, the current
+    stream make torch throw; that must come back as an exception: a C++ exception that leaves an extension module's
+    function ends the process."""
+    import torch
+    nat = B.native()
+    real = torch.zeros(1, 2, 128, 128, dtype=torch.bfloat16)
+    ints = torch.zeros(8, dtype=torch.int32)
+    calls = {
+        "prefill": lambda t: nat.prefill(t, real, real, ints, ints, ints, ints, None, None, 128, 128, 0, 0, 0.0, real, None, real),
+        "decode": lambda t: nat.decode(t[0], real, real, ints, ints, None, 4, real, None, 0.0, True, real, 0),
+        "decode_patterns": lambda t: nat.decode_patterns(t[0], real, real, ints, ints, ints, ints.view(2, 4), 3, 4, real, None, 0.0,
+                                                         real),
+        "capture_accumulate": lambda t: nat.capture_accumulate(t[0], t[0], real, None, 128, 0.0, None),
+        "mask_build": lambda t: nat.mask_build(B.MaskParams(), t, None, None, None, B.MaskOut(), None),
+        "mask_build_from_qk": lambda t: nat.mask_build_from_qk(B.MaskParams(), B.CaptureParams(), t, t, B.MaskOut(), None),
+    }
+    for name, call in calls.items():
+        with pytest.raises(RuntimeError):
+            torch.vmap(call)(torch.zeros(3, 1, 2, 128, 128, dtype=torch.bfloat16))
+            pytest.fail(f"{name} took a tensor without memory")
