@@ -808,6 +808,13 @@ __device__ __forceinline__ uint64_t diag_window(const uint64_t *__restrict__ rre
   return (lo >> sh) | (hi << (64 - sh));
 }
 
+// Keys of [64 wj, 64 wj + 64) that row i < L may keep in the true-mask block: causal, and columns below L.
+__device__ __forceinline__ uint64_t in_true_block(const Geom &g, int i, int wj) {
+  const int64_t u = (int64_t)i - (int64_t)wj * 64, left = (int64_t)g.L - (int64_t)wj * 64;
+  const uint64_t causal = u < 0 ? 0ull : u >= 63 ? ~0ull : ((2ull << u) - 1);
+  return left >= 64 ? causal : left <= 0 ? 0ull : causal & ((1ull << left) - 1);
+}
+
 __device__ __forceinline__ uint64_t mask_word(const Geom &g, const uint64_t *__restrict__ tb_h,
                                               const uint64_t *__restrict__ cb_h,
                                               const uint64_t *__restrict__ rr_h, int i, int wj) {
@@ -1094,6 +1101,10 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   const uint64_t *ca = col_any + (int64_t)h * g.occw, *cf = col_all + (int64_t)h * g.occw;
   const uint64_t *da = off_any + (int64_t)h * g.occw, *df = off_all + (int64_t)h * g.occw;
   const int words = g.tile_m * g.wpr;
+  const bool inner = i0 + g.tile_m <= min(g.L, g.S) && words <= 256;  // (words: 64 per lane and step, 4 steps)
+  int word_row[4], word_col[4];  // this lane's words of a tile
+#pragma unroll
+  for (int y = 0; y < 4; ++y) word_row[y] = (lane + 64 * y) / g.wpr, word_col[y] = (lane + 64 * y) % g.wpr;
   int total = 0;
   for (int w = 0; w <= (kmax >> 6); ++w) {  // (the words past the diagonal tile's are neither written nor read)
     const int kt = w * 64 + lane;
@@ -1122,6 +1133,37 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
     }
     uint64_t ow = __ballot(f & 1), fw = __ballot(f & 2);
     uint64_t need = __ballot(f & 4);
+    // A query tile inside the true-mask block: four tiles' words are fetched before the first is looked at (a word is one
+    // load from global memory; one tile after the other made a row of eight tiles wait eight times, and set the time of
+    // the launch: 32 heads x 4096 tokens, captured at 1024, whole build 73.7 -> 69.6 us).
+    while (inner && need) {  // wave-uniform
+      int b[4];
+      uint64_t m[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        b[u] = need ? __ffsll((unsigned long long)need) - 1 : b[u > 0 ? u - 1 : 0];  // (the last of them again)
+        need &= need - 1;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          if (64 * y >= words) break;
+          m[u][y] = tb[(int64_t)(i0 + word_row[y]) * g.tbw + min((w * 64 + b[u]) * g.wpr + word_col[y], g.tbw - 1)];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        bool any = false, all = true;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          if (64 * y >= words) break;
+          const int wj = (w * 64 + b[u]) * g.wpr + word_col[y];
+          const uint64_t x = m[u][y] & in_true_block(g, i0 + word_row[y], wj);
+          any |= x != 0;
+          all &= x == ~0ull;
+        }
+        if (__ballot(any) != 0) ow |= 1ull << b[u];
+        if (__ballot(!all) == 0) fw |= 1ull << b[u];
+      }
+    }
     while (need) {  // wave-uniform
       const int b = __ffsll((unsigned long long)need) - 1;
       need &= need - 1;
