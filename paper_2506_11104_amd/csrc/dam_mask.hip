@@ -1015,33 +1015,6 @@ __device__ __forceinline__ void gather_columns_of_head(const Geom &g, const uint
   }
 }
 
-// Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
-// per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
-// the two bitsets, the tile classes, the gathered column list.
-__global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, const uint8_t *__restrict__ diag_flag,
-                                                       const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
-                                                       uint64_t *__restrict__ rrev, bool classes,
-                                                       uint64_t *__restrict__ col_any, uint64_t *__restrict__ col_all,
-                                                       uint64_t *__restrict__ off_any, uint64_t *__restrict__ off_all,
-                                                       int gstride, int *__restrict__ gidx, int *__restrict__ gcnt,
-                                                       int *__restrict__ head_cnt, bool in_lds) {
-  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw]
-  const int h = blockIdx.x;
-  if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
-  pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, in_lds && classes ? prep_sets : nullptr);
-  if (!classes) return;  // uniform over the grid
-  __syncthreads();       // the sets are read back by other threads of this workgroup
-  // (from the LDS copy when they fit: the steps below are chains of dependent reads. One call per address space,
-  // so that the compiler knows which kind of read to use.)
-  if (in_lds) {
-    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, h, col_any, col_all, off_any, off_all);
-    if (gidx) gather_columns_of_head(g, prep_sets, gstride, h, gidx, gcnt);
-  } else {
-    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, h, col_any, col_all, off_any, off_all);
-    if (gidx) gather_columns_of_head(g, cbits + (int64_t)h * g.pw, gstride, h, gidx, gcnt);
-  }
-}
-
 // Transpose of the 64 x 64 bit matrix whose row l is the word x of lane l: lane r returns the word whose
 // bit l is bit r of lane l's x. Six exchange steps on blocks of 32, 16, ... 1 bits.
 __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
@@ -1053,6 +1026,110 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
     m ^= m << (j >> 1);
   }
   return x;
+}
+
+// a3 for short captures, inside the kernel that needs the flags: match counts of one head from its true bits, gamma >= mu,
+// flags and bitsets, by the 16 waves of one workgroup. A job is one word (64 patterns) of one kind over one chunk of 64 rows:
+// a lane per row, the 64 x 64 bits turned around, and a lane per pattern then counts its word. The jobs of the causal
+// triangle go round the waves and add into LDS.
+// In place of the two kernels that longer captures take (k_pattern_slices, k_pattern_finish), which cost 5 us each however
+// short they are. Whole builds: 2 heads x 64 29.4 -> 18.3 us, 32 heads x 256 40.1 -> 29.7, x 512 50.6 -> 39.9, x 768
+// 59.6 -> 53.2, x 1024 69.6 -> 68.2, 64 heads x 1024 116.6 -> 107.8. The jobs grow with the square of the capture and run
+// on one CU per head, so the line lies where the gain ends.
+constexpr int kDirectL = 1024;
+__device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
+                                                       float mu, int h, int *cnt,                       // LDS [2][kDirectL]
+                                                       int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
+                                                       uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,
+                                                       uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev,
+                                                       uint64_t *lds_copy) {  // both sets again, [2 pw], or nullptr
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  for (int x = threadIdx.x; x < 2 * kDirectL; x += blockDim.x) cnt[x] = 0;
+  __syncthreads();
+  const bool diag = wave & 1;
+  int chunk = 0, w = wave >> 1;  // the pair (chunk, word <= chunk) of this wave; both kinds take every n_waves / 2-th
+  auto settle = [&] {
+    while (w > chunk) w -= ++chunk;
+  };
+  uint64_t hi = 0, lo = 0;
+  auto fetch = [&] {
+    const int i = 64 * chunk + lane, wj = diag ? chunk - w : w;
+    const uint64_t *row = tb + (int64_t)min(i, g.L - 1) * g.tbw;
+    hi = lo = 0;
+    if (i < g.L) {
+      hi = row[wj];
+      if (diag && wj > 0) lo = row[wj - 1];
+    }
+  };
+  settle();
+  if (chunk < g.tbw) fetch();
+  while (chunk < g.tbw) {  // wave-uniform
+    // diagonals: the window of the row that ends at column i - 64 w, reversed: offset 64 w + t at bit t
+    uint64_t x = hi;
+    if (diag) x = __brevll(lane == 63 ? hi : (hi << (63 - lane)) | (lo >> (lane + 1)));
+    const int at = (diag ? kDirectL : 0) + 64 * w + lane;
+    w += n_waves / 2;
+    settle();
+    if (chunk < g.tbw) fetch();
+    atomicAdd(&cnt[at], __popcll(transpose64(x, lane)));
+  }
+  __syncthreads();
+  for (int x = wave; x < 2 * g.tbw; x += n_waves) {
+    const int word = x >> 1, p = 64 * word + lane, n = cnt[(x & 1) * kDirectL + p];
+    const bool hit = p < g.L && (float)n / (float)(g.L - p) >= mu;
+    const uint64_t set = __ballot(hit);
+    const int64_t e = (int64_t)h * g.L + p;
+    if (p < g.L) {
+      if (int *out = x & 1 ? diag_cnt : vert_cnt) out[e] = n;
+      (x & 1 ? diag_flag : vert_flag)[e] = (uint8_t)hit;
+    }
+    if (lane == 0) {
+      const int to = x & 1 ? g.pw - 1 - word : word;
+      const uint64_t v = x & 1 ? __brevll(set) : set;
+      (x & 1 ? rrev : cbits)[(int64_t)h * g.pw + to] = v;
+      if (lds_copy) lds_copy[(x & 1 ? g.pw : 0) + to] = v;
+    }
+  }
+}
+
+// Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
+// per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
+// the two bitsets, the tile classes, the gathered column list.
+struct CountArgs {  // true_bits: count the patterns here and write the flags, else the flags are given
+  const uint64_t *true_bits;
+  float mu;
+  int *vert_cnt, *diag_cnt;
+  uint8_t *vert_flag, *diag_flag;
+};
+__global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, const uint8_t *__restrict__ diag_flag,
+                                                       const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
+                                                       uint64_t *__restrict__ rrev, bool classes,
+                                                       uint64_t *__restrict__ col_any, uint64_t *__restrict__ col_all,
+                                                       uint64_t *__restrict__ off_any, uint64_t *__restrict__ off_all,
+                                                       int gstride, int *__restrict__ gidx, int *__restrict__ gcnt,
+                                                       int *__restrict__ head_cnt, bool in_lds) {
+  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw]
+  const int h = blockIdx.x;
+  if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
+  uint64_t *copy = in_lds && classes ? prep_sets : nullptr;
+  if (ca.true_bits) {  // uniform over the grid
+    __shared__ int cnt[2 * kDirectL];
+    count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
+                           ca.diag_flag, cbits, rrev, copy);
+  } else {
+    pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
+  }
+  if (!classes) return;  // uniform over the grid
+  __syncthreads();       // the sets are read back by other threads of this workgroup
+  // (from the LDS copy when they fit: the steps below are chains of dependent reads. One call per address space,
+  // so that the compiler knows which kind of read to use.)
+  if (in_lds) {
+    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, h, col_any, col_all, off_any, off_all);
+    if (gidx) gather_columns_of_head(g, prep_sets, gstride, h, gidx, gcnt);
+  } else {
+    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, h, col_any, col_all, off_any, off_all);
+    if (gidx) gather_columns_of_head(g, cbits + (int64_t)h * g.pw, gstride, h, gidx, gcnt);
+  }
 }
 
 // Row bitmap of one gathered slot for the rows of query tile qt: bit r of word k is row 64 k + r of the
@@ -2183,11 +2260,16 @@ Threshold stage_threshold(const dam_mask_params *p, const Geom &g, const Workspa
   return from_ws;
 }
 
-// a3: match scores of the true mask in o->true_bits; returns where the flags were written.
-void stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
+// a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
+// k_pattern_prep has to count for that.
+CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
                     hipStream_t stream, const uint8_t **dflag, const uint8_t **vflag, bool bmin_written) {
   uint8_t *df = o->diag_flag ? o->diag_flag : w.diag_flag;
   uint8_t *vf = o->vert_flag ? o->vert_flag : w.vert_flag;
+  *dflag = df;
+  *vflag = vf;
+  if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
+  if (g.L <= kDirectL) return CountArgs{o->true_bits, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
   if (g.tbw <= 128) {
     int W = 16;
@@ -2202,14 +2284,13 @@ void stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w,
   while ((g.L >> nb) != 0) ++nb;
   k_pattern_finish<<<dim3((g.tbw + kFinWords - 1) / kFinWords, g.H, 2), 256, 0, stream>>>(w.vslices, w.dslices, g.L, g.tbw, n_chunks, nb, p->mu,
                                                                        o->vert_cnt, o->diag_cnt, vf, df);
-  *dflag = df;
-  *vflag = vf;
-  if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
+  return CountArgs{};
 }
 
 // a4 + a5 and the kept lists: everything downstream of the stored artefact.
 void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
-                     const uint64_t *true_bits, const uint8_t *dflag, const uint8_t *vflag, hipStream_t stream) {
+                     const uint64_t *true_bits, const uint8_t *dflag, const uint8_t *vflag, const CountArgs &count,
+                     hipStream_t stream) {
   const bool want_blocks = o->blk_row_ptr != nullptr;
   const bool want_lists = o->kept_ptr != nullptr;
   const bool gather = want_blocks && (p->flags & DAM_MASK_GATHER_COLUMNS) != 0;
@@ -2217,9 +2298,9 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const int *gidx = gather ? o->gather_idx : nullptr, *gcnt = gather ? o->gather_cnt : nullptr;
   const int nrows = p->row_end - p->row_begin;
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
-  if (want_blocks || (want_lists && (plan || nrows > 1)) || o->dense_bits) {  // (a single row is listed from the flags)
+  if (want_blocks || (want_lists && (plan || nrows > 1)) || o->dense_bits || count.true_bits) {  // (a single row is listed from the flags)
     const size_t prep_lds = want_blocks && (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0;
-    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
+    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
                                                    w.off_all, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
@@ -2311,6 +2392,7 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
   const Workspace w = carve(p, ws);
   const uint8_t *dflag = diag_in, *vflag = vert_in;
   const uint64_t *true_bits = g.L > 0 ? o->true_bits : nullptr;
+  CountArgs count{};
 
   if (p->mode == DAM_FROM_ATTN_MAP) {
     bool bmin_written;
@@ -2327,9 +2409,9 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
       k_true_mask_rows<<<dim3(per_map, g.H), 256, 0, stream>>>(attn_sum, g.L, g.tbw, n_pairs, thr, o->true_bits);
     } else
       k_true_mask<true><<<grid, 256, 0, stream>>>(attn_sum, attn_cnt, g.L, g.tbw, p->eps, thr, o->true_bits);
-    stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
+    count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
   }
-  stage_extension(p, g, w, o, true_bits, dflag, vflag, stream);
+  stage_extension(p, g, w, o, true_bits, dflag, vflag, count, stream);
   return launch_status();
 }
 
@@ -2363,7 +2445,7 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
   // (one causal capture of two tokens or more: the minimum, and so the threshold, is known on the host)
   const Threshold thr = stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, &bmin_written);
   launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits, stream);
-  stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
-  stage_extension(p, g, w, o, o->true_bits, dflag, vflag, stream);
+  const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
+  stage_extension(p, g, w, o, o->true_bits, dflag, vflag, count, stream);
   return launch_status();
 }

@@ -1,0 +1,41 @@
+"""Short captures: pattern counts taken inside the prep kernel (up to 1024 tokens), and query tiles inside the true-mask
+block, whose tiles the scan looks at four at a time. Bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from dam_testlib import pack_rows_u64, u64
+from paper_2506_11104_amd import binding as B
+from test_gpu_mask import run_from_map, synth_map
+
+pytestmark = pytest.mark.gpu
+
+
+# one word, its neighbours, both sides of the longest capture counted there, one chunk more and less than a round of waves
+@pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 200, 512, 1023, 1024, 1025])
+@pytest.mark.parametrize("mu", [0.0, 0.3, 1.0])
+def test_pattern_counts_of_short_captures(L, mu):
+    A = synth_map(np.random.default_rng(L), 2, L)
+    run_from_map(A, None, L + 70, 64, 64, 0.5, 1e-8, 0.02, mu, dense=False)
+
+
+@pytest.mark.parametrize("L", [96, 1000])
+def test_pattern_counts_without_a_block_index(L):
+    A = synth_map(np.random.default_rng(L), 3, L)
+    art = oracle.derive(A, None, 0.5, 1e-8, 0.02, 0.3)
+    mask = B.build_mask(mode=B.DAM_FROM_ATTN_MAP, H=3, L=L, S=L, lam=0.5, eps=1e-8, tau=0.02, mu=0.3,
+                        attn_sum=torch.from_numpy(A).cuda(), blocks=False)
+    assert np.array_equal(u64(mask.true_bits), pack_rows_u64(art.true_mask))
+    for name in ("diag_cnt", "vert_cnt", "diag_flag", "vert_flag"):
+        assert np.array_equal(getattr(mask, name).cpu().numpy(), getattr(art, name)), name
+
+
+# tiles of 1, 2, 3 and 4 words per lane and one of 16 (the general form); 9 tiles are two steps of four and one more
+@pytest.mark.parametrize("tm,tn", [(64, 64), (128, 64), (192, 64), (128, 128), (64, 256), (256, 64), (256, 256)])
+@pytest.mark.parametrize("S", [575, 576, 700])
+def test_tiles_of_the_true_mask_block(tm, tn, S):
+    A = synth_map(np.random.default_rng(S), 2, 576)
+    A[0, :300, :300] = np.tril(np.full((300, 300), 0.5, np.float32))  # full tiles
+    A[1, 128:256, :128] = 0.0                                         # empty ones
+    run_from_map(A, None, S, tm, tn, 0.5, 1e-8, 0.02, 0.8)
