@@ -438,7 +438,7 @@ def bench_decode(args, torch, B, wl):
                 "roofline": {"bound": "hbm", "kernel": "k_decode_group_mfma", "achieved": ub / (dec_us * 1e-6) / 1e9,
                              "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ub / (dec_us * 1e-6) / 1e9 / PEAK_HBM_GBS,
                              "traffic": None,
-                             # `achieved` divides by the whole call (partial pass + merge pass) as timed by events inside
+                             # `achieved` divides by the whole call (splits and their merge) as timed by events inside
                              # the 256-step loop; the same call 50 times in a row, without events in between:
                              "achieved_back_to_back": ub / (main["decode_us_back_to_back"] * 1e-6) / 1e9,
                              "frac_back_to_back": ub / (main["decode_us_back_to_back"] * 1e-6) / 1e9 / PEAK_HBM_GBS},
