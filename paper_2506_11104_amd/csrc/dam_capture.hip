@@ -616,7 +616,7 @@ CapArgs make_args(const dam_capture_params *p) {
   a.out_bmin = nullptr;
   a.parts = 1;
   a.chunk = 0;
-  if (mfma_path(p)) {
+  if (mfma_path(p) && p->len > 0) {  // (the workspace queries come here before the length is checked)
     // A workgroup walks its row tile's stages one after the other, about a microsecond each: while the row tiles alone
     // leave the chip (three workgroups per CU) with room, up to four workgroups share a tile's stages, an even number
     // each. 32 heads x 1000 tokens, first pass: 18 -> 12 us.
@@ -675,7 +675,7 @@ int capture_validate(const dam_capture_params *p, const void *q, const void *k) 
 }
 
 size_t capture_lse_bytes(const dam_capture_params *p) {
-  return align_up((size_t)std::max(make_args(p).parts, 1) * p->hq * (size_t)p->pcl * sizeof(float), 256);
+  return align_up((size_t)make_args(p).parts * p->hq * (size_t)p->pcl * sizeof(float), 256);
 }
 
 void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
@@ -690,7 +690,7 @@ void launch_capture_true_bits(const dam_capture_params *p, const void *q, const 
 }  // namespace dam
 
 extern "C" size_t dam_capture_workspace(const dam_capture_params *p) {
-  if (!p || p->hq < 1 || p->pcl < 1 || p->len < 1) return 0;
+  if (!p || p->hq < 1 || p->pcl < 1) return 0;
   return dam::capture_lse_bytes(p);
 }
 

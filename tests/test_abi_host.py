@@ -207,6 +207,20 @@ def test_capture_argument_errors():
     assert both > L.dam_mask_build_workspace(ctypes.byref(mask_params()))
 
 
+def test_capture_workspace_queries_without_a_sequence():
+    """A length that no capture can have: the queries answer by the size of the statistics (the call itself then
+    refuses the length), for both kernels' parameters."""
+    L = B.lib()
+    for kw in ({}, {"dtype": B.DAM_F32}, {"hq": 64, "hkv": 8, "pcl": 4096}):
+        for n in (0, -200):
+            cp = capture_params(len=n, **kw)
+            need = L.dam_capture_workspace(ctypes.byref(cp))
+            assert need >= cp.hq * cp.pcl * 4
+            mp = mask_params(n_maps=cp.hq, pcl=cp.pcl, seq=4096)
+            both = L.dam_mask_build_from_qk_workspace(ctypes.byref(mp), ctypes.byref(cp))
+            assert both == L.dam_mask_build_workspace(ctypes.byref(mp)) + need
+
+
 def test_eviction_argument_errors():
     L = B.lib()
     p = B.EvictParams()
