@@ -147,6 +147,7 @@ constexpr int kRows = 128, kBlk = 32, kBlkBytes = kBlk * 256;
 constexpr int kXcd = 8;
 constexpr int kStageKeys = 64, kStageBytes = kStageKeys * 256;
 constexpr int kMaxParts = 4;
+constexpr int kPartTiles = 1024;  // row tiles times parts at most, where there is more than one part
 
 // One wave's quarter of a stage as four load-to-LDS copies (lane L of the wave fetches 16 bytes from
 // gbase + voff[it] and writes them to LDS byte lds_at + 4096 it + 16 L): rows wave * 4 + L / 16 + 16 it
@@ -616,12 +617,12 @@ CapArgs make_args(const dam_capture_params *p) {
   a.out_bmin = nullptr;
   a.parts = 1;
   a.chunk = 0;
-  if (mfma_path(p) && p->len > 0) {  // (the workspace queries come here before the length is checked)
+  if (mfma_path(p)) {
     // A workgroup walks its row tile's stages one after the other, about a microsecond each: while the row tiles alone
     // leave the chip (three workgroups per CU) with room, up to four workgroups share a tile's stages, an even number
     // each. 32 heads x 1000 tokens, first pass: 18 -> 12 us.
     const int n_stage = (p->len + kStageKeys - 1) / kStageKeys, tiles = p->hq * ((p->len + kRows - 1) / kRows);
-    const int parts = std::max(1, std::min(kMaxParts, 1024 / tiles));
+    const int parts = std::max(1, std::min(kMaxParts, kPartTiles / tiles));
     a.chunk = ((n_stage + parts - 1) / parts + 1) / 2 * 2;
     a.parts = (n_stage + a.chunk - 1) / a.chunk;
   }
@@ -674,8 +675,11 @@ int capture_validate(const dam_capture_params *p, const void *q, const void *k) 
   return DAM_OK;
 }
 
+// By the size of the statistics alone, whatever the length of the sequence: a caller sizes one workspace for several. A
+// sequence is cut into the more parts the fewer row tiles it has, so this is what one row tile per head could take.
 size_t capture_lse_bytes(const dam_capture_params *p) {
-  return align_up((size_t)make_args(p).parts * p->hq * (size_t)p->pcl * sizeof(float), 256);
+  const int most_parts = mfma_path(p) ? std::max(1, std::min(kMaxParts, kPartTiles / p->hq)) : 1;
+  return align_up((size_t)most_parts * p->hq * (size_t)p->pcl * sizeof(float), 256);
 }
 
 void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,

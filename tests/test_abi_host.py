@@ -221,6 +221,15 @@ def test_capture_workspace_queries_without_a_sequence():
             assert both == L.dam_mask_build_workspace(ctypes.byref(mp)) + need
 
 
+def test_one_capture_workspace_for_sequences_of_every_length():
+    L = B.lib()
+    for hq, hkv, pcl in ((2, 1, 64), (32, 8, 4096), (64, 8, 1024), (16, 4, 8192), (600, 600, 256), (1, 1, 700)):
+        for dtype in (B.DAM_BF16, B.DAM_F32):
+            sizes = {L.dam_capture_workspace(ctypes.byref(capture_params(hq=hq, hkv=hkv, pcl=pcl, len=n, dtype=dtype)))
+                     for n in {1, 63, 129, 500, 1000, pcl // 2, pcl} if n <= pcl}
+            assert len(sizes) == 1, (hq, pcl, dtype, sizes)
+
+
 def test_eviction_argument_errors():
     L = B.lib()
     p = B.EvictParams()

@@ -28,3 +28,20 @@ def test_parts_and_tiles(n, L, Hq, Hkv):
     assert (err <= ATOL + RTOL * A).all(), err.max()
     w = wl.scaled(wl.WORKLOADS["c2"], hq=Hq, hkv=Hkv, seq=n, pcl=n)
     fused_against_oracle(Q, K, w, n, 128, 128, 0.05, 0.8, "bf16")
+
+
+def test_sequences_of_several_lengths_in_one_workspace():
+    """A workspace sized for the longest sequence takes shorter ones, which are cut into more parts. It ends in bytes that
+    must stay as they are."""
+    Hq, Hkv, L, lens = 32, 8, 2048, (2048, 300, 1000, 1)
+    q, k = (dev(x, "bf16") for x in seq_pair(31, Hq, Hkv, L, 128, "bf16", std=1.2))
+    need = B.capture_workspace(B.capture_params(q, k, L), "cuda").numel()
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    got, want = (torch.zeros((Hq, L, L), dtype=torch.float32, device="cuda") for _ in range(2))
+    for n in lens:
+        B.dam_capture_accumulate(q[:, :n], k[:, :n], got, None, ws=ws[:need])
+        s = (q[:, :n].float().reshape(Hkv, -1, 128) @ k[:, :n].float().transpose(1, 2).contiguous()).reshape(Hq, n, n) / 128 ** 0.5
+        want[:, :n, :n] += s.masked_fill(torch.ones((n, n), dtype=torch.bool, device="cuda").triu(1), float("-inf")).softmax(-1)
+    torch.cuda.synchronize()
+    assert bool(((got - want).abs() <= len(lens) * ATOL + RTOL * want).all())
+    assert bool((ws[need:] == 0x5A).all())
