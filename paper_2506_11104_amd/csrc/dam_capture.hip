@@ -204,18 +204,23 @@ __device__ __forceinline__ void cap_numbering(const CapArgs &a, int items, int &
   item = within / G;
 }
 
-// The log2-sum-exp of row i of head h from the parts the first pass left: lse2[part][head][L], -inf where a part held no
-// key of the row.
+// The log2-sum-exp of row i of head h from what the first pass left: of a row in one part the number itself, of a row in
+// several (reference, sum) of every part, [part][head][L], with reference -inf where a part held no key of the row. (Not a
+// log-sum-exp of every part: rounding those as well made the probabilities' error against 64 bits 6 % larger, 7.4e-7 for
+// 7.0e-7 in the 2-norm over captures of 384 to 1936 tokens; this way it is
+// 6.9e-7.)
 __device__ __forceinline__ float row_lse(const CapArgs &a, const float *__restrict__ lse2, int h, int i) {
-  const float *at = lse2 + (int64_t)h * a.L + i;
-  if (a.parts == 1) return *at;
-  float v[kMaxParts], M = -INFINITY, sum = 0.0f;
+  const int64_t at = (int64_t)h * a.L + i;
+  if (a.parts == 1) return lse2[at];
+  const float2 *pair = reinterpret_cast<const float2 *>(lse2) + at;
+  float2 v[kMaxParts];
+  float M = -INFINITY, sum = 0.0f;
 #pragma unroll
-  for (int x = 0; x < kMaxParts; ++x) v[x] = x < a.parts ? at[(int64_t)x * a.Hq * a.L] : -INFINITY;
+  for (int x = 0; x < kMaxParts; ++x) v[x] = x < a.parts ? pair[(int64_t)x * a.Hq * a.L] : make_float2(-INFINITY, 0.0f);
 #pragma unroll
-  for (int x = 0; x < kMaxParts; ++x) M = fmaxf(M, v[x]);  // finite: part 0 holds key 0
+  for (int x = 0; x < kMaxParts; ++x) M = fmaxf(M, v[x].x);  // finite: part 0 holds key 0
 #pragma unroll
-  for (int x = 0; x < kMaxParts; ++x) sum += __builtin_amdgcn_exp2f(v[x] - M);
+  for (int x = 0; x < kMaxParts; ++x) sum += v[x].y * __builtin_amdgcn_exp2f(v[x].x - M);
   return M + __builtin_amdgcn_logf(sum);
 }
 
@@ -407,9 +412,10 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
       }
     }
   };
+  float2 *my_pair = reinterpret_cast<float2 *>(lse2) + ((int64_t)part * a.Hq + h) * a.L + i;  // (several parts; row_lse)
   if (key_first > last_row) {  // no key of this part lies below the tile's diagonal
     if (PASS == 1) clear_words(0);
-    else if (live && hf == 0) lse2[((int64_t)part * a.Hq + h) * a.L + i] = -INFINITY;
+    else if (live && hf == 0) *my_pair = make_float2(-INFINITY, 0.0f);
     return;
   }
   // this part's stages, of those that hold a key <= the tile's last live row. (In this form, quotient plus one: with the
@@ -596,8 +602,10 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
     const float m_o = __shfl_xor(m_ref, 32), l_o = __shfl_xor(l_run, 32);
     const float M = fmaxf(m_ref, m_o);  // (-inf: no key of the row in this part)
     const float tot = l_run * __builtin_amdgcn_exp2f(m_ref - M) + l_o * __builtin_amdgcn_exp2f(m_o - M);
-    if (live && hf == 0)
-      lse2[((int64_t)part * a.Hq + h) * a.L + i] = M == -INFINITY ? -INFINITY : M + __builtin_amdgcn_logf(tot);
+    if (live && hf == 0) {
+      if (a.parts == 1) lse2[(int64_t)h * a.L + i] = M == -INFINITY ? -INFINITY : M + __builtin_amdgcn_logf(tot);
+      else *my_pair = make_float2(M, M == -INFINITY ? 0.0f : tot);
+    }
   } else {
     clear_words(((n_stage + 1) / 2) * 4);
   }
@@ -679,7 +687,8 @@ int capture_validate(const dam_capture_params *p, const void *q, const void *k) 
 // sequence is cut into the more parts the fewer row tiles it has, so this is what one row tile per head could take.
 size_t capture_lse_bytes(const dam_capture_params *p) {
   const int most_parts = mfma_path(p) ? std::max(1, std::min(kMaxParts, kPartTiles / p->hq)) : 1;
-  return align_up((size_t)most_parts * p->hq * (size_t)p->pcl * sizeof(float), 256);
+  const size_t row_bytes = most_parts > 1 ? most_parts * sizeof(float2) : sizeof(float);
+  return align_up(row_bytes * p->hq * (size_t)p->pcl, 256);
 }
 
 void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
