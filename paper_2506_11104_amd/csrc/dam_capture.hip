@@ -600,11 +600,13 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
   }
   if (PASS == 0) {
     const float m_o = __shfl_xor(m_ref, 32), l_o = __shfl_xor(l_run, 32);
-    const float M = fmaxf(m_ref, m_o);  // (-inf: no key of the row in this part)
-    const float tot = l_run * __builtin_amdgcn_exp2f(m_ref - M) + l_o * __builtin_amdgcn_exp2f(m_o - M);
+    // M = -inf: no key of the row in this part, and the sums are zero; or no logit above -inf, and a NaN among the logits
+    // is in the sums. A part must hand that on; a row in one part has no log-sum-exp then (NaN).
+    const float M = fmaxf(m_ref, m_o), ref = M == -INFINITY && a.parts > 1 ? 0.0f : M;
+    const float tot = l_run * __builtin_amdgcn_exp2f(m_ref - ref) + l_o * __builtin_amdgcn_exp2f(m_o - ref);
     if (live && hf == 0) {
-      if (a.parts == 1) lse2[(int64_t)h * a.L + i] = M == -INFINITY ? -INFINITY : M + __builtin_amdgcn_logf(tot);
-      else *my_pair = make_float2(M, M == -INFINITY ? 0.0f : tot);
+      if (a.parts == 1) lse2[(int64_t)h * a.L + i] = M + __builtin_amdgcn_logf(tot);
+      else *my_pair = make_float2(M, tot);
     }
   } else {
     clear_words(((n_stage + 1) / 2) * 4);

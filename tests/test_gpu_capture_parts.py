@@ -67,3 +67,21 @@ def test_rows_in_several_parts_are_as_exact_as_rows_in_one():
             d2 += float((A[h].double() - p).pow(2).sum())
         errors.append(d2 ** 0.5)
     assert errors[0] <= 1.02 * errors[1], errors
+
+
+@pytest.mark.parametrize("copies,first,last", [(1, 256, 512), (1, 0, 900), (1, 256, 900), (40, 0, 900), (40, 256, 512)])
+def test_a_part_without_a_number_is_not_left_out(copies, first, last):
+    """Keys [first, last) are NaN, whole parts of the rows that hold them: every probability of such a row is NaN, in one
+    part (80 heads) and in several (2), and the rows above are those of a softmax over their own keys."""
+    n = 900
+    Q, K = seq_pair(43, 2, 1, n, 128, "bf16", std=1.2)
+    A, _ = oracle.capture(Q, K, n, want_cnt=False)
+    K[:, first:last] = np.nan
+    a_dev = torch.zeros((2 * copies, n, n), dtype=torch.float32, device="cuda")
+    B.dam_capture_accumulate(dev(Q, "bf16").repeat(copies, 1, 1), dev(K, "bf16").repeat(copies, 1, 1), a_dev, None)
+    torch.cuda.synchronize()
+    lower = np.tril(np.ones((n, n), bool))
+    for got in a_dev[[0, 2 * copies - 1]].cpu().numpy():
+        assert np.array_equal(np.isnan(got), lower & (np.arange(n) >= first)[:, None])
+    got = a_dev[0, :first].cpu().numpy()
+    assert (np.abs(got - A[0, :first]) <= ATOL + RTOL * A[0, :first]).all()
