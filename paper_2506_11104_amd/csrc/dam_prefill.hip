@@ -902,6 +902,14 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
         // first use of a fragment in each iteration)
 #pragma unroll
         for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(qf[c]));
+        // The variant with a reference multiplies the zero weights of the leading dummy blocks too, with V slots 2 and 3,
+        // which therefore have to be finite: not what an earlier kernel or item left there, whose V may hold an infinity
+        // or a NaN. (FAST leaves those products out. Each wave clears what it copies itself: nothing of its is in flight.)
+        if constexpr (!FAST) {
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            *reinterpret_cast<uint4 *>(lds + kVRing + 2 * kBlkBytes + x * 4096 + wave * 1024 + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
+        }
         __syncthreads();
         // S_b lives in sbuf[PH & 1] and S_{b+1} is written to the other one; P_b goes to pbuf[PH & 1] and
         // P_{b-1} is read from the other one, so nothing is copied between iterations
@@ -975,8 +983,8 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     // The rows go out as whole 256-byte lines: a lane holds eight bytes here and there of its query's row, so the wave
     // turns its 32 rows around in 8 KiB of the K ring (16-byte chunk c of row r at c ^ (r & 15)) and every store
     // instruction then covers four rows. (Eight bytes per lane and store straight from the accumulators: 2.6 us per item
-    // until the stores had drained, up to 20 us with every workgroup storing at once.) Not the V ring, which has to stay
-    // finite, and only when every wave's copies have landed; what the others still read of K belongs to no block.
+    // until the stores had drained, up to 20 us with every workgroup storing at once.) Only when every wave's copies have
+    // landed; what the others still read of K belongs to no block.
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     {
       int l = lane;  // (opaque, or the addresses below are computed once for all items and kept through the pipeline)
@@ -1044,12 +1052,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     sh.bad = 0;
     sh.redo = -1;
   }
-  // The first two iterations of an item multiply weights that are exactly zero (the leading dummy
-  // blocks) with whatever the V ring holds: it has to be finite. Later items find the previous item's
-  // V rows there; the first one would find what an earlier kernel left in LDS, so clear the ring once.
-  for (int at = tid * 16; at < kRing * kBlkBytes; at += 256 * 16)
-    *reinterpret_cast<uint4 *>(lds + kVRing + at) = make_uint4(0u, 0u, 0u, 0u);
-
   prefill_items<RAGGED, GATHER, FAST>(a, t, lds, sh, false);
   if constexpr (FAST) {
     __syncthreads();
