@@ -95,6 +95,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
   float m_run = -INFINITY, l_run = 0.0f;  // reference of the weights (raw logits), this lane's part of their sum
+  unsigned kept_any = 0;                  // the head keeps a key of this wave's
 
   if (nb > 0) {
     const unsigned char *kg = reinterpret_cast<const unsigned char *>(kc + b * a.kv_sb + hkv * a.kv_sh);
@@ -231,6 +232,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
       }
       if (n >= G) mine = 0;
+      kept_any |= mine;
 
       // S^T = K Q^T; accumulator e is key 8 (e / 4) + 4 hf + e % 4 and starts at 0 (kept) or -inf (masked)
       f32x16 s;
@@ -301,7 +303,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // The waves' results meet in LDS, dealt out in columns as everything from here on: column c G + x is dims 4 c .. + 3 of
   // head x, 16 bytes at 16 (c G + x) of the wave's own slots (lanes n < G hold a head); behind them the head's reference
   // (log2 units) and sum.
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  // (A head that keeps none of the wave's keys has nothing to hand on: a masked key's NaN would be in its sums. What is NaN
+  // after that comes from logits of the head's own and has to come out as NaN, in however many waves the list is split.)
+  const bool none = kept_any == 0;
+  const float l_both = l_run + __shfl_xor(l_run, 32), l_tot = none ? 0.0f : l_both;
   if (n < G) {
     float4 *mine_o = reinterpret_cast<float4 *>(lds) + n;
 #pragma unroll
@@ -309,7 +314,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         mine_o[(8 * db + 2 * g + hf) * G] =
-            make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
+            none ? make_float4(0.f, 0.f, 0.f, 0.f)
+                 : make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
     if (hf == 0) reinterpret_cast<float2 *>(lds + kMl)[n] = make_float2(m_run == -INFINITY ? -INFINITY : m_run * c2, l_tot);
   }
   __syncthreads();
@@ -330,17 +336,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float M = -INFINITY, L = 0.0f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int w = 0; w < a.waves; ++w) M = fmaxf(M, reinterpret_cast<const float2 *>(lds_all + w * kLds + kMl)[x].x);
-    if (M > -INFINITY)
-      for (int w = 0; w < a.waves; ++w) {  // weights 2^(reference - largest reference)
-        const float4 ow = reinterpret_cast<const float4 *>(lds_all + w * kLds)[col];
-        const float2 e = reinterpret_cast<const float2 *>(lds_all + w * kLds + kMl)[x];
-        const float wt = exp2f(e.x - M);
-        L += wt * e.y;
-        o.x += wt * ow.x;
-        o.y += wt * ow.y;
-        o.z += wt * ow.z;
-        o.w += wt * ow.w;
-      }
+    // (M = -inf: no wave met a logit above -inf. Their sums then count as they are: zero without a key, NaN with a NaN.)
+    const float ref = M == -INFINITY ? 0.0f : M;
+    for (int w = 0; w < a.waves; ++w) {  // weights 2^(reference - largest reference)
+      const float4 ow = reinterpret_cast<const float4 *>(lds_all + w * kLds)[col];
+      const float2 e = reinterpret_cast<const float2 *>(lds_all + w * kLds + kMl)[x];
+      const float wt = exp2f(e.x - ref);
+      L += wt * e.y;
+      o.x += wt * ow.x;
+      o.y += wt * ow.y;
+      o.z += wt * ow.z;
+      o.w += wt * ow.w;
+    }
     if (a.groups == 1) {
       finish(x, c, o, M, L);
     } else {
@@ -379,13 +386,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) top = fmaxf(top, gm[u]);
-      if (top == -INFINITY) continue;
-      const float corr = exp2f(M - top);
+      const float ref = top == -INFINITY ? 0.0f : top;
+      const float corr = exp2f(M - ref);
       L *= corr;
       o.x *= corr, o.y *= corr, o.z *= corr, o.w *= corr;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float wt = exp2f(gm[u] - top);
+        const float wt = exp2f(gm[u] - ref);
         L += wt * gl[u];
         o.x += wt * go[u].x;
         o.y += wt * go[u].y;
@@ -404,8 +411,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int y = 1; y < shares; ++y) {
       const float4 oy = sum[y * cols + col];
       const float2 e = sum_ml[y * cols + col];
-      if (e.x == -INFINITY) continue;
-      const float top = fmaxf(M, e.x), w0 = exp2f(M - top), w1 = exp2f(e.x - top);
+      const float top = fmaxf(M, e.x), ref = top == -INFINITY ? 0.0f : top, w0 = exp2f(M - ref), w1 = exp2f(e.x - ref);
       L = w0 * L + w1 * e.y;
       o.x = w0 * o.x + w1 * oy.x;
       o.y = w0 * o.y + w1 * oy.y;

@@ -70,3 +70,29 @@ def test_split_lists(dtype, d, Bn, Hkv, G, longest, grouped):
         if k % 2:
             other(ws)
             check_other()
+
+
+@pytest.mark.parametrize("Bn,n", [(1, 20), (1, 100), (1, 300), (1, 3000), (16, 600), (64, 5000)])
+def test_nan_logits_come_out_as_nan_however_the_list_is_split(Bn, n):
+    """One wave, several, several workgroups. Head 1's query is NaN and head 2 keeps no key, while every key of KV head 1's
+    list is NaN: the outputs are NaN for head 1 and for KV head 1's heads with keys, zero for its head without, and ordinary
+    for the others."""
+    Hkv, G, d, T = 2, 4, 128, n + 40
+    rng = np.random.default_rng(n)
+    q, Kc, Vc = (wl.to_storage(rng.standard_normal(s).astype(np.float32), "bf16") for s in ((Bn, 8, d), (Bn, Hkv, T, d), (Bn, Hkv, T, d)))
+    lists = [np.sort(rng.choice(T, n, replace=False)).astype(np.int32) for _ in range(8)]
+    lists[2] = lists[6] = np.zeros(0, np.int32)
+    kv_of = np.array([b * Hkv + h // G for b in range(Bn) for h in range(8)], np.int32)
+    ptr = np.concatenate([[0], np.cumsum([x.size for x in lists] * Bn)]).astype(np.int64)
+    O, _ = oracle.attend_lists(q.reshape(-1, d), Kc.reshape(-1, T, d), Vc.reshape(-1, T, d), kv_of, ptr, np.concatenate(lists * Bn))
+    gp, gi, gm = oracle.group_lists(lists, G)
+    q[:, 1] = np.nan
+    Kc[:, 1] = np.nan
+    t = lambda a, k: torch.from_numpy(np.ascontiguousarray(a.astype(k))).cuda()
+    out, lse = B.dam_sparse_attn_decode_grouped(dev(q, "bf16"), dev(Kc, "bf16"), dev(Vc, "bf16"), t(gp, np.int32), t(gi, np.int32),
+                                                t(gm, np.uint8), int(np.diff(gp).max()), want_lse=True, shared_lists=True)
+    torch.cuda.synchronize()
+    out, O = out.float().cpu().numpy(), O.reshape(Bn, 8, d)
+    assert np.isnan(out[:, [1, 4, 5, 7]]).all()
+    assert (out[:, [2, 6]] == 0).all() and bool(torch.isneginf(lse[:, [2, 6]]).all())
+    assert np.abs(out[:, [0, 3]] - O[:, [0, 3]]).max() <= TOL["bf16"]
