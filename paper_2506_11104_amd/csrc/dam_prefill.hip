@@ -89,6 +89,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
   struct Parts {
     float o[4][16 * kPad];
     float m[4][16], l[4][16];
+    unsigned any[4][16];
   };
   constexpr size_t kLds = sizeof(Lists) > sizeof(Parts) ? sizeof(Lists) : sizeof(Parts);
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
@@ -124,6 +125,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
 #pragma unroll
   for (int x = 0; x < HV * 4; ++x) o[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.0f;  // of the lane's row; l is this lane's part
+  unsigned any = 0;               // bits of kept keys
 
   for (int seg = t0; seg < t1; seg += kF32Seg) {
     const int n_seg = min(kF32Seg, t1 - seg);
@@ -198,6 +200,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
       }
       if (e + 4 < n_blk) load_k(k_next, e + 4);
       const unsigned kept = L.words[x][(b16 >> 1) * 16 + r16] >> (16 * (b16 & 1));  // low 16 bits: the block's keys
+      any |= kept & 0xFFFFu;
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: a product's result is ready only after the next has started
 #pragma unroll
       for (int c = 0; c < CK; ++c) {
@@ -280,6 +283,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
   if (g == 0) {
     P.m[wave][r16] = m;
     P.l[wave][r16] = l;
+    P.any[wave][r16] = any;
   }
 #pragma unroll
   for (int h = 0; h < HV; ++h)
@@ -296,7 +300,9 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
     wt[y] = P.m[y][row] > -INFINITY ? expf(P.m[y][row] - M) : 0.0f;  // (a wave that met no key of the row)
     sum += wt[y] * P.l[y][row];
   }
-  const float inv = sum > 0.0f ? 1.0f / sum : sum * 0.0f;  // (no key: 0; NaN stays NaN)
+  // no key: 0; NaN stays NaN, and a softmax over nothing but -inf has no value either
+  const bool has_key = (P.any[0][row] | P.any[1][row] | P.any[2][row] | P.any[3][row]) != 0;
+  const float inv = sum > 0.0f ? 1.0f / sum : sum == 0.0f && has_key ? NAN : sum * 0.0f;
 #pragma unroll
   for (int h = 0; h < HV; ++h) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -55,3 +55,21 @@ def test_a_row_does_not_see_what_it_does_not_keep():
         assert np.array_equal(np.isnan(out[h, :, 3]), keeps(37))
         assert np.array_equal(np.isinf(out[h, :, 70]), keeps(101))
         assert np.isfinite(out[h, :, 5]).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_with_nothing_but_minus_infinity_have_no_value(d):
+    """Keys 90 to 129 have logits of -inf: weight 0 beside an ordinary key, whichever comes first; a row that keeps only such
+    keys is NaN, as in the oracle, and one that keeps none is zero."""
+    S = 200
+    Q, K, V, art = inputs(2, 1, S, d, 6)
+    Q[:, :, 0], K[0, 90:130, 0] = 1.0, -np.inf
+    art.vert_flag[1] = 0
+    art.diag_flag[1] = 0
+    art.diag_flag[1, 1:4] = 1                       # head 1: rows 93 .. 130 keep three such keys, row 0 none
+    out, lse = run(Q, K, V, gpu_mask_from_art(art, S, 64, 64))
+    O, LSE = oracle.attend_prefill(Q, K, V, art)
+    none = np.arange(S) == 0
+    only = (np.arange(S) >= 93) & (np.arange(S) <= 130)
+    assert np.isnan(O[1, only]).all() and np.isnan(out[1, only]).all() and (out[1, none] == 0).all()
+    assert np.abs(out[0] - O[0]).max() <= TOL and np.abs(out[1, ~only] - O[1, ~only]).max() <= TOL
