@@ -1180,8 +1180,9 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
     a.gather_stride = mk->gather_stride;
   }
   if (p->dtype == DAM_F32) {
-    auto kern = mk->gather_idx ? (p->head_dim == 64 ? k_prefill_f32<64, true> : k_prefill_f32<128, true>)
-                               : (p->head_dim == 64 ? k_prefill_f32<64, false> : k_prefill_f32<128, false>);
+    // (a list shorter than a tile's slots holds no gathered tile, and the kernel that looks slots up would read past it)
+    auto kern = mk->gather_idx && mk->gather_stride >= p->tile_n ? (p->head_dim == 64 ? k_prefill_f32<64, true> : k_prefill_f32<128, true>)
+                                                                     : (p->head_dim == 64 ? k_prefill_f32<64, false> : k_prefill_f32<128, false>);
     kern<<<p->batch * p->hq * a.nQt * (p->tile_m / 16), 256, 0, st>>>(a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr, mk->blk_col,
                                                     mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
     return launch_status();

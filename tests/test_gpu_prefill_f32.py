@@ -73,3 +73,15 @@ def test_rows_with_nothing_but_minus_infinity_have_no_value(d):
     only = (np.arange(S) >= 93) & (np.arange(S) <= 130)
     assert np.isnan(O[1, only]).all() and np.isnan(out[1, only]).all() and (out[1, none] == 0).all()
     assert np.abs(out[0] - O[0]).max() <= TOL and np.abs(out[1, ~only] - O[1, ~only]).max() <= TOL
+
+
+def test_a_column_list_shorter_than_a_tile():
+    """gather_idx of 8 slots per head beside a plain block index (gather_rows 0): no slot is looked up, the list is not read."""
+    S = 300
+    Q, K, V, art = inputs(4, 2, S, 64, 8)
+    mask = gpu_mask_from_art(art, S, 64, 64)
+    want, _ = run(Q, K, V, mask)
+    mask.gather_idx = torch.full((4, 8), -1, dtype=torch.int32, device="cuda")
+    mask.gather_cnt = torch.zeros(4, dtype=torch.int32, device="cuda")
+    got, _ = run(Q, K, V, mask)
+    assert np.array_equal(got, want)
