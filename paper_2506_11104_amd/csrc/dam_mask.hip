@@ -1823,13 +1823,18 @@ __global__ __launch_bounds__(256) void k_row_fill(Geom g, const uint64_t *__rest
 // Two launches, count per (group, run, span) and fill, both straight from the flags (from the true bits for a row above
 // pcl): a piece is eight flag bytes of the columns and eight of the diagonals, and turning whole flag rows into
 // bitsets first is a launch of its own for twice the reading. The fill kernel adds up the counts before its own
-// itself, so there is no scan launch either (at most a few thousand counts). 8 KV heads of 4 maps at row 20000: 21 us
+// itself, so there is no scan launch either up to kAddedCounts of them. 8 KV heads of 4 maps at row 20000: 21 us
 // in four launches (bitsets, count, scan, fill) -> 13 us; 16 maps at row 4095: 13 -> 8 us.
 constexpr int kMaxGroup = 8;
 constexpr int kPieceBits = 8;
 constexpr int kPiecesPerWord = 64 / kPieceBits;
 constexpr int kChunkWords = 64 / kPiecesPerWord;  // mask words per wave
 constexpr int kListSpan = 256 * kPieceBits;       // keys per workgroup
+// Beyond this many counts a scan launch between the two is cheaper than every workgroup adding up what lies before it,
+// which grows with the square of (lists x spans). Time of the whole build, us, added / scanned: 32 maps at 20000 in groups
+// of four (400 counts) 12.0 / 14.5; 64 maps at 262144 in groups of four (10240) 32.5 / 34.2, one by one (16384) 50.9 /
+// 44.6; 64 maps at 2^20 one by one (65536) 377 / 156.
+constexpr int64_t kAddedCounts = 12288;
 
 // Eight flag bytes from p on as eight bits (p of any alignment).
 __device__ __forceinline__ unsigned flags8(const uint8_t *p) {
@@ -1904,6 +1909,8 @@ __global__ __launch_bounds__(256) void k_list_count(Geom g, const uint64_t *__re
         part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
 }
 
+// SCANNED: cnt is the exclusive scan of the counts, with the total behind it.
+template <bool SCANNED>
 __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__restrict__ true_bits,
                                                    const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int row,
                                                    int G, const int *__restrict__ cnt, int *__restrict__ kept_ptr,
@@ -1920,14 +1927,21 @@ __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__res
   row_pieces(g, true_bits, dflag, vflag, kv, G, row, key0, m, shared);
   __syncthreads();
   const int64_t at0 = (int64_t)kv * (G + 1) * spans + span, last = (int64_t)n_groups * (G + 1) * spans;
-  unsigned long long sum = 0;
-  for (int64_t e = threadIdx.x; e < at0; e += 256) sum += cnt[e];
-  for (int off = 32; off; off >>= 1) sum += __shfl_xor(sum, off);
-  if (lane == 0 && sum) atomicAdd(&before[0], sum);
-  for (int e = threadIdx.x; e < G * spans; e += 256) atomicAdd(&before[1 + e / spans], (unsigned long long)cnt[at0 + e]);
-  if (kv == n_groups - 1 && span == 0)  // the workgroup that reports the total adds up the counts from its last run on
-    for (int64_t e = at0 + (int64_t)G * spans + threadIdx.x; e < last; e += 256)
-      atomicAdd(&before[G + 1], (unsigned long long)cnt[e]);
+  if (SCANNED) {
+    if (threadIdx.x <= G + 1) {
+      const int64_t to = threadIdx.x <= G ? at0 + (int64_t)threadIdx.x * spans : last;
+      before[threadIdx.x] = (unsigned long long)(cnt[to] - (threadIdx.x > 0 ? cnt[at0 + (int64_t)(threadIdx.x - 1) * spans] : 0));
+    }
+  } else {
+    unsigned long long sum = 0;
+    for (int64_t e = threadIdx.x; e < at0; e += 256) sum += cnt[e];
+    for (int off = 32; off; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane == 0 && sum) atomicAdd(&before[0], sum);
+    for (int e = threadIdx.x; e < G * spans; e += 256) atomicAdd(&before[1 + e / spans], (unsigned long long)cnt[at0 + e]);
+    if (kv == n_groups - 1 && span == 0)  // the workgroup that reports the total adds up the counts from its last run on
+      for (int64_t e = at0 + (int64_t)G * spans + threadIdx.x; e < last; e += 256)
+        atomicAdd(&before[G + 1], (unsigned long long)cnt[e]);
+  }
   int incl[kMaxGroup + 1];
 #pragma unroll
   for (int r = 0; r <= kMaxGroup; ++r)
@@ -1947,7 +1961,7 @@ __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__res
       unsigned long long total = 0;
       for (int r = 0; r <= G + 1; ++r) total += before[r];
       kept_ptr[n_groups] = (int)min(total, clamp);
-      if (kept_total) *kept_total = (int64_t)total;
+      if (kept_total && !SCANNED) *kept_total = (int64_t)total;  // (the scan has written it)
     }
   }
   if (!kept_idx) return;
@@ -2147,6 +2161,12 @@ int list_group(const dam_mask_params *p) {
   return (p->flags & DAM_MASK_GROUP_LISTS) && p->group >= 1 && p->group <= kMaxGroup ? p->group : 1;
 }
 
+// Counts of the lists of a single row: one per list, run and span of keys.
+int64_t list_counts(const dam_mask_params *p) {
+  const int group = list_group(p);
+  return (int64_t)(p->n_maps / group) * (group + 1) * (p->row_begin / kListSpan + 1);
+}
+
 // Chunks of kChunkWords mask words covering keys 0..row (one wave each in the plan kernels).
 int group_chunks(int row) { return ((row >> 6) + 1 + kChunkWords - 1) / kChunkWords; }
 
@@ -2200,8 +2220,8 @@ Workspace carve(const dam_mask_params *p, void *ws) {
   size_t n_cnt = (size_t)g.H * (size_t)(nrows > 0 ? nrows : 1);
   size_t n_first = 1;
   if (nrows == 1 && p->row_begin >= 0) {  // a single row: the run sizes per span
-    const int group = list_group(p);
-    n_cnt = std::max(n_cnt, (size_t)(g.H / group) * (size_t)(p->row_begin / kListSpan + 1) * (size_t)(group + 1));
+    n_cnt = std::max(n_cnt, (size_t)list_counts(p));
+    if (list_counts(p) > kAddedCounts) n_first = (size_t)list_counts(p) + 1;
   }
   if (p->flags & DAM_MASK_PATTERN_PLAN) {  // two parts (diagonals, columns) over the P pattern positions
     const int group = list_group(p);
@@ -2348,9 +2368,13 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
     if (nrows == 1) {
       const int G = list_group(p);
       const dim3 grid(p->row_begin / kListSpan + 1, g.H / G);
+      const int64_t counts = list_counts(p);
+      const bool scan = counts > kAddedCounts;
       k_list_count<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, w.row_cnt);
-      k_list_fill<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, w.row_cnt, o->kept_ptr, o->kept_total,
-                                            o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member, o->kept_capacity);
+      if (scan) k_exclusive_scan<<<1, 1024, 0, stream>>>(w.row_cnt, counts, 0, w.group_first, o->kept_total, INT32_MAX);
+      auto fill = scan ? k_list_fill<true> : k_list_fill<false>;
+      fill<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, scan ? w.group_first : w.row_cnt, o->kept_ptr,
+                                     o->kept_total, o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member, o->kept_capacity);
     } else if (nrows > 0) {
       k_row_count<<<dim3(nrows, g.H), 256, 0, stream>>>(g, true_bits, w.cbits, w.rrev, p->row_begin, nrows, w.row_cnt);
       const bool fill_lists = o->kept_idx && o->kept_capacity > 0;
