@@ -272,6 +272,7 @@ typedef struct {
   int64_t k_stride[2];  /*   rows 16-byte aligned                                                  */
 } dam_capture_params;
 
+/* By hq and pcl: one workspace takes sequences of every length. */
 size_t dam_capture_workspace(const dam_capture_params *params);
 
 /* q         device [hq][len][head_dim], k device [hkv][len][head_dim] by the strides above.
@@ -379,7 +380,8 @@ typedef struct {
                             kept_ptr has hq + 1 entries                                             */
 } dam_decode_params;
 
-/* max_kept: upper bound of the kept keys of one (sequence, head) list. */
+/* max_kept: upper bound of the kept keys of one (sequence, head) list. A workspace of this size also takes every smaller
+ * batch and every smaller bound. */
 size_t dam_sparse_attn_decode_workspace(const dam_decode_params *params, int64_t max_kept);
 
 /* q, out      device [batch][hq][head_dim] by the strides above.
@@ -408,7 +410,7 @@ int dam_sparse_attn_decode(const dam_decode_params *params, const void *q, const
  * kept_ptr  device i32 [batch*hkv + 1] ([hkv + 1] with shared_lists); kept_idx i32 and kept_member u8
  *           device arrays of the same length. Entries of one list may come in any order, without
  *           duplicates; runs of entries with equal kept_member cost no arithmetic for the other heads.
- * max_kept  upper bound of the length of one list. Everything else as dam_sparse_attn_decode. */
+ * max_kept  upper bound of the length of one list. Everything else (the workspace too) as dam_sparse_attn_decode. */
 size_t dam_sparse_attn_decode_grouped_workspace(const dam_decode_params *params, int64_t max_kept);
 int dam_sparse_attn_decode_grouped(const dam_decode_params *params, const void *q, const void *kcache,
                                    const void *vcache, const int32_t *kept_ptr, const int32_t *kept_idx,

@@ -455,6 +455,28 @@ struct Partials {
   }
 };
 
+// What a call writes to its workspace: the per-head form, and the grouped one.
+Partials list_partials(void *ws, const dam_decode_params *p, int64_t max_kept) {
+  const int64_t lists = (int64_t)p->batch * p->hq;
+  return Partials(ws, p, pick_splits(lists, max_kept), lists);
+}
+Partials group_partials(void *ws, const dam_decode_params *p, int64_t max_kept) {
+  bool mfma;
+  return Partials(ws, p, group_splits(p, max_kept, &mfma).groups, (int64_t)p->batch * p->hkv);
+}
+
+// The workspace queries' answer: a workspace for a batch takes any smaller one too, which is split further and may need
+// more (a batch that sequences leave). Beyond kSplitBatch sequences no list is split, and the need grows with the batch.
+constexpr int kSplitBatch = 1024;
+template <typename F>
+size_t bytes_up_to_batch(const dam_decode_params *p, F partials) {
+  size_t most = partials(p).bytes;
+  dam_decode_params fewer = *p;
+  for (fewer.batch = std::min(p->batch, kSplitBatch); fewer.batch >= 1; --fewer.batch)
+    most = std::max(most, partials(&fewer).bytes);
+  return most;
+}
+
 int validate(const dam_decode_params *p, const void *q, const void *kc, const void *vc,
              const int32_t *kept_ptr, const int32_t *kept_idx, int64_t max_kept, const void *out) {
   if (!p || !q || !kc || !vc || !kept_ptr || !out) return DAM_ERR_INVALID_ARG;
@@ -498,8 +520,7 @@ uint64_t dam::fresh_flag() {
 
 extern "C" size_t dam_sparse_attn_decode_workspace(const dam_decode_params *p, int64_t max_kept) {
   if (!p || p->batch < 1 || p->hq < 1 || p->head_dim < 1 || max_kept < 0) return 0;
-  const int splits = pick_splits((int64_t)p->batch * p->hq, max_kept);
-  return Partials(nullptr, p, splits, (int64_t)p->batch * p->hq).bytes;
+  return bytes_up_to_batch(p, [&](const dam_decode_params *x) { return list_partials(nullptr, x, max_kept); });
 }
 
 extern "C" int dam_sparse_attn_decode(const dam_decode_params *p, const void *q, const void *kcache,
@@ -508,7 +529,8 @@ extern "C" int dam_sparse_attn_decode(const dam_decode_params *p, const void *q,
                                       void *stream_v) {
   const int bad = validate(p, q, kcache, vcache, kept_ptr, kept_idx, max_kept, out);
   if (bad != DAM_OK) return bad;
-  if (!ws || ws_bytes < dam_sparse_attn_decode_workspace(p, max_kept)) return DAM_ERR_WORKSPACE;
+  const Partials part = list_partials(ws, p, max_kept);
+  if (!ws || ws_bytes < part.bytes) return DAM_ERR_WORKSPACE;
   DecodeArgs a;
   a.B = p->batch; a.Hq = p->hq; a.Hkv = p->hkv; a.cap = p->kv_capacity;
   a.splits = pick_splits((int64_t)p->batch * p->hq, max_kept);
@@ -518,7 +540,6 @@ extern "C" int dam_sparse_attn_decode(const dam_decode_params *p, const void *q,
   a.kv_sb = p->kv_stride[0]; a.kv_sh = p->kv_stride[1]; a.kv_ss = p->kv_stride[2];
   a.o_sb = p->o_stride[0]; a.o_sh = p->o_stride[1];
   a.flag = a.splits > 1 ? fresh_flag() : 0;
-  const Partials part(ws, p, a.splits, (int64_t)a.B * a.Hq);
   hipStream_t st = static_cast<hipStream_t>(stream_v);
   if (p->dtype == DAM_BF16) {
     if (p->head_dim == 128) launch<__hip_bfloat16, 128>(a, q, kcache, vcache, kept_ptr, kept_idx, out, lse, part, st);
@@ -552,8 +573,7 @@ void launch_group(const DecodeArgs &a, const void *q, const void *kc, const void
 extern "C" size_t dam_sparse_attn_decode_grouped_workspace(const dam_decode_params *p, int64_t max_kept) {
   if (!p || p->batch < 1 || p->hq < 1 || p->hkv < 1 || p->head_dim < 1 || max_kept < 0) return 0;
   if (p->hq % p->hkv) return 0;
-  bool mfma;
-  return Partials(nullptr, p, group_splits(p, max_kept, &mfma).groups, (int64_t)p->batch * p->hkv).bytes;
+  return bytes_up_to_batch(p, [&](const dam_decode_params *x) { return group_partials(nullptr, x, max_kept); });
 }
 
 namespace {
@@ -611,7 +631,7 @@ extern "C" int dam_sparse_attn_decode_grouped(const dam_decode_params *p, const 
                                               void *ws, size_t ws_bytes, void *stream_v) {
   const int bad = validate_grouped(p, q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out);
   if (bad != DAM_OK) return bad;
-  if (!ws || ws_bytes < dam_sparse_attn_decode_grouped_workspace(p, max_kept)) return DAM_ERR_WORKSPACE;
+  if (!ws || ws_bytes < group_partials(nullptr, p, max_kept).bytes) return DAM_ERR_WORKSPACE;
   return decode_grouped_run(p, q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out, lse, ws,
                             static_cast<hipStream_t>(stream_v));
 }
@@ -628,7 +648,7 @@ extern "C" int dam_sparse_attn_decode_patterns(const dam_decode_params *p, const
   if (!decode_group_mfma_fits(p)) return DAM_ERR_UNSUPPORTED;  // bf16, head_dim 128, rows of a head within 4 GiB
   dam_decode_params shared = *p;
   shared.shared_lists = 1;  // a plan belongs to the heads, not to a sequence
-  if (!ws || ws_bytes < dam_sparse_attn_decode_grouped_workspace(&shared, max_entries)) return DAM_ERR_WORKSPACE;
+  if (!ws || ws_bytes < group_partials(nullptr, &shared, max_entries).bytes) return DAM_ERR_WORKSPACE;
   return decode_grouped_run(&shared, q, kcache, vcache, plan_ptr, plan_val, plan_member, max_entries, out, lse, ws,
                             static_cast<hipStream_t>(stream_v), plan_table, n_flags, pos);
 }
@@ -669,8 +689,7 @@ extern "C" int dam_sparse_attn_decode_grouped_static(const dam_decode_params *p,
                                                      int64_t max_kept, void *out, float *lse, void *stream_v) {
   const int bad = validate_grouped(p, q, kcache, vcache, kept_ptr, kept_idx, kept_member, max_kept, out);
   if (bad != DAM_OK) return bad;
-  bool mfma;
-  const Partials need(nullptr, p, group_splits(p, max_kept, &mfma).groups, (int64_t)p->batch * p->hkv);
+  const Partials need = group_partials(nullptr, p, max_kept);
   // the call does not fit the fixed array
   if (need.bytes - need.flag_bytes > kStaticScratchBytes || need.flag_bytes > kStaticFlagBytes) return DAM_ERR_WORKSPACE;
   void *ws = nullptr;

@@ -161,6 +161,26 @@ def test_decode_argument_errors():
     assert L.dam_sparse_attn_decode_grouped_workspace(ctypes.byref(p), 4000) > 0
 
 
+def test_one_decode_workspace_for_a_batch_that_shrinks():
+    """A workspace sized for a batch is large enough for every smaller one and for every shorter bound of the lists, in
+    each form and data type: the query never falls as the batch or the bound grows."""
+    L = B.lib()
+    for hq, hkv, d, dtype in ((32, 8, 128, B.DAM_BF16), (16, 16, 64, B.DAM_F32), (64, 8, 128, B.DAM_BF16), (1, 1, 128, B.DAM_BF16),
+                              (3, 1, 64, B.DAM_BF16)):
+        p = B.DecodeParams()
+        p.hq, p.hkv, p.kv_capacity, p.head_dim, p.dtype = hq, hkv, 70000, d, dtype
+        p.kv_stride = (ctypes.c_int64 * 3)(hkv * 70000 * d, 70000 * d, d)
+        for query in (L.dam_sparse_attn_decode_workspace, L.dam_sparse_attn_decode_grouped_workspace):
+            for bounds in ((6000,), (0, 1, 40, 200, 300, 700, 3000, 70000)):
+                sizes = []
+                for p.batch in (*range(1, 70), 128, 500, 513, 1023, 1024, 1025, 1026, 3000) if len(bounds) == 1 else (1, 5, 40):
+                    sizes += [query(ctypes.byref(p), n) for n in bounds]
+                    if len(bounds) > 1:
+                        assert sizes == sorted(sizes), (hq, hkv, p.batch, sizes)
+                        sizes = []
+                assert sizes == sorted(sizes), (hq, hkv, sizes)
+
+
 def capture_params(**kw):
     p = B.CaptureParams()
     p.hq, p.hkv, p.len, p.pcl, p.head_dim, p.dtype, p.scale = 2, 1, 64, 64, 128, B.DAM_BF16, 0.0
