@@ -440,12 +440,14 @@ int dam_sparse_attn_decode_patterns(const dam_decode_params *params, const void 
  * partial results of the list splits kept in a fixed array of DAM_DECODE_STATIC_SCRATCH_BYTES bytes of
  * device memory that belongs to the library (every GPU the library runs on holds its own copy until the
  * process ends). The call allocates nothing and synchronises nothing; inputs and outputs are the
- * caller's as before. A call whose dam_sparse_attn_decode_grouped_workspace() exceeds the array returns
- * DAM_ERR_WORKSPACE and launches nothing. All calls on one GPU share that GPU's array: calls that may
- * overlap there (different streams, several threads) race on it; calls on one stream do not. The array keeps
- * the last call's contents; nothing in it has to start at zero (every split writes its partial result
- * before the merge pass reads it). The first call made with a device current looks up the array's address on
- * that device and keeps it: the only state the library holds.
+ * caller's as before. A call whose dam_sparse_attn_decode_grouped_workspace() is within the array fits. A call whose
+ * own partial results (batch * hq * splits rows of head_dim + 2 floats; the query also covers smaller batches, and
+ * 8 bytes per split beside the rows) exceed the array returns DAM_ERR_WORKSPACE and launches nothing. All calls on one
+ * GPU share that GPU's array: calls that may overlap there (different streams, several threads) race on it; calls on
+ * one stream do not. The array keeps the last call's contents; nothing in it has to start at zero (every split writes
+ * its partial result before the last split of its list to finish reads it). The first call made with a device current
+ * looks up the array's address on that device and keeps it: with the counter that numbers the calls, all the state
+ * the library holds.
  * dam_sparse_attn_decode_grouped_static_limit() returns DAM_DECODE_STATIC_SCRATCH_BYTES. */
 #define DAM_DECODE_STATIC_SCRATCH_BYTES (8u << 20)
 size_t dam_sparse_attn_decode_grouped_static_limit(void);

@@ -417,8 +417,8 @@ __global__ __launch_bounds__(256) void k_decode_group(DecodeArgs a, const T *__r
 }
 
 int pick_splits(int64_t items, int64_t max_kept) {
-  // Enough workgroups to put two on every CU (512), each with at least 256 keys; one split (and no
-  // merge pass) when the batch alone provides them.
+  // Enough workgroups to put two on every CU (512), each with at least 256 keys; one split (and nothing
+  // to merge) when the batch alone provides them.
   int64_t s = (512 + items - 1) / items;
   s = std::min<int64_t>(s, std::max<int64_t>(1, max_kept / 256));
   return (int)std::min<int64_t>(std::max<int64_t>(s, 1), 64);
