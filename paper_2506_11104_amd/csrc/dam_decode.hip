@@ -156,7 +156,7 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, int b, int hq0
   const int64_t item0 = (int64_t)b * a.Hq + hq0;
   for (int x = wave; x < heads; x += 4) {
     float2 e = make_float2(-INFINITY, 0.0f);
-    if (lane < a.splits) e = reinterpret_cast<const float2 *>(part_ml)[(item0 + x) * a.splits + lane];
+    if (lane < a.splits) e = load_through(reinterpret_cast<const float2 *>(part_ml) + (item0 + x) * a.splits + lane);
     float M = e.x;
     for (int off = 32; off; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
     const float w = M > -INFINITY ? exp2f(e.x - M) : 0.0f;
@@ -171,18 +171,20 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, int b, int hq0
   const int x = col / kCols, c = col % kCols;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (share < shares && s_m[x] > -INFINITY) {
-    const float4 *po = reinterpret_cast<const float4 *>(part_o) + (item0 + x) * a.splits * kCols + c;
+    const float2 *po = reinterpret_cast<const float2 *>(part_o) + ((item0 + x) * a.splits * kCols + c) * 2;
     for (int s0 = share; s0 < a.splits; s0 += 4 * shares) {
-      float4 v[4];
+      float2 v[4][2];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = po[min(s0 + u * shares, a.splits - 1) * kCols];
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int z = 0; z < 2; ++z) v[u][z] = load_through(po + min(s0 + u * shares, a.splits - 1) * kCols * 2 + z);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const float w = s0 + u * shares < a.splits ? s_w[x][s0 + u * shares] : 0.0f;
-        acc.x += w * v[u].x;
-        acc.y += w * v[u].y;
-        acc.z += w * v[u].z;
-        acc.w += w * v[u].w;
+        acc.x += w * v[u][0].x;
+        acc.y += w * v[u][0].y;
+        acc.z += w * v[u][1].x;
+        acc.w += w * v[u][1].y;
       }
     }
   }

@@ -376,13 +376,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (share < shares)
     for (int g0 = share; g0 < a.groups; g0 += 4 * shares) {
       float gm[4], gl[4], top = M;
-      float4 go[4];
+      float2 go[4][2];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int gr = min(g0 + u * shares, a.groups - 1);
-        gm[u] = g0 + u * shares < a.groups ? ml[(gr * G + x) * 2] : -INFINITY;
-        gl[u] = ml[(gr * G + x) * 2 + 1];
-        go[u] = po[gr * cols + col];
+        const float2 e = load_through(reinterpret_cast<const float2 *>(ml) + gr * G + x);
+        gm[u] = g0 + u * shares < a.groups ? e.x : -INFINITY;
+        gl[u] = e.y;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) go[u][z] = load_through(reinterpret_cast<const float2 *>(po + gr * cols + col) + z);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) top = fmaxf(top, gm[u]);
@@ -394,10 +396,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int u = 0; u < 4; ++u) {
         const float wt = exp2f(gm[u] - ref);
         L += wt * gl[u];
-        o.x += wt * go[u].x;
-        o.y += wt * go[u].y;
-        o.z += wt * go[u].z;
-        o.w += wt * go[u].w;
+        o.x += wt * go[u][0].x;
+        o.y += wt * go[u][0].y;
+        o.z += wt * go[u][1].x;
+        o.w += wt * go[u][1].y;
       }
       M = top;
     }
