@@ -1179,9 +1179,15 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   const uint64_t *da = off_any + (int64_t)h * g.occw, *df = off_all + (int64_t)h * g.occw;
   const int words = g.tile_m * g.wpr;
   const bool inner = i0 + g.tile_m <= min(g.L, g.S) && words <= 256;  // (words: 64 per lane and step, 4 steps)
-  int word_row[4], word_col[4];  // this lane's words of a tile
+  // This lane's words of a tile, divided by a multiplication (four divisions by a variable cost every wave of the launch
+  // about a microsecond, also where it looks at no tile of the true-mask block): a row has 1 to 4 words, x is below 256.
+  const int inv_wpr = g.wpr == 1 ? 65537 : g.wpr == 2 ? 32769 : g.wpr == 3 ? 21846 : 16385;
+  int word_row[4], word_col[4];
 #pragma unroll
-  for (int y = 0; y < 4; ++y) word_row[y] = (lane + 64 * y) / g.wpr, word_col[y] = (lane + 64 * y) % g.wpr;
+  for (int y = 0; y < 4; ++y) {
+    word_row[y] = ((lane + 64 * y) * inv_wpr) >> 16;
+    word_col[y] = lane + 64 * y - word_row[y] * g.wpr;
+  }
   int total = 0;
   for (int w = 0; w <= (kmax >> 6); ++w) {  // (the words past the diagonal tile's are neither written nor read)
     const int kt = w * 64 + lane;
