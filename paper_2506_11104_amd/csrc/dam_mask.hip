@@ -1035,8 +1035,11 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
 // In place of the two kernels that longer captures take (k_pattern_slices, k_pattern_finish), which cost 5 us each however
 // short they are. Whole builds: 2 heads x 64 29.4 -> 18.3 us, 32 heads x 256 40.1 -> 29.7, x 512 50.6 -> 39.9, x 768
 // 59.6 -> 53.2, x 1024 69.6 -> 68.2, 64 heads x 1024 116.6 -> 107.8. The jobs grow with the square of the capture and run
-// on one CU per head, so the line lies where the gain ends.
-constexpr int kDirectL = 1024;
+// on one CU per head, so the line lies where the gain ends: at kDirectL where k_pattern_prep is launched anyway or where many
+// heads keep the chip busy, and lower where it would be launched for this alone. There, two kernels / this, us: 1 head x 896
+// 19.0 / 18.6, x 960 19.2 / 20.5, x 1024 19.2 / 22.1; 32 heads x 896 32.6 / 31.8, x 1024 35.9 / 37.8; 64 heads x 1024
+// 54.4 / 53.9; 48 heads x 960 45.0 / 44.3, x 1024 46.9 / 48.0; 96 heads x 1024 82.6 / 77.3.
+constexpr int kDirectL = 1024, kDirectAloneL = 896, kDirectHeads = 48;
 __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
                                                        float mu, int h, int *cnt,                       // LDS [2][kDirectL]
                                                        int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
@@ -2286,6 +2289,12 @@ Threshold stage_threshold(const dam_mask_params *p, const Geom &g, const Workspa
   return from_ws;
 }
 
+// What follows needs k_pattern_prep whether or not it counts (a single row is listed from the flags).
+bool needs_prep(const dam_mask_params *p, const dam_mask_out *o) {
+  const bool rows = (p->flags & DAM_MASK_PATTERN_PLAN) != 0 || p->row_end - p->row_begin > 1;
+  return o->blk_row_ptr || o->dense_bits || (o->kept_ptr && rows);
+}
+
 // a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
 // k_pattern_prep has to count for that.
 CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
@@ -2295,7 +2304,8 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   *dflag = df;
   *vflag = vf;
   if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
-  if (g.L <= kDirectL) return CountArgs{o->true_bits, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
+  if (g.L <= kDirectL && (g.L <= kDirectAloneL || g.H >= kDirectHeads || needs_prep(p, o)))
+    return CountArgs{o->true_bits, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
   if (g.tbw <= 128) {
     int W = 16;
@@ -2324,7 +2334,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const int *gidx = gather ? o->gather_idx : nullptr, *gcnt = gather ? o->gather_cnt : nullptr;
   const int nrows = p->row_end - p->row_begin;
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
-  if (want_blocks || (want_lists && (plan || nrows > 1)) || o->dense_bits || count.true_bits) {  // (a single row is listed from the flags)
+  if (needs_prep(p, o) || count.true_bits) {
     const size_t prep_lds = want_blocks && (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0;
     k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
                                                    w.off_all, gstride, gather ? o->gather_idx : nullptr,

@@ -39,3 +39,15 @@ def test_tiles_of_the_true_mask_block(tm, tn, S):
     A[0, :300, :300] = np.tril(np.full((300, 300), 0.5, np.float32))  # full tiles
     A[1, 128:256, :128] = 0.0                                         # empty ones
     run_from_map(A, None, S, tm, tn, 0.5, 1e-8, 0.02, 0.8)
+
+
+# both sides of the lines for captures whose patterns are counted with nothing else to do: 896 tokens, 48 heads
+@pytest.mark.parametrize("L,copies", [(895, 1), (896, 1), (897, 1), (1024, 1), (897, 23), (897, 24), (1024, 24)])
+def test_pattern_counts_alone_on_both_sides_of_the_lines(L, copies):
+    A = synth_map(np.random.default_rng(L + copies), 2, L)
+    art = oracle.derive(A, None, 0.5, 1e-8, 0.02, 0.3)
+    a_dev = torch.from_numpy(A).cuda().repeat(copies, 1, 1)
+    mask = B.build_mask(mode=B.DAM_FROM_ATTN_MAP, H=2 * copies, L=L, S=L, lam=0.5, eps=1e-8, tau=0.02, mu=0.3, attn_sum=a_dev,
+                        blocks=False)
+    for name in ("diag_cnt", "vert_cnt", "diag_flag", "vert_flag"):
+        assert np.array_equal(getattr(mask, name).cpu().numpy(), np.tile(getattr(art, name), (copies, 1))), name
