@@ -51,3 +51,24 @@ def test_a_sequence_with_nan_values_leaves_its_neighbour_alone(polluted_first, f
     torch.cuda.synchronize()
     assert bool(torch.isnan(out[bad]).all())
     against_oracle(out[1 - bad], lse[1 - bad], Q * 64.0, K, V, art, 0.0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,S,odd_only,flags", [
+    (16, 16, 4096, False, 0), (16, 4, 4001, False, B.DAM_MASK_GATHER_COLUMNS), (16, 8, 4096, True, B.DAM_MASK_GATHER_COLUMNS),
+    (6, 3, 6001, False, 0), (6, 3, 6016, True, 0),     # six pairs: round robin over the queues
+])
+def test_workgroups_redo_several_items(Hq, Hkv, S, odd_only, flags):
+    """564 to 1024 items, all of them (or those of every other head) beyond the plain exponential: the lists of items to
+    redo have several entries, of first items and of drawn ones, in both layouts, whole and ragged."""
+    Q, K, V = qkv(7 + S, Hq, S)
+    K, V = K[:Hkv], V[:Hkv]
+    Q[1 if odd_only else 0 :: 2 if odd_only else 1] *= 64.0
+    art = patterns(Hq, S)
+    mask = gpu_mask_from_art(art, S, 128, 128, flags=flags)
+    q, k, v = (torch.stack([dev(x, "bf16")] * 2) for x in (Q, K, V))
+    v[1] *= 2  # (every sum and rounding scales by it exactly, but for outputs below bf16's normal range, 2^-126; negated values round differently in the matrix instruction's
+               # sums: 18 of 8 388 608 outputs by one bf16 unit, with the plain exponential as well)
+    out, lse = B.dam_sparse_attn_prefill(q, k, v, mask, want_lse=True)
+    torch.cuda.synchronize()
+    against_oracle(out[0], lse[0], Q, K, V, art, 0.0)
+    assert float((out[1].float() - 2 * out[0].float()).abs().max()) <= 2.0 ** -126 and torch.equal(lse[1], lse[0])
