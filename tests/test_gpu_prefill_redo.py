@@ -66,8 +66,9 @@ def test_workgroups_redo_several_items(Hq, Hkv, S, odd_only, flags):
     art = patterns(Hq, S)
     mask = gpu_mask_from_art(art, S, 128, 128, flags=flags)
     q, k, v = (torch.stack([dev(x, "bf16")] * 2) for x in (Q, K, V))
-    v[1] *= 2  # (every sum and rounding scales by it exactly, but for outputs below bf16's normal range, 2^-126; negated values round differently in the matrix instruction's
-               # sums: 18 of 8 388 608 outputs by one bf16 unit, with the plain exponential as well)
+    # Every sum and rounding scales with V by a power of two, but for outputs below bf16's normal range, 2^-126. (Negated
+    # values do not: the matrix instruction's sums round 18 of 8 388 608 outputs another way, redone or not.)
+    v[1] *= 2
     out, lse = B.dam_sparse_attn_prefill(q, k, v, mask, want_lse=True)
     torch.cuda.synchronize()
     against_oracle(out[0], lse[0], Q, K, V, art, 0.0)
