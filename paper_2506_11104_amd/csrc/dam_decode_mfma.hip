@@ -306,6 +306,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // (A head that keeps none of the wave's keys has nothing to hand on: a masked key's NaN would be in its sums. What is NaN
   // after that comes from logits of the head's own and has to come out as NaN, in however many waves the list is split.)
   const bool none = kept_any == 0;
+  if (__ballot(none && n < G) != 0) {  // (wave-uniform: most waves have a key for every head, and 64 selects take 0.1 us)
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[db][e] = none ? 0.0f : oacc[db][e];
+  }
   const float l_both = l_run + __shfl_xor(l_run, 32), l_tot = none ? 0.0f : l_both;
   if (n < G) {
     float4 *mine_o = reinterpret_cast<float4 *>(lds) + n;
@@ -314,8 +320,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         mine_o[(8 * db + 2 * g + hf) * G] =
-            none ? make_float4(0.f, 0.f, 0.f, 0.f)
-                 : make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
+            make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
     if (hf == 0) reinterpret_cast<float2 *>(lds + kMl)[n] = make_float2(m_run == -INFINITY ? -INFINITY : m_run * c2, l_tot);
   }
   __syncthreads();
