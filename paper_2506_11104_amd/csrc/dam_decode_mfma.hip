@@ -64,8 +64,9 @@ __device__ __forceinline__ void lds_copy4_at(unsigned lds_at, uint64_t addr) {
 //
 // The waves of a workgroup have LDS slots of their own (still no barrier inside the loop), and at the end they
 // merge their partial results through LDS. One workgroup per list: it normalises and stores the output. Several: the
-// partial results go to the workspace and the last workgroup (arrive_last) merges them: one sequence at 8k, 8 KV
-// heads, 13.9 -> 9.4 us; batch 16 at 64k, two groups per list, 91 -> 86 us, against a merge kernel of its own.
+// partial results go to the workspace and the last workgroup (arrive_last) merges them. Against a merge kernel of its
+// own: one sequence at 8k, 8 KV heads, 14.1 -> 9.4 us; batch 16 at 64k, two groups per list, 93.9 -> 89.3 us on the same
+// card (90 to 93 before, 86 to 89 now from card to card).
 template <bool PLAN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decode_group_mfma(
     MfmaArgs a, const __hip_bfloat16 *__restrict__ q, const __hip_bfloat16 *__restrict__ kc,

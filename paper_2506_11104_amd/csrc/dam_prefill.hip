@@ -63,9 +63,12 @@ struct AttnArgs {
 // registers. The dims are dealt out so that every operand is a 16-byte load straight from memory in the product's
 // layout: K and Q lane (row, g) holds dims 16 c + 4 g .. + 3 of chunk c, V lane m dims 64 h + 4 m .. + 3. The V rows of
 // a block are fetched before its Q K products, the K rows of the next one too.
-// Bound by the fp32 matrix rate (64 flop per cycle and SIMD) on the occupied blocks and, for short rows, by the
-// latency of the first loads. 2 sequences x 8 heads x 1500 keys, d 128: 415 -> 74 us against a row per d / 4 plain lanes
-// (Q in LDS for a third workgroup per CU spilled: 154 us).
+// Bound by the latency of a block's loads: the matrix rate (64 flop per cycle and SIMD) is used to about 27 % on the blocks
+// that are issued, each of which brings 16 KiB of K and V from L2 however few of its entries are kept. 2 sequences x 8
+// heads x 1500 keys, d 128, windows and stripes (46 % of the issued entries kept): 391 -> 60 us against a row per d / 4
+// plain lanes, each visiting its kept keys only (Q in LDS for a third workgroup per CU spilled: 154 us). At the same size
+// a window of 64 101 -> 34 us; where nothing but isolated diagonals is kept (9 to 14 entries per block) the plain lanes
+// were faster, 1 % of the diagonals 50 -> 63 us, 4 % 92 -> 114, 10 % 176 -> 130.
 constexpr int kF32Seg = 64;  // listed tiles expanded at a time
 
 // GATHER: the block index may hold gathered column tiles, whose key rows are looked up in gather_idx. (A template

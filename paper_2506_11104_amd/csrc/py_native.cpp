@@ -1,7 +1,7 @@
-// The hot entry points of libdam.so for Python, without ctypes: a decode step of one sequence is two launches of about
-// 3 us of host time each, and filling a parameter structure through ctypes, taking six tensors' addresses and asking
-// torch for its stream cost another 9 us (14.4 us per call, host bound). Reading shapes, strides and addresses from the
-// tensor objects here costs about 1 us.
+// The hot entry points of libdam.so for Python, without ctypes: a decode step of one sequence from a plan is one launch of
+// about 3 us of host time, and filling a parameter structure through ctypes, taking six tensors' addresses and asking
+// torch for its stream cost another 9 us (while a step was two launches, 14.4 us per call, host bound). Reading shapes,
+// strides and addresses from the tensor objects here costs about 1 us.
 //
 // Argument marshalling only, as in binding.py: every function takes tensors (or None) and numbers, enqueues on torch's
 // current stream and returns the dam_status, or one of the codes below for what the wrappers in binding.py report as a
