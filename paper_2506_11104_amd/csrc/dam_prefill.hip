@@ -43,6 +43,11 @@ constexpr int kXcd = 8;
 // workgroups still at work took up to 9 us for an iteration of 0.7: 2000 tokens, 32 heads.)
 constexpr int kCtlStep = 64, kCtlWords = kXcd, kCtlBytes = kCtlWords * kCtlStep * 4;
 
+// Longest queue whose items are put into order of their length (order_items): eight items per workgroup, 64 of them on an
+// XCD. Longer queues stay in the order of their numbers: by length neighbours in time no longer share windows of K and V, which
+// with 16 items per workgroup (32 heads x 32768 tokens) costs 1 % and more than the ends, even already, give back.
+constexpr int kOrderMax = 512;
+
 struct AttnArgs {
   int B, Hq, Hkv, S, nQt, nKt, tile_m, tile_n, wpr;
   int gather_rows, gather_stride;  // gathered column tiles (tile index >= nKt), 0 when the index has none
@@ -361,6 +366,17 @@ constexpr int kSegTiles = 128;                      // listed tiles expanded int
 constexpr int kListEntries = kSegTiles * 4 + 1;     // up to four blocks per tile, and the dummy that ends the list
 constexpr int kPipeLds = kBlkList + kListEntries * 8;
 
+// Inclusive prefix sum over the wave, in the vector registers alone (row shifts, then the row totals handed on).
+__device__ __forceinline__ int wave_prefix(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // last lane of rows 0 and 2 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
+  return v;
+}
+
 struct Blk {
   int key0;        // first key of the block (gathered tile: first row of the block in the gathered copy)
   int bits_off;    // byte offset of row 0's mask word for the block from the tile row's first mask word
@@ -625,6 +641,107 @@ __device__ __forceinline__ void pipe_iter_seg(const unsigned char *__restrict__ 
   }
 }
 
+// The queues of work items, a (batch, query head, query tile) each. Where the (sequence, KV head) pairs divide evenly among
+// the XCDs a queue holds whole pairs, whose K and V then stay in that XCD's L2; otherwise every eighth item of all pairs (with
+// four pairs half the chip would have nothing to start with). Numbered with the longest rows of a pair's causal triangle
+// first.
+struct Queues {
+  int G, n_pairs, per_pair, nQt, Hkv;
+  bool even;
+  __device__ __forceinline__ explicit Queues(const AttnArgs &a)
+      : G(a.Hq / a.Hkv), n_pairs(a.B * a.Hkv), per_pair(a.Hq / a.Hkv * a.nQt), nQt(a.nQt), Hkv(a.Hkv), even(a.B * a.Hkv % kXcd == 0) {}
+  __device__ __forceinline__ int items(int qu) const {
+    return even ? n_pairs / kXcd * per_pair : (n_pairs * per_pair - qu + kXcd - 1) / kXcd;
+  }
+  __device__ __forceinline__ int pair_of(int item, int qu) const { return even ? item / per_pair * kXcd + qu : (item * kXcd + qu) % n_pairs; }
+  __device__ __forceinline__ int within_of(int item, int qu) const { return even ? item % per_pair : (item * kXcd + qu) / n_pairs; }
+  // offsets of an item's listed tiles
+  __device__ __forceinline__ const int *span(const int *row_ptr, int item, int qu) const {
+    const int within = within_of(item, qu), hkv = pair_of(item, qu) % Hkv;
+    return row_ptr + (int64_t)(hkv * G + within % G) * (nQt + 1) + (nQt - 1 - within / G);
+  }
+};
+
+// A queue's items in falling order of their number of blocks: {item, t0, t1, -} each, so that a workgroup that draws one has
+// its listed tiles with it. By numbers alone a dense head's long items started among the last ones: 32 heads x 4096 tokens
+// (2 items per workgroup) took 57 us where the workgroups worked 42 us on average; by length the launch takes 54 instead of 61
+// us in a kernel trace, 4 x 32 heads x 3001 tokens 165 instead of 170. A counting sort by one workgroup per queue, in the
+// launch that precedes the attention kernel anyway (5.3 us with it, 5.2 without).
+// Where a queue holds several pairs they are taken in groups of at least kOrderGroup items, three per workgroup: all at once they
+// share the L2 badly (3001 tokens: 166 us), in smaller groups the last one has too few items to end evenly (96: 171 us).
+// (Blocks are counted over an item's first 64 tiles, the others taken for two each.)
+constexpr int kOrderBins = 512, kOrderGroup = 192;
+template <int THREADS>
+__device__ __forceinline__ void order_items(const AttnArgs &a, const int *__restrict__ row_ptr, const uint8_t *__restrict__ blk_kind, int qu,
+                                            int4 *__restrict__ order) {
+  __shared__ int start[kOrderBins];
+  __shared__ int wave_sum[THREADS / 64];
+  const Queues qs(a);
+  const int n = qs.items(qu), tid = threadIdx.x;
+  int4 *out = order + (int64_t)qu * kOrderMax;
+  constexpr int kEach = kOrderMax / THREADS;
+  int t0[kEach], t1[kEach], bin[kEach];
+#pragma unroll
+  for (int x = 0; x < kEach; ++x) {
+    const int item = x * THREADS + tid;
+    t0[x] = t1[x] = 0;
+    if (item < n) {
+      const int *rp = qs.span(row_ptr, item, qu);
+      t0[x] = rp[0];
+      t1[x] = rp[1];
+    }
+  }
+  const int group_pairs = (kOrderGroup + qs.per_pair - 1) / qs.per_pair;
+  const int groups = qs.even ? max(1, qs.n_pairs / kXcd / group_pairs) : 1, bins_each = kOrderBins / groups;
+  for (int x = tid; x < kOrderBins; x += THREADS) start[x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kEach; ++x) {
+    const int item = x * THREADS + tid;
+    if (item < n) {
+      // kinds as aligned words, bytes outside the item cleared
+      const uintptr_t first = reinterpret_cast<uintptr_t>(blk_kind) + t0[x];
+      const int lo = (int)(first & 3), m = min(t1[x] - t0[x], 64);
+      const unsigned *w = reinterpret_cast<const unsigned *>(first - lo);
+      int blocks = 2 * (t1[x] - t0[x] - m);
+      for (int y = 0; y * 4 < lo + m; ++y) {
+        unsigned v = w[y] & 0x1E1E1E1Eu;
+        if (y == 0) v &= ~0u << (8 * lo);
+        if (y * 4 + 4 > lo + m) v &= ~0u >> (8 * (y * 4 + 4 - lo - m));
+        blocks += __popc(v);
+      }
+      const int group = groups > 1 ? min(item / (group_pairs * qs.per_pair), groups - 1) : 0;
+      bin[x] = (group + 1) * bins_each - 1 - min(blocks, bins_each - 1);
+      atomicAdd(&start[bin[x]], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive prefix over the bins, kOrderBins / THREADS consecutive ones per thread
+  constexpr int kPer = (kOrderBins + THREADS - 1) / THREADS;
+  int c[kPer], mine = 0;
+#pragma unroll
+  for (int y = 0; y < kPer; ++y) {
+    c[y] = tid * kPer + y < kOrderBins ? start[tid * kPer + y] : 0;
+    mine += c[y];
+  }
+  int incl = wave_prefix(mine);
+  if ((tid & 63) == 63) wave_sum[tid >> 6] = incl;
+  __syncthreads();
+  int at = incl - mine;
+  for (int y = 0; y < (tid >> 6); ++y) at += wave_sum[y];
+#pragma unroll
+  for (int y = 0; y < kPer; ++y) {
+    if (tid * kPer + y < kOrderBins) start[tid * kPer + y] = at;
+    at += c[y];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kEach; ++x) {
+    const int item = x * THREADS + tid;
+    if (item < n) out[atomicAdd(&start[bin[x]], 1)] = make_int4(item, t0[x], t1[x], 0);
+  }
+}
+
 // RAGGED: the sequence length is not a multiple of the block size, so the last block of a row of tiles
 // may reach past the end of K and V.
 // GATHER: the block index may hold gathered column tiles (tile index >= nKt), whose K / V rows come from
@@ -647,6 +764,7 @@ struct Operands {
   __hip_bfloat16 *out;
   float *lse;
   int *ctl, *next;
+  const int4 *order;  // the queues' items by length, or nullptr
   const __hip_bfloat16 *kgath, *vgath;
 };
 
@@ -680,7 +798,8 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
   const unsigned lds_kv = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);              // this wave's part of a K/V slot
   const unsigned lds_bits = __builtin_amdgcn_readfirstlane(lds_base + kBitsRing + wave * 256);  // ... of a bits slot
 
-  const int G = a.Hq / a.Hkv, n_pairs = a.B * a.Hkv, per_pair = G * a.nQt;
+  const Queues qs(a);
+  const int G = qs.G;
   const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcd - 1);  // XCC_ID, 4 bits
   uint2 *blk_list = reinterpret_cast<uint2 *>(lds + kBlkList);
   // The listed tiles [seg0, seg0 + n_seg) of an item that starts at t0 -> list of block descriptors in LDS (two words:
@@ -701,11 +820,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
         full = kind & 1;
       }
       const int cnt = __popc(quarters);
-      int incl = cnt;
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
+      const int incl = wave_prefix(cnt);
       int at = before + incl - cnt;
       before += __builtin_amdgcn_readlane(incl, 63);
       while (quarters) {
@@ -726,12 +841,6 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
   // The queues. A workgroup's first item is its rank among those numbered for the same queue, without an atomic (all 512
   // of them start at once, and atomics on one counter are served one after the other: up to 7 us); the counters hand out
   // what follows.
-  // (Where the pairs do not divide evenly among the XCDs the queues hold every eighth item of all pairs instead: with
-  // four pairs half the chip would have nothing to start with.)
-  const bool even = n_pairs % kXcd == 0;
-  auto queue_items = [&](int qu) { return even ? n_pairs / kXcd * per_pair : (n_pairs * per_pair - qu + kXcd - 1) / kXcd; };
-  auto pair_of = [&](int item, int qu) { return even ? item / per_pair * kXcd + qu : (item * kXcd + qu) % n_pairs; };
-  auto within_of = [&](int item, int qu) { return even ? item % per_pair : (item * kXcd + qu) / n_pairs; };
   auto queue_starts = [&](int qu) { return ((int)gridDim.x - qu + kXcd - 1) / kXcd; };
   // (Each draws when its item is finished: with the ticket's way laid under the stores of the item before, the prefill of
   // the 32k layer took up to 5 % longer.)
@@ -739,7 +848,8 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
   int prev_item = -1, prev_queue = 0;  // (wave 0) the item just finished
   bool first = true;
   while (true) {
-    __syncthreads();  // previous item: every wave is done with the LDS rings, with s_item and with sh.bad
+    // previous item: every wave is done with the LDS rings, with s_item and with sh.bad (its stores stay in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (wave == 0) {
       int item = -1, queue = 0;
       if (FAST && prev_item >= 0 && sh.bad && lane == 0) {  // some row of the previous item needs the running reference
@@ -758,18 +868,18 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
       } else {
         if (first) {
           queue = blockIdx.x % kXcd;
-          if ((int)blockIdx.x / kXcd < queue_items(queue)) item = blockIdx.x / kXcd;
+          if ((int)blockIdx.x / kXcd < qs.items(queue)) item = blockIdx.x / kXcd;
         }
         while (item < 0 && hop < kXcd) {
           queue = (my_xcd + hop) & (kXcd - 1);
           int got = 0;
-          if (queue_items(queue) <= queue_starts(queue)) {  // all of them handed out as first items
+          if (qs.items(queue) <= queue_starts(queue)) {  // all of them handed out as first items
             ++hop;
             continue;
           }
           if (lane == 0) got = atomicAdd(&t.ctl[queue * kCtlStep], 1);
           got = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
-          if (got < queue_items(queue)) item = got;
+          if (got < qs.items(queue)) item = got;
           else ++hop;
         }
       }
@@ -778,10 +888,16 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
       prev_queue = queue;
       int t0 = 0, t1 = 0;
       if (item >= 0) {
-        const int within = within_of(item, queue), hkv = pair_of(item, queue) % a.Hkv;
-        const int *rp = row_ptr + (int64_t)(hkv * G + within % G) * (a.nQt + 1) + (a.nQt - 1 - within / G);
-        t0 = __builtin_amdgcn_readfirstlane(rp[0]);
-        t1 = __builtin_amdgcn_readfirstlane(rp[1]);
+        if ((FAST || !from_list) && t.order) {  // item: the place in the order
+          const int4 e = t.order[queue * kOrderMax + item];
+          prev_item = item = __builtin_amdgcn_readfirstlane(e.x);
+          t0 = __builtin_amdgcn_readfirstlane(e.y);
+          t1 = __builtin_amdgcn_readfirstlane(e.z);
+        } else {
+          const int *rp = qs.span(row_ptr, item, queue);
+          t0 = __builtin_amdgcn_readfirstlane(rp[0]);
+          t1 = __builtin_amdgcn_readfirstlane(rp[1]);
+        }
         expand(t0, t0, min(kSegTiles, t1 - t0));
       }
       if (lane == 0) {
@@ -794,7 +910,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(sh.item[0]), queue = __builtin_amdgcn_readfirstlane(sh.item[1]);
     if (item < 0) break;
-    const int pair = pair_of(item, queue), within = within_of(item, queue);
+    const int pair = qs.pair_of(item, queue), within = qs.within_of(item, queue);
     const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
     const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
     const int t0 = __builtin_amdgcn_readfirstlane(sh.item[2]), t1 = __builtin_amdgcn_readfirstlane(sh.item[3]);
@@ -1013,12 +1129,14 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int row_first = wqt * kBM + wave * 32;
-      __hip_bfloat16 *op = out + wb * a.o_sb + whq * a.o_sh + (int64_t)row_first * a.o_ss + 8 * (l & 15);
+      __hip_bfloat16 *op = out + wb * a.o_sb + whq * a.o_sh + (int64_t)(row_first + (l >> 4)) * a.o_ss + 8 * (l & 15);
+      const int64_t four_rows = 4 * a.o_ss;
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
         const int r = 4 * it + (l >> 4);
         const uint4 x = *reinterpret_cast<const uint4 *>(turn + r * 256 + (((l & 15) ^ (r & 15)) << 4));
-        if (row_first + r < a.S) *reinterpret_cast<uint4 *>(op + (int64_t)r * a.o_ss) = x;
+        if (row_first + r < a.S) *reinterpret_cast<uint4 *>(op) = x;
+        op += four_rows;
       }
     }
     if (qlive && lse && hf == 0)
@@ -1079,10 +1197,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloat16 *__restrict__ k,
                                                    const __hip_bfloat16 *__restrict__ v, const int *__restrict__ gather_idx,
                                                    __hip_bfloat16 *__restrict__ kgath, __hip_bfloat16 *__restrict__ vgath,
-                                                   int *__restrict__ queue_next) {
-  // (also resets the work queues of the attention kernel that follows: one launch less per call)
+                                                   int *__restrict__ queue_next, const int *__restrict__ row_ptr,
+                                                   const uint8_t *__restrict__ blk_kind, int4 *__restrict__ order) {
+  // (also prepares the work queues of the attention kernel that follows: one launch less per call. The workgroups that
+  // order them come first.)
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kCtlWords) queue_next[threadIdx.x * kCtlStep] = 0;
-  const int bh = blockIdx.y, b = bh / a.Hq, hq = bh % a.Hq, hkv = hq / (a.Hq / a.Hkv);
+  const int lead = order ? kXcd : 0;  // rows of the grid in front
+  if ((int)blockIdx.y < lead) {
+    if (blockIdx.x == 0) order_items<256>(a, row_ptr, blk_kind, blockIdx.y, order);
+    return;
+  }
+  const int bh = blockIdx.y - lead, b = bh / a.Hq, hq = bh % a.Hq, hkv = hq / (a.Hq / a.Hkv);
   const int s = blockIdx.x * 16 + (threadIdx.x >> 4), chunk = threadIdx.x & 15;
   if (s >= a.gather_rows) return;
   const int c = s < a.gather_stride ? gather_idx[(int64_t)hq * a.gather_stride + s] : -1;
@@ -1096,8 +1221,10 @@ __global__ __launch_bounds__(256) void k_gather_kv(AttnArgs a, const __hip_bfloa
   *reinterpret_cast<uint4 *>(vgath + row * a.v_ss + chunk * 8) = vv;
 }
 
-__global__ void k_zero_queues(int *queue_next) {
-  if (threadIdx.x < kCtlWords) queue_next[threadIdx.x * kCtlStep] = 0;
+__global__ __launch_bounds__(kOrderMax) void k_order_items(AttnArgs a, int *__restrict__ queue_next, const int *__restrict__ row_ptr,
+                                                      const uint8_t *__restrict__ blk_kind, int4 *__restrict__ order) {
+  if (threadIdx.x == 0) queue_next[blockIdx.x * kCtlStep] = 0;
+  if (order) order_items<kOrderMax>(a, row_ptr, blk_kind, blockIdx.x, order);
 }
 
 int validate(const dam_attn_params *p, const void *q, const void *k, const void *v, const dam_mask_view *mk,
@@ -1159,14 +1286,26 @@ static size_t redo_bytes(const dam_attn_params *p) {
   return ((items + kXcd) * sizeof(int) + 255) / 256 * 256;
 }
 
+// bytes of the queues' order: none where a queue is too long, or where most items are some workgroup's first one and the look-up
+// costs more than the order brings (512 workgroups on this chip; 576 items 39.8 us by number, 41.7 by length, 960 items 53.5 / 52)
+static size_t order_bytes(const dam_attn_params *p) {
+  const int64_t items = (int64_t)p->batch * p->hq * ((p->seq + p->tile_m - 1) / p->tile_m);
+  const int64_t longest = p->batch * p->hkv % kXcd == 0 ? items / kXcd : (items + kXcd - 1) / kXcd;
+  return items >= 768 && longest <= kOrderMax ? (size_t)kXcd * kOrderMax * sizeof(int4) : 0;
+}
+
+// the control words of the bf16 kernel (queue counters), the links of the redo lists, then the gathered K and V copies
+// (rows at the caches' strides); what the kernel cannot do without
+static size_t least_bytes(const dam_attn_params *p) {
+  return kCtlBytes + redo_bytes(p) +
+         (size_t)p->batch * p->hq * p->gather_rows * (size_t)(p->k_stride[2] + p->v_stride[2]) * sizeof(__hip_bfloat16);
+}
+
 extern "C" size_t dam_sparse_attn_prefill_workspace(const dam_attn_params *p) {
   if (!p || p->batch < 1 || p->hkv < 1 || p->hq < 1 || p->seq < 1 || p->gather_rows < 0) return 0;
   if (p->dtype != DAM_BF16) return 0;
   if (p->hq % p->hkv || p->tile_m < 64) return 0;
-  // the control words of the bf16 kernel (queue counters), the links of the redo lists, then the gathered K and V copies
-  // (rows at the caches' strides)
-  return kCtlBytes + redo_bytes(p) +
-         (size_t)p->batch * p->hq * p->gather_rows * (size_t)(p->k_stride[2] + p->v_stride[2]) * sizeof(__hip_bfloat16);
+  return least_bytes(p) + order_bytes(p);
 }
 
 extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, const void *k, const void *v,
@@ -1174,8 +1313,8 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
                                        void *stream_v) {
   const int bad = validate(p, q, k, v, mk, out);
   if (bad != DAM_OK) return bad;
-  const size_t need = dam_sparse_attn_prefill_workspace(p);
-  if (need && (!ws || ws_bytes < need)) return DAM_ERR_WORKSPACE;
+  // (a workspace without room for the order, one sized for a larger batch for instance, does without it)
+  if (p->dtype == DAM_BF16 && (!ws || ws_bytes < least_bytes(p))) return DAM_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream_v);
   AttnArgs a = make_args(p);
   if (mk->gather_idx) {
@@ -1200,12 +1339,15 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
   int *next = reinterpret_cast<int *>(static_cast<char *>(ws) + kCtlBytes);
   __hip_bfloat16 *kgath = reinterpret_cast<__hip_bfloat16 *>(static_cast<char *>(ws) + kCtlBytes + redo_bytes(p));
   __hip_bfloat16 *vgath = kgath + (size_t)p->batch * p->hq * a.gather_rows * (size_t)a.k_ss;
+  int4 *order = nullptr;
+  if (blocks > 2 * n_cu && order_bytes(p) && ws_bytes >= least_bytes(p) + order_bytes(p))
+    order = reinterpret_cast<int4 *>(static_cast<char *>(ws) + least_bytes(p));
   if (a.gather_rows > 0)
-    k_gather_kv<<<dim3((a.gather_rows + 15) / 16, p->batch * p->hq), 256, 0, st>>>(
+    k_gather_kv<<<dim3((a.gather_rows + 15) / 16, p->batch * p->hq + (order ? kXcd : 0)), 256, 0, st>>>(
         a, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->gather_idx,
-        kgath, vgath, ctl);
+        kgath, vgath, ctl, mk->blk_row_ptr, mk->blk_kind, order);
   else if (blocks > 2 * n_cu)  // (fewer items are all first items: no counter is asked)
-    k_zero_queues<<<1, 64, 0, st>>>(ctl);
+    k_order_items<<<kXcd, kOrderMax, 0, st>>>(a, ctl, mk->blk_row_ptr, mk->blk_kind, order);
   const int persistent = std::min(blocks, 2 * n_cu);  // two workgroups fit a CU (registers and LDS)
   const bool ragged = p->seq % kBlkKeys != 0, gather = a.gather_rows > 0;
   using Kernel = void (*)(AttnArgs, Operands);
@@ -1219,7 +1361,7 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kPipeLds) != hipSuccess)
     return DAM_ERR_DEVICE;
   const Operands t{(const __hip_bfloat16 *)q, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->blk_row_ptr, mk->blk_col,
-                   mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl, next, kgath, vgath};
+                   mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl, next, order, kgath, vgath};
   kern<<<persistent, 256, kPipeLds, st>>>(a, t);
   return launch_status();
 }
