@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "dam_internal.h"
+#include "dam_slices.h"
 
 namespace {
 using namespace dam;
@@ -31,6 +32,7 @@ struct CapArgs {
   int parts, chunk;  // matrix-core path: a row tile's stages of keys are shared by `parts` workgroups, `chunk` stages each
   unsigned theta_key;          // fused form: the threshold as an ordered key,
   float bmin, *out_bmin;       // and the minimum it was found against, stored by the second pass when wanted
+  uint64_t *vslices, *dslices; // the patterns' chunk counts, when the second pass takes them
   float c2;  // scale * log2(e): logits in log2 units
   int64_t q_sh, q_ss, k_sh, k_ss;
 };
@@ -610,8 +612,18 @@ __global__ __launch_bounds__(256) void k_capture_pipe(CapArgs a, const __hip_bfl
     }
   } else {
     clear_words(((n_stage + 1) / 2) * 4);
+    if (a.vslices) {
+      // The tile's 128 rows are one chunk of the pattern counts: counted here, where its words come out of L2 and other
+      // workgroups' products run meanwhile. (64 heads x 4096 tokens, whole call: 342 us with the counts in a launch of 56 us,
+      // 321 with the launch as it is now, 316 so.)
+      __syncthreads();
+      const int64_t at = ((int64_t)h * nQt + qt) * kSlices * a.tbw;
+      count_chunk(true_bits + ((int64_t)h * a.L + qt * kRows) * a.tbw, min(kRows, a.n - qt * kRows), a.tbw, qt,
+                  reinterpret_cast<uint64_t *>(lds), a.vslices + at, a.dslices + at);
+    }
   }
 }
+static_assert(kRows == kChunkRows && kSliceLds <= 2 * kStageBytes, "a row tile is a chunk, counted in the LDS of its stages");
 
 bool mfma_path(const dam_capture_params *p) { return p->dtype == DAM_BF16 && p->head_dim == 128; }
 
@@ -625,6 +637,7 @@ CapArgs make_args(const dam_capture_params *p) {
   a.theta_key = 0;
   a.bmin = 0.0f;
   a.out_bmin = nullptr;
+  a.vslices = a.dslices = nullptr;
   a.parts = 1;
   a.chunk = 0;
   if (mfma_path(p)) {
@@ -693,13 +706,20 @@ size_t capture_lse_bytes(const dam_capture_params *p) {
   return align_up(row_bytes * p->hq * (size_t)p->pcl, 256);
 }
 
-void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
-                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, hipStream_t st) {
+bool launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
+                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, uint64_t *vslices,
+                              uint64_t *dslices, hipStream_t st) {
   CapArgs a = make_args(p);
   a.theta_key = theta_key;
   a.bmin = bmin;
   a.out_bmin = out_bmin;
+  const bool counts = vslices && mfma_path(p) && a.parts == 1 && p->len == p->pcl;  // (no workgroup has whole rows otherwise)
+  if (counts) {
+    a.vslices = vslices;
+    a.dslices = dslices;
+  }
   launch<kEmitBits>(p, a, q, k, lse2, true_bits, nullptr, nullptr, st);
+  return counts;
 }
 
 }  // namespace dam

@@ -72,11 +72,13 @@ __device__ __forceinline__ bool arrive_last(uint64_t *flags, int n, int self, ui
 
 // dam_capture.hip: argument check of a capture, bytes of its row log-sum-exp buffer, and the fused
 // form that writes the true mask of one captured sequence (bit = probability >= threshold, the
-// threshold given as the ordered fp32 key the mask builder uses).
+// threshold given as the ordered fp32 key the mask builder uses). vslices != nullptr: the patterns' chunk counts are wanted
+// too (dam_slices.h); says whether they were written.
 int capture_validate(const dam_capture_params *p, const void *q, const void *k);
 size_t capture_lse_bytes(const dam_capture_params *p);
-void launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
-                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, hipStream_t stream);
+bool launch_capture_true_bits(const dam_capture_params *p, const void *q, const void *k, float *lse2,
+                              unsigned theta_key, float bmin, float *out_bmin, uint64_t *true_bits, uint64_t *vslices,
+                              uint64_t *dslices, hipStream_t stream);
 
 // dam_decode_mfma.hip: the partial pass of the grouped-query decode on the matrix cores. `fits` says
 // whether a call can take it (bf16, head_dim 128, at most 8 query heads per KV head, a head's cache rows

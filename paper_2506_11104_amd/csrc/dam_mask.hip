@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "dam_internal.h"
+#include "dam_slices.h"
 
 #pragma clang fp contract(off)
 
@@ -444,23 +445,8 @@ __global__ __launch_bounds__(256) void k_true_mask_rows(const float *__restrict_
   else true_mask_pairs<false>(A, L, tbw, n_pairs, theta, true_bits);
 }
 
-// Sec. 4.2.4 numerators: kept entries per column and per diagonal of the true mask, counted with
-// carry-save adders on whole 64-bit words. A wave takes a chunk of 64 rows; lane l owns word l of
-// every row (64 columns) and adds the 64 row words into a bit-sliced counter (slice k holds bit k of
-// the 64 column counts), two logic operations per full adder. For the diagonals the row word is first
-// re-aligned: word l of row i then holds m[i][i - r] for r = 64 l .. 64 l + 63 (a funnel shift of two
-// adjacent words and a bit reversal), after which diagonals are columns. The slices of every chunk
-// go to the workspace; k_pattern_finish sums them per pattern and applies the ratio test. No atomics.
-constexpr int kSlices = 7;      // counts 0 .. 64
-constexpr int kChunkRows = 64;
-
-__device__ __forceinline__ void csa(uint64_t &carry, uint64_t &sum, uint64_t a, uint64_t b, uint64_t c) {
-  const uint64_t u = a ^ b;
-  carry = (a & b) | (u & c);
-  sum = u ^ c;
-}
-
-// Form for rows of more than 128 words (capture lengths above 8192): a wave per 64 rows and 64 words,
+// Sec. 4.2.4 numerators (see dam_slices.h).
+// Form for rows of more than 128 words (capture lengths above 8192): a wave per chunk and 64 words,
 // every word fetched from global memory by the lane that owns it (one launch for both pattern kinds: the
 // upper half of the grid's x range counts diagonals).
 __global__ __launch_bounds__(256) void k_pattern_slices_wide(const uint64_t *__restrict__ true_bits, int L, int tbw,
@@ -503,148 +489,21 @@ __global__ __launch_bounds__(256) void k_pattern_slices_wide(const uint64_t *__r
         }
         w[u] = x;
       }
-      uint64_t t0, t1, f0, f1, e;
-      csa(t0, s[0], s[0], w[0], w[1]);
-      csa(t1, s[0], s[0], w[2], w[3]);
-      csa(f0, s[1], s[1], t0, t1);
-      csa(t0, s[0], s[0], w[4], w[5]);
-      csa(t1, s[0], s[0], w[6], w[7]);
-      csa(f1, s[1], s[1], t0, t1);
-      csa(e, s[2], s[2], f0, f1);
-      // add the eights into slices 3 .. 6 (ripple)
-#pragma unroll
-      for (int k = 3; k < kSlices; ++k) {
-        const uint64_t c = s[k] & e;
-        s[k] ^= e;
-        e = c;
-      }
+      add_eight(s, w);
     }
   }
-  uint64_t *out = slices + (((int64_t)h * n_chunks + chunk) * kSlices) * tbw + wl;
+  uint64_t *out = slices + (((int64_t)h * n_chunks + chunk) * tbw + wl) * kSlices;
 #pragma unroll
-  for (int k = 0; k < kSlices; ++k) out[(int64_t)k * tbw] = s[k];
+  for (int k = 0; k < kSlices; ++k) out[k] = s[k];
 }
 
-// Form for rows of up to 128 words: one workgroup per (head, chunk of 64 rows) counts both pattern
-// kinds from one copy of the chunk in LDS, so that the true mask is read once (its lower triangle
-// only: a word past the chunk's diagonal holds nothing). W = the number of words up to that diagonal
-// rounded up to a power of two (16 .. 128); thread t owns word t % W of the rows t / W, t / W + 256 / W, ...:
-// for the columns that is the row's word itself, for the diagonals the window of the row that ends
-// at column i - 64 w, reversed (two neighbouring words of the LDS copy, a funnel shift and a bit
-// reversal). The 256 / W partial counters of a word are added through LDS (bit-sliced, 7 + 7 bits).
-__global__ __launch_bounds__(256) void k_pattern_slices(const uint64_t *__restrict__ true_bits, int L, int tbw,
-                                                        int n_chunks, int Wmax, uint64_t *__restrict__ vslices,
-                                                        uint64_t *__restrict__ dslices) {
-  extern __shared__ uint64_t sm[];  // [64][W] row words, afterwards [2][256 / W][kSlices][W] partial counters
-  const int chunk = blockIdx.x, h = blockIdx.y, i0 = chunk * kChunkRows;
-  const int rows = min(kChunkRows, L - i0);
-  const int wmax = min(tbw, chunk + 1);  // words that can hold a kept entry of these rows
-  int W = 16;                            // ... rounded up to a power of two: the threads share those words only
-  while (W < wmax) W *= 2;
-  W = min(W, Wmax);
-  const int wl = threadIdx.x & (W - 1), sub = threadIdx.x / W, nsub = 256 / W;
-  const uint64_t *tb = true_bits + ((int64_t)h * L + i0) * tbw;
-  for (int r0 = sub; r0 < kChunkRows; r0 += 8 * nsub) {  // eight loads in flight per thread
-    uint64_t v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = r0 + u * nsub;
-      v[u] = (r < rows && wl < wmax) ? __builtin_nontemporal_load(tb + (int64_t)r * tbw + wl) : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = r0 + u * nsub;
-      if (r < kChunkRows) sm[r * W + wl] = v[u];
-    }
-  }
-  __syncthreads();
-  uint64_t sc[kSlices], sd[kSlices];
-#pragma unroll
-  for (int k = 0; k < kSlices; ++k) sc[k] = sd[k] = 0;
-  const int wj = chunk - wl;  // word of column i - 64 wl, the same for every row of the chunk
-  const int per_thread = kChunkRows / nsub;
-  for (int g = 0; g < per_thread; g += 8) {
-    uint64_t c[8], d[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = sub + nsub * (g + u);  // rows past the chunk's end are zero in LDS
-      uint64_t xc = 0, xd = 0;
-      if (g + u < per_thread) {
-        xc = sm[r * W + wl];
-        if (wj >= 0) {
-          const int sh = r + 1;  // window = bits jhi - 63 .. jhi of the row, jhi = 64 wj + r
-          const uint64_t hi = sm[r * W + wj];
-          const uint64_t lo = wj > 0 ? sm[r * W + wj - 1] : 0;
-          const uint64_t win = sh == 64 ? hi : ((hi << (64 - sh)) | (lo >> sh));
-          xd = __brevll(win);  // offset r = 64 wl + t at bit t
-        }
-      }
-      c[u] = xc;
-      d[u] = xd;
-    }
-    uint64_t t0, t1, f0, f1, e;
-    csa(t0, sc[0], sc[0], c[0], c[1]);
-    csa(t1, sc[0], sc[0], c[2], c[3]);
-    csa(f0, sc[1], sc[1], t0, t1);
-    csa(t0, sc[0], sc[0], c[4], c[5]);
-    csa(t1, sc[0], sc[0], c[6], c[7]);
-    csa(f1, sc[1], sc[1], t0, t1);
-    csa(e, sc[2], sc[2], f0, f1);
-#pragma unroll
-    for (int k = 3; k < kSlices; ++k) {
-      const uint64_t cy = sc[k] & e;
-      sc[k] ^= e;
-      e = cy;
-    }
-    csa(t0, sd[0], sd[0], d[0], d[1]);
-    csa(t1, sd[0], sd[0], d[2], d[3]);
-    csa(f0, sd[1], sd[1], t0, t1);
-    csa(t0, sd[0], sd[0], d[4], d[5]);
-    csa(t1, sd[0], sd[0], d[6], d[7]);
-    csa(f1, sd[1], sd[1], t0, t1);
-    csa(e, sd[2], sd[2], f0, f1);
-#pragma unroll
-    for (int k = 3; k < kSlices; ++k) {
-      const uint64_t cy = sd[k] & e;
-      sd[k] ^= e;
-      e = cy;
-    }
-  }
-  __syncthreads();  // the row words are no longer needed: their place takes the partial counters
-#pragma unroll
-  for (int k = 0; k < kSlices; ++k) {
-    sm[((0 * nsub + sub) * kSlices + k) * W + wl] = sc[k];
-    sm[((1 * nsub + sub) * kSlices + k) * W + wl] = sd[k];
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < 2 * W) {
-    const int kind = threadIdx.x / W;  // 0 columns, 1 diagonals
-    uint64_t acc[kSlices];
-#pragma unroll
-    for (int k = 0; k < kSlices; ++k) acc[k] = 0;
-    for (int x = 0; x < nsub; ++x) {
-      uint64_t carry = 0;
-#pragma unroll
-      for (int k = 0; k < kSlices; ++k) {
-        const uint64_t in = sm[((kind * nsub + x) * kSlices + k) * W + wl];
-        const uint64_t u = acc[k] ^ in;
-        const uint64_t cy = (acc[k] & in) | (u & carry);
-        acc[k] = u ^ carry;
-        carry = cy;
-      }
-    }
-    if (wl < tbw) {
-      uint64_t *out = (kind ? dslices : vslices) + (((int64_t)h * n_chunks + chunk) * kSlices) * tbw + wl;
-#pragma unroll
-      for (int k = 0; k < kSlices; ++k) out[(int64_t)k * tbw] = acc[k];
-    }
-  }
-  // words past the chunk's diagonal: nothing counted
-  const int rest = tbw - W;
-  for (int x = threadIdx.x; x < 2 * kSlices * rest; x += 256) {
-    const int kind = x / (kSlices * rest), k = (x / rest) % kSlices, w = W + x % rest;
-    ((kind ? dslices : vslices) + (((int64_t)h * n_chunks + chunk) * kSlices) * tbw)[(int64_t)k * tbw + w] = 0;
-  }
+// Form for rows of up to 128 words: one workgroup per (head, chunk).
+__global__ __launch_bounds__(256) void k_pattern_slices(const uint64_t *__restrict__ true_bits, int L, int tbw, int n_chunks,
+                                                        uint64_t *__restrict__ vslices, uint64_t *__restrict__ dslices) {
+  __shared__ uint64_t sm[kSliceLds / sizeof(uint64_t)];
+  const int chunk = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, i0 = chunk * kChunkRows;  // the long rows first
+  const int64_t at = ((int64_t)h * n_chunks + chunk) * kSlices * tbw;
+  count_chunk(true_bits + ((int64_t)h * L + i0) * tbw, min(kChunkRows, L - i0), tbw, chunk, sm, vslices + at, dslices + at);
 }
 
 // gamma = count / size >= mu for pattern p of head h (Sec. 4.2.4), counts summed over the row chunks.
@@ -693,9 +552,9 @@ __global__ __launch_bounds__(256) void k_pattern_finish(const uint64_t *__restri
   // rows above pattern p hold nothing of it: start at the chunk of the group's first pattern
   for (int chunk = word0 * 64 / kChunkRows + sub; chunk < n_chunks; chunk += 16) {
     uint64_t in[kSlices];
-    const int64_t at = (((int64_t)h * n_chunks + chunk) * kSlices) * tbw + wl;
+    const int64_t at = (((int64_t)h * n_chunks + chunk) * tbw + wl) * kSlices;
 #pragma unroll
-    for (int k = 0; k < kSlices; ++k) in[k] = wl < tbw ? slices[at + (int64_t)k * tbw] : 0;
+    for (int k = 0; k < kSlices; ++k) in[k] = wl < tbw ? slices[at + k] : 0;
     sliced_add(acc, in, nb);
   }
   for (int half = 8; half >= 1; half >>= 1) {
@@ -1032,14 +891,11 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
 // flags and bitsets, by the 16 waves of one workgroup. A job is one word (64 patterns) of one kind over one chunk of 64 rows:
 // a lane per row, the 64 x 64 bits turned around, and a lane per pattern then counts its word. The jobs of the causal
 // triangle go round the waves and add into LDS.
-// In place of the two kernels that longer captures take (k_pattern_slices, k_pattern_finish), which cost 5 us each however
-// short they are. Whole builds: 2 heads x 64 29.4 -> 18.3 us, 32 heads x 256 40.1 -> 29.7, x 512 50.6 -> 39.9, x 768
-// 59.6 -> 53.2, x 1024 69.6 -> 68.2, 64 heads x 1024 116.6 -> 107.8. The jobs grow with the square of the capture and run
-// on one CU per head, so the line lies where the gain ends: at kDirectL where k_pattern_prep is launched anyway or where many
-// heads keep the chip busy, and lower where it would be launched for this alone. There, two kernels / this, us: 1 head x 896
-// 19.0 / 18.6, x 960 19.2 / 20.5, x 1024 19.2 / 22.1; 32 heads x 896 32.6 / 31.8, x 1024 35.9 / 37.8; 64 heads x 1024
-// 54.4 / 53.9; 48 heads x 960 45.0 / 44.3, x 1024 46.9 / 48.0; 96 heads x 1024 82.6 / 77.3.
-constexpr int kDirectL = 1024, kDirectAloneL = 896, kDirectHeads = 48;
+// In place of the launches that longer captures take (k_pattern_slices, and k_pattern_finish or sum_slices_of_head), which
+// cost 5 us each however short they are. The jobs grow with the square of the capture and run on one CU per head, so the line
+// lies where the gain ends; whole builds, the launches / this, us: 32 heads x 320 35.9 / 31.8, x 512 42.7 / 40.0, x 768 52.1 /
+// 52.4, x 1024 63.1 / 68.0, 16 x 640 38.8 / 37.8, 64 x 768 72.8 / 72.2, 64 x 1024 98.3 / 102.7, 8 x 1024 42.0 / 47.8.
+constexpr int kDirectL = 768;
 __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
                                                        float mu, int h, int *cnt,                       // LDS [2][kDirectL]
                                                        int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
@@ -1095,11 +951,50 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
   }
 }
 
+// The same from the chunk counts of k_pattern_slices, for captures where adding those up is little work for one workgroup
+// (kSlicesInPrep): a wave per word of patterns, a lane per pattern; the slices of a word and chunk are wave-uniform, so a
+// chunk's count is built bit by bit from scalar registers. Saves the launch of k_pattern_finish: whole builds at 32 heads x 1024
+// 67.9 us counted in the prep kernel, 63.1 so; x 1536 100.8 us with k_pattern_finish, 96.3; x 2048 161.1, 161.8.
+constexpr int kSlicesInPrep = 1536;
+__device__ __forceinline__ void sum_slices_of_head(const Geom &g, const uint64_t *__restrict__ vslices, const uint64_t *__restrict__ dslices,
+                                                   float mu, int h, int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
+                                                   uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,
+                                                   uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev, uint64_t *lds_copy) {
+  const int lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
+  const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
+  for (int x = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); x < 2 * g.tbw; x += n_waves) {
+    const int word = x >> 1, p = 64 * word + lane;
+    const uint64_t *slices = (x & 1 ? dslices : vslices) + ((int64_t)h * n_chunks * g.tbw + word) * kSlices;
+    int n = 0;
+    // rows above pattern p hold nothing of it
+    for (int chunk = word * 64 / kChunkRows; chunk < n_chunks; ++chunk) {
+      int v = 0;
+#pragma unroll
+      for (int k = kSlices - 1; k >= 0; --k)
+        v = 2 * v + (__builtin_amdgcn_inverse_ballot_w64(slices[(int64_t)chunk * g.tbw * kSlices + k]) ? 1 : 0);
+      n += v;
+    }
+    const bool hit = p < g.L && (float)n / (float)(g.L - p) >= mu;
+    const uint64_t set = __ballot(hit);
+    const int64_t e = (int64_t)h * g.L + p;
+    if (p < g.L) {
+      if (int *out = x & 1 ? diag_cnt : vert_cnt) out[e] = n;
+      (x & 1 ? diag_flag : vert_flag)[e] = (uint8_t)hit;
+    }
+    if (lane == 0) {
+      const int to = x & 1 ? g.pw - 1 - word : word;
+      const uint64_t v = x & 1 ? __brevll(set) : set;
+      (x & 1 ? rrev : cbits)[(int64_t)h * g.pw + to] = v;
+      if (lds_copy) lds_copy[(x & 1 ? g.pw : 0) + to] = v;
+    }
+  }
+}
+
 // Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
 // per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
 // the two bitsets, the tile classes, the gathered column list.
-struct CountArgs {  // true_bits: count the patterns here and write the flags, else the flags are given
-  const uint64_t *true_bits;
+struct CountArgs {  // true_bits: count the patterns here and write the flags; vslices: add up the chunks' counts; else the flags are given
+  const uint64_t *true_bits, *vslices, *dslices;
   float mu;
   int *vert_cnt, *diag_cnt;
   uint8_t *vert_flag, *diag_flag;
@@ -1119,6 +1014,8 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, con
     __shared__ int cnt[2 * kDirectL];
     count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
                            ca.diag_flag, cbits, rrev, copy);
+  } else if (ca.vslices) {
+    sum_slices_of_head(g, ca.vslices, ca.dslices, ca.mu, h, ca.vert_cnt, ca.diag_cnt, ca.vert_flag, ca.diag_flag, cbits, rrev, copy);
   } else {
     pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
   }
@@ -2295,27 +2192,30 @@ bool needs_prep(const dam_mask_params *p, const dam_mask_out *o) {
   return o->blk_row_ptr || o->dense_bits || (o->kept_ptr && rows);
 }
 
+// Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
+bool counts_in_prep(const Geom &g) { return g.L <= kDirectL; }
+
 // a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
-// k_pattern_prep has to count for that.
+// k_pattern_prep has to count for that. counted: the chunks' slices are there already.
 CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
-                    hipStream_t stream, const uint8_t **dflag, const uint8_t **vflag, bool bmin_written) {
+                    hipStream_t stream, const uint8_t **dflag, const uint8_t **vflag, bool bmin_written, bool counted) {
   uint8_t *df = o->diag_flag ? o->diag_flag : w.diag_flag;
   uint8_t *vf = o->vert_flag ? o->vert_flag : w.vert_flag;
   *dflag = df;
   *vflag = vf;
   if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
-  if (g.L <= kDirectL && (g.L <= kDirectAloneL || g.H >= kDirectHeads || needs_prep(p, o)))
-    return CountArgs{o->true_bits, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
+  if (counts_in_prep(g))
+    return CountArgs{o->true_bits, nullptr, nullptr, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
-  if (g.tbw <= 128) {
-    int W = 16;
-    while (W < g.tbw) W *= 2;
-    const size_t lds = std::max<size_t>((size_t)kChunkRows * W, (size_t)2 * 256 * kSlices) * sizeof(uint64_t);
-    k_pattern_slices<<<dim3(n_chunks, g.H), 256, lds, stream>>>(o->true_bits, g.L, g.tbw, n_chunks, W, w.vslices, w.dslices);
+  if (counted) {
+  } else if (g.tbw <= 128) {
+    k_pattern_slices<<<dim3(n_chunks, g.H), 256, 0, stream>>>(o->true_bits, g.L, g.tbw, n_chunks, w.vslices, w.dslices);
   } else {
     const dim3 sgrid(2 * ((g.tbw + 63) / 64), (n_chunks + 3) / 4, g.H);
     k_pattern_slices_wide<<<sgrid, 256, 0, stream>>>(o->true_bits, g.L, g.tbw, n_chunks, w.vslices, w.dslices);
   }
+  if (g.L <= kSlicesInPrep && needs_prep(p, o))
+    return CountArgs{nullptr, w.vslices, w.dslices, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   int nb = 1;  // bits of the largest possible count, L
   while ((g.L >> nb) != 0) ++nb;
   k_pattern_finish<<<dim3((g.tbw + kFinWords - 1) / kFinWords, g.H, 2), 256, 0, stream>>>(w.vslices, w.dslices, g.L, g.tbw, n_chunks, nb, p->mu,
@@ -2449,7 +2349,7 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
       k_true_mask_rows<<<dim3(per_map, g.H), 256, 0, stream>>>(attn_sum, g.L, g.tbw, n_pairs, thr, o->true_bits);
     } else
       k_true_mask<true><<<grid, 256, 0, stream>>>(attn_sum, attn_cnt, g.L, g.tbw, p->eps, thr, o->true_bits);
-    count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
+    count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, false);
   }
   stage_extension(p, g, w, o, true_bits, dflag, vflag, count, stream);
   return launch_status();
@@ -2484,8 +2384,9 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
   bool bmin_written;
   // (one causal capture of two tokens or more: the minimum, and so the threshold, is known on the host)
   const Threshold thr = stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, &bmin_written);
-  launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits, stream);
-  const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written);
+  const bool counted = launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits,
+                                                counts_in_prep(g) ? nullptr : w.vslices, w.dslices, stream);
+  const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, counted);
   stage_extension(p, g, w, o, o->true_bits, dflag, vflag, count, stream);
   return launch_status();
 }

@@ -1,4 +1,4 @@
-"""Short captures: pattern counts taken inside the prep kernel (up to 1024 tokens), and query tiles inside the true-mask
+"""Short captures: pattern counts taken inside the prep kernel (up to 768 tokens), and query tiles inside the true-mask
 block, whose tiles the scan looks at four at a time. Bit for bit against the oracle."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ from test_gpu_mask import run_from_map, synth_map
 pytestmark = pytest.mark.gpu
 
 
-# one word, its neighbours, both sides of the longest capture counted there, one chunk more and less than a round of waves
+# one word, its neighbours, whole and ragged chunks, one chunk more and less than a round of waves
 @pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 200, 512, 1023, 1024, 1025])
 @pytest.mark.parametrize("mu", [0.0, 0.3, 1.0])
 def test_pattern_counts_of_short_captures(L, mu):
@@ -41,7 +41,7 @@ def test_tiles_of_the_true_mask_block(tm, tn, S):
     run_from_map(A, None, S, tm, tn, 0.5, 1e-8, 0.02, 0.8)
 
 
-# both sides of the lines for captures whose patterns are counted with nothing else to do: 896 tokens, 48 heads
+# captures whose patterns are counted with nothing else to do
 @pytest.mark.parametrize("L,copies", [(895, 1), (896, 1), (897, 1), (1024, 1), (897, 23), (897, 24), (1024, 24)])
 def test_pattern_counts_alone_on_both_sides_of_the_lines(L, copies):
     A = synth_map(np.random.default_rng(L + copies), 2, L)
