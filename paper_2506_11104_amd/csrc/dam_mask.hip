@@ -27,6 +27,10 @@ using namespace dam;
 // 256 threads); each takes several items in turn.
 constexpr int kGridTarget = 4096;
 constexpr int kHeadSub = 16;  // partial sums per head of the listed-tile counts
+// Query tiles of a head up to which k_pattern_prep scans them itself, a wave each, and the scan launch is saved. Whole builds,
+// launch / this, us: 2 heads x 4 tiles 17.8 / 16.9, 32 x 8 (capture of 256) 30.4 / 28.0, 64 x 8 35.9 / 32.7, 32 x 8 from patterns
+// 29.3 / 27.6; 32 x 16 29.0 / 29.8 (a wave per tile still, but on one CU per head), 32 x 32 31.7 / 38.3.
+constexpr int kScanInPrep = 8;
 
 struct Geom {
   int H, L, S, P;            // P: length of the pattern flag arrays (L from a map, S when given)
@@ -990,48 +994,6 @@ __device__ __forceinline__ void sum_slices_of_head(const Geom &g, const uint64_t
   }
 }
 
-// Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
-// per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
-// the two bitsets, the tile classes, the gathered column list.
-struct CountArgs {  // true_bits: count the patterns here and write the flags; vslices: add up the chunks' counts; else the flags are given
-  const uint64_t *true_bits, *vslices, *dslices;
-  float mu;
-  int *vert_cnt, *diag_cnt;
-  uint8_t *vert_flag, *diag_flag;
-};
-__global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, const uint8_t *__restrict__ diag_flag,
-                                                       const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
-                                                       uint64_t *__restrict__ rrev, bool classes,
-                                                       uint64_t *__restrict__ col_any, uint64_t *__restrict__ col_all,
-                                                       uint64_t *__restrict__ off_any, uint64_t *__restrict__ off_all,
-                                                       int gstride, int *__restrict__ gidx, int *__restrict__ gcnt,
-                                                       int *__restrict__ head_cnt, bool in_lds) {
-  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw]
-  const int h = blockIdx.x;
-  if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
-  uint64_t *copy = in_lds && classes ? prep_sets : nullptr;
-  if (ca.true_bits) {  // uniform over the grid
-    __shared__ int cnt[2 * kDirectL];
-    count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
-                           ca.diag_flag, cbits, rrev, copy);
-  } else if (ca.vslices) {
-    sum_slices_of_head(g, ca.vslices, ca.dslices, ca.mu, h, ca.vert_cnt, ca.diag_cnt, ca.vert_flag, ca.diag_flag, cbits, rrev, copy);
-  } else {
-    pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
-  }
-  if (!classes) return;  // uniform over the grid
-  __syncthreads();       // the sets are read back by other threads of this workgroup
-  // (from the LDS copy when they fit: the steps below are chains of dependent reads. One call per address space,
-  // so that the compiler knows which kind of read to use.)
-  if (in_lds) {
-    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, h, col_any, col_all, off_any, off_all);
-    if (gidx) gather_columns_of_head(g, prep_sets, gstride, h, gidx, gcnt);
-  } else {
-    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, h, col_any, col_all, off_any, off_all);
-    if (gidx) gather_columns_of_head(g, cbits + (int64_t)h * g.pw, gstride, h, gidx, gcnt);
-  }
-}
-
 // Row bitmap of one gathered slot for the rows of query tile qt: bit r of word k is row 64 k + r of the
 // tile. c < 0: an empty slot.
 __device__ __forceinline__ void slot_rows(const Geom &g, const uint64_t *__restrict__ rr, int i0, int c,
@@ -1232,6 +1194,65 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   }
   if (lane == 0) cnt[(int64_t)h * g.nQt + qt] = total;
   return total;
+}
+
+// Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
+// per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
+// the two bitsets, the tile classes, the gathered column list.
+struct CountArgs {  // true_bits: count the patterns here and write the flags; vslices: add up the chunks' counts; else the flags are given
+  const uint64_t *true_bits, *vslices, *dslices;
+  float mu;
+  int *vert_cnt, *diag_cnt;
+  uint8_t *vert_flag, *diag_flag;
+};
+// scan.on: and pass 1 of the block index (tile_scan_row, below as a kernel of its own), a wave per query tile, which saves that
+// launch where the query tiles of a head are few (see scans_in_prep).
+struct ScanArgs {
+  bool on;
+  uint64_t *occ, *full, *vocc, *vfull;
+  int *cnt;
+  const uint64_t *true_bits;
+};
+__global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, ScanArgs scan, const uint8_t *__restrict__ diag_flag,
+                                                       const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
+                                                       uint64_t *__restrict__ rrev, bool classes,
+                                                       uint64_t *__restrict__ col_any, uint64_t *__restrict__ col_all,
+                                                       uint64_t *__restrict__ off_any, uint64_t *__restrict__ off_all,
+                                                       int gstride, int *__restrict__ gidx, int *__restrict__ gcnt,
+                                                       int *__restrict__ head_cnt, bool in_lds) {
+  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw]
+  const int h = blockIdx.x;
+  if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
+  uint64_t *copy = in_lds && classes ? prep_sets : nullptr;
+  if (ca.true_bits) {  // uniform over the grid
+    __shared__ int cnt[2 * kDirectL];
+    count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
+                           ca.diag_flag, cbits, rrev, copy);
+  } else if (ca.vslices) {
+    sum_slices_of_head(g, ca.vslices, ca.dslices, ca.mu, h, ca.vert_cnt, ca.diag_cnt, ca.vert_flag, ca.diag_flag, cbits, rrev, copy);
+  } else {
+    pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
+  }
+  if (!classes) return;  // uniform over the grid
+  __syncthreads();       // the sets are read back by other threads of this workgroup
+  // (from the LDS copy when they fit: the steps below are chains of dependent reads. One call per address space,
+  // so that the compiler knows which kind of read to use.)
+  if (in_lds) {
+    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, h, col_any, col_all, off_any, off_all);
+    if (gidx) gather_columns_of_head(g, prep_sets, gstride, h, gidx, gcnt);
+  } else {
+    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, h, col_any, col_all, off_any, off_all);
+    if (gidx) gather_columns_of_head(g, cbits + (int64_t)h * g.pw, gstride, h, gidx, gcnt);
+  }
+  if (!scan.on) return;  // uniform over the grid
+  __syncthreads();  // classes and columns are read back by other threads of this workgroup
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t *tb = scan.true_bits ? scan.true_bits + (int64_t)h * g.L * g.tbw : nullptr;
+  int mine = 0;
+  for (int qt = wave; qt < g.nQt; qt += blockDim.x >> 6)
+    mine += tile_scan_row(g, tb, prep_sets, prep_sets + g.pw, col_any, col_all, off_any, off_all, scan.occ, scan.full, scan.cnt, gidx, gcnt,
+                          gstride, scan.vocc, scan.vfull, h, qt, lane);
+  if (lane == 0) head_cnt[h * kHeadSub + wave] = mine;
 }
 
 // Exclusive scan of n counts by one block. group > 0: the result is laid out as [n / group]
@@ -2192,6 +2213,10 @@ bool needs_prep(const dam_mask_params *p, const dam_mask_out *o) {
   return o->blk_row_ptr || o->dense_bits || (o->kept_ptr && rows);
 }
 
+// Whether k_pattern_prep scans the tiles too: sets in LDS, and few query tiles for a wave to take.
+size_t prep_lds_bytes(const Geom &g) { return (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0; }
+bool scans_in_prep(const Geom &g, const dam_mask_out *o) { return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= kScanInPrep; }
+
 // Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
 bool counts_in_prep(const Geom &g) { return g.L <= kDirectL; }
 
@@ -2235,8 +2260,9 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const int nrows = p->row_end - p->row_begin;
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
   if (needs_prep(p, o) || count.true_bits) {
-    const size_t prep_lds = want_blocks && (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0;
-    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
+    const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
+    const ScanArgs scan{scans_in_prep(g, o), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
+    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
                                                    w.off_all, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
@@ -2244,7 +2270,8 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   if (want_blocks) {
     const size_t lds_sets = staged_bytes(g);
     const bool fill = o->blk_col || o->blk_kind || o->tile_bits;
-    k_tile_scan<<<dim3((g.nQt + 3) / 4, g.H), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
+    if (!scans_in_prep(g, o))
+      k_tile_scan<<<dim3((g.nQt + 3) / 4, g.H), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
                                                                      w.off_all, w.occ, w.full, w.tile_cnt, lds_sets > 0, gidx,
                                                                      gcnt, gstride, w.vocc, w.vfull, w.head_cnt);
     if (fill) {

@@ -7,6 +7,7 @@ import torch
 import oracle
 from dam_testlib import pack_rows_u64, u64
 from paper_2506_11104_amd import binding as B
+import test_gpu_mask
 from test_gpu_mask import run_from_map, synth_map
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,12 @@ def test_pattern_counts_alone_on_both_sides_of_the_lines(L, copies):
                         blocks=False)
     for name in ("diag_cnt", "vert_cnt", "diag_flag", "vert_flag"):
         assert np.array_equal(getattr(mask, name).cpu().numpy(), np.tile(getattr(art, name), (copies, 1))), name
+
+
+# one query tile, the most and one more than the prep kernel scans itself; ragged, inside and beyond the true-mask block
+@pytest.mark.parametrize("S,tm,tn,L", [(60, 64, 64, 200), (500, 64, 64, 130), (512, 64, 64, 512), (513, 64, 64, 200), (1000, 128, 64, 300),
+                                       (1024, 128, 128, 200), (1025, 128, 128, 200), (700, 256, 64, 64)])
+def test_scan_inside_the_prep_kernel(S, tm, tn, L):
+    run_from_map(synth_map(np.random.default_rng(S), 3, L), None, S, tm, tn, 0.5, 1e-8, 0.02, 0.4)
+    if S > tm:
+        test_gpu_mask.test_gathered_column_tiles_match_oracle(S, tm, tn, min(L, S // 2))
