@@ -40,6 +40,17 @@ struct Carver {
 uint64_t fresh_flag();  // dam_decode.hip; never 0
 
 #ifdef __HIPCC__
+// Inclusive prefix sum over the wave, in the vector registers alone (row shifts, then the row totals handed on).
+__device__ __forceinline__ int wave_prefix(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // last lane of rows 0 and 2 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
+  return v;
+}
+
 // 16 bytes to memory past this XCD's L2, for readers on other XCDs; not complete before stores_done()
 __device__ __forceinline__ void store_through(void *p, float x, float y, float z, float w) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;

@@ -1811,10 +1811,7 @@ __device__ __forceinline__ void row_pieces(const Geom &g, const uint64_t *__rest
   }
 }
 
-__device__ __forceinline__ int wave_total(int v) {
-  for (int off = 32; off; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_prefix(v), 63); }
 
 // cnt[(kv * (G + 1) + run) * spans + span]
 __global__ __launch_bounds__(256) void k_list_count(Geom g, const uint64_t *__restrict__ true_bits,
@@ -1873,11 +1870,7 @@ __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__res
 #pragma unroll
   for (int r = 0; r <= kMaxGroup; ++r)
     if (r <= G) {
-      incl[r] = __popc(r == 0 ? shared : m[r - 1] & ~shared);
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl[r], off);
-        if (lane >= off) incl[r] += up;
-      }
+      incl[r] = wave_prefix(__popc(r == 0 ? shared : m[r - 1] & ~shared));
       if (lane == 63) part[wave][r] = incl[r];
     }
   __syncthreads();

@@ -366,17 +366,6 @@ constexpr int kSegTiles = 128;                      // listed tiles expanded int
 constexpr int kListEntries = kSegTiles * 4 + 1;     // up to four blocks per tile, and the dummy that ends the list
 constexpr int kPipeLds = kBlkList + kListEntries * 8;
 
-// Inclusive prefix sum over the wave, in the vector registers alone (row shifts, then the row totals handed on).
-__device__ __forceinline__ int wave_prefix(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // last lane of rows 0 and 2 to rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
-  return v;
-}
-
 struct Blk {
   int key0;        // first key of the block (gathered tile: first row of the block in the gathered copy)
   int bits_off;    // byte offset of row 0's mask word for the block from the tile row's first mask word
