@@ -1015,6 +1015,21 @@ __device__ __forceinline__ void slot_rows(const Geom &g, const uint64_t *__restr
   }
 }
 
+// The largest tile distance with a matched offset, 0 if there is none: the first set bit of the head's reversed class words.
+// By a whole wave.
+__device__ __forceinline__ int64_t farthest_tile(const uint64_t *__restrict__ off_any_h, int occw, int lane) {
+  for (int w0 = 0; w0 < occw; w0 += 64) {
+    const uint64_t word = w0 + lane < occw ? off_any_h[w0 + lane] : 0;
+    const uint64_t nz = __ballot(word != 0);
+    if (nz) {
+      const int wl = __ffsll((unsigned long long)nz) - 1;
+      const unsigned hi = __builtin_amdgcn_readlane((int)(word >> 32), wl), lo = __builtin_amdgcn_readlane((int)word, wl);
+      return (int64_t)(occw - w0 - wl) * 64 - __ffsll((unsigned long long)((uint64_t)hi << 32 | lo));
+    }
+  }
+  return 0;
+}
+
 // Pass 1 of the block index: which key tiles of query tile (h, qt) hold a kept entry / are full.
 // One wave per query tile, 64 key tiles (one occupancy word) at a time, one lane per key tile. Tiles
 // strictly below the diagonal and outside the true-mask block are decided by their lane alone (from
@@ -1036,6 +1051,17 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   const bool by_class = g.tile_m == g.tile_n && i0 >= g.L && i0 + g.tile_m <= g.S;
   // gathered columns: in a query tile of the pattern region the ordinary tiles hold the diagonal part only
   const bool split = gidx != nullptr && i0 >= g.L;
+  // (the first 64 gathered tiles' first and last columns are fetched here: a load issued behind the stores below waits for
+  // them. Slots past the count hold -1.)
+  int n_cols = 0, g_first = -1, g_last = -1;
+  const int *gi = split ? gidx + (int64_t)h * gstride : nullptr;
+  if (split) {
+    n_cols = gcnt[h];
+    if ((lane + 1) * g.tile_n <= gstride) {
+      g_first = gi[lane * g.tile_n];
+      g_last = gi[lane * g.tile_n + g.tile_n - 1];
+    }
+  }
   const uint64_t *cbw = split ? nullptr : cb;
   const uint64_t *ca = col_any + (int64_t)h * g.occw, *cf = col_all + (int64_t)h * g.occw;
   const uint64_t *da = off_any + (int64_t)h * g.occw, *df = off_all + (int64_t)h * g.occw;
@@ -1050,124 +1076,132 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
     word_row[y] = ((lane + 64 * y) * inv_wpr) >> 16;
     word_col[y] = lane + 64 * y - word_row[y] * g.wpr;
   }
+  // Occupancy words whose 64 tiles all lie further above the query tile than any matched diagonal reaches, and hold no
+  // matched column (or leave those to the gathered tiles), are empty: a lane per word finds that out, and the walk, whose
+  // steps wait for memory one after the other, takes the other words only. (64 heads x 128k tokens, captured at 4096, 16 words
+  // a row at most: scan 281 -> 226 us; with the diagonal and the incomplete gathered tile decided by bounds, 191.) From two
+  // words in front of the diagonal's on, or where the gathered tiles want the bound anyway: below that it saves nothing.
+  const int n_words = (kmax >> 6) + 1;
+  const int64_t dmax = by_class && (n_words > 2 || split) ? farthest_tile(da, g.occw, lane) : INT64_MAX;
   int total = 0;
-  for (int w = 0; w <= (kmax >> 6); ++w) {  // (the words past the diagonal tile's are neither written nor read)
-    const int kt = w * 64 + lane;
-    int f = 0;
-    if (kt <= kmax) {
-      const int j0 = kt * g.tile_n, j1 = min(j0 + g.tile_n - 1, g.S - 1);
-      f = 4;  // evaluate word by word
-      if (i0 >= g.L && j1 <= i0) {
-        bool exact = true;
-        if (by_class) {
-          const int d = qt - kt;  // >= 1 here
-          const int64_t pos = (int64_t)g.occw * 64 - 1 - d;
-          const bool c_any = !split && ((ca[w] >> lane) & 1), c_all = !split && ((cf[w] >> lane) & 1);
-          const bool d_any = (da[pos >> 6] >> (pos & 63)) & 1, d_all = (df[pos >> 6] >> (pos & 63)) & 1;
-          if (!(c_any && !c_all && d_any && !d_all)) {
-            exact = false;
-            f = ((c_any || d_any) ? 1 : 0) | ((c_all || d_all) ? 3 : 0);
+  for (int wb = 0; wb < n_words; wb += 64) {  // (the words past the diagonal tile's are neither written nor read)
+    const int mine = wb + lane;
+    const bool empty = dmax != INT64_MAX && mine < n_words && qt - (mine * 64 + 63) > dmax && (split || ca[mine] == 0);
+    if (empty) {
+      occ[((int64_t)h * g.nQt + qt) * g.occw + mine] = 0;
+      full[((int64_t)h * g.nQt + qt) * g.occw + mine] = 0;
+    }
+    uint64_t todo = __ballot(mine < n_words && !empty);
+    while (todo) {
+      const int w = wb + __ffsll((unsigned long long)todo) - 1;
+      todo &= todo - 1;
+      const int kt = w * 64 + lane;
+      int f = 0;
+      if (kt <= kmax) {
+        const int j0 = kt * g.tile_n, j1 = min(j0 + g.tile_n - 1, g.S - 1);
+        f = 4;  // evaluate word by word
+        if (i0 >= g.L && j1 <= i0) {
+          bool exact = true;
+          if (by_class) {
+            const int d = qt - kt;  // >= 1 here
+            const int64_t pos = (int64_t)g.occw * 64 - 1 - d;
+            const bool c_any = !split && ((ca[w] >> lane) & 1), c_all = !split && ((cf[w] >> lane) & 1);
+            const bool d_any = (da[pos >> 6] >> (pos & 63)) & 1, d_all = (df[pos >> 6] >> (pos & 63)) & 1;
+            if (!(c_any && !c_all && d_any && !d_all)) {
+              exact = false;
+              f = ((c_any || d_any) ? 1 : 0) | ((c_all || d_all) ? 3 : 0);
+            }
+          }
+          if (exact) {
+            f = pattern_tile_flags(cbw, rr, g.pw, i0, i_last, j0, j1);
+            // a tile cut by the end of the sequence is never full (its bits past S are zero)
+            if (j0 + g.tile_n > g.S || i0 + g.tile_m > g.S) f &= 1;
+          }
+        } else if (by_class && kt == qt) {
+          // the diagonal tile of a row of the pattern region, never full: it meets the offsets 0 .. T - 1, each in its last
+          // row too, and a matched column at least in the column's own row
+          const int64_t Q = (int64_t)g.pw * 64 - 1;
+          f = range_any(rr, g.pw, Q - (g.tile_n - 1), Q) || (!split && ((ca[w] >> lane) & 1)) ? 1 : 0;
+        }
+      }
+      uint64_t ow = __ballot(f & 1), fw = __ballot(f & 2);
+      uint64_t need = __ballot(f & 4);
+      // A query tile inside the true-mask block: four tiles' words are fetched before the first is looked at (a word is one
+      // load from global memory; one tile after the other made a row of eight tiles wait eight times, and set the time of
+      // the launch: 32 heads x 4096 tokens, captured at 1024, whole build 73.7 -> 69.6 us).
+      while (inner && need) {  // wave-uniform
+        int b[4];
+        uint64_t m[4][4];
+  #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          b[u] = need ? __ffsll((unsigned long long)need) - 1 : b[u > 0 ? u - 1 : 0];  // (the last of them again)
+          need &= need - 1;
+  #pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            if (64 * y >= words) break;
+            m[u][y] = tb[(int64_t)(i0 + word_row[y]) * g.tbw + min((w * 64 + b[u]) * g.wpr + word_col[y], g.tbw - 1)];
           }
         }
-        if (exact) {
-          f = pattern_tile_flags(cbw, rr, g.pw, i0, i_last, j0, j1);
-          // a tile cut by the end of the sequence is never full (its bits past S are zero)
-          if (j0 + g.tile_n > g.S || i0 + g.tile_m > g.S) f &= 1;
+  #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          bool any = false, all = true;
+  #pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            if (64 * y >= words) break;
+            const int wj = (w * 64 + b[u]) * g.wpr + word_col[y];
+            const uint64_t x = m[u][y] & in_true_block(g, i0 + word_row[y], wj);
+            any |= x != 0;
+            all &= x == ~0ull;
+          }
+          if (__ballot(any) != 0) ow |= 1ull << b[u];
+          if (__ballot(!all) == 0) fw |= 1ull << b[u];
         }
       }
-    }
-    uint64_t ow = __ballot(f & 1), fw = __ballot(f & 2);
-    uint64_t need = __ballot(f & 4);
-    // A query tile inside the true-mask block: four tiles' words are fetched before the first is looked at (a word is one
-    // load from global memory; one tile after the other made a row of eight tiles wait eight times, and set the time of
-    // the launch: 32 heads x 4096 tokens, captured at 1024, whole build 73.7 -> 69.6 us).
-    while (inner && need) {  // wave-uniform
-      int b[4];
-      uint64_t m[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        b[u] = need ? __ffsll((unsigned long long)need) - 1 : b[u > 0 ? u - 1 : 0];  // (the last of them again)
+      while (need) {  // wave-uniform
+        const int b = __ffsll((unsigned long long)need) - 1;
         need &= need - 1;
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          if (64 * y >= words) break;
-          m[u][y] = tb[(int64_t)(i0 + word_row[y]) * g.tbw + min((w * 64 + b[u]) * g.wpr + word_col[y], g.tbw - 1)];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
         bool any = false, all = true;
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          if (64 * y >= words) break;
-          const int wj = (w * 64 + b[u]) * g.wpr + word_col[y];
-          const uint64_t x = m[u][y] & in_true_block(g, i0 + word_row[y], wj);
-          any |= x != 0;
-          all &= x == ~0ull;
+        for (int x = lane; x < words; x += 64) {
+          const uint64_t m = mask_word(g, tb, cbw, rr, i0 + x / g.wpr, (w * 64 + b) * g.wpr + x % g.wpr);
+          any |= m != 0;
+          all &= m == ~0ull;
         }
-        if (__ballot(any) != 0) ow |= 1ull << b[u];
-        if (__ballot(!all) == 0) fw |= 1ull << b[u];
+        if (__ballot(any) != 0) ow |= 1ull << b;
+        if (__ballot(!all) == 0) fw |= 1ull << b;
       }
-    }
-    while (need) {  // wave-uniform
-      const int b = __ffsll((unsigned long long)need) - 1;
-      need &= need - 1;
-      bool any = false, all = true;
-      for (int x = lane; x < words; x += 64) {
-        const uint64_t m = mask_word(g, tb, cbw, rr, i0 + x / g.wpr, (w * 64 + b) * g.wpr + x % g.wpr);
-        any |= m != 0;
-        all &= m == ~0ull;
+      if (lane == 0) {
+        occ[((int64_t)h * g.nQt + qt) * g.occw + w] = ow;
+        full[((int64_t)h * g.nQt + qt) * g.occw + w] = fw;
       }
-      if (__ballot(any) != 0) ow |= 1ull << b;
-      if (__ballot(!all) == 0) fw |= 1ull << b;
+      total += __popcll(ow);
     }
-    if (lane == 0) {
-      occ[((int64_t)h * g.nQt + qt) * g.occw + w] = ow;
-      full[((int64_t)h * g.nQt + qt) * g.occw + w] = fw;
-    }
-    total += __popcll(ow);
   }
   if (gidx) {
     // the gathered tiles of this query tile: one lane per slot, the rows of the tile as a bitmap
-    const int n_gt = split ? (gcnt[h] + g.tile_n - 1) / g.tile_n : 0;
-    const int *gi = gidx + (int64_t)h * gstride;
+    const int n_gt = (n_cols + g.tile_n - 1) / g.tile_n;
     const int row_words = g.tile_m / 64;
-    // No matched diagonal lies beyond r_bound: the largest tile distance with a matched offset (the first set bit
-    // of the reversed class words) covers offsets up to T d + T - 1. (Square tiles only: the classes are theirs.)
-    int64_t r_bound = INT64_MAX;
-    if (n_gt >= 4 && g.tile_m == g.tile_n) {  // (with a handful of gathered tiles the look-up costs more than it saves)
-      int64_t first = -1;
-      for (int w0 = 0; w0 < g.occw && first < 0; w0 += 64) {
-        const uint64_t word = w0 + lane < g.occw ? da[w0 + lane] : 0;
-        const uint64_t nz = __ballot(word != 0);
-        if (nz) {
-          const int wl = __ffsll((unsigned long long)nz) - 1;
-          const uint64_t hit = __shfl(word, wl);
-          first = (int64_t)(w0 + wl) * 64 + __ffsll((unsigned long long)hit) - 1;
-        }
-      }
-      const int64_t dmax = first < 0 ? 0 : (int64_t)g.occw * 64 - 1 - first;
-      r_bound = dmax * g.tile_n + g.tile_n - 1;
-    }
-    const int n_cols = split ? gcnt[h] : 0;
+    // No matched diagonal lies beyond r_bound: the largest tile distance with a matched offset covers offsets up to
+    // T d + T - 1. (Square tiles only: the classes are theirs.)
+    const int64_t r_bound = dmax != INT64_MAX ? dmax * g.tile_n + g.tile_n - 1 : INT64_MAX;
     for (int w = 0; w * 64 < n_gt; ++w) {  // (only the words that hold a gathered tile are written, and read)
-      // A complete gathered tile whose columns all lie further above this query tile than any matched diagonal
-      // reaches is full without looking: every row is causal for every slot and no offset i - c is a matched
-      // one. A tile whose first column lies below the query tile's last row holds nothing (its columns ascend).
-      // One lane per tile; the other tiles are evaluated slot by slot.
-      bool certain = false, nothing = false;
+      // A gathered tile whose columns all lie further above this query tile than any matched diagonal reaches keeps
+      // every row of every filled slot: every row is causal for it and no offset i - c is a matched one. It is full
+      // if it is complete. A tile whose first column lies below the query tile's last row holds nothing (its columns
+      // ascend). One lane per tile; the other tiles are evaluated slot by slot.
+      bool certain = false, nothing = false, complete = false;
       {
         const int v = w * 64 + lane;
         if (v < n_gt) {
-          nothing = gi[v * g.tile_n] > i_last;
-          if (r_bound != INT64_MAX && (v + 1) * g.tile_n <= n_cols && i0 + g.tile_m <= g.S) {
-            const int cmax = gi[v * g.tile_n + g.tile_n - 1];  // the columns of a tile ascend
-            certain = cmax >= 0 && (int64_t)i0 - cmax > r_bound;
+          nothing = (w == 0 ? g_first : gi[v * g.tile_n]) > i_last;
+          complete = (v + 1) * g.tile_n <= n_cols;
+          if (r_bound != INT64_MAX) {
+            const int cmax = w == 0 && complete ? g_last : gi[min((v + 1) * g.tile_n, n_cols) - 1];
+            certain = (int64_t)i0 - cmax > r_bound;
           }
         }
       }
       const uint64_t sure = __ballot(certain), skip = sure | __ballot(nothing);
-      uint64_t ow = sure, fw = sure;
+      uint64_t ow = sure, fw = __ballot(certain && complete);
       for (int v = w * 64; v < min(n_gt, w * 64 + 64); ++v) {
         if ((skip >> (v & 63)) & 1) continue;  // wave-uniform
         bool any = false, all = true;
@@ -1397,7 +1431,8 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
                                                    bool skip_full_bits,
                                                    const int *__restrict__ gidx, const int *__restrict__ gcnt,
                                                    int gstride, const uint64_t *__restrict__ vocc,
-                                                   const uint64_t *__restrict__ vfull, int share) {
+                                                   const uint64_t *__restrict__ vfull, const uint64_t *__restrict__ off_any,
+                                                   int share) {
   extern __shared__ uint64_t lds_sets[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int h = blockIdx.y;
@@ -1409,16 +1444,37 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   const uint64_t *rr = rrev + (int64_t)h * g.pw;
   const uint64_t *oc = occ + ((int64_t)h * g.nQt + qt) * g.occw;
   const uint64_t *fl = full + ((int64_t)h * g.nQt + qt) * g.occw;
-  // the walk below is a chain of dependent steps: its index words are fetched one word of 64 tiles ahead,
-  // the first ones before the sets are staged, so that no step of the chain waits for memory alone
+  const int i_last = min(g.S - 1, qt * g.tile_m + g.tile_m - 1);
+  const int kmax = i_last / g.tile_n, n_words = (kmax >> 6) + 1;
   // where this query tile's entries start: the listed tiles of the heads before h and of the query tiles before
   // qt (no scan kernel between the two passes: the counts are few enough for every wave to add up its own prefix)
   int64_t part = 0;
-  for (int x = lane; x < h * kHeadSub; x += 64) part += head_cnt[x];
+  auto add_up = [&](const int *p, int n) {  // eight loads in flight: with 1024 query tiles one after the other were 16 waits
+    for (int x0 = lane; x0 < n; x0 += 512) {
+      int v[8];
+#pragma unroll
+      for (int y = 0; y < 8; ++y) v[y] = x0 + 64 * y < n ? p[x0 + 64 * y] : 0;
+#pragma unroll
+      for (int y = 0; y < 8; ++y) part += v[y];
+    }
+  };
+  add_up(head_cnt, h * kHeadSub);
   const int *cnt_h = tile_cnt + (int64_t)h * g.nQt;
-  for (int x = lane; x < qt; x += 64) part += cnt_h[x];
+  add_up(cnt_h, qt);
   const int my_cnt = cnt_h[qt];
-  uint64_t ow_next = oc[0], fw_next = fl[0];
+  // the walk's index words, a word of 64 tiles per lane, the first 64 of them before the sets are staged
+  uint64_t ow_mine = lane < n_words ? oc[lane] : 0, fw_mine = lane < n_words ? fl[lane] : 0;
+  // gathered columns: the ordinary tiles of a query tile of the pattern region hold the diagonal part only
+  const bool split = gidx != nullptr && qt * g.tile_m >= g.L;
+  // (their first index word too: a load issued behind the stores of the ordinary tiles waits for them)
+  const uint64_t *voc = split ? vocc + ((int64_t)h * g.nQt + qt) * g.occw : nullptr;
+  const uint64_t *vfl = split ? vfull + ((int64_t)h * g.nQt + qt) * g.occw : nullptr;
+  const int n_gt = split ? (gcnt[h] + g.tile_n - 1) / g.tile_n : 0;
+  // no matched diagonal lies beyond r_bound (as in tile_scan_row)
+  int64_t r_bound = INT64_MAX;
+  if (split && g.tile_m == g.tile_n && (qt + 1) * g.tile_m <= g.S)
+    r_bound = farthest_tile(off_any + (int64_t)h * g.occw, g.occw, lane) * g.tile_n + g.tile_n - 1;
+  const uint64_t vow0 = split ? voc[0] : 0, vfw0 = split ? vfl[0] : 0;  // (not written where there is no gathered tile)
   if (STAGED) stage_sets(lds_sets, g.pw, cb, rr);
   if (!live) return;
   for (int off = 32; off; off >>= 1) part += __shfl_xor(part, off);
@@ -1431,25 +1487,32 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
       if (h == (int)gridDim.y - 1 && blk_total) *blk_total = first + my_cnt;
     }
   }
-  const int i_last = min(g.S - 1, qt * g.tile_m + g.tile_m - 1);
-  const int kmax = i_last / g.tile_n;
   const int words = g.tile_m * g.wpr;
   const int qw = g.tile_n / 4;  // quarter width in keys, a multiple of 16
-  // gathered columns: the ordinary tiles of a query tile of the pattern region hold the diagonal part only
-  const bool split = gidx != nullptr && qt * g.tile_m >= g.L;
   // the walk, once for sets in LDS and once for sets in global memory (see stage_sets)
   auto walk = [&](const uint64_t *cb, const uint64_t *rr, auto in_lds) __attribute__((always_inline)) {
   constexpr bool IN_LDS = decltype(in_lds)::value;
   if (split) cb = nullptr;
   // walk the listed tiles of this query tile in ascending order
   int rank = 0;
-  for (int ow_i = 0; ow_i <= (kmax >> 6); ++ow_i) {
-    uint64_t ow = ow_next;
-    const uint64_t fw = fw_next;
-    if (ow_i + 1 <= (kmax >> 6)) {
-      ow_next = oc[ow_i + 1];
-      fw_next = fl[ow_i + 1];
+  uint64_t todo = __ballot(ow_mine != 0);  // (empty words are passed over: 446 -> 432 us at 64 heads x 128k)
+  for (int wb = 0; wb < n_words;) {
+    if (!todo) {
+      wb += 64;
+      if (wb >= n_words) break;
+      ow_mine = wb + lane < n_words ? oc[wb + lane] : 0;
+      fw_mine = wb + lane < n_words ? fl[wb + lane] : 0;
+      todo = __ballot(ow_mine != 0);
+      continue;
     }
+    const int from = __ffsll((unsigned long long)todo) - 1, ow_i = wb + from;
+    todo &= todo - 1;
+    auto word_of = [&](uint64_t x) {
+      return (uint64_t)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), from) << 32 |
+             (unsigned)__builtin_amdgcn_readlane((int)x, from);
+    };
+    uint64_t ow = word_of(ow_mine);
+    const uint64_t fw = word_of(fw_mine);
     const uint64_t listed = ow;
     if (skip_full_bits) {
       // full tiles get a column and a kind only: all of the word's at once, lane j takes tile 64 ow_i + j
@@ -1581,16 +1644,13 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   }
   if (!split) return;
   // the gathered tiles, after the ordinary ones: tile index nKt + v
-  const uint64_t *voc = vocc + ((int64_t)h * g.nQt + qt) * g.occw;
-  const uint64_t *vfl = vfull + ((int64_t)h * g.nQt + qt) * g.occw;
-  const int n_gt = (gcnt[h] + g.tile_n - 1) / g.tile_n;
   const int *gi = gidx + (int64_t)h * gstride;
   const int i0 = qt * g.tile_m;
   // (a tile's columns are fetched while the tile before it is written: a load issued behind stores waits for them)
   int v_pre = -1, c_pre[4] = {-1, -1, -1, -1};  // (tiles are at most 256 wide: four groups of 64 slots)
   for (int ow_i = 0; ow_i * 64 < n_gt; ++ow_i) {
-    uint64_t ow = voc[ow_i];
-    const uint64_t vfw = vfl[ow_i];
+    uint64_t ow = ow_i == 0 ? vow0 : voc[ow_i];
+    const uint64_t vfw = ow_i == 0 ? vfw0 : vfl[ow_i];
     if (skip_full_bits) {
       // full tiles get a column and a kind only: all of the word's at once, lane j takes gathered tile 64 ow_i + j
       const uint64_t listed = ow;
@@ -1632,7 +1692,10 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
         if (wg >= g.wpr) break;
         const int c = c_all[wg];
         uint64_t keep[4];
-        slot_rows(g, rr, i0, c, keep);
+        // (filled slots above every matched diagonal keep every row)
+        const bool far = r_bound != INT64_MAX && __ballot(c >= 0 && (int64_t)i0 - c <= r_bound) == 0;
+        if (far) keep[0] = keep[1] = keep[2] = keep[3] = c >= 0 ? ~0ull : 0ull;
+        else slot_rows(g, rr, i0, c, keep);
         const bool any = (keep[0] | keep[1] | keep[2] | keep[3]) != 0;
         const uint64_t lanes_any = __ballot(any);
         for (int q = 0; q < 4; ++q) {  // quarter q: slots [q qw, (q + 1) qw)
@@ -1652,7 +1715,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
               // slot l. Where every filled slot keeps all 64 rows (no row above a column, no matched offset met:
               // the usual case away from the diagonal) every row's word is the set of filled slots; otherwise the
               // 64 x 64 bits are transposed.
-              const bool plain = __ballot(keep[k] != (c >= 0 ? ~0ull : 0ull)) == 0;  // wave-uniform
+              const bool plain = far || __ballot(keep[k] != (c >= 0 ? ~0ull : 0ull)) == 0;  // wave-uniform
               tile_bits[t * words + (int64_t)(64 * k + lane) * g.wpr + wg] = plain ? filled : transpose64(keep[k], lane);
             }
         }
@@ -2275,11 +2338,11 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       if (lds_sets > 0)
         k_tile_fill<true><<<fill_grid, 256, lds_sets, stream>>>(
             g, true_bits, w.cbits, w.rrev, w.occ, w.full, w.tile_cnt, w.head_cnt, o->blk_row_ptr, o->blk_total, o->blk_col,
-            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, share);
+            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.off_any, share);
       else
         k_tile_fill<false><<<fill_grid, 256, 0, stream>>>(
             g, true_bits, w.cbits, w.rrev, w.occ, w.full, w.tile_cnt, w.head_cnt, o->blk_row_ptr, o->blk_total, o->blk_col,
-            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, share);
+            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.off_any, share);
     } else {  // the sizing call: offsets and total only
       k_exclusive_scan<<<1, 1024, 0, stream>>>(w.tile_cnt, (int64_t)g.H * g.nQt, g.nQt, o->blk_row_ptr, o->blk_total, INT64_MAX);
     }

@@ -1,0 +1,54 @@
+"""Block index of rows of tiles that span several occupancy words (64 tiles each): words that no matched diagonal or column
+reaches are passed over by the scan and by the fill, the diagonal tile and gathered tiles beyond every matched diagonal are
+decided without looking at their entries. Bit for bit against the oracle, in the plain and in the gathered layout."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from dam_testlib import pack_rows_u64
+from paper_2506_11104_amd import binding as B
+from test_gpu_mask import check_against_oracle, check_gathered
+
+pytestmark = pytest.mark.gpu
+
+
+def patterns(S):
+    rng = np.random.default_rng(S)
+    d, v = (np.zeros((8, S), np.uint8) for _ in range(2))
+    d[0, :40] = 1                                       # a window alone: one word per row of tiles
+    d[1, :40] = 1                                       # ... sinks
+    v[1, :4] = 1
+    d[2, 64] = 1                                        # nothing on the diagonal tile's main diagonal, columns in the middle word
+    v[2, [4500, 4600]] = 1
+    v[3, rng.choice(S, 200, replace=False)] = 1         # columns only, the last gathered tile incomplete
+    d[4, [0, 63, 127, 4096 + 63, 4096 + 64]] = 1        # the reach ends at a word's edge
+    v[4, rng.choice(S, 64, replace=False)] = 1          # one complete gathered tile (of 64) and no more
+    d[5, S - 1] = 1                                     # the farthest diagonal of all, and nothing else
+    d[7, 0] = 1                                         # (head 6: nothing at all) the main diagonal
+    v[7, rng.choice(S, 700, replace=False)] = 1
+    return d, v
+
+
+# one, two, three and four words; whole rows of tiles and a ragged last one; a true-mask block that ends inside a tile row;
+# tiles of two words (128) and of unequal sides, which have no classes
+@pytest.mark.parametrize("S,tm,tn,L", [(4096, 64, 64, 0), (8192, 64, 64, 0), (8256, 64, 64, 100), (12290, 64, 64, 64), (12352, 64, 64, 0),
+                                       (16640, 128, 128, 0), (16700, 128, 128, 130), (8300, 128, 64, 0)])
+def test_words_and_tiles_that_no_diagonal_reaches(S, tm, tn, L):
+    d, v = patterns(max(S, 8192))
+    d, v = np.ascontiguousarray(d[:, :S]), np.ascontiguousarray(v[:, :S])
+    rng = np.random.default_rng(L)
+    t = (rng.random((8, L, L)) < 0.3).astype(np.uint8) * np.tril(np.ones((L, L), np.uint8)) if L else None
+    art = oracle.from_patterns(d, v, t)
+    tb = torch.from_numpy(pack_rows_u64(t).view(np.int64)).cuda() if L else None
+    d_in, v_in = torch.from_numpy(d).cuda(), torch.from_numpy(v).cuda()
+
+    def build(flags):
+        m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=8, L=L, S=S, tile_m=tm, tile_n=tn, diag_in=d_in, vert_in=v_in, true_bits=tb,
+                         flags=flags)
+        torch.cuda.synchronize()
+        return m
+
+    check_against_oracle(art, S, tm, tn, build(0), dense=False)
+    check_gathered(art, S, tm, tn, build(B.DAM_MASK_GATHER_COLUMNS))
+    check_gathered(art, S, tm, tn, build(B.DAM_MASK_GATHER_COLUMNS | B.DAM_MASK_SKIP_FULL_TILE_BITS), skip_full=True)
