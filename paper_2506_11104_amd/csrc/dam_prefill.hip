@@ -757,18 +757,26 @@ struct Operands {
   const __hip_bfloat16 *kgath, *vgath;
 };
 
+// The kernel's arguments, read where they arrive by whatever part of an item needs them (scalar loads, opaque to the compiler so
+// that it does not load them all at the start). Kept in scalar registers through the items, 54 to 102 of those were spilled to
+// vector lanes and taken back lane by lane, how many by the allocator's chance: an argument more had cost every ragged length
+// 1 to 2 %. Now none is. 2 x 32 heads x 1017 tokens 35.0 -> 34.1 us, 8 x 700 20.3 -> 19.5, 32 x 2048 38.5 -> 37.7,
+// 8 x 16 x 2000 94 -> 90; 32 x 32768 as before.
+struct KernelArgs {
+  AttnArgs a;
+  Operands t;
+};
+using ArgsAt = const __attribute__((address_space(4))) KernelArgs *;
+__device__ __forceinline__ const KernelArgs &reread(ArgsAt at) {
+  asm volatile("" : "+s"(at));
+  return *(const KernelArgs *)at;
+}
+
 template <bool RAGGED, bool GATHER, bool FAST>
-__device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands &t, unsigned char *lds, Shared &sh, bool from_list) {
-  const __hip_bfloat16 *__restrict__ q = t.q, *__restrict__ k = t.k, *__restrict__ v = t.v;
-  const int *__restrict__ row_ptr = t.row_ptr, *__restrict__ blk_col = t.blk_col;
-  const uint8_t *__restrict__ blk_kind = t.blk_kind;
-  const uint64_t *__restrict__ tile_bits = t.tile_bits;
-  __hip_bfloat16 *__restrict__ out = t.out;
-  float *__restrict__ lse = t.lse;
-  const __hip_bfloat16 *__restrict__ kgath = t.kgath, *__restrict__ vgath = t.vgath;
+__device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds, Shared &sh, bool from_list) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, hf = lane >> 5;
-  const float c2 = a.scale * 1.4426950408889634f;
+  const float c2 = reread(args_at).a.scale * 1.4426950408889634f;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
 
   // LDS byte offsets of this lane's operand fragments inside a block (layout note above), chunk pair 0
@@ -779,7 +787,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
   // lane's byte offset from the block's first row is constant
   const int sub = lane >> 4, pos = lane & 15;
   const int row0 = wave * 4 + sub;
-  const unsigned kss2 = (unsigned)a.k_ss * 2u, vss2 = (unsigned)a.v_ss * 2u;  // row strides in bytes
+  const unsigned kss2 = (unsigned)reread(args_at).a.k_ss * 2u, vss2 = (unsigned)reread(args_at).a.v_ss * 2u;  // row strides in bytes
   const unsigned koff = (unsigned)row0 * kss2 + ((pos ^ (row0 & 15)) << 4);
   const unsigned voff = (unsigned)row0 * vss2 + ((pos ^ (sub << 2)) << 4);
   const unsigned boff = (unsigned)((wave * 32 + n) * 16);  // this lane's row in a tile's mask words
@@ -787,14 +795,16 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
   const unsigned lds_kv = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);              // this wave's part of a K/V slot
   const unsigned lds_bits = __builtin_amdgcn_readfirstlane(lds_base + kBitsRing + wave * 256);  // ... of a bits slot
 
-  const Queues qs(a);
-  const int G = qs.G;
   const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcd - 1);  // XCC_ID, 4 bits
   uint2 *blk_list = reinterpret_cast<uint2 *>(lds + kBlkList);
   // The listed tiles [seg0, seg0 + n_seg) of an item that starts at t0 -> list of block descriptors in LDS (two words:
   // first key, and mask offset | flags << 28), closed by a dummy entry that every read past the end returns. By wave 0
   // alone, two tiles per lane: between two barriers, whatever the other waves do.
   auto expand = [&](int t0, int seg0, int n_seg) {
+    const KernelArgs &args = reread(args_at);
+    const AttnArgs &a = args.a;
+    const int *__restrict__ blk_col = args.t.blk_col;
+    const uint8_t *__restrict__ blk_kind = args.t.blk_kind;
     int before = 0;
 #pragma unroll
     for (int half = 0; half < kSegTiles / 64; ++half) {
@@ -840,6 +850,9 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     // previous item: every wave is done with the LDS rings, with s_item and with sh.bad (its stores stay in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (wave == 0) {
+      const KernelArgs &args = reread(args_at);
+      const Operands &t = args.t;
+      const Queues qs(args.a);
       int item = -1, queue = 0;
       if (FAST && prev_item >= 0 && sh.bad && lane == 0) {  // some row of the previous item needs the running reference
         const int id = prev_item * kXcd + prev_queue;
@@ -883,7 +896,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
           t0 = __builtin_amdgcn_readfirstlane(e.y);
           t1 = __builtin_amdgcn_readfirstlane(e.z);
         } else {
-          const int *rp = qs.span(row_ptr, item, queue);
+          const int *rp = qs.span(t.row_ptr, item, queue);
           t0 = __builtin_amdgcn_readfirstlane(rp[0]);
           t1 = __builtin_amdgcn_readfirstlane(rp[1]);
         }
@@ -899,20 +912,24 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(sh.item[0]), queue = __builtin_amdgcn_readfirstlane(sh.item[1]);
     if (item < 0) break;
+    const KernelArgs &args = reread(args_at);
+    const AttnArgs &a = args.a;
+    const Queues qs(a);
+    const int G = qs.G, S = a.S;
     const int pair = qs.pair_of(item, queue), within = qs.within_of(item, queue);
     const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
     const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
     const int t0 = __builtin_amdgcn_readfirstlane(sh.item[2]), t1 = __builtin_amdgcn_readfirstlane(sh.item[3]);
     const int qrow_l = wave * 32 + n;  // this lane's query row inside the tile
     const int qrow = wqt * kBM + qrow_l;
-    const bool qlive = qrow < a.S;
-    const unsigned char *kg = reinterpret_cast<const unsigned char *>(k + wb * a.k_sb + whkv * a.k_sh);
-    const unsigned char *vg = reinterpret_cast<const unsigned char *>(v + wb * a.v_sb + whkv * a.v_sh);
+    const bool qlive = qrow < S;
+    const unsigned char *kg = reinterpret_cast<const unsigned char *>(args.t.k + wb * a.k_sb + whkv * a.k_sh);
+    const unsigned char *vg = reinterpret_cast<const unsigned char *>(args.t.v + wb * a.v_sb + whkv * a.v_sh);
     // the head's gathered column rows (tiles with index >= nKt): [gather_rows] rows at the row stride of K
     // (of V), so that a block of them is addressed exactly like a block of the cache
     const int64_t g_rows = ((int64_t)wb * a.Hq + whq) * a.gather_rows;
-    const unsigned char *kgg = reinterpret_cast<const unsigned char *>(kgath) + g_rows * kss2;
-    const unsigned char *vgg = reinterpret_cast<const unsigned char *>(vgath) + g_rows * vss2;
+    const unsigned char *kgg = reinterpret_cast<const unsigned char *>(args.t.kgath) + g_rows * kss2;
+    const unsigned char *vgg = reinterpret_cast<const unsigned char *>(args.t.vgath) + g_rows * vss2;
 
     // ---- the stream of occupied 32-key blocks of this query tile. The listed tiles are expanded, kSegTiles at
     // a time, into a list of block descriptors in LDS. The pipeline then reads one descriptor per
@@ -934,14 +951,14 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     auto copy_blk = [&](auto slot_off, const unsigned char *g, unsigned stride2, unsigned lane_off, int chunk_xor, int key0,
                         unsigned blk_off, bool gathered) {
       constexpr int SO = decltype(slot_off)::value;
-      if (!RAGGED || gathered || key0 + kBlkKeys <= a.S) {
+      if (!RAGGED || gathered || key0 + kBlkKeys <= S) {
         const unsigned o0 = lane_off + blk_off;
         lds_copy16<SO>(lds_kv, g, o0);
         lds_copy16<SO + 4096>(lds_kv, g, o0 + 16u * stride2);
       } else {
         const unsigned c = (unsigned)((pos ^ chunk_xor) << 4);
-        lds_copy16<SO>(lds_kv, g, (unsigned)min(key0 + row0, a.S - 1) * stride2 + c);
-        lds_copy16<SO + 4096>(lds_kv, g, (unsigned)min(key0 + 16 + row0, a.S - 1) * stride2 + c);
+        lds_copy16<SO>(lds_kv, g, (unsigned)min(key0 + row0, S - 1) * stride2 + c);
+        lds_copy16<SO + 4096>(lds_kv, g, (unsigned)min(key0 + 16 + row0, S - 1) * stride2 + c);
       }
     };
     auto copy_k = [&](const Blk &d, auto slot) {
@@ -956,7 +973,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     };
     // the block's mask word of every row of this wave (also issued for full and dummy blocks, so that
     // every iteration has the same number of copies in flight)
-    const unsigned char *bits_row = reinterpret_cast<const unsigned char *>(tile_bits) + (int64_t)t0 * (kBM * 16);
+    const unsigned char *bits_row = reinterpret_cast<const unsigned char *>(args.t.tile_bits) + (int64_t)t0 * (kBM * 16);
     auto copy_bits = [&](const Blk &d, auto slot) {
       lds_copy4<decltype(slot)::value * 1024>(lds_bits, bits_row, boff + (unsigned)d.bits_off);
     };
@@ -981,7 +998,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
       // 16c + 8 hf .. + 7 of its query row.
       bf16x8 qf[8];
       {
-        const __hip_bfloat16 *qp = q + wb * a.q_sb + whq * a.q_sh + (int64_t)qrow * a.q_ss + 8 * hf;
+        const __hip_bfloat16 *qp = args.t.q + wb * a.q_sb + whq * a.q_sh + (int64_t)qrow * a.q_ss + 8 * hf;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
           u32x4 raw = {0u, 0u, 0u, 0u};
@@ -1100,6 +1117,7 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
     // until the stores had drained, up to 20 us with every workgroup storing at once.) Only when every wave's copies have
     // landed; what the others still read of K belongs to no block.
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    const KernelArgs &end = reread(args_at);
     {
       int l = lane;  // (opaque, or the addresses below are computed once for all items and kept through the pipeline)
       asm volatile("" : "+v"(l));
@@ -1118,49 +1136,36 @@ __device__ __forceinline__ void prefill_items(const AttnArgs &a, const Operands 
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int row_first = wqt * kBM + wave * 32;
-      __hip_bfloat16 *op = out + wb * a.o_sb + whq * a.o_sh + (int64_t)(row_first + (l >> 4)) * a.o_ss + 8 * (l & 15);
-      const int64_t four_rows = 4 * a.o_ss;
+      __hip_bfloat16 *op = end.t.out + wb * end.a.o_sb + whq * end.a.o_sh + (int64_t)(row_first + (l >> 4)) * end.a.o_ss + 8 * (l & 15);
+      const int64_t four_rows = 4 * end.a.o_ss;
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
         const int r = 4 * it + (l >> 4);
         const uint4 x = *reinterpret_cast<const uint4 *>(turn + r * 256 + (((l & 15) ^ (r & 15)) << 4));
-        if (row_first + r < a.S) *reinterpret_cast<uint4 *>(op) = x;
+        if (row_first + r < S) *reinterpret_cast<uint4 *>(op) = x;
         op += four_rows;
       }
     }
-    if (qlive && lse && hf == 0)
-      lse[((int64_t)wb * a.Hq + whq) * a.S + qrow] =
+    if (qlive && end.t.lse && hf == 0)
+      end.t.lse[((int64_t)wb * end.a.Hq + whq) * S + qrow] =
           l_tot > 0.0f ? ((FAST ? 0.0f : m_run * c2) + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
   }  // next work item
 }
 
 // The second variant behind the first is a function of its own, called when there is something on the list: inlined, it
-// spilled registers of the first. It finds its arguments in LDS (every wave takes them back into scalar registers).
-struct Spilled {
-  AttnArgs a;
-  Operands t;
-};
-template <typename T>
-__device__ __forceinline__ T uniform_copy(const T &from) {
-  T to;
-  static_assert(sizeof(T) % 4 == 0, "copied by words");
-  const int *src = reinterpret_cast<const int *>(&from);
-  int *dst = reinterpret_cast<int *>(&to);
-#pragma unroll
-  for (unsigned x = 0; x < sizeof(T) / 4; ++x) dst[x] = __builtin_amdgcn_readfirstlane(src[x]);
-  return to;
-}
+// spilled registers of the first.
 template <bool RAGGED, bool GATHER>
-__device__ __attribute__((noinline)) void prefill_with_reference(
-    __attribute__((address_space(3))) const Spilled *args, __attribute__((address_space(3))) unsigned char *lds,
-    __attribute__((address_space(3))) Shared *sh) {
-  const Spilled s = uniform_copy(*(const Spilled *)args);
-  prefill_items<RAGGED, GATHER, false>(s.a, s.t, (unsigned char *)lds, *(Shared *)sh, true);
+__device__ __attribute__((noinline)) void prefill_with_reference(uint64_t args_at, __attribute__((address_space(3))) unsigned char *lds,
+                                                                 __attribute__((address_space(3))) Shared *sh) {
+  // (an argument in vector registers, the same in every lane)
+  const uint64_t at = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(args_at >> 32)) << 32 |
+                      (unsigned)__builtin_amdgcn_readfirstlane((int)args_at);
+  prefill_items<RAGGED, GATHER, false>((ArgsAt)at, (unsigned char *)lds, *(Shared *)sh, true);
 }
 
 // FAST = false: every item with the running reference (DAM_ATTN_RUNNING_REFERENCE).
 template <bool RAGGED, bool GATHER, bool FAST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prefill_bf16_pipe(AttnArgs a, Operands t) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prefill_bf16_pipe(KernelArgs) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   __shared__ Shared sh;
   const int tid = threadIdx.x;
@@ -1168,15 +1173,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     sh.bad = 0;
     sh.redo = -1;
   }
-  prefill_items<RAGGED, GATHER, FAST>(a, t, lds, sh, false);
+  const ArgsAt args_at = (ArgsAt)__builtin_amdgcn_kernarg_segment_ptr();
+  prefill_items<RAGGED, GATHER, FAST>(args_at, lds, sh, false);
   if constexpr (FAST) {
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sh.redo) < 0) return;
-    __shared__ Spilled args;
-    if (tid == 0) args = Spilled{a, t};
-    __syncthreads();
-    prefill_with_reference<RAGGED, GATHER>((__attribute__((address_space(3))) const Spilled *)&args,
-                                           (__attribute__((address_space(3))) unsigned char *)lds,
+    prefill_with_reference<RAGGED, GATHER>((uint64_t)args_at, (__attribute__((address_space(3))) unsigned char *)lds,
                                            (__attribute__((address_space(3))) Shared *)&sh);
   }
 }
@@ -1339,7 +1341,7 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
     k_order_items<<<kXcd, kOrderMax, 0, st>>>(a, ctl, mk->blk_row_ptr, mk->blk_kind, order);
   const int persistent = std::min(blocks, 2 * n_cu);  // two workgroups fit a CU (registers and LDS)
   const bool ragged = p->seq % kBlkKeys != 0, gather = a.gather_rows > 0;
-  using Kernel = void (*)(AttnArgs, Operands);
+  using Kernel = void (*)(KernelArgs);
   static const Kernel kernels[2][4] = {
       {k_prefill_bf16_pipe<false, false, false>, k_prefill_bf16_pipe<true, false, false>,
        k_prefill_bf16_pipe<false, true, false>, k_prefill_bf16_pipe<true, true, false>},
@@ -1349,9 +1351,9 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
   // (idempotent; set on every call rather than remembered in a static)
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kPipeLds) != hipSuccess)
     return DAM_ERR_DEVICE;
-  const Operands t{(const __hip_bfloat16 *)q, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->blk_row_ptr, mk->blk_col,
-                   mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl, next, order, kgath, vgath};
-  kern<<<persistent, 256, kPipeLds, st>>>(a, t);
+  const KernelArgs t{a, {(const __hip_bfloat16 *)q, (const __hip_bfloat16 *)k, (const __hip_bfloat16 *)v, mk->blk_row_ptr, mk->blk_col,
+                   mk->blk_kind, mk->tile_bits, (__hip_bfloat16 *)out, lse, ctl, next, order, kgath, vgath}};
+  kern<<<persistent, 256, kPipeLds, st>>>(t);
   return launch_status();
 }
 
