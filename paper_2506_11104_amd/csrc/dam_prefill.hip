@@ -30,6 +30,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "dam_blocks.h"
 #include "dam_internal.h"
 #include "dam_mfma.h"
 
@@ -688,17 +689,8 @@ __device__ __forceinline__ void order_items(const AttnArgs &a, const int *__rest
   for (int x = 0; x < kEach; ++x) {
     const int item = x * THREADS + tid;
     if (item < n) {
-      // kinds as aligned words, bytes outside the item cleared
-      const uintptr_t first = reinterpret_cast<uintptr_t>(blk_kind) + t0[x];
-      const int lo = (int)(first & 3), m = min(t1[x] - t0[x], 64);
-      const unsigned *w = reinterpret_cast<const unsigned *>(first - lo);
-      int blocks = 2 * (t1[x] - t0[x] - m);
-      for (int y = 0; y * 4 < lo + m; ++y) {
-        unsigned v = w[y] & 0x1E1E1E1Eu;
-        if (y == 0) v &= ~0u << (8 * lo);
-        if (y * 4 + 4 > lo + m) v &= ~0u >> (8 * (y * 4 + 4 - lo - m));
-        blocks += __popc(v);
-      }
+      const int n_tiles = t1[x] - t0[x], m = min(n_tiles, 64);
+      const int blocks = blocks_of_tiles(blk_kind + t0[x], m) + 2 * (n_tiles - m);
       const int group = groups > 1 ? min(item / (group_pairs * qs.per_pair), groups - 1) : 0;
       bin[x] = (group + 1) * bins_each - 1 - min(blocks, bins_each - 1);
       atomicAdd(&start[bin[x]], 1);
