@@ -749,11 +749,10 @@ struct Operands {
   const __hip_bfloat16 *kgath, *vgath;
 };
 
-// The kernel's arguments, read where they arrive by whatever part of an item needs them (scalar loads, opaque to the compiler so
-// that it does not load them all at the start). Kept in scalar registers through the items, 54 to 102 of those were spilled to
-// vector lanes and taken back lane by lane, how many by the allocator's chance: an argument more had cost every ragged length
-// 1 to 2 %. Now none is. 2 x 32 heads x 1017 tokens 35.0 -> 34.1 us, 8 x 700 20.3 -> 19.5, 32 x 2048 38.5 -> 37.7,
-// 8 x 16 x 2000 94 -> 90; 32 x 32768 as before.
+// The kernel's arguments, read where they arrive at every item's start and end (opaque to the compiler, so that it does not keep
+// them). Held in scalar registers through the items, 54 to 102 of those were spilled to vector lanes and taken back lane by lane,
+// how many by the allocator's chance: an argument more had cost every ragged length 1 to 2 %. Now one is at most. 2 x 32 heads x 1017
+// tokens 35.2 -> 34.6 us, 8 x 700 20.3 -> 19.5, 32 x 2048 38.5 -> 37.8, 8 x 16 x 2000 94 -> 91; 16k tokens and more as before.
 struct KernelArgs {
   AttnArgs a;
   Operands t;
@@ -762,6 +761,18 @@ using ArgsAt = const __attribute__((address_space(4))) KernelArgs *;
 __device__ __forceinline__ const KernelArgs &reread(ArgsAt at) {
   asm volatile("" : "+s"(at));
   return *(const KernelArgs *)at;
+}
+
+// These values stand in scalar registers here: their loads are issued together and waited for once. (Left to the compiler each
+// was fetched where it was first used, ten waits one after the other: 64 heads x 128k tokens 1628 -> 1642 us, 1636 so.)
+template <typename T>
+__device__ __forceinline__ int arrived_one(T &x) {
+  asm volatile("" : "+s"(x));
+  return 0;
+}
+template <typename... T>
+__device__ __forceinline__ void arrived(T &...x) {
+  (void)(arrived_one(x) + ...);
 }
 
 template <bool RAGGED, bool GATHER, bool FAST>
@@ -792,8 +803,7 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
   // The listed tiles [seg0, seg0 + n_seg) of an item that starts at t0 -> list of block descriptors in LDS (two words:
   // first key, and mask offset | flags << 28), closed by a dummy entry that every read past the end returns. By wave 0
   // alone, two tiles per lane: between two barriers, whatever the other waves do.
-  auto expand = [&](int t0, int seg0, int n_seg) {
-    const KernelArgs &args = reread(args_at);
+  auto expand = [&](const KernelArgs &args, int t0, int seg0, int n_seg) {
     const AttnArgs &a = args.a;
     const int *__restrict__ blk_col = args.t.blk_col;
     const uint8_t *__restrict__ blk_kind = args.t.blk_kind;
@@ -840,9 +850,14 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
   bool first = true;
   while (true) {
     // previous item: every wave is done with the LDS rings, with s_item and with sh.bad (its stores stay in flight)
+    KernelArgs args = reread(args_at);
+    arrived(args.a.B, args.a.Hq, args.a.Hkv, args.a.S, args.a.nQt, args.a.nKt, args.a.gather_rows, args.t.row_ptr, args.t.blk_col,
+            args.t.blk_kind, args.t.ctl, args.t.order);
+    arrived(args.t.q, args.t.k, args.t.v, args.t.tile_bits, args.a.q_sb, args.a.q_sh, args.a.q_ss, args.a.k_sb, args.a.k_sh, args.a.v_sb,
+            args.a.v_sh);
+    if (GATHER) arrived(args.t.kgath, args.t.vgath);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (wave == 0) {
-      const KernelArgs &args = reread(args_at);
       const Operands &t = args.t;
       const Queues qs(args.a);
       int item = -1, queue = 0;
@@ -892,7 +907,7 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
           t0 = __builtin_amdgcn_readfirstlane(rp[0]);
           t1 = __builtin_amdgcn_readfirstlane(rp[1]);
         }
-        expand(t0, t0, min(kSegTiles, t1 - t0));
+        expand(args, t0, t0, min(kSegTiles, t1 - t0));
       }
       if (lane == 0) {
         sh.item[0] = item;
@@ -904,7 +919,6 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(sh.item[0]), queue = __builtin_amdgcn_readfirstlane(sh.item[1]);
     if (item < 0) break;
-    const KernelArgs &args = reread(args_at);
     const AttnArgs &a = args.a;
     const Queues qs(a);
     const int G = qs.G, S = a.S;
@@ -1003,7 +1017,7 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
       for (int seg0 = t0; seg0 < t1; seg0 += kSegTiles) {
         if (seg0 > t0) {
           __syncthreads();  // every wave is done with the previous list and with the rings
-          if (wave == 0) expand(t0, seg0, min(kSegTiles, t1 - seg0));
+          if (wave == 0) expand(reread(args_at), t0, seg0, min(kSegTiles, t1 - seg0));
           __syncthreads();
         }
         n_blk = __builtin_amdgcn_readfirstlane(sh.nblk);
@@ -1083,6 +1097,8 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
         // which therefore starts at phase 2
         if (!step(I0{}, std::integral_constant<int, FAST ? kChainOnly : kAll>{}) &&
             !step(I1{}, std::integral_constant<int, FAST ? kNoPV : kAll>{})) {
+          // (from a line of the instruction cache on, wherever the code in front of it ends: up to 0.5 %)
+          asm volatile(".p2align 6" ::: "memory");
           while (true) {
             if (step(I2{}, PAll{})) break;
             if (step(I3{}, PAll{})) break;
@@ -1108,8 +1124,9 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
     // instruction then covers four rows. (Eight bytes per lane and store straight from the accumulators: 2.6 us per item
     // until the stores had drained, up to 20 us with every workgroup storing at once.) Only when every wave's copies have
     // landed; what the others still read of K belongs to no block.
+    KernelArgs end = reread(args_at);
+    arrived(end.t.out, end.t.lse, end.a.o_sb, end.a.o_sh, end.a.o_ss, end.a.Hq);
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    const KernelArgs &end = reread(args_at);
     {
       int l = lane;  // (opaque, or the addresses below are computed once for all items and kept through the pipeline)
       asm volatile("" : "+v"(l));
