@@ -17,6 +17,7 @@
 
 #include "dam_internal.h"
 #include "dam_slices.h"
+#include "dam_turns.h"
 
 #pragma clang fp contract(off)
 
@@ -1370,20 +1371,11 @@ __global__ __launch_bounds__(1024) void k_exclusive_scan(const int *__restrict__
   block_exclusive_scan<1024>(cnt, n, group, ptr, total, clamp);
 }
 
-// The head and the group of `each` query tiles of a workgroup of the two passes. The query tiles of the true-mask block come
-// first, for all heads: their tiles are loaded and evaluated word by word, one after the other, and where each head's turn
-// came by itself the last heads' were still at it when the chip had nothing else left to do. Then the others, the longest
-// rows first. (64 heads x 128k tokens, captured at 4096: scan 191 -> 141 us, fill 422 -> 270; 32 heads x 4096, captured at
-// 1024: scan 11.2 -> 10.0, fill the same.) Patterns without a true-mask block go head by head: 32 heads x 32k the fill 43 us
-// so, 46 in the other order.
-struct QueryTiles {
-  int h, at;
-};
-__device__ __forceinline__ QueryTiles query_tiles_of(const Geom &g, int each) {
-  const int n = (g.nQt + each - 1) / each, b = (int)blockIdx.x, rows = each * g.tile_m;
-  if (g.L == 0) return QueryTiles{b / n, b % n};
-  const int inside = min(n, (min(g.L, g.S) + rows - 1) / rows), turn = b / g.H;
-  return QueryTiles{b % g.H, turn < inside ? inside - 1 - turn : n - 1 - (turn - inside)};
+// This workgroup's turn among the query tiles, `each` of a head at a time (dam_turns.h).
+__device__ __forceinline__ QueryTiles my_query_tiles(const Geom &g, int each) {
+  const int n = (g.nQt + each - 1) / each, rows = each * g.tile_m;
+  const int inside = g.L > 0 ? min(n, (min(g.L, g.S) + rows - 1) / rows) : 0;
+  return query_tiles_of(g.H, n, inside, blockIdx.y * kGridRow + blockIdx.x);  // (a second row follows a full one)
 }
 
 // Pass 1 as a kernel: a wave per query tile; the workgroup adds its four counts to the head's total. The CSR offsets
@@ -1406,7 +1398,8 @@ __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__res
   extern __shared__ uint64_t lds_sets[];
   __shared__ int wave_cnt[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const QueryTiles my = query_tiles_of(g, 4);
+  const QueryTiles my = my_query_tiles(g, 4);
+  if (my.at < 0) return;  // the whole workgroup
   const int h = my.h, qt = my.at * 4 + wave;
   const uint64_t *tb = true_bits ? true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   const uint64_t *cb = cbits + (int64_t)h * g.pw;
@@ -1452,7 +1445,8 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
                                                    int share) {
   extern __shared__ uint64_t lds_sets[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const QueryTiles my = query_tiles_of(g, share == 4 ? 1 : 4);
+  const QueryTiles my = my_query_tiles(g, share == 4 ? 1 : 4);
+  if (my.at < 0) return;  // the whole workgroup
   const int h = my.h;
   const int my_qt = share == 4 ? my.at : my.at * 4 + wave, my_turn = share == 4 ? wave : 0;
   const bool live = my_qt < g.nQt;
@@ -2344,14 +2338,18 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   if (want_blocks) {
     const size_t lds_sets = staged_bytes(g);
     const bool fill = o->blk_col || o->blk_kind || o->tile_bits;
+    auto grid_of = [&](int each) {
+      const TurnGrid t = turn_grid((int64_t)((g.nQt + each - 1) / each) * g.H);
+      return dim3(t.x, t.y);
+    };
     if (!scans_in_prep(g, o))
-      k_tile_scan<<<(unsigned)((g.nQt + 3) / 4 * (int64_t)g.H), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
+      k_tile_scan<<<grid_of(4), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
                                                                      w.off_all, w.occ, w.full, w.tile_cnt, lds_sets > 0, gidx,
                                                                      gcnt, gstride, w.vocc, w.vfull, w.head_cnt);
     if (fill) {
       // (the CSR offsets come out of the fill kernel: no scan launch between the two passes)
       const int share = (int64_t)g.H * g.nQt >= 2048 ? 1 : 4;  // enough query tiles to give every wave its own
-      const unsigned fill_grid = (unsigned)((share == 4 ? g.nQt : (g.nQt + 3) / 4) * (int64_t)g.H);
+      const dim3 fill_grid = grid_of(share == 4 ? 1 : 4);
       const bool skip_full = (p->flags & DAM_MASK_SKIP_FULL_TILE_BITS) != 0;
       if (lds_sets > 0)
         k_tile_fill<true><<<fill_grid, 256, lds_sets, stream>>>(

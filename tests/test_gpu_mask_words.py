@@ -52,3 +52,32 @@ def test_words_and_tiles_that_no_diagonal_reaches(S, tm, tn, L):
     check_against_oracle(art, S, tm, tn, build(0), dense=False)
     check_gathered(art, S, tm, tn, build(B.DAM_MASK_GATHER_COLUMNS))
     check_gathered(art, S, tm, tn, build(B.DAM_MASK_GATHER_COLUMNS | B.DAM_MASK_SKIP_FULL_TILE_BITS), skip_full=True)
+
+
+# more workgroups than a row of the grid holds (16384): every map the same as in a build of eight
+@pytest.mark.parametrize("L", [0, 130])
+def test_maps_beyond_the_first_row_of_the_grid(L):
+    S, H = 1000, 4200
+    d, v = (np.zeros((8, S), np.uint8) for _ in range(2))
+    rng = np.random.default_rng(L + 1)
+    for h in range(8):
+        d[h, :1 + 9 * h] = 1
+        v[h, rng.choice(S, 3 * h, replace=False)] = 1
+    t = (rng.random((8, L, L)) < 0.3).astype(np.uint8) * np.tril(np.ones((L, L), np.uint8)) if L else None
+
+    def build(copies):
+        tb = torch.from_numpy(pack_rows_u64(t).view(np.int64)).cuda().repeat(copies, 1, 1) if L else None
+        m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=8 * copies, L=L, S=S, tile_m=64, tile_n=64, diag_in=torch.from_numpy(d).cuda().repeat(copies, 1),
+                         vert_in=torch.from_numpy(v).cuda().repeat(copies, 1), true_bits=tb)
+        torch.cuda.synchronize()
+        return m
+
+    few, many = build(1), build(H // 8)
+    check_against_oracle(oracle.from_patterns(d, v, t), S, 64, 64, few, dense=False)
+    n = few.n_tiles
+    assert many.n_tiles == n * (H // 8)
+    ptr = many.blk_row_ptr.view(H // 8, 8, -1) - n * torch.arange(H // 8, device="cuda", dtype=torch.int32)[:, None, None]
+    assert torch.equal(ptr, few.blk_row_ptr[None].expand_as(ptr))
+    for name in ("blk_col", "blk_kind", "tile_bits"):
+        got, want = getattr(many, name).view(H // 8, n, -1), getattr(few, name).view(1, n, -1)
+        assert torch.equal(got, want.expand_as(got)), name
