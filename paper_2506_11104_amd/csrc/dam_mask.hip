@@ -1372,10 +1372,10 @@ __global__ __launch_bounds__(1024) void k_exclusive_scan(const int *__restrict__
 }
 
 // This workgroup's turn among the query tiles, `each` of a head at a time (dam_turns.h).
-__device__ __forceinline__ QueryTiles my_query_tiles(const Geom &g, int each) {
+__device__ __forceinline__ QueryTiles my_query_tiles(const Geom &g, int each, bool by_heads) {
   const int n = (g.nQt + each - 1) / each, rows = each * g.tile_m;
   const int inside = g.L > 0 ? min(n, (min(g.L, g.S) + rows - 1) / rows) : 0;
-  return query_tiles_of(g.H, n, inside, blockIdx.y * kGridRow + blockIdx.x);  // (a second row follows a full one)
+  return query_tiles_of(g.H, n, inside, blockIdx.y * kGridRow + blockIdx.x, by_heads);  // (a second row follows a full one)
 }
 
 // Pass 1 as a kernel: a wave per query tile; the workgroup adds its four counts to the head's total. The CSR offsets
@@ -1398,7 +1398,7 @@ __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__res
   extern __shared__ uint64_t lds_sets[];
   __shared__ int wave_cnt[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const QueryTiles my = my_query_tiles(g, 4);
+  const QueryTiles my = my_query_tiles(g, 4, false);
   if (my.at < 0) return;  // the whole workgroup
   const int h = my.h, qt = my.at * 4 + wave;
   const uint64_t *tb = true_bits ? true_bits + (int64_t)h * g.L * g.tbw : nullptr;
@@ -1445,7 +1445,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
                                                    int share) {
   extern __shared__ uint64_t lds_sets[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const QueryTiles my = my_query_tiles(g, share == 4 ? 1 : 4);
+  const QueryTiles my = my_query_tiles(g, share == 4 ? 1 : 4, true);
   if (my.at < 0) return;  // the whole workgroup
   const int h = my.h;
   const int my_qt = share == 4 ? my.at : my.at * 4 + wave, my_turn = share == 4 ? wave : 0;
