@@ -45,7 +45,8 @@ typedef enum {
   DAM_OK = 0,
   DAM_ERR_INVALID_ARG = -1, /* null required pointer, non-positive size, hq % hkv != 0, bad ranges */
   DAM_ERR_UNSUPPORTED = -2, /* a head_dim / dtype / tile / lambda outside the built set          */
-  DAM_ERR_WORKSPACE = -3,   /* ws_bytes smaller than the matching *_workspace() query             */
+  DAM_ERR_WORKSPACE = -3,   /* ws_bytes smaller than the matching *_workspace() query (the prefill's names a
+                               part it can do without)                                              */
   /* -4 is not used: a capacity overflow cannot be known on the host without a synchronisation. It is
      reported through the device scalars blk_total / kept_total / col_total, and the offsets written
      never exceed the capacity (see dam_mask_out).                                                 */
@@ -348,6 +349,11 @@ typedef struct {
   int32_t gather_stride;
 } dam_mask_view;
 
+/* A workspace of this size also takes every call of fewer sequences or shorter ones (same heads, tiles, strides and
+ * gather_rows). From batch * hq * ceil(seq / tile_m) = 768 on it includes DAM_PREFILL_ORDER_BYTES in which a call may put its
+ * work items into order of their length. They are the one part that is not required: a workspace that is smaller by no
+ * more than that is accepted, the items are then taken by number, and the results are the same. */
+#define DAM_PREFILL_ORDER_BYTES (64u << 10)
 size_t dam_sparse_attn_prefill_workspace(const dam_attn_params *params);
 
 /* q, k, v, out  device, laid out by the strides above ([batch][heads][seq][head_dim] when dense).

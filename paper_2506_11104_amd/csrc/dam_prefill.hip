@@ -1286,13 +1286,12 @@ static size_t redo_bytes(const dam_attn_params *p) {
   return ((items + kXcd) * sizeof(int) + 255) / 256 * 256;
 }
 
-// bytes of the queues' order: none where a queue is too long, or where most items are some workgroup's first one and the look-up
-// costs more than the order brings (512 workgroups on this chip; 576 items 39.8 us by number, 41.7 by length, 960 items 53.5 / 52)
-static size_t order_bytes(const dam_attn_params *p) {
-  const int64_t items = (int64_t)p->batch * p->hq * ((p->seq + p->tile_m - 1) / p->tile_m);
-  const int64_t longest = p->batch * p->hkv % kXcd == 0 ? items / kXcd : (items + kXcd - 1) / kXcd;
-  return items >= 768 && longest <= kOrderMax ? (size_t)kXcd * kOrderMax * sizeof(int4) : 0;
-}
+// Items from which they are taken by length: with fewer most are some workgroup's first one and the look-up costs more than the
+// order brings (512 workgroups on this chip; 576 items 39.8 us by number, 41.7 by length, 960 items 53.5 / 52).
+constexpr int64_t kOrderMin = 768;
+
+// bytes of the queues' order, in the workspace of every call that a smaller one of kOrderMin items or more may share
+static size_t order_bytes(int64_t items) { return items >= kOrderMin ? (size_t)kXcd * kOrderMax * sizeof(int4) : 0; }
 
 // the control words of the bf16 kernel (queue counters), the links of the redo lists, then the gathered K and V copies
 // (rows at the caches' strides); what the kernel cannot do without
@@ -1305,7 +1304,7 @@ extern "C" size_t dam_sparse_attn_prefill_workspace(const dam_attn_params *p) {
   if (!p || p->batch < 1 || p->hkv < 1 || p->hq < 1 || p->seq < 1 || p->gather_rows < 0) return 0;
   if (p->dtype != DAM_BF16) return 0;
   if (p->hq % p->hkv || p->tile_m < 64) return 0;
-  return least_bytes(p) + order_bytes(p);
+  return least_bytes(p) + order_bytes((int64_t)p->batch * p->hq * ((p->seq + p->tile_m - 1) / p->tile_m));
 }
 
 extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, const void *k, const void *v,
@@ -1313,7 +1312,7 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
                                        void *stream_v) {
   const int bad = validate(p, q, k, v, mk, out);
   if (bad != DAM_OK) return bad;
-  // (a workspace without room for the order, one sized for a larger batch for instance, does without it)
+  // (a workspace without room for the order does without it)
   if (p->dtype == DAM_BF16 && (!ws || ws_bytes < least_bytes(p))) return DAM_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream_v);
   AttnArgs a = make_args(p);
@@ -1340,7 +1339,9 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
   __hip_bfloat16 *kgath = reinterpret_cast<__hip_bfloat16 *>(static_cast<char *>(ws) + kCtlBytes + redo_bytes(p));
   __hip_bfloat16 *vgath = kgath + (size_t)p->batch * p->hq * a.gather_rows * (size_t)a.k_ss;
   int4 *order = nullptr;
-  if (blocks > 2 * n_cu && order_bytes(p) && ws_bytes >= least_bytes(p) + order_bytes(p))
+  const bool even = p->batch * p->hkv % kXcd == 0;
+  const int longest_queue = even ? blocks / kXcd : (blocks + kXcd - 1) / kXcd;
+  if (blocks > 2 * n_cu && blocks >= kOrderMin && longest_queue <= kOrderMax && ws_bytes >= least_bytes(p) + order_bytes(blocks))
     order = reinterpret_cast<int4 *>(static_cast<char *>(ws) + least_bytes(p));
   if (a.gather_rows > 0)
     k_gather_kv<<<dim3((a.gather_rows + 15) / 16, p->batch * p->hq + (order ? kXcd : 0)), 256, 0, st>>>(

@@ -127,6 +127,20 @@ def test_prefill_argument_errors():
         assert call_prefill(attn_params(), ws_bytes=need - 1) == B.DAM_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("gather_rows", [0, 256])
+def test_prefill_workspace_takes_every_smaller_call(gather_rows):
+    """The query does not fall as sequences are added or grow."""
+    def need(batch, seq, hq=32, hkv=8):
+        return B.lib().dam_sparse_attn_prefill_workspace(ctypes.byref(attn_params(batch=batch, seq=seq, hq=hq, hkv=hkv, gather_rows=gather_rows)))
+    for seq in (100, 1000, 3001, 4096, 16384):
+        sizes = [need(batch, seq) for batch in range(1, 40)]
+        assert sizes == sorted(sizes), (seq, sizes)
+    for batch in (1, 2, 5):
+        sizes = [need(batch, seq) for seq in range(100, 40000, 333)]
+        assert sizes == sorted(sizes), (batch, sizes)
+    assert need(1, 32768) - need(1, 128) >= 64 << 10  # the part for the order of the items, DAM_PREFILL_ORDER_BYTES
+
+
 def test_decode_argument_errors():
     L = B.lib()
     p = B.DecodeParams()

@@ -70,3 +70,24 @@ def test_the_order_of_the_items_changes_nothing(batch, hq, hkv, S, flags, shift)
     (o1, l1), (o2, l2) = got
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
     assert not bool((o1 == 7.0).all(-1).any())
+
+
+def test_a_workspace_of_a_larger_batch_has_room_for_the_order():
+    """Queues of more than 512 items are not sorted, but their workspace serves a smaller batch, whose queues are."""
+    hq, hkv, S = 32, 8, 2176
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rng = np.random.default_rng(1)
+    d = np.zeros((hq, S), np.uint8)
+    for h in range(hq):
+        d[h, : 1 + rng.integers(0, 700)] = 1
+    mask = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=hq, L=0, S=S, diag_in=torch.from_numpy(d).cuda(), vert_in=torch.zeros_like(torch.from_numpy(d)).cuda())
+    q, k, v = (torch.randn((8, h, S, 128), generator=gen, device="cuda", dtype=torch.bfloat16) for h in (hq, hkv, hkv))
+    ws, small = (B.prefill_workspace(B.attn_params(q[:b], k[:b], v[:b], torch.empty_like(q[:b]), 128, 128), "cuda") for b in (8, 2))
+    assert small.numel() <= ws.numel()
+    ws.fill_(0xFF)
+    out = B.dam_sparse_attn_prefill(q, k, v, mask, ws=ws)
+    torch.cuda.synchronize()
+    assert bool((ws[-ORDER:] == 0xFF).all())
+    few = B.dam_sparse_attn_prefill(q[:2], k[:2], v[:2], mask, ws=ws)
+    check_order(ws[small.numel() - ORDER:small.numel()].cpu().numpy().view(np.int32).reshape(8, 512, 4), mask, 2, hq, hkv, S)
+    assert torch.equal(few, out[:2])
