@@ -1399,7 +1399,6 @@ __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__res
   __shared__ int wave_cnt[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const QueryTiles my = my_query_tiles(g, 4, false);
-  if (my.at < 0) return;  // the whole workgroup
   const int h = my.h, qt = my.at * 4 + wave;
   const uint64_t *tb = true_bits ? true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   const uint64_t *cb = cbits + (int64_t)h * g.pw;
@@ -1446,7 +1445,6 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   extern __shared__ uint64_t lds_sets[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const QueryTiles my = my_query_tiles(g, share == 4 ? 1 : 4, true);
-  if (my.at < 0) return;  // the whole workgroup
   const int h = my.h;
   const int my_qt = share == 4 ? my.at : my.at * 4 + wave, my_turn = share == 4 ? wave : 0;
   const bool live = my_qt < g.nQt;

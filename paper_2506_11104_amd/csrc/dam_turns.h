@@ -17,7 +17,7 @@ constexpr TurnGrid turn_grid(int64_t n_turns) {
 }
 
 struct QueryTiles {
-  int h, at;  // head, and which group of `each` query tiles of it; at < 0: the grid's last row is longer than needed
+  int h, at;  // head, and which group of query tiles of it; behind the last one where the grid's last row is longer than needed
 };
 
 // Workgroup b of H heads with n groups of query tiles each (fewer than 2^31 in all), the first `inside` of which start in the
@@ -35,7 +35,7 @@ struct QueryTiles {
 // (1024) 61.9 / 62.5; 64 x 12000 at 512 (1536) 66.5 / 62.9, 64 x 14300 at 512 (1792) 67.3 / 65.0.
 constexpr unsigned kStartsAtOnce = 1024;
 constexpr QueryTiles query_tiles_of(unsigned H, unsigned n, unsigned inside, unsigned b, bool by_heads) {
-  if (b >= H * n) return QueryTiles{0, -1};
+  if (b >= H * n) return QueryTiles{0, (int)n};
   if (inside == 0) return QueryTiles{(int)(b / n), (int)(b % n)};
   const unsigned turn = b / H;
   if (turn < inside) return QueryTiles{(int)(b % H), (int)(inside - 1 - turn)};

@@ -24,9 +24,9 @@ int main() {
           for (unsigned x = 0; x < g.x; ++x) {
             const int64_t b = (int64_t)y * g.x + x;
             const QueryTiles t = query_tiles_of((unsigned)H, n, inside, (unsigned)b, by_heads);
-            CHECK((t.at < 0) == (b >= H * n));
-            if (t.at < 0) continue;
-            CHECK(t.h >= 0 && t.h < H && t.at < n && !seen[t.h * n + t.at]);
+            CHECK((t.at == n) == (b >= H * n));
+            if (t.at == n) continue;
+            CHECK(t.h >= 0 && t.h < H && t.at >= 0 && t.at < n && !seen[t.h * n + t.at]);
             seen[t.h * n + t.at] = 1;
             // the true-mask block first, then every head's last group; whose turn it is next, by heads and by turns
             CHECK(inside == 0 || (b < H * inside) == (t.at < inside));
