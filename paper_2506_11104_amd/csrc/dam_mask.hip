@@ -899,16 +899,18 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
 // In place of the launches that longer captures take (k_pattern_slices, and k_pattern_finish or sum_slices_of_head), which
 // cost 5 us each however short they are. The jobs grow with the square of the capture and run on one CU per head, so the line
 // lies where the gain ends; whole builds, the launches / this, us: 32 heads x 320 35.9 / 31.8, x 512 42.7 / 40.0, x 768 52.1 /
-// 52.4, x 1024 63.1 / 68.0, 16 x 640 38.8 / 37.8, 64 x 768 72.8 / 72.2, 64 x 1024 98.3 / 102.7, 8 x 1024 42.0 / 47.8.
-constexpr int kDirectL = 768;
+// 52.4, x 1024 63.1 / 68.0, 16 x 640 38.8 / 37.8, 64 x 768 72.8 / 72.2, 64 x 1024 98.3 / 102.7, 8 x 1024 42.0 / 47.8. A word
+// further where nothing follows the counts, so that the launches are two where this is one: 1 head x 832 17.8 / 17.1, 8 x 832
+// 19.8 / 18.9, 96 x 832 57.9 / 56.1, 96 x 769 60.6 / 58.9; 1 x 896 18.1 / 18.8, 32 x 896 30.4 / 31.6, 96 x 896 61.8 / 61.6.
+constexpr int kDirectL = 768, kDirectAloneL = 832;
 __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
-                                                       float mu, int h, int *cnt,                       // LDS [2][kDirectL]
+                                                       float mu, int h, int *cnt,                       // LDS [2][kDirectAloneL]
                                                        int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
                                                        uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,
                                                        uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev,
                                                        uint64_t *lds_copy) {  // both sets again, [2 pw], or nullptr
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-  for (int x = threadIdx.x; x < 2 * kDirectL; x += blockDim.x) cnt[x] = 0;
+  for (int x = threadIdx.x; x < 2 * kDirectAloneL; x += blockDim.x) cnt[x] = 0;
   __syncthreads();
   const bool diag = wave & 1;
   int chunk = 0, w = wave >> 1;  // the pair (chunk, word <= chunk) of this wave; both kinds take every n_waves / 2-th
@@ -931,7 +933,7 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
     // diagonals: the window of the row that ends at column i - 64 w, reversed: offset 64 w + t at bit t
     uint64_t x = hi;
     if (diag) x = __brevll(lane == 63 ? hi : (hi << (63 - lane)) | (lo >> (lane + 1)));
-    const int at = (diag ? kDirectL : 0) + 64 * w + lane;
+    const int at = (diag ? kDirectAloneL : 0) + 64 * w + lane;
     w += n_waves / 2;
     settle();
     if (chunk < g.tbw) fetch();
@@ -939,7 +941,7 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
   }
   __syncthreads();
   for (int x = wave; x < 2 * g.tbw; x += n_waves) {
-    const int word = x >> 1, p = 64 * word + lane, n = cnt[(x & 1) * kDirectL + p];
+    const int word = x >> 1, p = 64 * word + lane, n = cnt[(x & 1) * kDirectAloneL + p];
     const bool hit = p < g.L && (float)n / (float)(g.L - p) >= mu;
     const uint64_t set = __ballot(hit);
     const int64_t e = (int64_t)h * g.L + p;
@@ -1260,7 +1262,7 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
   uint64_t *copy = in_lds && classes ? prep_sets : nullptr;
   if (ca.true_bits) {  // uniform over the grid
-    __shared__ int cnt[2 * kDirectL];
+    __shared__ int cnt[2 * kDirectAloneL];
     count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
                            ca.diag_flag, cbits, rrev, copy);
   } else if (ca.vslices) {
@@ -2284,7 +2286,9 @@ size_t prep_lds_bytes(const Geom &g) { return (size_t)g.pw * 16 <= kMaxStagedByt
 bool scans_in_prep(const Geom &g, const dam_mask_out *o) { return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= kScanInPrep; }
 
 // Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
-bool counts_in_prep(const Geom &g) { return g.L <= kDirectL; }
+bool counts_in_prep(const dam_mask_params *p, const Geom &g, const dam_mask_out *o) {
+  return g.L <= kDirectL || (g.L <= kDirectAloneL && !needs_prep(p, o));
+}
 
 // a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
 // k_pattern_prep has to count for that. counted: the chunks' slices are there already.
@@ -2295,7 +2299,7 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   *dflag = df;
   *vflag = vf;
   if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
-  if (counts_in_prep(g))
+  if (counts_in_prep(p, g, o))
     return CountArgs{o->true_bits, nullptr, nullptr, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
   if (counted) {
@@ -2482,7 +2486,7 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
   // (one causal capture of two tokens or more: the minimum, and so the threshold, is known on the host)
   const Threshold thr = stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, &bmin_written);
   const bool counted = launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits,
-                                                counts_in_prep(g) ? nullptr : w.vslices, w.dslices, stream);
+                                                counts_in_prep(p, g, o) ? nullptr : w.vslices, w.dslices, stream);
   const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, counted);
   stage_extension(p, g, w, o, o->true_bits, dflag, vflag, count, stream);
   return launch_status();

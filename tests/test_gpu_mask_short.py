@@ -1,4 +1,4 @@
-"""Short captures: pattern counts taken inside the prep kernel (up to 768 tokens), and query tiles inside the true-mask
+"""Short captures: pattern counts taken inside the prep kernel (up to 768 tokens, 832 where nothing follows them), and query tiles inside the true-mask
 block, whose tiles the scan looks at four at a time. Bit for bit against the oracle."""
 import numpy as np
 import pytest
@@ -42,9 +42,11 @@ def test_tiles_of_the_true_mask_block(tm, tn, S):
     run_from_map(A, None, S, tm, tn, 0.5, 1e-8, 0.02, 0.8)
 
 
-# captures whose patterns are counted with nothing else to do
-@pytest.mark.parametrize("L,copies", [(895, 1), (896, 1), (897, 1), (1024, 1), (897, 23), (897, 24), (1024, 24)])
-def test_pattern_counts_alone_on_both_sides_of_the_lines(L, copies):
+# captures whose patterns are counted with nothing else to do: in the prep kernel up to 832 tokens, in chunks of 128 rows beyond,
+# with whole and ragged last chunks, for few and for many maps
+@pytest.mark.parametrize("L,copies", [(768, 1), (769, 1), (800, 30), (831, 1), (832, 1), (833, 1), (895, 1), (896, 1), (897, 1), (1024, 1), (897, 23),
+                                      (897, 24), (1024, 24)])
+def test_pattern_counts_alone_on_both_sides_of_the_line(L, copies):
     A = synth_map(np.random.default_rng(L + copies), 2, L)
     art = oracle.derive(A, None, 0.5, 1e-8, 0.02, 0.3)
     a_dev = torch.from_numpy(A).cuda().repeat(copies, 1, 1)
