@@ -27,9 +27,11 @@ def check_counts(mask, L, mu):
             assert torch.equal(getattr(mask, name)[h].to(want[name].dtype), want[name]), (h, name)
 
 
-# one word per thread and row (768 words' end), 16 / 32 / 64 / 128 words per row, more than that; a block index or none
-@pytest.mark.parametrize("L,blocks", [(768, False), (769, False), (769, True), (1024, True), (1500, False), (1536, True), (1537, True), (2048, False),
-                                      (2049, False), (4096, False), (4097, False), (8192, False), (8193, False)])
+# both sides of the line at which captures are counted in chunks (768 tokens, 832 where nothing follows), 16 / 32 / 64 / 128 words
+# per row, more than that (two waves per chunk: a last chunk of one row, one of 65, a whole one); a block index or none
+@pytest.mark.parametrize("L,blocks", [(768, False), (769, False), (769, True), (832, False), (833, False), (1024, True), (1500, False), (1536, True), (1537, True), (2048, False),
+                                      (2049, False), (4096, False), (4097, False), (8192, False), (8193, False),
+                                      (8257, False), (8320, True), (12300, False)])
 def test_counts_in_chunks(L, blocks):
     gen = torch.Generator(device="cuda").manual_seed(L)
     A = torch.rand((2, L, L), generator=gen, device="cuda").tril_()
@@ -39,8 +41,10 @@ def test_counts_in_chunks(L, blocks):
     check_counts(m, L, 0.4)
 
 
-# a row tile per workgroup (whole rows: counted by the capture), several workgroups per row tile, short captures
-@pytest.mark.parametrize("hq,hkv,L", [(64, 8, 1100), (32, 8, 2048), (64, 8, 1024), (16, 4, 1000), (128, 8, 700)])
+# a row tile per workgroup (whole rows: counted by the capture), several workgroups per row tile, short captures; more than 64
+# words per row, which the waves of a workgroup hand each other behind barriers
+@pytest.mark.parametrize("hq,hkv,L", [(64, 8, 1100), (32, 8, 2048), (64, 8, 1024), (16, 4, 1000), (128, 8, 700), (64, 8, 832), (64, 8, 833),
+                                      (16, 4, 4100), (16, 8, 5000), (16, 4, 8192)])
 def test_counts_of_a_fused_capture(hq, hkv, L):
     gen = torch.Generator(device="cuda").manual_seed(L)
     q, k = (torch.randn((h, L, 128), generator=gen, device="cuda", dtype=torch.bfloat16) for h in (hq, hkv))
