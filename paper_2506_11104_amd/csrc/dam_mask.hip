@@ -1109,6 +1109,9 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
       full[((int64_t)h * g.nQt + qt) * g.occw + mine] = 0;
     }
     uint64_t todo = __ballot(mine < n_words && !empty);
+    // (from a line of the instruction cache on, as the words' loop below, whatever code stands in front: 64 heads x 8192 tokens
+    // captured at 4096 scan 46.8 us, 48.3 from elsewhere in a line)
+    asm volatile(".p2align 6" ::: "memory");
     while (todo) {
       const int w = wb + __ffsll((unsigned long long)todo) - 1;
       todo &= todo - 1;
@@ -1178,6 +1181,7 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
         const int b = __ffsll((unsigned long long)need) - 1;
         need &= need - 1;
         bool any = false, all = true;
+        asm volatile(".p2align 6" ::: "memory");
         for (int x = lane; x < words; x += 64) {
           const uint64_t m = mask_word(g, tb, cbw, rr, i0 + x / g.wpr, (w * 64 + b) * g.wpr + x % g.wpr);
           any |= m != 0;
