@@ -30,8 +30,11 @@ constexpr int kGridTarget = 4096;
 constexpr int kHeadSub = 16;  // partial sums per head of the listed-tile counts
 // Query tiles of a head up to which k_pattern_prep scans them itself, a wave each, and the scan launch is saved. Whole builds,
 // launch / this, us: 2 heads x 4 tiles 17.8 / 16.9, 32 x 8 (capture of 256) 30.4 / 28.0, 64 x 8 35.9 / 32.7, 32 x 8 from patterns
-// 29.3 / 27.6; 32 x 16 29.0 / 29.8 (a wave per tile still, but on one CU per head), 32 x 32 31.7 / 38.3.
-constexpr int kScanInPrep = 8;
+// 29.3 / 27.6; 32 x 16 29.0 / 29.8 (a wave per tile still, but on one CU per head), 32 x 32 31.7 / 38.3. Patterns alone in the
+// plain layout have tiles of columns and diagonals both, which keep a lane busy, and a ragged last row of nothing else: there the
+// line lies lower. 32 heads x 7 tiles (ragged) 25.7 / 24.5, x 8 (1000 tokens) 37.5 / 39.9, x 8 (1024) 33.4 / 33.9, 8 x 8 (1000)
+// 36.2 / 37.3, (1024) 31.0 / 29.5; in the gathered layout 32 x 8 (1000) 28.6 / 27.2.
+constexpr int kScanInPrep = 8, kScanRaggedInPrep = 7;
 
 struct Geom {
   int H, L, S, P;            // P: length of the pattern flag arrays (L from a map, S when given)
@@ -2301,7 +2304,9 @@ bool needs_prep(const dam_mask_params *p, const dam_mask_out *o) {
 
 // Whether k_pattern_prep scans the tiles too: sets in LDS, and few query tiles for a wave to take.
 size_t prep_lds_bytes(const Geom &g) { return (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0; }
-bool scans_in_prep(const Geom &g, const dam_mask_out *o) { return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= kScanInPrep; }
+bool scans_in_prep(const Geom &g, const dam_mask_out *o, bool gather) {
+  return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= (g.L > 0 || gather || g.S % g.tile_m == 0 ? kScanInPrep : kScanRaggedInPrep);
+}
 
 // Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
 bool counts_in_prep(const dam_mask_params *p, const Geom &g, const dam_mask_out *o) {
@@ -2349,7 +2354,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
   if (needs_prep(p, o) || count.true_bits) {
     const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
-    const ScanArgs scan{scans_in_prep(g, o), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
+    const ScanArgs scan{scans_in_prep(g, o, gather), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
     k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
                                                    w.off_all, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
@@ -2362,7 +2367,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       const TurnGrid t = turn_grid((int64_t)((g.nQt + each - 1) / each) * g.H);
       return dim3(t.x, t.y);
     };
-    if (!scans_in_prep(g, o))
+    if (!scans_in_prep(g, o, gather))
       k_tile_scan<<<grid_of(4), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
                                                                      w.off_all, w.occ, w.full, w.tile_cnt, lds_sets > 0, gidx,
                                                                      gcnt, gstride, w.vocc, w.vfull, w.head_cnt);

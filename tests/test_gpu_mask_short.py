@@ -63,3 +63,21 @@ def test_scan_inside_the_prep_kernel(S, tm, tn, L):
     run_from_map(synth_map(np.random.default_rng(S), 3, L), None, S, tm, tn, 0.5, 1e-8, 0.02, 0.4)
     if S > tm:
         test_gpu_mask.test_gathered_column_tiles_match_oracle(S, tm, tn, min(L, S // 2))
+
+
+# the same from patterns alone, whose line in the plain layout is seven query tiles for a ragged length
+@pytest.mark.parametrize("S", [440, 448, 500, 512, 520])
+def test_scan_of_patterns_inside_the_prep_kernel(S):
+    rng = np.random.default_rng(S)
+    d, v = (np.zeros((4, S), np.uint8) for _ in range(2))
+    for h in range(3):
+        d[h, :1 + 60 * h] = 1
+        d[h, rng.choice(S, 5, replace=False)] = 1
+        v[h, rng.choice(S, 9 * h + 2, replace=False)] = 1
+    art = oracle.from_patterns(d, v)
+    for flags, check in ((0, lambda m: test_gpu_mask.check_against_oracle(art, S, 64, 64, m, dense=False)),
+                         (B.DAM_MASK_GATHER_COLUMNS, lambda m: test_gpu_mask.check_gathered(art, S, 64, 64, m))):
+        m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=4, L=0, S=S, tile_m=64, tile_n=64, diag_in=torch.from_numpy(d).cuda(),
+                         vert_in=torch.from_numpy(v).cuda(), flags=flags)
+        torch.cuda.synchronize()
+        check(m)
