@@ -530,7 +530,7 @@ __global__ __launch_bounds__(256) void k_pattern_slices(const uint64_t *__restri
 
 // gamma = count / size >= mu for pattern p of head h (Sec. 4.2.4), counts summed over the row chunks.
 // The chunk counts stay bit-sliced while they are added: a thread owns one word of 64 patterns and a
-// sixteenth of the chunks, ripple-adds their 7-slice counts into a wider bit-sliced sum (a full adder is
+// sixteenth of the chunks, ripple-adds their 8-slice counts into a wider bit-sliced sum (a full adder is
 // five logic operations on 64 patterns at once), the sixteen sums of a word are added pairwise, and only
 // then every thread extracts the integer counts of its patterns.
 // blockIdx.z: 0 vertical, 1 diagonal patterns; blockIdx.x: group of 16 words.
@@ -1053,8 +1053,9 @@ __device__ __forceinline__ int64_t farthest_tile(const uint64_t *__restrict__ of
 // Pass 1 of the block index: which key tiles of query tile (h, qt) hold a kept entry / are full.
 // One wave per query tile, 64 key tiles (one occupancy word) at a time, one lane per key tile. Tiles
 // strictly below the diagonal and outside the true-mask block are decided by their lane alone (from
-// the class bitsets, or by pattern_tile_flags); only the tiles on the diagonal or inside the
-// true-mask block are then evaluated word by word by the whole wave. No LDS, no barrier.
+// the class bitsets, or by pattern_tile_flags), and so is the diagonal tile of a query tile that lies wholly in the pattern
+// region (square tiles); the other tiles on the diagonal and those inside the true-mask block are then evaluated word by word
+// by the whole wave. No LDS, no barrier.
 __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__restrict__ tb, const uint64_t *__restrict__ cb,
                                               const uint64_t *__restrict__ rr, const uint64_t *__restrict__ col_any,
                                               const uint64_t *__restrict__ col_all, const uint64_t *__restrict__ off_any,

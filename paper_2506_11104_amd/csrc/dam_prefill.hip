@@ -654,11 +654,15 @@ struct Queues {
 
 // A queue's items in falling order of their number of blocks: {item, t0, t1, -} each, so that a workgroup that draws one has
 // its listed tiles with it. By numbers alone a dense head's long items started among the last ones: 32 heads x 4096 tokens
-// (2 items per workgroup) took 57 us where the workgroups worked 42 us on average; by length the launch takes 54 instead of 61
-// us in a kernel trace, 4 x 32 heads x 3001 tokens 165 instead of 170. A counting sort by one workgroup per queue, in the
-// launch that precedes the attention kernel anyway (5.3 us with it, 5.2 without).
+// (2 items per workgroup) took 57 us where the workgroups worked 42 us on average. A counting sort by one workgroup per queue, in
+// the launch that precedes the attention kernel anyway (5.3 us with it, 5.2 without). By number / by length, us, whole prefills:
+// captured masks, whose heads differ most, 32 heads x 4096 captured at 1024 57.7 / 51.0, 32 x 12345 at 1024 134 / 122, 16 x 16000
+// at 1024 88.6 / 78.7, 32 x 16384 at 256 119 / 117, 64 x 8000 at 2048 278 / 279; patterns of several sequences 8 x 16 x 2000 98 /
+// 90, 3 x 16 x 3500 92 / 80, 4 x 32 x 3001 158 / 150 (159 / 157 on another chip); patterns of one long sequence, whose heads are
+// alike, 32 x 8000 149 / 146, 32 x 12345 283 / 285, 16 x 30000 524 / 527, 16 x 8000 (16 KV heads) 87 / 92.
 // Where a queue holds several pairs they are taken in groups of at least kOrderGroup items, three per workgroup: all at once they
-// share the L2 badly (3001 tokens: 166 us), in smaller groups the last one has too few items to end evenly (96: 171 us).
+// share the L2 less, in small groups the last one has too few items to end evenly. (21 shapes of 8 to 160 items per pair: groups
+// of 96 -2 to +4.5 %, 384 -1 to +3, all -1.5 to +3.)
 // (Blocks are counted over an item's first 64 tiles, the others taken for two each.)
 constexpr int kOrderBins = 512, kOrderGroup = 192;
 template <int THREADS>
