@@ -737,7 +737,7 @@ __device__ __forceinline__ void order_items(const AttnArgs &a, const int *__rest
 // the lists stay empty. (Behind the items, not among them: both variants inside one loop over the items spilled registers
 // in its pipeline. As a launch of its own the second variant cost 4 to 5 us per call, almost always for nothing.)
 struct Shared {
-  int item[4];  // the next item: its number and queue, its listed tiles [t0, t1)
+  int4 item[2];  // the next item: its number and queue, its listed tiles [t0, t1); its sequence, KV head, query head, query tile
   int nblk, bad;
   int redo;     // first item of the workgroup's redo list (8 * item + queue), or -1
 };
@@ -779,6 +779,13 @@ __device__ __forceinline__ void arrived(T &...x) {
   (void)(arrived_one(x) + ...);
 }
 
+// A pointer that came out of the arguments in memory, as one into global memory (unknown to the compiler, whose flat loads and
+// stores count as LDS operations too: every wait for one kind then waits for the other).
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *in_global(T *p) {
+  return (__attribute__((address_space(1))) T *)p;
+}
+
 template <bool RAGGED, bool GATHER, bool FAST>
 __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds, Shared &sh, bool from_list) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -806,24 +813,31 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
   uint2 *blk_list = reinterpret_cast<uint2 *>(lds + kBlkList);
   // The listed tiles [seg0, seg0 + n_seg) of an item that starts at t0 -> list of block descriptors in LDS (two words:
   // first key, and mask offset | flags << 28), closed by a dummy entry that every read past the end returns. By wave 0
-  // alone, two tiles per lane: between two barriers, whatever the other waves do.
-  auto expand = [&](const KernelArgs &args, int t0, int seg0, int n_seg) {
-    const AttnArgs &a = args.a;
-    const int *__restrict__ blk_col = args.t.blk_col;
-    const uint8_t *__restrict__ blk_kind = args.t.blk_kind;
+  // alone, two tiles per lane: between two barriers, whatever the other waves do. In two steps, so that the loads of the
+  // item's query rows can be issued behind those of its tiles and travel while the list is written.
+  struct Tiles {
+    int col[kSegTiles / 64], kind[kSegTiles / 64];
+  };
+  auto fetch_tiles = [&](const Operands &t, int seg0, int n_seg) {
+    Tiles x;
+#pragma unroll
+    for (int half = 0; half < kSegTiles / 64; ++half) {
+      const int at = seg0 + min(half * 64 + lane, n_seg - 1);
+      x.col[half] = in_global(t.blk_col)[at];
+      x.kind[half] = in_global(t.blk_kind)[at];
+    }
+    return x;
+  };
+  auto expand = [&](const AttnArgs &a, const Tiles &tiles, int t0, int seg0, int n_seg) {
     int before = 0;
 #pragma unroll
     for (int half = 0; half < kSegTiles / 64; ++half) {
       const int x = half * 64 + lane;
-      int quarters = 0, col = 0, full = 0;
-      if (x < n_seg) {
-        const int kind = blk_kind[seg0 + x];
-        // a column outside the index's range (a list that was never filled) is pulled inside it: the result is
-        // then wrong, but every address formed from it stays within the head's rows
-        col = min(max(blk_col[seg0 + x], 0), a.nKt + (GATHER ? a.gather_rows / kBN : 0) - 1);
-        quarters = (kind >> 1) & 15;
-        full = kind & 1;
-      }
+      // a column outside the index's range (a list that was never filled) is pulled inside it: the result is
+      // then wrong, but every address formed from it stays within the head's rows
+      const int col = min(max(tiles.col[half], 0), a.nKt + (GATHER ? a.gather_rows / kBN : 0) - 1);
+      int quarters = x < n_seg ? (tiles.kind[half] >> 1) & 15 : 0;
+      const int full = tiles.kind[half] & 1;
       const int cnt = __popc(quarters);
       const int incl = wave_prefix(cnt);
       int at = before + incl - cnt;
@@ -846,90 +860,97 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
   // The queues. A workgroup's first item is its rank among those numbered for the same queue, without an atomic (all 512
   // of them start at once, and atomics on one counter are served one after the other: up to 7 us); the counters hand out
   // what follows.
+  // Between two items the matrix pipe of the workgroup idles for a chain of round trips to memory, so each of them travels
+  // under something else: wave 0 asks for the next item when the blocks of the one before are done, and the answer is under
+  // way while the rows are divided; where the item's tiles lie, while the rows are turned around, and is looked at in front of
+  // their stores (a load behind stores waits for them); the tiles in front of the query rows, and both while the list is
+  // written; and the pipeline starts on its first block, with the copies of three more in flight. Atomic, look-up, list, query
+  // rows and four blocks one after the other, with two more barriers, took 6.1 us an item where this takes 5.0: 4 x 32 heads x
+  // 3001 tokens (19 blocks an item) 159.4 -> 153.0 us, 8 x 32 x 700 57.9 -> 55.6, 32 x 32768 1169 -> 1156, 64 x 128k captured
+  // at 4096 9603 -> 9464 (whole layers). Asked in the item's last iterations: no gain, the wave's own copies in flight take
+  // as long as the answer.
   auto queue_starts = [&](int qu) { return ((int)gridDim.x - qu + kXcd - 1) / kXcd; };
-  // (Each draws when its item is finished: with the ticket's way laid under the stores of the item before, the prefill of
-  // the 32k layer took up to 5 % longer.)
   int hop = 0;  // (wave 0) queue of the next draw
-  int prev_item = -1, prev_queue = 0;  // (wave 0) the item just finished
-  bool first = true;
+  // asks the first queue from `hop` on that hands out more than first items
+  auto ask = [&](const Queues &qs, int *ctl) {
+    int got = 0;
+    while (hop < kXcd) {
+      const int queue = (my_xcd + hop) & (kXcd - 1);
+      if (qs.items(queue) > queue_starts(queue)) {
+        if (lane == 0)
+          got = __hip_atomic_fetch_add(in_global(ctl) + queue * kCtlStep, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+      ++hop;
+    }
+    return got;
+  };
+  // the answer: an item and its queue, or -1
+  auto answer = [&](const Queues &qs, int *ctl, int got, int &queue) {
+    while (hop < kXcd) {
+      queue = (my_xcd + hop) & (kXcd - 1);
+      const int item = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
+      if (item < qs.items(queue)) return item;
+      ++hop;
+      got = ask(qs, ctl);
+    }
+    return -1;
+  };
+  // Where an item's listed tiles lie, fetched without waiting: lanes 1 and 2 the offsets, from the index or, with lane 0 the
+  // item's number, from its entry in the order (`item` is then the place in it).
+  auto ordered = [&](const Operands &t) { return (FAST || !from_list) && t.order; };
+  auto look_up = [&](const Operands &t, const Queues &qs, int item, int queue) {
+    const int *at = ordered(t) ? reinterpret_cast<const int *>(t.order + queue * kOrderMax + item) : qs.span(t.row_ptr, item, queue) - 1;
+    return in_global(at)[min(max(lane, ordered(t) ? 0 : 1), 2)];
+  };
+  auto publish = [&](const Operands &t, const Queues &qs, int item, int e, int queue) {
+    if (ordered(t) && item >= 0) item = __builtin_amdgcn_readlane(e, 0);
+    const int pair = qs.pair_of(item, queue), within = qs.within_of(item, queue);
+    const int wb = pair / qs.Hkv, whkv = pair % qs.Hkv;
+    if (lane == 0) {
+      sh.item[0] = make_int4(item, queue, __builtin_amdgcn_readlane(e, 1), __builtin_amdgcn_readlane(e, 2));
+      sh.item[1] = make_int4(wb, whkv, whkv * qs.G + within % qs.G, qs.nQt - 1 - within / qs.G);
+    }
+  };
+  if (wave == 0) {
+    const KernelArgs &args = reread(args_at);
+    const Queues qs(args.a);
+    int item = -1, queue = blockIdx.x % kXcd;
+    if (!FAST && from_list) {
+      const int id = __builtin_amdgcn_readfirstlane(sh.redo);  // (not empty)
+      item = id / kXcd;
+      queue = id % kXcd;
+      if (lane == 0) sh.redo = args.t.next[id];
+    } else if ((int)blockIdx.x / kXcd < qs.items(queue)) {
+      item = blockIdx.x / kXcd;
+    } else {
+      item = answer(qs, args.t.ctl, ask(qs, args.t.ctl), queue);
+    }
+    publish(args.t, qs, item, item < 0 ? 0 : look_up(args.t, qs, item, queue), queue);
+  }
+  int id = -1;  // (item, queue) as the redo list has it
   while (true) {
-    // previous item: every wave is done with the LDS rings, with s_item and with sh.bad (its stores stay in flight)
+    // previous item: every wave is done with the LDS rings (its stores stay in flight), the next one is known
     KernelArgs args = reread(args_at);
-    arrived(args.a.B, args.a.Hq, args.a.Hkv, args.a.S, args.a.nQt, args.a.nKt, args.a.gather_rows, args.t.row_ptr, args.t.blk_col,
-            args.t.blk_kind, args.t.ctl, args.t.order);
+    arrived(args.a.S, args.a.nKt, args.a.gather_rows, args.a.Hq, args.t.blk_col, args.t.blk_kind);
     arrived(args.t.q, args.t.k, args.t.v, args.t.tile_bits, args.a.q_sb, args.a.q_sh, args.a.q_ss, args.a.k_sb, args.a.k_sh, args.a.v_sb,
             args.a.v_sh);
     if (GATHER) arrived(args.t.kgath, args.t.vgath);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (wave == 0) {
-      const Operands &t = args.t;
-      const Queues qs(args.a);
-      int item = -1, queue = 0;
-      if (FAST && prev_item >= 0 && sh.bad && lane == 0) {  // some row of the previous item needs the running reference
-        const int id = prev_item * kXcd + prev_queue;
-        t.next[id] = sh.redo;
-        sh.redo = id;
-        sh.bad = 0;
-      }
-      if (!FAST && from_list) {
-        const int id = __builtin_amdgcn_readfirstlane(sh.redo);
-        if (id >= 0) {
-          item = id / kXcd;
-          queue = id % kXcd;
-          if (lane == 0) sh.redo = t.next[id];
-        }
-      } else {
-        if (first) {
-          queue = blockIdx.x % kXcd;
-          if ((int)blockIdx.x / kXcd < qs.items(queue)) item = blockIdx.x / kXcd;
-        }
-        while (item < 0 && hop < kXcd) {
-          queue = (my_xcd + hop) & (kXcd - 1);
-          int got = 0;
-          if (qs.items(queue) <= queue_starts(queue)) {  // all of them handed out as first items
-            ++hop;
-            continue;
-          }
-          if (lane == 0) got = atomicAdd(&t.ctl[queue * kCtlStep], 1);
-          got = __builtin_amdgcn_readfirstlane(got) + queue_starts(queue);
-          if (got < qs.items(queue)) item = got;
-          else ++hop;
-        }
-      }
-      first = false;
-      prev_item = item;
-      prev_queue = queue;
-      int t0 = 0, t1 = 0;
-      if (item >= 0) {
-        if ((FAST || !from_list) && t.order) {  // item: the place in the order
-          const int4 e = t.order[queue * kOrderMax + item];
-          prev_item = item = __builtin_amdgcn_readfirstlane(e.x);
-          t0 = __builtin_amdgcn_readfirstlane(e.y);
-          t1 = __builtin_amdgcn_readfirstlane(e.z);
-        } else {
-          const int *rp = qs.span(t.row_ptr, item, queue);
-          t0 = __builtin_amdgcn_readfirstlane(rp[0]);
-          t1 = __builtin_amdgcn_readfirstlane(rp[1]);
-        }
-        expand(args, t0, t0, min(kSegTiles, t1 - t0));
-      }
-      if (lane == 0) {
-        sh.item[0] = item;
-        sh.item[1] = queue;
-        sh.item[2] = t0;
-        sh.item[3] = t1;
-      }
+    if (FAST && wave == 0 && id >= 0 && sh.bad && lane == 0) {  // some row of the previous item needs the running reference
+      args.t.next[id] = sh.redo;
+      sh.redo = id;
+      sh.bad = 0;
     }
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(sh.item[0]), queue = __builtin_amdgcn_readfirstlane(sh.item[1]);
+    const int4 what = sh.item[0], where = sh.item[1];
+    const int item = __builtin_amdgcn_readfirstlane(what.x), queue = __builtin_amdgcn_readfirstlane(what.y);
     if (item < 0) break;
+    id = item * kXcd + queue;
     const AttnArgs &a = args.a;
-    const Queues qs(a);
-    const int G = qs.G, S = a.S;
-    const int pair = qs.pair_of(item, queue), within = qs.within_of(item, queue);
-    const int wb = pair / a.Hkv, whkv = pair % a.Hkv;
-    const int wqt = a.nQt - 1 - within / G, whq = whkv * G + within % G;
-    const int t0 = __builtin_amdgcn_readfirstlane(sh.item[2]), t1 = __builtin_amdgcn_readfirstlane(sh.item[3]);
+    const int S = a.S;
+    const int t0 = __builtin_amdgcn_readfirstlane(what.z), t1 = __builtin_amdgcn_readfirstlane(what.w);
+    const int wb = __builtin_amdgcn_readfirstlane(where.x), whkv = __builtin_amdgcn_readfirstlane(where.y);
+    const int whq = __builtin_amdgcn_readfirstlane(where.z), wqt = __builtin_amdgcn_readfirstlane(where.w);
     const int qrow_l = wave * 32 + n;  // this lane's query row inside the tile
     const int qrow = wqt * kBM + qrow_l;
     const bool qlive = qrow < S;
@@ -1004,26 +1025,38 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
     int seen_full = 0;                      // tile was met: together "the row has a kept entry"
 
     if (t1 > t0) {
-      // Q fragments: B operand of S^T = K Q^T. Chunk c covers dims 16c .. 16c+15; this lane holds dims
-      // 16c + 8 hf .. + 7 of its query row.
+      // the first segment's tiles (wave 0), then the Q fragments, B operand of S^T = K Q^T: chunk c covers dims
+      // 16c .. 16c+15; this lane holds dims 16c + 8 hf .. + 7 of its query row. (A row past the sequence's end is its last
+      // one: nothing is kept for it, and nothing of it stored.)
+      const int n_first = min(kSegTiles, t1 - t0);
+      Tiles tiles;
+      if (wave == 0) tiles = fetch_tiles(args.t, t0, n_first);
       bf16x8 qf[8];
       {
-        const __hip_bfloat16 *qp = args.t.q + wb * a.q_sb + whq * a.q_sh + (int64_t)qrow * a.q_ss + 8 * hf;
+        const auto qp = in_global(args.t.q + wb * a.q_sb + whq * a.q_sh + (int64_t)min(qrow, S - 1) * a.q_ss + 8 * hf);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          u32x4 raw = {0u, 0u, 0u, 0u};
-          if (qlive) raw = *reinterpret_cast<const u32x4 *>(qp + 16 * c);
-          qf[c] = __builtin_bit_cast(bf16x8, raw);
-        }
+        for (int c = 0; c < 8; ++c)
+          qf[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const __attribute__((address_space(1))) u32x4 *>(qp + 16 * c));
       }
+      if (wave == 0) expand(a, tiles, t0, t0, n_first);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       // one pass of the pipeline per segment of kSegTiles listed tiles (a query tile of c3 has at most 32;
       // the accumulators, the softmax state and the Q fragments carry over)
       for (int seg0 = t0; seg0 < t1; seg0 += kSegTiles) {
         if (seg0 > t0) {
           __syncthreads();  // every wave is done with the previous list and with the rings
-          if (wave == 0) expand(reread(args_at), t0, seg0, min(kSegTiles, t1 - seg0));
+          if (wave == 0) {
+            const KernelArgs &again = reread(args_at);
+            const int n_seg = min(kSegTiles, t1 - seg0);
+            expand(again.a, fetch_tiles(again.t, seg0, n_seg), t0, seg0, n_seg);
+          }
           __syncthreads();
         }
+        // the Q fragments are waited for here (the compiler waits in front of an empty statement that takes them), before
+        // there are copies in flight, which the compiler cannot count: it would wait for all of them at the first use of a
+        // fragment in each iteration
+#pragma unroll
+        for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(qf[c]));
         n_blk = __builtin_amdgcn_readfirstlane(sh.nblk);
         d[0] = decode(list_read(0));
         d[1] = decode(list_read(1));
@@ -1037,12 +1070,8 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
         copy_k(d[2], I2{});
         copy_bits(d[2], I2{});
         copy_v(d[0], I0{});
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // the Q fragments have arrived with that wait; passing them through an empty statement tells the
-        // compiler so (it cannot see the wait, and would otherwise wait for every copy in flight at the
-        // first use of a fragment in each iteration)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(qf[c]));
+        // the first block's K and mask words; the eight copies behind them count like those of two iterations
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         // The variant with a reference multiplies the zero weights of the leading dummy blocks too, with V slots 2 and 3,
         // which therefore have to be finite: not what an earlier kernel or item left there, whose V may hold an infinity
         // or a NaN. (FAST leaves those products out. Each wave clears what it copies itself: nothing of its is in flight.)
@@ -1111,56 +1140,86 @@ __device__ __forceinline__ void prefill_items(ArgsAt args_at, unsigned char *lds
           }
         }
       }
+    } else {
+      asm volatile("s_barrier" ::: "memory");  // (the next item is not written before every wave has this one)
     }
 
     // finish: total sum over both half-waves, normalise, store. Accumulator e of block db is dim
     // 32 db + 8 (e / 4) + 4 hf + e % 4 of this lane's query.
+    KernelArgs end = reread(args_at);
+    arrived(end.t.out, end.t.lse, end.a.o_sb, end.a.o_sh, end.a.o_ss, end.a.Hq, end.a.B, end.a.Hkv, end.a.nQt, end.t.ctl, end.t.order,
+            end.t.row_ptr);
+    const Queues qs(end.a);
+    int got = 0;
+    if (wave == 0 && !(!FAST && from_list)) got = ask(qs, end.t.ctl);
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
     if (FAST) {
       // a row with a kept entry whose sum of weights is zero, tiny, huge, infinite or NaN: its logits lie outside
       // what exp2 without a reference can carry (|logit * log2 e| of the order of 100)
       const bool bad = qlive && (seen != 0u || seen_full) && !(l_tot >= 0x1p-100f && l_tot <= 0x1p100f);
-      if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) sh.bad = 1;  // read by thread 0 after the loop's barrier
+      if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) sh.bad = 1;  // read by wave 0 after the loop's barrier
+    }
+    uint2 pr[16];
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        pr[4 * db + g].x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
+        pr[4 * db + g].y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
+        asm volatile("" : "+v"(pr[4 * db + g].x), "+v"(pr[4 * db + g].y));  // (while the answer is on its way)
+      }
+    int next = -1, next_queue = 0, next_at = 0;
+    if (wave == 0) {
+      if (!FAST && from_list) {
+        const int next_id = __builtin_amdgcn_readfirstlane(sh.redo);
+        if (next_id >= 0) {
+          next = next_id / kXcd;
+          next_queue = next_id % kXcd;
+          if (lane == 0) sh.redo = end.t.next[next_id];
+        }
+      } else {
+        next = answer(qs, end.t.ctl, got, next_queue);
+      }
     }
     // The rows go out as whole 256-byte lines: a lane holds eight bytes here and there of its query's row, so the wave
-    // turns its 32 rows around in 8 KiB of the K ring (16-byte chunk c of row r at c ^ (r & 15)) and every store
-    // instruction then covers four rows. (Eight bytes per lane and store straight from the accumulators: 2.6 us per item
-    // until the stores had drained, up to 20 us with every workgroup storing at once.) Only when every wave's copies have
-    // landed; what the others still read of K belongs to no block.
-    KernelArgs end = reread(args_at);
-    arrived(end.t.out, end.t.lse, end.a.o_sb, end.a.o_sh, end.a.o_ss, end.a.Hq);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    // turns its 32 rows around in LDS (16-byte chunk c of row r at c ^ (r & 15)) and every store instruction then covers
+    // four rows. (Eight bytes per lane and store straight from the accumulators: 2.6 us per item until the stores had
+    // drained, up to 20 us with every workgroup storing at once.) The place is the 8 KiB of the K ring that this wave's own
+    // copies fill (four rows at 1024 wave of every 4 KiB), so nobody else is waited for: its own copies have landed, and
+    // what the other waves still read of K in their last iteration belongs to no block.
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the builtin, so that the compiler knows and waits for nothing below
+    asm volatile("" ::: "memory");
+    if (wave == 0 && next >= 0) next_at = look_up(end.t, qs, next, next_queue);
     {
       int l = lane;  // (opaque, or the addresses below are computed once for all items and kept through the pipeline)
       asm volatile("" : "+v"(l));
-      unsigned char *turn = lds + wave * 8192;
-      unsigned char *row_at = turn + (l & 31) * 256 + 8 * (l >> 5);
+      unsigned char *turn = lds + wave * 1024;
+      unsigned char *row_at = turn + ((l & 31) >> 2) * 4096 + (l & 3) * 256 + 8 * (l >> 5);
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 pr;
-          pr.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
-          pr.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
-          *reinterpret_cast<uint2 *>(row_at + (((4 * db + g) ^ (l & 15)) << 4)) = pr;
-        }
+      for (int x = 0; x < 16; ++x) *reinterpret_cast<uint2 *>(row_at + ((x ^ (l & 15)) << 4)) = pr[x];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      u32x4 line[8];
+#pragma unroll
+      for (int it = 0; it < 8; ++it)
+        line[it] = *reinterpret_cast<const u32x4 *>(turn + it * 4096 + (l >> 4) * 256 + (((l & 15) ^ ((4 * it + (l >> 4)) & 15)) << 4));
+      if (wave == 0) {
+        asm volatile("" : "+v"(next_at));  // (looked at here, not where it was fetched)
+        publish(end.t, qs, next, next_at, next_queue);
+      }
       const int row_first = wqt * kBM + wave * 32;
-      __hip_bfloat16 *op = end.t.out + wb * end.a.o_sb + whq * end.a.o_sh + (int64_t)(row_first + (l >> 4)) * end.a.o_ss + 8 * (l & 15);
+      auto op = in_global(end.t.out + wb * end.a.o_sb + whq * end.a.o_sh + (int64_t)(row_first + (l >> 4)) * end.a.o_ss + 8 * (l & 15));
       const int64_t four_rows = 4 * end.a.o_ss;
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
-        const int r = 4 * it + (l >> 4);
-        const uint4 x = *reinterpret_cast<const uint4 *>(turn + r * 256 + (((l & 15) ^ (r & 15)) << 4));
-        if (row_first + r < S) *reinterpret_cast<uint4 *>(op) = x;
+        if (row_first + 4 * it + (l >> 4) < S) *reinterpret_cast<__attribute__((address_space(1))) u32x4 *>(op) = line[it];
         op += four_rows;
       }
     }
     if (qlive && end.t.lse && hf == 0)
-      end.t.lse[((int64_t)wb * end.a.Hq + whq) * S + qrow] =
+      in_global(end.t.lse)[((int64_t)wb * end.a.Hq + whq) * S + qrow] =
           l_tot > 0.0f ? ((FAST ? 0.0f : m_run * c2) + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
   }  // next work item
 }
