@@ -897,16 +897,34 @@ __device__ __forceinline__ void gather_columns_of_head(const Geom &g, const uint
 }
 
 // Transpose of the 64 x 64 bit matrix whose row l is the word x of lane l: lane r returns the word whose
-// bit l is bit r of lane l's x. Six exchange steps on blocks of 32, 16, ... 1 bits.
+// bit l is bit r of lane l's x. Six exchange steps on blocks of 32, 16, ... 1 bits, all in the vector registers (lane
+// swaps, row rotations, byte permutes: some 45 instructions; exchanges through LDS waited for it six times).
 __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
-  uint64_t m = 0x00000000FFFFFFFFull;
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  // blocks of 32: the upper halves of lanes 0 .. 31 against the lower halves of lanes 32 .. 63
+  u32x2 v = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)(x >> 32), false, false);
+  const unsigned sel16 = lane & 16 ? 0x07060302u : 0x05040100u, sel8 = lane & 8 ? 0x03070105u : 0x06020400u;
 #pragma unroll
-  for (int j = 32; j > 0; j >>= 1) {
-    const uint64_t other = __shfl_xor(x, j);
-    x = (lane & j) ? (((other >> j) & m) | (x & ~m)) : ((x & m) | ((other & m) << j));
-    m ^= m << (j >> 1);
+  for (int k = 0; k < 2; ++k) {
+    unsigned w = v[k];
+    // 16: even rows' values and odd rows' values, in all lanes
+    const u32x2 rows = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+    w = __builtin_amdgcn_perm(rows[1], rows[0], sel16);
+    // 8: lane ^ 8 is the row turned by eight
+    unsigned other = __builtin_amdgcn_update_dpp(0, w, 0x128, 0xF, 0xF, false);
+    w = __builtin_amdgcn_perm(other, w, sel8);
+    auto step = [&](unsigned from, int j, unsigned low) {  // low: the lower j bits of every 2 j
+      const bool up = (lane & j) != 0;
+      const unsigned turned = __builtin_amdgcn_alignbit(from, from, up ? j : 32 - j), take = up ? low : ~low;
+      return (turned & take) | (w & ~take);
+    };
+    other = __builtin_amdgcn_update_dpp(0, w, 0x141, 0xF, 0xF, false);      // lane ^ 7, and
+    other = __builtin_amdgcn_update_dpp(0, other, 0x1B, 0xF, 0xF, false);   // ^ 3: lane ^ 4
+    w = step(other, 4, 0x0F0F0F0Fu);
+    w = step(__builtin_amdgcn_update_dpp(0, w, 0x4E, 0xF, 0xF, false), 2, 0x33333333u);
+    v[k] = step(__builtin_amdgcn_update_dpp(0, w, 0xB1, 0xF, 0xF, false), 1, 0x55555555u);
   }
-  return x;
+  return (uint64_t)v[1] << 32 | v[0];
 }
 
 // a3 for short captures, inside the kernel that needs the flags: match counts of one head from its true bits, gamma >= mu,
@@ -975,29 +993,52 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
   }
 }
 
-// The same from the chunk counts of k_pattern_slices, for captures where adding those up is little work for one workgroup
-// (kSlicesInPrep): a wave per word of patterns, a lane per pattern; the slices of a word and chunk are wave-uniform, so a
-// chunk's count is built bit by bit from scalar registers. Saves the launch of k_pattern_finish: whole builds at 32 heads x 1024
-// 67.9 us counted in the prep kernel, 63.1 so; x 1536 100.8 us with k_pattern_finish, 96.3; x 2048 161.1, 161.8.
-constexpr int kSlicesInPrep = 1536;
+// The same from the chunk counts of k_pattern_slices (kSlicesInPrep), a wave per word of patterns: a lane fetches one of the
+// eight slices of one chunk, and the 64 x 64 bits of eight chunks turned around are, in the lane of a pattern, its eight
+// counts, a byte each. Bound by one trip to memory per job, so the next job's slices are under way.
+// Saves the launch of k_pattern_finish. Whole layers at 32 heads, us, each slice a wave-uniform load of its own / this: 4096
+// tokens captured at 1024 111.9 / 108.4, 6000 at 1536 187.1 / 180.2; 8000 at 2048, where k_pattern_finish did it, 267.3 / 262.6;
+// 16 heads x 8000 at 3072 and 64 x 9000 at 4096 k_pattern_finish 245.7 / 1158, this 245.6 / 1157.
+constexpr int kSlicesInPrep = 2048;
 __device__ __forceinline__ void sum_slices_of_head(const Geom &g, const uint64_t *__restrict__ vslices, const uint64_t *__restrict__ dslices,
                                                    float mu, int h, int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
                                                    uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,
                                                    uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev, uint64_t *lds_copy) {
+  static_assert(kSlices == 8, "a count is a byte");
+  constexpr int kEach = (kSlicesInPrep / kChunkRows + 7) / 8;  // fetches per lane and job
   const int lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
-  for (int x = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); x < 2 * g.tbw; x += n_waves) {
-    const int word = x >> 1, p = 64 * word + lane;
-    const uint64_t *slices = (x & 1 ? dslices : vslices) + ((int64_t)h * n_chunks * g.tbw + word) * kSlices;
-    int n = 0;
-    // rows above pattern p hold nothing of it
-    for (int chunk = word * 64 / kChunkRows; chunk < n_chunks; ++chunk) {
-      int v = 0;
+  uint64_t next[kEach];
+  // rows above pattern p hold nothing of it: start at the chunk of the word's first
+  auto fetch = [&](int x) {
+    const int word = x >> 1, from = word * 64 / kChunkRows;
+    const uint64_t *slices = (x & 1 ? dslices : vslices) + ((int64_t)h * n_chunks * g.tbw + word) * kSlices + (lane & 7);
 #pragma unroll
-      for (int k = kSlices - 1; k >= 0; --k)
-        v = 2 * v + (__builtin_amdgcn_inverse_ballot_w64(slices[(int64_t)chunk * g.tbw * kSlices + k]) ? 1 : 0);
-      n += v;
+    for (int u = 0; u < kEach; ++u) {
+      const int chunk = from + 8 * u + (lane >> 3);
+      next[u] = 0;
+      if (from + 8 * u < n_chunks) {  // wave-uniform
+        const uint64_t v = slices[(int64_t)min(chunk, n_chunks - 1) * g.tbw * kSlices];
+        next[u] = chunk < n_chunks ? v : 0;
+      }
     }
+  };
+  int x = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (x < 2 * g.tbw) fetch(x);
+  for (; x < 2 * g.tbw; x += n_waves) {
+    uint64_t w[kEach];
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) w[u] = next[u];
+    if (x + n_waves < 2 * g.tbw) fetch(x + n_waves);
+    const int word = x >> 1, p = 64 * word + lane;
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < kEach; ++u)
+      if (word * 64 / kChunkRows + 8 * u < n_chunks) {  // wave-uniform
+        const uint64_t counts = transpose64(w[u], lane);
+        n = __builtin_amdgcn_udot4((unsigned)counts, 0x01010101u, n, false);
+        n = __builtin_amdgcn_udot4((unsigned)(counts >> 32), 0x01010101u, n, false);
+      }
     const bool hit = p < g.L && (float)n / (float)(g.L - p) >= mu;
     const uint64_t set = __ballot(hit);
     const int64_t e = (int64_t)h * g.L + p;
