@@ -785,32 +785,39 @@ __device__ __forceinline__ void tile_classes_of_head(const Geom &g, const uint64
                                                      const uint64_t *__restrict__ rr, int h, uint64_t *__restrict__ col_any,
                                                      uint64_t *__restrict__ col_all, uint64_t *__restrict__ off_any,
                                                      uint64_t *__restrict__ off_all) {
-  const int lane = threadIdx.x & 63;
-  const int T = g.tile_n;
-  const int64_t Q = (int64_t)g.pw * 64 - 1;
-  for (int w = threadIdx.x >> 6; w < g.occw; w += blockDim.x >> 6) {  // a wave per occupancy word
-    {
+  // Tiles are whole words wide: the columns of a key tile are W = T / 64 words of the column set, the offsets of distance d
+  // the 2 W words from pw - W (d + 1) on of the reversed diagonal set, but for the last bit (offset T (d - 1), which the tile
+  // does not meet). So a lane reads its words side by side and waits once; a wave per word of either kind.
+  const int lane = threadIdx.x & 63, W = g.tile_n / 64;
+  for (int x = threadIdx.x >> 6; x < 2 * g.occw; x += blockDim.x >> 6) {
+    const int w = x >> 1;
+    uint64_t any = 0, all = ~0ull;
+    bool live;
+    if (x & 1) {
       const int kt = w * 64 + lane;
-      const int64_t j0 = (int64_t)kt * T, j1 = j0 + T - 1;
-      const bool any = kt < g.nKt && range_any(cb, g.pw, j0, j1);
-      const bool all = kt < g.nKt && j1 <= Q && range_all(cb, j0, j1);
-      const uint64_t wa = __ballot(any), wf = __ballot(all);
-      if (lane == 0) {
-        col_any[(int64_t)h * g.occw + w] = wa;
-        col_all[(int64_t)h * g.occw + w] = wf;
-      }
+      live = kt < g.nKt;
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        if (y < W) {
+          const uint64_t v = set_word(cb, kt * W + y, g.pw);
+          any |= v;
+          all &= v;
+        }
+    } else {
+      const int d = g.occw * 64 - 1 - (w * 64 + lane), first = g.pw - W * (d + 1);
+      live = d >= 1 && d < g.nQt;
+#pragma unroll
+      for (int y = 0; y < 8; ++y)
+        if (y < 2 * W) {
+          const uint64_t v = set_word(rr, first + y, g.pw), spare = y == 2 * W - 1 ? 1ull << 63 : 0;
+          any |= v & ~spare;
+          all &= v | spare;
+        }
     }
-    {
-      const int64_t d = (int64_t)g.occw * 64 - 1 - ((int64_t)w * 64 + lane);
-      const int64_t a = d * T - (T - 1), b = d * T + (T - 1);  // offsets of the tile, a >= 1 when d >= 1
-      const bool live = d >= 1 && d < g.nQt;
-      const bool any = live && range_any(rr, g.pw, Q - b, Q - a);
-      const bool all = live && b <= Q && range_all(rr, Q - b, Q - a);
-      const uint64_t wa = __ballot(any), wf = __ballot(all);
-      if (lane == 0) {
-        off_any[(int64_t)h * g.occw + w] = wa;
-        off_all[(int64_t)h * g.occw + w] = wf;
-      }
+    const uint64_t wa = __ballot(live && any != 0), wf = __ballot(live && all == ~0ull);
+    if (lane == 0) {
+      (x & 1 ? col_any : off_any)[(int64_t)h * g.occw + w] = wa;
+      (x & 1 ? col_all : off_all)[(int64_t)h * g.occw + w] = wf;
     }
   }
 }
@@ -848,40 +855,38 @@ __device__ __forceinline__ void stage_sets(uint64_t *lds_sets, int pw, const uin
 // c = gidx[s] <= i and i - c is not a matched diagonal (those entries belong to the diagonal part).
 // A vertical stripe then costs its share of one dense tile per query tile instead of a whole tile.
 
-// The matched columns below S of one head, ascending, padded with -1 up to the stride. One workgroup per
-// head, a word of the column bitset per thread and pass.
+// The matched columns below S of one head, ascending, padded with -1 up to the stride. One workgroup of 16 waves per
+// head, a word of the column set per lane and pass; the words with more than two columns (sinks, the last columns of a
+// capture) are then written by the whole wave, a lane per bit. (Bit by bit in the word's own lane, 64 dependent steps for a
+// full word, this and the classes took 5.5 us of the prep kernel's 8 at 32 heads x 4096 tokens captured at 1024.)
 __device__ __forceinline__ void gather_columns_of_head(const Geom &g, const uint64_t *__restrict__ cb,  // the head's column set
                                                        int stride, int h, int *__restrict__ gidx, int *__restrict__ gcnt) {
-  __shared__ int s_wave[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ int s_wave[2][16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int *out = gidx + (int64_t)h * stride;
-  const int n_cols = min(g.P, g.S);
+  const int n_cols = min(g.P, g.S), n_words = (n_cols + 63) / 64;
   int base = 0;  // the same value in every thread
-  for (int w0 = 0; w0 * 64 < n_cols; w0 += 1024) {  // a word of the column set per thread
-    const int w = w0 + threadIdx.x;
-    uint64_t m = (w < g.pw && w * 64 < n_cols) ? cb[w] : 0;
+  for (int w0 = 0, pass = 0; w0 < n_words; w0 += 1024, ++pass) {
+    const int each = (min(n_words - w0, 1024) + 15) / 16;  // words per wave
+    const int w = w0 + wave * each + lane;
+    uint64_t m = lane < each && w < n_words ? cb[w] : 0;
     if (w * 64 + 64 > n_cols && w * 64 < n_cols) m &= ~0ull >> (64 - (n_cols - w * 64));
-    const int v = __popcll(m);
-    int incl = v;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
+    const int v = __popcll(m), incl = wave_prefix(v);
+    if (lane == 63) s_wave[pass & 1][wave] = incl;
+    __syncthreads();  // one per pass: the totals of consecutive passes lie in alternating words
+    const int totals = wave_prefix(lane < 16 ? s_wave[pass & 1][lane] : 0);
+    const int before = base + (wave > 0 ? __builtin_amdgcn_readlane(totals, (wave - 1) & 15) : 0), at = before + incl - v;
+    base += __builtin_amdgcn_readlane(totals, 15);
+    if (v == 1 || v == 2) {
+      out[at] = w * 64 + __ffsll((unsigned long long)m) - 1;
+      if (v == 2) out[at + 1] = w * 64 + 63 - __clzll((long long)m);
     }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    int before = base, all = 0;
-    for (int x = 0; x < 16; ++x) {
-      const int t = s_wave[x];
-      if (x < wave) before += t;
-      all += t;
+    for (uint64_t many = __ballot(v > 2); many; many &= many - 1) {
+      const int from = __ffsll((unsigned long long)many) - 1;
+      const unsigned lo = __builtin_amdgcn_readlane((int)m, from), hi = __builtin_amdgcn_readlane((int)(m >> 32), from);
+      const int to = __builtin_amdgcn_readlane(at, from) + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+      if ((lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1) out[to] = (w0 + wave * each + from) * 64 + lane;
     }
-    int at = before + incl - v;
-    while (m) {
-      out[at++] = w * 64 + __ffsll((unsigned long long)m) - 1;
-      m &= m - 1;
-    }
-    base += all;
-    __syncthreads();  // s_wave is rewritten in the next pass
   }
   if (threadIdx.x == 0) gcnt[h] = base;
   // the empty slots: 16 bytes per store where the row allows it (rows are `stride` ints apart, a multiple of 64)
