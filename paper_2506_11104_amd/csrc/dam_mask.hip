@@ -615,51 +615,76 @@ __global__ __launch_bounds__(256) void k_pattern_finish(const uint64_t *__restri
 // i.e. the diagonal set reversed, so that the 64 offsets i-j, i-j-1, ... of one mask word are 64
 // consecutive ascending bits. Four lanes build one word: each turns 16 flag bytes (one 16-byte
 // load when the row is aligned) into 16 bits.
-__device__ __forceinline__ unsigned flags16(const uint8_t *__restrict__ row, int first, int P, bool aligned) {
+__device__ __forceinline__ unsigned bits_of_16(const uint4 &v) {
+  const unsigned x[4] = {v.x, v.y, v.z, v.w};
   unsigned bits = 0;
-  if (aligned && first + 16 <= P) {
-    const uint4 v = *reinterpret_cast<const uint4 *>(row + first);
-    const unsigned x[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      // per byte: non-zero -> 1, then gather the four 0/1 bytes into four adjacent bits
-      const unsigned nz = ((((x[k] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x[k]) & 0x80808080u) >> 7;
-      bits |= (((nz * 0x00204081u) >> 21) & 0xFu) << (4 * k);
-    }
-  } else {
-    for (int k = 0; k < 16; ++k)
-      if (first + k < P && row[first + k] != 0) bits |= 1u << k;
+  for (int k = 0; k < 4; ++k) {
+    // per byte: non-zero -> 1, then gather the four 0/1 bytes into four adjacent bits
+    const unsigned nz = ((((x[k] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x[k]) & 0x80808080u) >> 7;
+    bits |= (((nz * 0x00204081u) >> 21) & 0xFu) << (4 * k);
   }
   return bits;
 }
 
-// (every thread of the workgroup calls this; 256 words per pass)
+// (every thread of the workgroup calls this; 512 words per pass)
+// A piece is read where it lies, at any alignment, and one that the row's end cuts from 16 bytes before that end and shifted:
+// no lane is asked, so all of a pass's loads are under way together. (Aligned rows by 16 bytes with a branch around the last
+// piece, others byte by byte: 4.2 us of the prep kernel at 32 heads x 32768 tokens, now 2.7.)
 __device__ __forceinline__ void pattern_bitsets_of_head(const uint8_t *__restrict__ diag_flag,
                                                         const uint8_t *__restrict__ vert_flag, int P, int pw, int h,
                                                         uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev,
                                                         uint64_t *lds_copy) {  // both sets again, [2 pw], or nullptr
   const int part = threadIdx.x & 3;
-  const uint8_t *drow = diag_flag + (int64_t)h * P, *vrow = vert_flag + (int64_t)h * P;
-  const bool d_al = (reinterpret_cast<uintptr_t>(drow) & 15) == 0, v_al = (reinterpret_cast<uintptr_t>(vrow) & 15) == 0;
-  for (int w0 = 0; w0 < pw; w0 += blockDim.x / 4) {
-    const int w = w0 + (threadIdx.x >> 2);
-    const bool live = w < pw;
-    uint64_t cw = 0, rw = 0;
-    if (live) {
-      cw = (uint64_t)flags16(vrow, w * 64 + part * 16, P, v_al) << (16 * part);
-      rw = (uint64_t)flags16(drow, (pw - 1 - w) * 64 + part * 16, P, d_al) << (16 * part);  // ascending offsets
+  const uint8_t *rows[2] = {vert_flag + (int64_t)h * P, diag_flag + (int64_t)h * P};
+  const int each = blockDim.x / 4;
+  constexpr int kWords = 2;
+  for (int w0 = 0; w0 < pw; w0 += kWords * each) {
+    unsigned piece[kWords][2];
+    if (P >= 16) {
+      uint4 v[kWords][2];
+      int past[kWords][2];
+#pragma unroll
+      for (int u = 0; u < kWords; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int w = w0 + u * each + (int)(threadIdx.x >> 2);
+          const int first = (k ? pw - 1 - w : w) * 64 + part * 16;  // ascending offsets in a reversed word
+          const int at = min(max(first, 0), P - 16);
+          past[u][k] = min(first - at, 16);  // (below 0 only for a word that does not exist)
+          __builtin_memcpy(&v[u][k], rows[k] + at, 16);
+        }
+#pragma unroll
+      for (int u = 0; u < kWords; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) piece[u][k] = bits_of_16(v[u][k]) >> max(past[u][k], 0);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kWords; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          piece[u][k] = 0;
+          const int w = w0 + u * each + (int)(threadIdx.x >> 2);
+          if (w == 0 && part == 0)
+            for (int y = 0; y < P; ++y) piece[u][k] |= (rows[k][y] != 0 ? 1u : 0u) << y;
+        }
     }
-    cw |= __shfl_xor(cw, 1);
-    cw |= __shfl_xor(cw, 2);
-    rw |= __shfl_xor(rw, 1);
-    rw |= __shfl_xor(rw, 2);
-    if (live && part == 0) {
-      const uint64_t rev = __brevll(rw);  // bit q of the word <- offset (pw*64 - 1) - (64 w + q)
-      cbits[(int64_t)h * pw + w] = cw;
-      rrev[(int64_t)h * pw + w] = rev;
-      if (lds_copy) {
-        lds_copy[w] = cw;
-        lds_copy[pw + w] = rev;
+#pragma unroll
+    for (int u = 0; u < kWords; ++u) {
+      const int w = w0 + u * each + (int)(threadIdx.x >> 2);
+      uint64_t cw = (uint64_t)piece[u][0] << (16 * part), rw = (uint64_t)piece[u][1] << (16 * part);
+      cw |= __shfl_xor(cw, 1);
+      cw |= __shfl_xor(cw, 2);
+      rw |= __shfl_xor(rw, 1);
+      rw |= __shfl_xor(rw, 2);
+      if (w < pw && part == 0) {
+        const uint64_t rev = __brevll(rw);  // bit q of the word <- offset (pw*64 - 1) - (64 w + q)
+        cbits[(int64_t)h * pw + w] = cw;
+        rrev[(int64_t)h * pw + w] = rev;
+        if (lds_copy) {
+          lds_copy[w] = cw;
+          lds_copy[pw + w] = rev;
+        }
       }
     }
   }
@@ -781,10 +806,11 @@ __device__ int pattern_tile_flags(const uint64_t *__restrict__ cb, const uint64_
 // property of kt alone and "some offset matched" / "all offsets matched" of d alone. The d classes
 // are stored reversed (d at position 64 dw - 1 - d), like the diagonal set, so that the 64 key tiles
 // of an occupancy word are 64 consecutive bits.
+// A head's words lie together: [some columns, all columns, some offsets, all offsets][occw].
+enum { kColAny = 0, kColAll = 1, kOffAny = 2, kOffAll = 3 };
 __device__ __forceinline__ void tile_classes_of_head(const Geom &g, const uint64_t *__restrict__ cb,  // the head's sets
-                                                     const uint64_t *__restrict__ rr, int h, uint64_t *__restrict__ col_any,
-                                                     uint64_t *__restrict__ col_all, uint64_t *__restrict__ off_any,
-                                                     uint64_t *__restrict__ off_all) {
+                                                     const uint64_t *__restrict__ rr, uint64_t *__restrict__ classes,
+                                                     uint64_t *lds_copy) {  // or nullptr
   // Tiles are whole words wide: the columns of a key tile are W = T / 64 words of the column set, the offsets of distance d
   // the 2 W words from pw - W (d + 1) on of the reversed diagonal set, but for the last bit (offset T (d - 1), which the tile
   // does not meet). So a lane reads its words side by side and waits once; a wave per word of either kind.
@@ -816,8 +842,13 @@ __device__ __forceinline__ void tile_classes_of_head(const Geom &g, const uint64
     }
     const uint64_t wa = __ballot(live && any != 0), wf = __ballot(live && all == ~0ull);
     if (lane == 0) {
-      (x & 1 ? col_any : off_any)[(int64_t)h * g.occw + w] = wa;
-      (x & 1 ? col_all : off_all)[(int64_t)h * g.occw + w] = wf;
+      const int at = (x & 1 ? kColAny : kOffAny) * g.occw + w;
+      classes[at] = wa;
+      classes[at + g.occw] = wf;
+      if (lds_copy) {
+        lds_copy[at] = wa;
+        lds_copy[at + g.occw] = wf;
+      }
     }
   }
 }
@@ -834,10 +865,15 @@ inline size_t staged_bytes(const Geom &g) {
   const size_t b = ((size_t)g.pw * 2 + kGuardFront + kGuardBack) * sizeof(uint64_t);
   return b <= kMaxStagedBytes ? b : 0;
 }
+inline size_t class_bytes(const Geom &g) { return (size_t)g.occw * 4 * sizeof(uint64_t); }
+constexpr size_t kMaxWithClasses = 56 * 1024;  // (64 KiB less what the kernels hold besides)
 
 // Layout: the column set (pw words), kGuardFront zero words, the reversed diagonal set (pw words), kGuardBack zero
-// words: words -kGuardFront .. -1 and pw, pw + 1 of the staged diagonal set read as empty without a test.
-__device__ __forceinline__ void stage_sets(uint64_t *lds_sets, int pw, const uint64_t *cb, const uint64_t *rr) {
+// words: words -kGuardFront .. -1 and pw, pw + 1 of the staged diagonal set read as empty without a test; behind them the
+// head's class words, where they are wanted (n_classes).
+__device__ __forceinline__ void stage_sets(uint64_t *lds_sets, int pw, const uint64_t *cb, const uint64_t *rr,
+                                           const uint64_t *classes = nullptr, int n_classes = 0) {
+  for (int x = threadIdx.x; x < n_classes; x += blockDim.x) lds_sets[2 * pw + kGuardFront + kGuardBack + x] = classes[x];
   for (int x = threadIdx.x; x < pw; x += blockDim.x) {
     lds_sets[x] = cb[x];
     lds_sets[pw + kGuardFront + x] = rr[x];
@@ -1102,12 +1138,30 @@ __device__ __forceinline__ int64_t farthest_tile(const uint64_t *__restrict__ of
 // the class bitsets, or by pattern_tile_flags), and so is the diagonal tile of a query tile that lies wholly in the pattern
 // region (square tiles); the other tiles on the diagonal and those inside the true-mask block are then evaluated word by word
 // by the whole wave. No LDS, no barrier.
+// (What a row needs of the gathered columns, fetched in front of everything else: a load issued behind the stores below waits for
+// them. The first 64 gathered tiles' first and last columns; slots past the count hold -1.)
+struct RowColumns {
+  int n_cols, first, last;
+};
+__device__ __forceinline__ RowColumns fetch_columns(const Geom &g, const int *__restrict__ gidx, const int *__restrict__ gcnt, int gstride,
+                                                    int h, int qt, int lane) {
+  RowColumns c{0, -1, -1};
+  if (gidx != nullptr && qt * g.tile_m >= g.L) {
+    const int *gi = gidx + (int64_t)h * gstride;
+    c.n_cols = gcnt[h];
+    if ((lane + 1) * g.tile_n <= gstride) {
+      c.first = gi[lane * g.tile_n];
+      c.last = gi[lane * g.tile_n + g.tile_n - 1];
+    }
+  }
+  return c;
+}
+template <bool TRUE_BLOCK>  // there is a true-mask block (L > 0)
 __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__restrict__ tb, const uint64_t *__restrict__ cb,
-                                              const uint64_t *__restrict__ rr, const uint64_t *__restrict__ col_any,
-                                              const uint64_t *__restrict__ col_all, const uint64_t *__restrict__ off_any,
-                                              const uint64_t *__restrict__ off_all, uint64_t *__restrict__ occ,
+                                              const uint64_t *__restrict__ rr, const uint64_t *__restrict__ classes,  // of the head
+                                              uint64_t *__restrict__ occ,
                                               uint64_t *__restrict__ full, int *__restrict__ cnt, const int *__restrict__ gidx,
-                                              const int *__restrict__ gcnt, int gstride, uint64_t *__restrict__ vocc,
+                                              const RowColumns &columns, int gstride, uint64_t *__restrict__ vocc,
                                               uint64_t *__restrict__ vfull, int h, int qt, int lane) {
   const int i0 = qt * g.tile_m;
   const int i_last = min(g.S - 1, i0 + g.tile_m - 1);
@@ -1118,22 +1172,13 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   const bool by_class = g.tile_m == g.tile_n && i0 >= g.L && i0 + g.tile_m <= g.S;
   // gathered columns: in a query tile of the pattern region the ordinary tiles hold the diagonal part only
   const bool split = gidx != nullptr && i0 >= g.L;
-  // (the first 64 gathered tiles' first and last columns are fetched here: a load issued behind the stores below waits for
-  // them. Slots past the count hold -1.)
-  int n_cols = 0, g_first = -1, g_last = -1;
+  const int n_cols = columns.n_cols, g_first = columns.first, g_last = columns.last;
   const int *gi = split ? gidx + (int64_t)h * gstride : nullptr;
-  if (split) {
-    n_cols = gcnt[h];
-    if ((lane + 1) * g.tile_n <= gstride) {
-      g_first = gi[lane * g.tile_n];
-      g_last = gi[lane * g.tile_n + g.tile_n - 1];
-    }
-  }
   const uint64_t *cbw = split ? nullptr : cb;
-  const uint64_t *ca = col_any + (int64_t)h * g.occw, *cf = col_all + (int64_t)h * g.occw;
-  const uint64_t *da = off_any + (int64_t)h * g.occw, *df = off_all + (int64_t)h * g.occw;
+  const uint64_t *ca = classes + kColAny * g.occw, *cf = classes + kColAll * g.occw;
+  const uint64_t *da = classes + kOffAny * g.occw, *df = classes + kOffAll * g.occw;
   const int words = g.tile_m * g.wpr;
-  const bool inner = i0 + g.tile_m <= min(g.L, g.S) && words <= 256;  // (words: 64 per lane and step, 4 steps)
+  const bool inner = TRUE_BLOCK && i0 + g.tile_m <= min(g.L, g.S) && words <= 256;  // (words: 64 per lane and step, 4 steps)
   // This lane's words of a tile, divided by a multiplication (four divisions by a variable cost every wave of the launch
   // about a microsecond, also where it looks at no tile of the true-mask block): a row has 1 to 4 words, x is below 256.
   const int inv_wpr = g.wpr == 1 ? 65537 : g.wpr == 2 ? 32769 : g.wpr == 3 ? 21846 : 16385;
@@ -1320,15 +1365,13 @@ struct ScanArgs {
 };
 __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, ScanArgs scan, const uint8_t *__restrict__ diag_flag,
                                                        const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
-                                                       uint64_t *__restrict__ rrev, bool classes,
-                                                       uint64_t *__restrict__ col_any, uint64_t *__restrict__ col_all,
-                                                       uint64_t *__restrict__ off_any, uint64_t *__restrict__ off_all,
+                                                       uint64_t *__restrict__ rrev, bool want_classes, uint64_t *__restrict__ classes,
                                                        int gstride, int *__restrict__ gidx, int *__restrict__ gcnt,
                                                        int *__restrict__ head_cnt, bool in_lds) {
-  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw]
+  extern __shared__ uint64_t prep_sets[];  // in_lds: the head's two sets, [2 pw], and its class words, [4 occw]
   const int h = blockIdx.x;
   if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
-  uint64_t *copy = in_lds && classes ? prep_sets : nullptr;
+  uint64_t *copy = in_lds && want_classes ? prep_sets : nullptr;
   if (ca.true_bits) {  // uniform over the grid
     __shared__ int cnt[2 * kDirectAloneL];
     count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
@@ -1338,15 +1381,16 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   } else {
     pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
   }
-  if (!classes) return;  // uniform over the grid
+  if (!want_classes) return;  // uniform over the grid
   __syncthreads();       // the sets are read back by other threads of this workgroup
   // (from the LDS copy when they fit: the steps below are chains of dependent reads. One call per address space,
   // so that the compiler knows which kind of read to use.)
+  uint64_t *classes_h = classes + (int64_t)h * 4 * g.occw;
   if (in_lds) {
-    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, h, col_any, col_all, off_any, off_all);
+    tile_classes_of_head(g, prep_sets, prep_sets + g.pw, classes_h, prep_sets + 2 * g.pw);
     if (gidx) gather_columns_of_head(g, prep_sets, gstride, h, gidx, gcnt);
   } else {
-    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, h, col_any, col_all, off_any, off_all);
+    tile_classes_of_head(g, cbits + (int64_t)h * g.pw, rrev + (int64_t)h * g.pw, classes_h, nullptr);
     if (gidx) gather_columns_of_head(g, cbits + (int64_t)h * g.pw, gstride, h, gidx, gcnt);
   }
   if (!scan.on) return;  // uniform over the grid
@@ -1355,8 +1399,8 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   const uint64_t *tb = scan.true_bits ? scan.true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   int mine = 0;
   for (int qt = wave; qt < g.nQt; qt += blockDim.x >> 6)
-    mine += tile_scan_row(g, tb, prep_sets, prep_sets + g.pw, col_any, col_all, off_any, off_all, scan.occ, scan.full, scan.cnt, gidx, gcnt,
-                          gstride, scan.vocc, scan.vfull, h, qt, lane);
+    mine += tile_scan_row<true>(g, tb, prep_sets, prep_sets + g.pw, prep_sets + 2 * g.pw, scan.occ, scan.full, scan.cnt, gidx,
+                          fetch_columns(g, gidx, gcnt, gstride, h, qt, lane), gstride, scan.vocc, scan.vfull, h, qt, lane);
   if (lane == 0) head_cnt[h * kHeadSub + wave] = mine;
 }
 
@@ -1453,15 +1497,13 @@ __device__ __forceinline__ QueryTiles my_query_tiles(const Geom &g, int each, bo
 // counts of the query tiles before its own. (Folding a scan into the last workgroup to finish was measured and
 // dropped: it needs a device-wide release fence in every workgroup, which on this chip writes back the L2 of its
 // XCD each time: 20 -> 190 us at S = 32768.)
+template <bool TRUE_BLOCK, bool STAGED>
 __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__restrict__ true_bits,
                                                    const uint64_t *__restrict__ cbits,
                                                    const uint64_t *__restrict__ rrev,
-                                                   const uint64_t *__restrict__ col_any,
-                                                   const uint64_t *__restrict__ col_all,
-                                                   const uint64_t *__restrict__ off_any,
-                                                   const uint64_t *__restrict__ off_all,
+                                                   const uint64_t *__restrict__ classes,
                                                    uint64_t *__restrict__ occ,
-                                                   uint64_t *__restrict__ full, int *__restrict__ cnt, bool staged,
+                                                   uint64_t *__restrict__ full, int *__restrict__ cnt,
                                                    const int *__restrict__ gidx, const int *__restrict__ gcnt,
                                                    int gstride, uint64_t *__restrict__ vocc,
                                                    uint64_t *__restrict__ vfull, int *__restrict__ head_cnt) {
@@ -1473,20 +1515,21 @@ __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__res
   const uint64_t *tb = true_bits ? true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   const uint64_t *cb = cbits + (int64_t)h * g.pw;
   const uint64_t *rr = rrev + (int64_t)h * g.pw;
+  const uint64_t *classes_h = classes + (int64_t)h * 4 * g.occw;
   int mine = 0;
-  if (staged) {  // uniform over the grid
-    stage_sets(lds_sets, g.pw, cb, rr);
+  const RowColumns columns = fetch_columns(g, gidx, gcnt, gstride, h, min(qt, g.nQt - 1), lane);
+  if constexpr (STAGED) {
+    stage_sets(lds_sets, g.pw, cb, rr, classes_h, 4 * g.occw);
     if (qt < g.nQt)
-      mine = tile_scan_row(g, tb, lds_sets, lds_sets + g.pw + kGuardFront, col_any, col_all, off_any, off_all, occ, full, cnt, gidx, gcnt,
-                           gstride, vocc, vfull, h, qt, lane);
+      mine = tile_scan_row<TRUE_BLOCK>(g, tb, lds_sets, lds_sets + g.pw + kGuardFront, lds_sets + 2 * g.pw + kGuardFront + kGuardBack, occ, full, cnt,
+                           gidx, columns, gstride, vocc, vfull, h, qt, lane);
   } else if (qt < g.nQt) {
-    mine = tile_scan_row(g, tb, cb, rr, col_any, col_all, off_any, off_all, occ, full, cnt, gidx, gcnt, gstride, vocc, vfull, h,
-                         qt, lane);
+    mine = tile_scan_row<TRUE_BLOCK>(g, tb, cb, rr, classes_h, occ, full, cnt, gidx, columns, gstride, vocc, vfull, h, qt, lane);
   }
   // the head's total, for the offsets that the fill kernel derives itself (plain atomics, read by the next kernel
   // only; spread over kHeadSub words per head, because atomics on one address are served one after the other)
   if (lane == 0) wave_cnt[wave] = mine;
-  __syncthreads();
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (not the library's barrier, which waits for the stores above)
   if (threadIdx.x == 0)
     atomicAdd(head_cnt + h * kHeadSub + (my.at & (kHeadSub - 1)), wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3]);
 }
@@ -1510,7 +1553,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
                                                    bool skip_full_bits,
                                                    const int *__restrict__ gidx, const int *__restrict__ gcnt,
                                                    int gstride, const uint64_t *__restrict__ vocc,
-                                                   const uint64_t *__restrict__ vfull, const uint64_t *__restrict__ off_any,
+                                                   const uint64_t *__restrict__ vfull, const uint64_t *__restrict__ classes,
                                                    int share) {
   extern __shared__ uint64_t lds_sets[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1529,29 +1572,23 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   // where this query tile's entries start: the listed tiles of the heads before h and of the query tiles before
   // qt (no scan kernel between the two passes: the counts are few enough for every wave to add up its own prefix)
   int64_t part = 0;
-  // (eight loads in flight where there are many counts, one by one 1024 query tiles were 16 waits; and in whole batches: a test
-  // per load, eight of them for 97 counts too, was up to 4 % of the kernel. 64 heads x 128k tokens captured at 512, whole
-  // build 280 -> 267 us, 128 heads x 4096 tokens of patterns 44.7 -> 40.6, 32 x 12345 in the plain layout 94.5 -> 93.0)
-  auto add_up = [&](const int *p, int n) {
-    int x0 = 0;
-    auto batch = [&](auto k) {  // whole ones, so that no lane is asked
-      constexpr int K = decltype(k)::value;
-      for (; x0 + 64 * K <= n; x0 += 64 * K) {
-        int v[K];
-#pragma unroll
-        for (int y = 0; y < K; ++y) v[y] = p[x0 + 64 * y + lane];
-#pragma unroll
-        for (int y = 0; y < K; ++y) part += v[y];
-      }
-    };
-    batch(std::integral_constant<int, 8>{});
-    batch(std::integral_constant<int, 4>{});
-    batch(std::integral_constant<int, 1>{});
-    if (x0 + lane < n) part += p[x0 + lane];
-  };
-  add_up(head_cnt, h * kHeadSub);
+  // (Both as one list, in batches of loads that travel together, the last of them with the places past the end repeated and
+  // left out: one trip for up to 512 counts. In whole batches of eight, four and one and each list by itself the waits were up
+  // to nine, at 32 heads x 32 query tiles 2.6 us of the kernel's 11.)
+  const int n_head = h * kHeadSub, n_before = n_head + qt;
   const int *cnt_h = tile_cnt + (int64_t)h * g.nQt;
-  add_up(cnt_h, qt);
+  auto count_at = [&](int x) { return x < n_head ? head_cnt + x : cnt_h + (x - n_head); };
+  auto batch = [&](int x0, auto k) {
+    constexpr int K = decltype(k)::value;
+    int v[K];
+#pragma unroll
+    for (int y = 0; y < K; ++y) v[y] = *count_at(min(x0 + 64 * y + lane, n_before - 1));
+#pragma unroll
+    for (int y = 0; y < K; ++y) part += x0 + 64 * y + lane < n_before ? v[y] : 0;
+  };
+  int x0 = 0;
+  for (; x0 + 128 < n_before; x0 += 512) batch(x0, std::integral_constant<int, 8>{});
+  if (x0 < n_before) batch(x0, std::integral_constant<int, 2>{});
   const int my_cnt = cnt_h[qt];
   // the walk's index words, a word of 64 tiles per lane, the first 64 of them before the sets are staged
   uint64_t ow_mine = lane < n_words ? oc[lane] : 0, fw_mine = lane < n_words ? fl[lane] : 0;
@@ -1564,7 +1601,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   // no matched diagonal lies beyond r_bound (as in tile_scan_row)
   int64_t r_bound = INT64_MAX;
   if (split && g.tile_m == g.tile_n && (qt + 1) * g.tile_m <= g.S)
-    r_bound = farthest_tile(off_any + (int64_t)h * g.occw, g.occw, lane) * g.tile_n + g.tile_n - 1;
+    r_bound = farthest_tile(classes + ((int64_t)h * 4 + kOffAny) * g.occw, g.occw, lane) * g.tile_n + g.tile_n - 1;
   const uint64_t vow0 = split ? voc[0] : 0, vfw0 = split ? vfl[0] : 0;  // (not written where there is no gathered tile)
   if (STAGED) stage_sets(lds_sets, g.pw, cb, rr);
   if (!live) return;
@@ -2224,7 +2261,7 @@ struct Workspace {
   TransformStats *stats;
   uint64_t *vslices, *dslices;
   uint8_t *diag_flag, *vert_flag;
-  uint64_t *cbits, *rrev, *occ, *full, *col_any, *col_all, *off_any, *off_all, *vocc, *vfull;
+  uint64_t *cbits, *rrev, *occ, *full, *classes, *vocc, *vfull;
   int *tile_cnt, *head_cnt, *row_cnt, *group_first;
   size_t bytes;
 };
@@ -2279,10 +2316,7 @@ Workspace carve(const dam_mask_params *p, void *ws) {
   w.vert_flag = c.take<uint8_t>(HL);
   w.cbits = c.take<uint64_t>((size_t)g.H * g.pw);
   w.rrev = c.take<uint64_t>((size_t)g.H * g.pw);
-  w.col_any = c.take<uint64_t>((size_t)g.H * g.occw);
-  w.col_all = c.take<uint64_t>((size_t)g.H * g.occw);
-  w.off_any = c.take<uint64_t>((size_t)g.H * g.occw);
-  w.off_all = c.take<uint64_t>((size_t)g.H * g.occw);
+  w.classes = c.take<uint64_t>((size_t)g.H * 4 * g.occw);
   w.occ = c.take<uint64_t>((size_t)g.H * g.nQt * g.occw);
   w.full = c.take<uint64_t>((size_t)g.H * g.nQt * g.occw);
   const bool gather = (p->flags & DAM_MASK_GATHER_COLUMNS) != 0;
@@ -2361,7 +2395,10 @@ bool needs_prep(const dam_mask_params *p, const dam_mask_out *o) {
 }
 
 // Whether k_pattern_prep scans the tiles too: sets in LDS, and few query tiles for a wave to take.
-size_t prep_lds_bytes(const Geom &g) { return (size_t)g.pw * 16 <= kMaxStagedBytes ? (size_t)g.pw * 16 : 0; }
+size_t prep_lds_bytes(const Geom &g) {
+  const size_t sets = (size_t)g.pw * 16, all = sets + class_bytes(g);
+  return sets <= kMaxStagedBytes && all <= kMaxWithClasses ? all : 0;
+}
 bool scans_in_prep(const Geom &g, const dam_mask_out *o, bool gather) {
   return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= (g.L > 0 || gather || g.S % g.tile_m == 0 ? kScanInPrep : kScanRaggedInPrep);
 }
@@ -2413,8 +2450,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   if (needs_prep(p, o) || count.true_bits) {
     const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
     const ScanArgs scan{scans_in_prep(g, o, gather), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
-    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.col_any, w.col_all, w.off_any,
-                                                   w.off_all, gstride, gather ? o->gather_idx : nullptr,
+    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.classes, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
   // a4 + a5: tile occupancy, CSR offsets, tile bits
@@ -2425,10 +2461,12 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       const TurnGrid t = turn_grid((int64_t)((g.nQt + each - 1) / each) * g.H);
       return dim3(t.x, t.y);
     };
-    if (!scans_in_prep(g, o, gather))
-      k_tile_scan<<<grid_of(4), 256, lds_sets, stream>>>(g, true_bits, w.cbits, w.rrev, w.col_any, w.col_all, w.off_any,
-                                                                     w.off_all, w.occ, w.full, w.tile_cnt, lds_sets > 0, gidx,
-                                                                     gcnt, gstride, w.vocc, w.vfull, w.head_cnt);
+    if (!scans_in_prep(g, o, gather)) {
+      const size_t lds = lds_sets > 0 && lds_sets + class_bytes(g) <= kMaxWithClasses ? lds_sets + class_bytes(g) : 0;
+      auto scan = g.L > 0 ? (lds > 0 ? k_tile_scan<true, true> : k_tile_scan<true, false>)
+                          : (lds > 0 ? k_tile_scan<false, true> : k_tile_scan<false, false>);
+      scan<<<grid_of(4), 256, lds, stream>>>(g, true_bits, w.cbits, w.rrev, w.classes, w.occ, w.full, w.tile_cnt, gidx, gcnt, gstride, w.vocc, w.vfull, w.head_cnt);
+    }
     if (fill) {
       // (the CSR offsets come out of the fill kernel: no scan launch between the two passes)
       const int share = (int64_t)g.H * g.nQt >= 2048 ? 1 : 4;  // enough query tiles to give every wave its own
@@ -2437,11 +2475,11 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       if (lds_sets > 0)
         k_tile_fill<true><<<fill_grid, 256, lds_sets, stream>>>(
             g, true_bits, w.cbits, w.rrev, w.occ, w.full, w.tile_cnt, w.head_cnt, o->blk_row_ptr, o->blk_total, o->blk_col,
-            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.off_any, share);
+            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.classes, share);
       else
         k_tile_fill<false><<<fill_grid, 256, 0, stream>>>(
             g, true_bits, w.cbits, w.rrev, w.occ, w.full, w.tile_cnt, w.head_cnt, o->blk_row_ptr, o->blk_total, o->blk_col,
-            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.off_any, share);
+            o->blk_kind, o->tile_bits, o->blk_capacity, skip_full, gidx, gcnt, gstride, w.vocc, w.vfull, w.classes, share);
     } else {  // the sizing call: offsets and total only
       k_exclusive_scan<<<1, 1024, 0, stream>>>(w.tile_cnt, (int64_t)g.H * g.nQt, g.nQt, o->blk_row_ptr, o->blk_total, INT64_MAX);
     }
