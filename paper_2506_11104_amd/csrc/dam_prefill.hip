@@ -67,11 +67,13 @@ struct AttnArgs {
 // Both products keep a lane on one query (lane % 16): S^T = K Q^T leaves key 4 (lane / 16) + r in accumulator r, and
 // that is the B operand of step r of O^T += V^T P^T when the lanes of group g fetch V row 4 g + r, so P stays in
 // registers. The dims are dealt out so that every operand is a 16-byte load straight from memory in the product's
-// layout: K and Q lane (row, g) holds dims 16 c + 4 g .. + 3 of chunk c, V lane m dims 64 h + 4 m .. + 3. The V rows of
-// a block are fetched before its Q K products, the K rows of the next one too.
-// Bound by the latency of a block's loads: the matrix rate (64 flop per cycle and SIMD) is used to about 27 % on the blocks
-// that are issued, each of which brings 16 KiB of K and V from L2 however few of its entries are kept. 2 sequences x 8
-// heads x 1500 keys, d 128, windows and stripes (46 % of the issued entries kept): 391 -> 60 us against a row per d / 4
+// layout: K and Q lane (row, g) holds dims 16 c + 4 g .. + 3 of chunk c, V lane m dims 64 h + 4 m .. + 3. What an iteration
+// has used of its block's K and V rows is replaced at once by that part of the wave's next block.
+// A wave has three blocks on average in the size below, so the time is as much the list in front of them (4 us, a chain of
+// loads) and the first block's loads as the products: the matrix rate (64 flop per cycle and SIMD) is used to about 30 % on the
+// blocks that are issued, each of which brings 16 KiB of K and V from L2 however few of its entries are kept. 2 sequences x 8
+// heads x 1500 keys, d 128, windows and stripes (46 % of the issued entries kept) 51.5 us, 55.7 with V fetched in front of its
+// own block's Q K products; 4 x 16 heads x 2000 351 -> 336, d 64 186 -> 183; 1 x 4 x 300 12.8 -> 11.7. With the older form: 391 -> 60 us against a row per d / 4
 // plain lanes, each visiting its kept keys only (Q in LDS for a third workgroup per CU spilled: 154 us). At the same size
 // a window of 64 101 -> 34 us; where nothing but isolated diagonals is kept (9 to 14 entries per block) the plain lanes
 // were faster, 1 % of the diagonals 50 -> 63 us, 4 % 92 -> 114, 10 % 176 -> 130.
@@ -172,11 +174,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
     __syncthreads();
     // ---- the block list: every wave adds up the same prefix, wave 0 writes
     unsigned occ = lane < n_seg ? L.occ[lane] : 0u;
-    int at = __popc(occ);
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(at, off);
-      if (lane >= off) at += up;
-    }
+    int at = wave_prefix(__popc(occ));
     const int n_blk = __builtin_amdgcn_readlane(at, 63);
     if (wave == 0)
       for (at -= __popc(occ); occ; occ &= occ - 1) L.blk[at++] = (unsigned short)(lane * 8 + __builtin_ctz(occ));
@@ -192,22 +190,22 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
       }
       return min(max(j, 0), a.S - 1);
     };
-    auto load_k = [&](float4 (&kf)[CK], int e) {  // lane's row of the block: r16, dims 16 c + 4 g
-      const int blk = __builtin_amdgcn_readfirstlane(L.blk[e]);
-      const float *kp = kb + key_row(blk >> 3, (blk & 7) * 16 + r16) * a.k_ss;
+    // A block's K and V rows sit in registers; where an iteration has used a part of them it fetches that part of the wave's
+    // next block, a whole iteration ahead of its use.
+    float4 kf[CK], vf[4][HV];  // K row r16, dims 16 c + 4 g; V row 4 g + s, dims 64 h + 4 r16
+    const float *kp, *vp[4];
+    auto find_rows = [&](int e) {  // the rows of block e; returns its entry
+      const int blk = __builtin_amdgcn_readfirstlane(L.blk[e]), x = blk >> 3, s0 = (blk & 7) * 16;
+      kp = kb + key_row(x, s0 + r16) * a.k_ss;
 #pragma unroll
-      for (int c = 0; c < CK; ++c) kf[c] = *reinterpret_cast<const float4 *>(kp + 16 * c);
+      for (int s = 0; s < 4; ++s) vp[s] = vb + key_row(x, s0 + 4 * g + s) * a.v_ss + 4 * r16;
+      return blk;
     };
-    auto compute = [&](const float4 (&kf)[CK], float4 (&k_next)[CK], int e) {
-      const int blk = __builtin_amdgcn_readfirstlane(L.blk[e]), x = blk >> 3, b16 = blk & 7;
-      float4 vf[4][HV];  // V row 4 g + s, dims 64 h + 4 r16
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const float *vp = vb + key_row(x, b16 * 16 + 4 * g + s) * a.v_ss + 4 * r16;
-#pragma unroll
-        for (int h = 0; h < HV; ++h) vf[s][h] = *reinterpret_cast<const float4 *>(vp + 64 * h);
-      }
-      if (e + 4 < n_blk) load_k(k_next, e + 4);
+    auto take = [](const float *at) { return *reinterpret_cast<const float4 *>(at); };
+    // more: there is a next block, whose rows find_rows has found
+    auto compute = [&](int blk, auto more) {
+      constexpr bool MORE = decltype(more)::value;
+      const int x = blk >> 3, b16 = blk & 7;
       const unsigned kept = L.words[x][(b16 >> 1) * 16 + r16] >> (16 * (b16 & 1));  // low 16 bits: the block's keys
       any |= kept & 0xFFFFu;
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: a product's result is ready only after the next has started
@@ -217,6 +215,10 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
         s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].y, qf[c].y, s1, 0, 0, 0);
         s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].z, qf[c].z, s0, 0, 0, 0);
         s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c].w, qf[c].w, s1, 0, 0, 0);
+        if (MORE) {
+          kf[c] = take(kp + 16 * c);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       float p[4], mx = m, odd = 0.0f;
 #pragma unroll
@@ -224,8 +226,12 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
         p[r] = (kept >> (4 * g + r)) & 1 ? (s0[r] + s1[r]) * a.scale : -INFINITY;
         mx = fmaxf(mx, p[r]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      {  // the maximum of the row's four lanes: the rows of 16 lanes in pairs, then the halves of the wave
+        u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      }
       if (__ballot(mx > m)) {
         const float corr = mx > m ? expf(m - mx) : 1.0f;  // m = -inf: 0
         l *= corr;
@@ -253,6 +259,10 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
             o[4 * h + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].y, p[s], o[4 * h + 1], 0, 0, 0);
             o[4 * h + 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].z, p[s], o[4 * h + 2], 0, 0, 0);
             o[4 * h + 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][h].w, p[s], o[4 * h + 3], 0, 0, 0);
+            if (MORE) {
+              vf[s][h] = take(vp[s] + 64 * h);
+              __builtin_amdgcn_sched_barrier(0);
+            }
           }
       } else {
         // a V row of the block holds an infinity or a NaN: it must reach the rows that keep that key and no others
@@ -260,28 +270,41 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
 #pragma unroll 1
         for (int key = 0; key < 16; ++key) {
           const float pk = __shfl(key & 2 ? (key & 1 ? p[3] : p[2]) : (key & 1 ? p[1] : p[0]), r16 + 16 * (key >> 2));
-          const float *vp = vb + key_row(x, b16 * 16 + key) * a.v_ss + 16 * g;
+          const float *at = vb + key_row(x, b16 * 16 + key) * a.v_ss + 16 * g;
           if (!((kept >> key) & 1)) continue;
 #pragma unroll
           for (int h = 0; h < HV; ++h)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const float4 vv = *reinterpret_cast<const float4 *>(vp + 64 * h + 4 * r);
+              const float4 vv = *reinterpret_cast<const float4 *>(at + 64 * h + 4 * r);
               o[4 * h + 0][r] = fmaf(pk, vv.x, o[4 * h + 0][r]);
               o[4 * h + 1][r] = fmaf(pk, vv.y, o[4 * h + 1][r]);
               o[4 * h + 2][r] = fmaf(pk, vv.z, o[4 * h + 2][r]);
               o[4 * h + 3][r] = fmaf(pk, vv.w, o[4 * h + 3][r]);
             }
         }
+        if (MORE) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int h = 0; h < HV; ++h) vf[s][h] = take(vp[s] + 64 * h);
+        }
       }
     };
-    float4 ka[CK], kc[CK];
-    int e = wave;
-    if (e < n_blk) load_k(ka, e);
-    for (; e < n_blk; e += 8) {
-      compute(ka, kc, e);
-      if (e + 4 >= n_blk) break;
-      compute(kc, ka, e + 4);
+    if (wave < n_blk) {
+      int e = wave, blk = find_rows(e);
+#pragma unroll
+      for (int c = 0; c < CK; ++c) kf[c] = take(kp + 16 * c);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int h = 0; h < HV; ++h) vf[s][h] = take(vp[s] + 64 * h);
+      for (; e + 4 < n_blk; e += 4) {
+        const int next = find_rows(e + 4);
+        compute(blk, std::true_type{});
+        blk = next;
+      }
+      compute(blk, std::false_type{});
     }
   }
 
