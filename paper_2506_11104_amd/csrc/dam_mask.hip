@@ -752,52 +752,20 @@ __device__ __forceinline__ bool range_any(const uint64_t *__restrict__ bs, int n
   return false;
 }
 
-// Every bit set among positions [lo, hi] (all inside the bitset).
-__device__ __forceinline__ bool range_all(const uint64_t *__restrict__ bs, int64_t lo, int64_t hi) {
-  for (int64_t w = lo >> 6; w <= (hi >> 6); ++w) {
-    uint64_t need = ~0ull;
-    if (w == (lo >> 6)) need &= ~0ull << (lo & 63);
-    if (w == (hi >> 6)) need &= ~0ull >> (63 - (hi & 63));
-    if ((bs[w] & need) != need) return false;
-  }
-  return true;
+// A tile strictly below the diagonal and outside the true-mask block holds only pattern entries:
+// (i, j) is kept iff column j is matched or offset i - j is. Rows [i0, i1], columns [j0, j1]: some column of the tile is matched,
+// or some offset in [i0 - j1, i1 - j0] is. (cb == nullptr: no columns.)
+__device__ __forceinline__ bool pattern_tile_any(const uint64_t *__restrict__ cb, const uint64_t *__restrict__ rr, int pw, int i0, int i1,
+                                                 int j0, int j1) {
+  const int64_t Q = (int64_t)pw * 64 - 1;  // offset u sits at position Q - u of the reversed set
+  return (cb && range_any(cb, pw, j0, j1)) || range_any(rr, pw, Q - (i1 - j0), Q - (i0 - j1));
 }
 
-// A tile strictly below the diagonal and outside the true-mask block holds only pattern entries:
-// (i, j) is kept iff column j is matched or offset i - j is. Rows [i0, i1], columns [j0, j1].
-//   any:  some column of the tile is matched, or some offset in [i0 - j1, i1 - j0] is;
-//   full: every offset of that range is matched, or every column is, or every unmatched offset u
-//         ("hole") only meets matched columns: columns [max(j0, i0 - u), min(j1, i1 - u)].
-// Both are decided by one lane from a handful of bitset words. Returns bit0 any, bit1 full.
-__device__ int pattern_tile_flags(const uint64_t *__restrict__ cb, const uint64_t *__restrict__ rr, int pw,
-                                  int i0, int i1, int j0, int j1) {
-  const int64_t Q = (int64_t)pw * 64 - 1;  // offset u sits at position Q - u of the reversed set
-  const int a = i0 - j1, b = i1 - j0;      // offsets met by the tile, 0 <= a <= b
-  const bool cols_in = cb && j0 <= Q;      // columns past the bitset are never matched; cb == nullptr: no columns
-  const int jc1 = (int)min((int64_t)j1, Q);
-  const bool any_c = cols_in && range_any(cb, pw, j0, jc1);
-  const bool any_r = range_any(rr, pw, Q - b, Q - a);
-  if (!any_c && !any_r) return 0;
-  if (cols_in && j1 <= Q && range_all(cb, j0, j1)) return 3;
-  // holes: offsets of [a, b] that are not matched (those past the bitset are all holes)
-  bool full = true;
-  if (b > Q) {  // offsets Q+1 .. b: their entries lie in columns [max(j0, i0 - b), min(j1, i1 - (Q + 1))]
-    const int64_t lo = max((int64_t)j0, (int64_t)i0 - b), hi = min((int64_t)j1, (int64_t)i1 - (Q + 1));
-    if (lo <= hi) full = cb && hi <= Q && range_all(cb, lo, hi);
-  }
-  const int64_t p_lo = max(Q - b, (int64_t)0), p_hi = Q - a;
-  for (int64_t w = p_lo >> 6; full && w <= (p_hi >> 6); ++w) {
-    uint64_t holes = ~rr[w];
-    if (w == (p_lo >> 6)) holes &= ~0ull << (p_lo & 63);
-    if (w == (p_hi >> 6)) holes &= ~0ull >> (63 - (p_hi & 63));
-    while (holes && full) {
-      const int64_t u = Q - (w * 64 + (__ffsll((unsigned long long)holes) - 1));
-      holes &= holes - 1;
-      const int64_t lo = max((int64_t)j0, (int64_t)i0 - u), hi = min((int64_t)j1, (int64_t)i1 - u);
-      if (lo <= hi) full = cb && hi <= Q && range_all(cb, lo, hi);
-    }
-  }
-  return full ? 3 : 1;
+// Every entry of row i in the words [w0, w0 + W) is kept, the columns' part as above.
+__device__ __forceinline__ bool pattern_row_full(const uint64_t *__restrict__ cb, const uint64_t *__restrict__ rr, int pw, int i, int w0, int W) {
+  uint64_t all = ~0ull;
+  for (int w = w0; w < w0 + W; ++w) all &= (cb ? set_word(cb, w, pw) : 0) | diag_window(rr, pw, (int64_t)i - (int64_t)w * 64);
+  return all == ~0ull;
 }
 
 // Classes of whole tiles for square tiles of width T, per head (pattern region, tile strictly below
@@ -1135,7 +1103,7 @@ __device__ __forceinline__ int64_t farthest_tile(const uint64_t *__restrict__ of
 // Pass 1 of the block index: which key tiles of query tile (h, qt) hold a kept entry / are full.
 // One wave per query tile, 64 key tiles (one occupancy word) at a time, one lane per key tile. Tiles
 // strictly below the diagonal and outside the true-mask block are decided by their lane alone (from
-// the class bitsets, or by pattern_tile_flags), and so is the diagonal tile of a query tile that lies wholly in the pattern
+// the class bitsets, or from its first and last row), and so is the diagonal tile of a query tile that lies wholly in the pattern
 // region (square tiles); the other tiles on the diagonal and those inside the true-mask block are then evaluated word by word
 // by the whole wave. No LDS, no barrier.
 // (What a row needs of the gathered columns, fetched in front of everything else: a load issued behind the stores below waits for
@@ -1228,9 +1196,15 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
             }
           }
           if (exact) {
-            f = pattern_tile_flags(cbw, rr, g.pw, i0, i_last, j0, j1);
-            // a tile cut by the end of the sequence is never full (its bits past S are zero)
-            if (j0 + g.tile_n > g.S || i0 + g.tile_m > g.S) f &= 1;
+            f = pattern_tile_any(cbw, rr, g.pw, i0, i_last, j0, j1) ? 1 : 0;
+            // Full only if its first and its last row are, which few are: those are evaluated by the whole wave. (A tile cut
+            // by the end of the sequence never is, its bits past S are zero.) A lane that went through the unmatched offsets
+            // itself, each with the columns it meets, held the wave for as long as the longest took: 6 heads x 1000 tokens,
+            // captured at 256, in the plain layout, whole layer 50.9 -> 36.5 us; builds of 32 heads of patterns there, 1024 tokens 29.7 ->
+            // 14.3, 8000 57.4 -> 36.5, 32768 140 -> 121.
+            if (f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S && pattern_row_full(cbw, rr, g.pw, i0, kt * g.wpr, g.wpr) &&
+                pattern_row_full(cbw, rr, g.pw, i_last, kt * g.wpr, g.wpr))
+              f = 4;
           }
         } else if (by_class && kt == qt) {
           // the diagonal tile of a row of the pattern region, never full: it meets the offsets 0 .. T - 1, each in its last
