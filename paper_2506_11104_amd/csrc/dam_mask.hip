@@ -28,13 +28,11 @@ using namespace dam;
 // 256 threads); each takes several items in turn.
 constexpr int kGridTarget = 4096;
 constexpr int kHeadSub = 16;  // partial sums per head of the listed-tile counts
-// Query tiles of a head up to which k_pattern_prep scans them itself, a wave each, and the scan launch is saved. Whole builds,
-// launch / this, us: 2 heads x 4 tiles 17.8 / 16.9, 32 x 8 (capture of 256) 30.4 / 28.0, 64 x 8 35.9 / 32.7, 32 x 8 from patterns
-// 29.3 / 27.6; 32 x 16 29.0 / 29.8 (a wave per tile still, but on one CU per head), 32 x 32 31.7 / 38.3. Patterns alone in the
-// plain layout have tiles of columns and diagonals both, which keep a lane busy, and a ragged last row of nothing else: there the
-// line lies lower. 32 heads x 7 tiles (ragged) 25.7 / 24.5, x 8 (1000 tokens) 37.5 / 39.9, x 8 (1024) 33.4 / 33.9, 8 x 8 (1000)
-// 36.2 / 37.3, (1024) 31.0 / 29.5; in the gathered layout 32 x 8 (1000) 28.6 / 27.2.
-constexpr int kScanInPrep = 8, kScanRaggedInPrep = 7;
+// Query tiles of a head up to which k_pattern_prep scans them itself, a wave each, and the scan launch is saved. Whole layers,
+// launch / this, us: 2 fp32 heads x 4 tiles 23.6 / 22.1, 8 x 10 37.4 / 35.1, 6 x 16 36.5 / 34.6, 32 heads x 16 (2048 tokens of
+// patterns) 53.7 / 52.8, 64 x 16 (captured at 256) 67.8 / 66.8; builds in the plain layout 32 x 8 (1000 tokens) 18.9 / 17.2, 32 x 16
+// 22.4 / 21.9. Two tiles per wave, on one CU per head: 32 x 32 (captured at 1024) 103.8 / 107.0, builds 8 x 32 21.2 / 25.9.
+constexpr int kScanInPrep = 16;
 
 struct Geom {
   int H, L, S, P;            // P: length of the pattern flag arrays (L from a map, S when given)
@@ -2373,9 +2371,7 @@ size_t prep_lds_bytes(const Geom &g) {
   const size_t sets = (size_t)g.pw * 16, all = sets + class_bytes(g);
   return sets <= kMaxStagedBytes && all <= kMaxWithClasses ? all : 0;
 }
-bool scans_in_prep(const Geom &g, const dam_mask_out *o, bool gather) {
-  return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= (g.L > 0 || gather || g.S % g.tile_m == 0 ? kScanInPrep : kScanRaggedInPrep);
-}
+bool scans_in_prep(const Geom &g, const dam_mask_out *o) { return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= kScanInPrep; }
 
 // Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
 bool counts_in_prep(const dam_mask_params *p, const Geom &g, const dam_mask_out *o) {
@@ -2423,7 +2419,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
   if (needs_prep(p, o) || count.true_bits) {
     const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
-    const ScanArgs scan{scans_in_prep(g, o, gather), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
+    const ScanArgs scan{scans_in_prep(g, o), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
     k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.classes, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
@@ -2435,7 +2431,7 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       const TurnGrid t = turn_grid((int64_t)((g.nQt + each - 1) / each) * g.H);
       return dim3(t.x, t.y);
     };
-    if (!scans_in_prep(g, o, gather)) {
+    if (!scans_in_prep(g, o)) {
       const size_t lds = lds_sets > 0 && lds_sets + class_bytes(g) <= kMaxWithClasses ? lds_sets + class_bytes(g) : 0;
       auto scan = g.L > 0 ? (lds > 0 ? k_tile_scan<true, true> : k_tile_scan<true, false>)
                           : (lds > 0 ? k_tile_scan<false, true> : k_tile_scan<false, false>);
