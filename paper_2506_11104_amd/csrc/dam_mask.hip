@@ -314,10 +314,10 @@ __global__ void k_transform_threshold(int kind, float lambda, float eps, float t
 // The threshold key comes from the workspace (theta_key) or, when the host found it, by value (theta_key == nullptr:
 // theta_val, and bmin_val goes to the caller's bmin from here, this being the first kernel of the chain).
 struct Threshold {
-  const unsigned *theta_key;
-  unsigned theta_val;
-  float bmin_val;
-  float *bmin_out;
+  const unsigned *theta_key = nullptr;
+  unsigned theta_val = 0;
+  float bmin_val = 0.0f;
+  float *bmin_out = nullptr;
 };
 
 __device__ __forceinline__ unsigned take_threshold(const Threshold &t) {
@@ -945,14 +945,15 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
 // further where nothing follows the counts, so that the launches are two where this is one: 1 head x 832 17.8 / 17.1, 8 x 832
 // 19.8 / 18.9, 96 x 832 57.9 / 56.1, 96 x 769 60.6 / 58.9; 1 x 896 18.1 / 18.8, 32 x 896 30.4 / 31.6, 96 x 896 61.8 / 61.6.
 constexpr int kDirectL = 768, kDirectAloneL = 832;
+template <int MOST>
 __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
-                                                       float mu, int h, int *cnt,                       // LDS [2][kDirectAloneL]
+                                                       float mu, int h, int *cnt,                       // LDS [2][MOST]
                                                        int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
                                                        uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,
                                                        uint64_t *__restrict__ cbits, uint64_t *__restrict__ rrev,
                                                        uint64_t *lds_copy) {  // both sets again, [2 pw], or nullptr
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-  for (int x = threadIdx.x; x < 2 * kDirectAloneL; x += blockDim.x) cnt[x] = 0;
+  for (int x = threadIdx.x; x < 2 * MOST; x += blockDim.x) cnt[x] = 0;
   __syncthreads();
   const bool diag = wave & 1;
   int chunk = 0, w = wave >> 1;  // the pair (chunk, word <= chunk) of this wave; both kinds take every n_waves / 2-th
@@ -975,7 +976,7 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
     // diagonals: the window of the row that ends at column i - 64 w, reversed: offset 64 w + t at bit t
     uint64_t x = hi;
     if (diag) x = __brevll(lane == 63 ? hi : (hi << (63 - lane)) | (lo >> (lane + 1)));
-    const int at = (diag ? kDirectAloneL : 0) + 64 * w + lane;
+    const int at = (diag ? MOST : 0) + 64 * w + lane;
     w += n_waves / 2;
     settle();
     if (chunk < g.tbw) fetch();
@@ -983,7 +984,7 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
   }
   __syncthreads();
   for (int x = wave; x < 2 * g.tbw; x += n_waves) {
-    const int word = x >> 1, p = 64 * word + lane, n = cnt[(x & 1) * kDirectAloneL + p];
+    const int word = x >> 1, p = 64 * word + lane, n = cnt[(x & 1) * MOST + p];
     const bool hit = p < g.L && (float)n / (float)(g.L - p) >= mu;
     const uint64_t set = __ballot(hit);
     const int64_t e = (int64_t)h * g.L + p;
@@ -1321,12 +1322,53 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
 // Everything the block index needs from the pattern flags of one head, in one launch (one workgroup of 1024
 // per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
 // the two bitsets, the tile classes, the gathered column list.
-struct CountArgs {  // true_bits: count the patterns here and write the flags; vslices: add up the chunks' counts; else the flags are given
-  const uint64_t *true_bits, *vslices, *dslices;
-  float mu;
-  int *vert_cnt, *diag_cnt;
-  uint8_t *vert_flag, *diag_flag;
+// SOURCE says where the flags come from: they are given; the patterns are counted here, from the true mask, or from the
+// attention map itself, whose true mask is made first; or the chunks' counts are added up.
+enum PrepSource { kFlagsGiven, kFromTrueBits, kFromMap, kFromSlices };
+struct CountArgs {
+  PrepSource source = kFlagsGiven;
+  const float *map = nullptr;  // kFromMap, with its threshold
+  Threshold thr{};
+  uint64_t *true_bits = nullptr;
+  const uint64_t *vslices = nullptr, *dslices = nullptr;
+  float mu = 0.0f;
+  int *vert_cnt = nullptr, *diag_cnt = nullptr;
+  uint8_t *vert_flag = nullptr, *diag_flag = nullptr;
 };
+
+// a2 of one short map by the 16 waves of its workgroup: a lane per key and a ballot per word, every word up to the diagonal
+// under way at once, into LDS (which the counts and the scan read) and from there, with the zero words above the diagonal, to
+// memory as whole lines. In place of a launch of k_true_mask_rows. The map is read by one CU per head, so the line is low; whole
+// layers, launch / this, us: 2 fp32 heads x 256 tokens captured at 64 22.2 / 19.7, 8 x 400 at 128 25.7 / 23.9, 8 x 600 at 192 34.8 /
+// 35.5, 6 x 1000 at 256 34.1 / 37.6 (64 x 2000 at 256 66.0 / 63.3).
+constexpr int kMapInPrep = 128;
+__device__ __forceinline__ void true_mask_of_head(const Geom &g, const float *__restrict__ map, unsigned theta, uint64_t *words,  // LDS
+                                                  uint64_t *__restrict__ true_bits) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kWords = kMapInPrep / 64;
+  float v[kWords][4 * kWords];
+  // word w of rows 64 w + wave + 16 k
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int w = 0; w < kWords; ++w)
+#pragma unroll
+      for (int k = 0; k < 4 * (kWords - w); ++k)
+        if (64 * w + wave + 16 * k < g.L) f(w, k, 64 * w + wave + 16 * k, 64 * w + lane);  // wave-uniform
+  };
+  each([&](int w, int k, int i, int j) { v[w][k] = map[(int64_t)i * g.L + min(j, i)]; });
+  each([&](int w, int k, int i, int j) {
+    const float x = v[w][k] != v[w][k] ? -INFINITY : v[w][k];
+    const uint64_t word = __ballot(j <= i && key_of(x) >= theta);
+    if (lane == 0) words[i * g.tbw + w] = word;
+  });
+  __syncthreads();
+  for (int x = threadIdx.x; x < g.L * g.tbw; x += blockDim.x) {
+    const int i = x / g.tbw, w = x - i * g.tbw;
+    const uint64_t word = 64 * w <= i ? words[x] : 0;
+    if (64 * w > i) words[x] = 0;  // (the scan reads them)
+    true_bits[x] = word;
+  }
+}
 // scan.on: and pass 1 of the block index (tile_scan_row, below as a kernel of its own), a wave per query tile, which saves that
 // launch where the query tiles of a head are few (see scans_in_prep).
 struct ScanArgs {
@@ -1335,6 +1377,7 @@ struct ScanArgs {
   int *cnt;
   const uint64_t *true_bits;
 };
+template <PrepSource SOURCE>
 __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, ScanArgs scan, const uint8_t *__restrict__ diag_flag,
                                                        const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
                                                        uint64_t *__restrict__ rrev, bool want_classes, uint64_t *__restrict__ classes,
@@ -1344,11 +1387,16 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   const int h = blockIdx.x;
   if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
   uint64_t *copy = in_lds && want_classes ? prep_sets : nullptr;
-  if (ca.true_bits) {  // uniform over the grid
-    __shared__ int cnt[2 * kDirectAloneL];
-    count_patterns_of_head(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
-                           ca.diag_flag, cbits, rrev, copy);
-  } else if (ca.vslices) {
+  __shared__ int cnt[SOURCE == kFromTrueBits ? 2 * kDirectAloneL : SOURCE == kFromMap ? 2 * kMapInPrep : 1];
+  __shared__ uint64_t true_words[SOURCE == kFromMap ? kMapInPrep * kMapInPrep / 64 : 1];
+  if constexpr (SOURCE == kFromTrueBits) {
+    count_patterns_of_head<kDirectAloneL>(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
+                                          ca.diag_flag, cbits, rrev, copy);
+  } else if constexpr (SOURCE == kFromMap) {
+    true_mask_of_head(g, ca.map + (int64_t)h * g.L * g.L, take_threshold(ca.thr), true_words, ca.true_bits + (int64_t)h * g.L * g.tbw);
+    __syncthreads();
+    count_patterns_of_head<kMapInPrep>(g, true_words, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag, ca.diag_flag, cbits, rrev, copy);
+  } else if constexpr (SOURCE == kFromSlices) {
     sum_slices_of_head(g, ca.vslices, ca.dslices, ca.mu, h, ca.vert_cnt, ca.diag_cnt, ca.vert_flag, ca.diag_flag, cbits, rrev, copy);
   } else {
     pattern_bitsets_of_head(diag_flag, vert_flag, g.P, g.pw, h, cbits, rrev, copy);
@@ -1368,7 +1416,7 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   if (!scan.on) return;  // uniform over the grid
   __syncthreads();  // classes and columns are read back by other threads of this workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t *tb = scan.true_bits ? scan.true_bits + (int64_t)h * g.L * g.tbw : nullptr;
+  const uint64_t *tb = SOURCE == kFromMap ? true_words : scan.true_bits ? scan.true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   int mine = 0;
   for (int qt = wave; qt < g.nQt; qt += blockDim.x >> 6)
     mine += tile_scan_row<true>(g, tb, prep_sets, prep_sets + g.pw, prep_sets + 2 * g.pw, scan.occ, scan.full, scan.cnt, gidx,
@@ -2379,16 +2427,18 @@ bool counts_in_prep(const dam_mask_params *p, const Geom &g, const dam_mask_out 
 }
 
 // a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
-// k_pattern_prep has to count for that. counted: the chunks' slices are there already.
+// k_pattern_prep has to count for that. counted: the chunks' slices are there already. map: k_pattern_prep makes the true mask
+// too (maps_in_prep).
 CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
-                    hipStream_t stream, const uint8_t **dflag, const uint8_t **vflag, bool bmin_written, bool counted) {
+                    hipStream_t stream, const uint8_t **dflag, const uint8_t **vflag, bool bmin_written, bool counted,
+                    const float *map = nullptr, const Threshold &thr = {}) {
   uint8_t *df = o->diag_flag ? o->diag_flag : w.diag_flag;
   uint8_t *vf = o->vert_flag ? o->vert_flag : w.vert_flag;
   *dflag = df;
   *vflag = vf;
   if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
   if (counts_in_prep(p, g, o))
-    return CountArgs{o->true_bits, nullptr, nullptr, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
+    return CountArgs{map ? kFromMap : kFromTrueBits, map, thr, o->true_bits, nullptr, nullptr, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
   if (counted) {
   } else if (g.tbw <= 128) {
@@ -2398,7 +2448,7 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
     k_pattern_slices_wide<<<sgrid, 256, 0, stream>>>(o->true_bits, g.L, g.tbw, n_chunks, w.vslices, w.dslices);
   }
   if (g.L <= kSlicesInPrep && needs_prep(p, o))
-    return CountArgs{nullptr, w.vslices, w.dslices, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
+    return CountArgs{kFromSlices, nullptr, {}, nullptr, w.vslices, w.dslices, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   int nb = 1;  // bits of the largest possible count, L
   while ((g.L >> nb) != 0) ++nb;
   k_pattern_finish<<<dim3((g.tbw + kFinWords - 1) / kFinWords, g.H, 2), 256, 0, stream>>>(w.vslices, w.dslices, g.L, g.tbw, n_chunks, nb, p->mu,
@@ -2417,10 +2467,12 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   const int *gidx = gather ? o->gather_idx : nullptr, *gcnt = gather ? o->gather_cnt : nullptr;
   const int nrows = p->row_end - p->row_begin;
   const bool plan = (p->flags & DAM_MASK_PATTERN_PLAN) != 0;
-  if (needs_prep(p, o) || count.true_bits) {
+  if (needs_prep(p, o) || count.source != kFlagsGiven) {
     const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
     const ScanArgs scan{scans_in_prep(g, o), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
-    k_pattern_prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.classes, gstride, gather ? o->gather_idx : nullptr,
+    auto prep = count.source == kFromMap ? k_pattern_prep<kFromMap> : count.source == kFromTrueBits ? k_pattern_prep<kFromTrueBits>
+                : count.source == kFromSlices ? k_pattern_prep<kFromSlices> : k_pattern_prep<kFlagsGiven>;
+    prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.classes, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
   // a4 + a5: tile occupancy, CSR offsets, tile bits
@@ -2528,8 +2580,10 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
     bool bmin_written;
     const Threshold thr = stage_threshold(p, g, w, attn_sum, attn_cnt, stream, o->bmin, &bmin_written);
     // a2: true mask, one comparison per element
+    const bool in_prep = !attn_cnt && g.L <= kMapInPrep;
     dim3 grid((g.tbw + 3) / 4, (g.L + kTmRows - 1) / kTmRows, g.H);
-    if (attn_cnt && p->transform == DAM_T_RAW_SUM)
+    if (in_prep) {
+    } else if (attn_cnt && p->transform == DAM_T_RAW_SUM)
       k_true_mask<false, true><<<grid, 256, 0, stream>>>(attn_sum, attn_cnt, g.L, g.tbw, p->eps, thr, o->true_bits);
     else if (attn_cnt)
       k_true_mask<false><<<grid, 256, 0, stream>>>(attn_sum, attn_cnt, g.L, g.tbw, p->eps, thr, o->true_bits);
@@ -2539,7 +2593,7 @@ extern "C" int dam_mask_build(const dam_mask_params *p, const float *attn_sum, c
       k_true_mask_rows<<<dim3(per_map, g.H), 256, 0, stream>>>(attn_sum, g.L, g.tbw, n_pairs, thr, o->true_bits);
     } else
       k_true_mask<true><<<grid, 256, 0, stream>>>(attn_sum, attn_cnt, g.L, g.tbw, p->eps, thr, o->true_bits);
-    count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, false);
+    count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, false, in_prep ? attn_sum : nullptr, thr);
   }
   stage_extension(p, g, w, o, true_bits, dflag, vflag, count, stream);
   return launch_status();

@@ -56,17 +56,59 @@ def test_pattern_counts_alone_on_both_sides_of_the_line(L, copies):
         assert np.array_equal(getattr(mask, name).cpu().numpy(), np.tile(getattr(art, name), (copies, 1))), name
 
 
+# captures whose true mask the prep kernel makes itself (up to 128 tokens), maps of any alignment, values that no threshold takes
+@pytest.mark.parametrize("L", [1, 3, 62, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_true_mask_of_short_maps(L, shift):
+    A = synth_map(np.random.default_rng(L), 3, L)
+    A[1, L // 2] = np.nan
+    A[2, L - 1, 0] = np.inf
+    room = torch.empty(A.size + shift, device="cuda")
+    room[shift:] = torch.from_numpy(A.ravel()).cuda()
+    m = B.build_mask(mode=B.DAM_FROM_ATTN_MAP, H=3, L=L, S=L, lam=0.5, eps=1e-8, tau=0.02, mu=0.3, attn_sum=room[shift:].view(A.shape),
+                     blocks=False)
+    art = oracle.derive(A, None, 0.5, 1e-8, 0.02, 0.3)
+    assert np.array_equal(u64(m.true_bits), pack_rows_u64(art.true_mask))
+    for name in ("diag_cnt", "vert_cnt", "diag_flag", "vert_flag"):
+        assert np.array_equal(getattr(m, name).cpu().numpy(), getattr(art, name)), name
+
+
+# tiles that are full by columns and diagonals together: the one unmatched offset meets matched columns only (its tiles' first
+# column), or misses one by a column
+@pytest.mark.parametrize("T", [64, 128])
+@pytest.mark.parametrize("S", [1024, 1100, 3072])  # scanned in the prep kernel, and by a launch
+def test_full_tiles_of_columns_and_diagonals(S, T):
+    d, v = (np.zeros((3, S), np.uint8) for _ in range(2))
+    d[:] = 1
+    d[:, 2 * T + T - 1] = 0           # of tile distance 2 the last offset: column 0 of the tile alone, in its last row
+    d[:, 5 * T] = 0                   # of distance 5 the middle one: every column
+    v[0, ::T] = 1
+    v[1, 1::T] = 1
+    v[2] = 1
+    v[2, T + 3] = 0
+    art = oracle.from_patterns(d, v)
+    m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=3, L=0, S=S, tile_m=T, tile_n=T, diag_in=torch.from_numpy(d).cuda(),
+                     vert_in=torch.from_numpy(v).cuda())
+    torch.cuda.synchronize()
+    test_gpu_mask.check_against_oracle(art, S, T, T, m, dense=False)
+    row_ptr, col, kind = (getattr(m, x).cpu().numpy() for x in ("blk_row_ptr", "blk_col", "blk_kind"))
+    full = [{(qt, c) for qt in range(S // T) for c, k in zip(col[row_ptr[h, qt]:row_ptr[h, qt + 1]], kind[row_ptr[h, qt]:row_ptr[h, qt + 1]])
+             if k & 1} for h in range(3)]
+    assert (2, 0) in full[0] and (2, 0) not in full[1] and (2, 0) in full[2] and (5, 0) in full[2] and (6, 1) not in full[2]
+
+
 # one query tile, the most and one more than the prep kernel scans itself; ragged, inside and beyond the true-mask block
 @pytest.mark.parametrize("S,tm,tn,L", [(60, 64, 64, 200), (500, 64, 64, 130), (512, 64, 64, 512), (513, 64, 64, 200), (1000, 128, 64, 300),
-                                       (1024, 128, 128, 200), (1025, 128, 128, 200), (700, 256, 64, 64)])
+                                       (1024, 128, 128, 200), (1025, 128, 128, 200), (700, 256, 64, 64), (1024, 64, 64, 128),
+                                       (1025, 64, 64, 129), (2048, 128, 128, 100), (2060, 128, 128, 300)])
 def test_scan_inside_the_prep_kernel(S, tm, tn, L):
     run_from_map(synth_map(np.random.default_rng(S), 3, L), None, S, tm, tn, 0.5, 1e-8, 0.02, 0.4)
     if S > tm:
         test_gpu_mask.test_gathered_column_tiles_match_oracle(S, tm, tn, min(L, S // 2))
 
 
-# the same from patterns alone, whose line in the plain layout is seven query tiles for a ragged length
-@pytest.mark.parametrize("S", [440, 448, 500, 512, 520])
+# the same from patterns alone
+@pytest.mark.parametrize("S", [440, 448, 500, 512, 520, 1000, 1024, 1030])
 def test_scan_of_patterns_inside_the_prep_kernel(S):
     rng = np.random.default_rng(S)
     d, v = (np.zeros((4, S), np.uint8) for _ in range(2))
