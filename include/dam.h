@@ -527,9 +527,14 @@ int dam_kv_remap_lists(const dam_evict_params *params, const int32_t *window, co
  *   written in practice). Flop launched: workgroups * 4 * iters * 16 * 32768.
  * dam_probe_stream_read: reads `bytes` (a multiple of 32 KiB is read completely) from src with 16-byte
  *   loads and discards them. src device, 16-byte aligned; sink device, one word.
- * Both only enqueue on `stream`; the caller times them. */
+ * Both only enqueue on `stream`; the caller times them.
+ * dam_probe_row_lists: the kept lists of one row from patterns, as dam_mask_build makes them where one launch does, with every
+ *   list's workgroup counting all lists in front of its own itself instead of learning their totals from the others (what
+ *   dam_mask_build does for a total that is late). DAM_ERR_UNSUPPORTED where dam_mask_build takes another way. */
 int dam_probe_mfma(const void *operands, float *sink, int32_t workgroups, int32_t iters, void *stream);
 int dam_probe_stream_read(const void *src, size_t bytes, uint32_t *sink, int32_t workgroups, void *stream);
+int dam_probe_row_lists(const dam_mask_params *params, const uint8_t *diag_in, const uint8_t *vert_in,
+                        const dam_mask_out *out, void *ws, size_t ws_bytes, void *stream);
 
 /* Library version, for the loader's sanity check. */
 int dam_version(void);

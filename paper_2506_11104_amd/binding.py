@@ -97,7 +97,7 @@ EXPORTS = ["dam_gather_stride", "dam_kv_evict_workspace", "dam_kv_evict_plan", "
            "dam_sparse_attn_prefill", "dam_sparse_attn_decode_workspace", "dam_sparse_attn_decode",
            "dam_sparse_attn_decode_grouped_workspace", "dam_sparse_attn_decode_grouped",
            "dam_sparse_attn_decode_patterns", "dam_sparse_attn_decode_grouped_static_limit", "dam_sparse_attn_decode_grouped_static", "dam_probe_mfma",
-           "dam_probe_stream_read", "dam_version"]
+           "dam_probe_stream_read", "dam_probe_row_lists", "dam_version"]
 
 _lib = None
 
@@ -160,6 +160,8 @@ def lib() -> ctypes.CDLL:
         L.dam_probe_mfma.argtypes = [vp, vp, ctypes.c_int32, ctypes.c_int32, vp]
         L.dam_probe_stream_read.restype = ctypes.c_int
         L.dam_probe_stream_read.argtypes = [vp, sz, vp, ctypes.c_int32, vp]
+        L.dam_probe_row_lists.restype = ctypes.c_int
+        L.dam_probe_row_lists.argtypes = [ctypes.POINTER(MaskParams), vp, vp, ctypes.POINTER(MaskOut), vp, sz, vp]
         L.dam_version.restype = ctypes.c_int
         _lib = L
     return _lib

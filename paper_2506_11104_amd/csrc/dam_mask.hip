@@ -613,17 +613,14 @@ __global__ __launch_bounds__(256) void k_pattern_finish(const uint64_t *__restri
 // i.e. the diagonal set reversed, so that the 64 offsets i-j, i-j-1, ... of one mask word are 64
 // consecutive ascending bits. Four lanes build one word: each turns 16 flag bytes (one 16-byte
 // load when the row is aligned) into 16 bits.
-__device__ __forceinline__ unsigned bits_of_16(const uint4 &v) {
-  const unsigned x[4] = {v.x, v.y, v.z, v.w};
-  unsigned bits = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    // per byte: non-zero -> 1, then gather the four 0/1 bytes into four adjacent bits
-    const unsigned nz = ((((x[k] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x[k]) & 0x80808080u) >> 7;
-    bits |= (((nz * 0x00204081u) >> 21) & 0xFu) << (4 * k);
-  }
-  return bits;
+// Eight flag bytes, four to a word, as eight bits: each byte's top bit is set where the byte is not zero, and a dot product with
+// the bits' places adds them up (128 times the result). The multiplications that gather such bits otherwise run at a quarter of
+// the rate.
+__device__ __forceinline__ unsigned bits_of_8(unsigned lo, unsigned hi) {
+  auto not_zero = [](unsigned x) { return (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u; };
+  return __builtin_amdgcn_udot4(not_zero(hi), 0x80402010u, __builtin_amdgcn_udot4(not_zero(lo), 0x08040201u, 0, false), false) >> 7;
 }
+__device__ __forceinline__ unsigned bits_of_16(const uint4 &v) { return bits_of_8(v.x, v.y) | bits_of_8(v.z, v.w) << 8; }
 
 // (every thread of the workgroup calls this; 512 words per pass)
 // A piece is read where it lies, at any alignment, and one that the row's end cuts from 16 bytes before that end and shifted:
@@ -1974,12 +1971,10 @@ constexpr int kListSpan = 256 * kPieceBits;       // keys per workgroup
 // 44.6; 64 maps at 2^20 one by one (65536) 377 / 156.
 constexpr int64_t kAddedCounts = 12288;
 
-// Eight flag bytes from p on as eight bits (p of any alignment).
-__device__ __forceinline__ unsigned flags8(const uint8_t *p) {
+__device__ __forceinline__ unsigned flags8(const uint8_t *p) {  // (p of any alignment)
   uint64_t v;
   __builtin_memcpy(&v, p, 8);
-  const uint64_t nz = ((((v & 0x7F7F7F7F7F7F7F7Full) + 0x7F7F7F7F7F7F7F7Full) | v) & 0x8080808080808080ull) >> 7;
-  return (unsigned)((nz * 0x0102040810204080ull) >> 56);  // byte k's bit to bit k
+  return bits_of_8((unsigned)v, (unsigned)(v >> 32));
 }
 
 // The mask bits of row i, keys [key0, key0 + 8) of one map; key0 a multiple of 8.
@@ -2118,6 +2113,235 @@ __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__res
         }
         ++at;
       }
+    }
+  }
+}
+
+// The same in one launch, a workgroup per list, for rows of up to 1024 W keys and up to 64 lists. What a list needs of the
+// others is how many entries lie in front of its own, the totals of the lists before it: every workgroup says its total where
+// the others can read it past their L2 (two words that only this call's number makes a total of: nothing has to be cleared, and a
+// captured launch, whose number would be the same at every replay, takes the two launches above) and looks at those in front.
+// Nobody waits for longer than `polls` looks: a total that is not there by then is counted again from the flags.
+// Bound by the chain flags -> counts -> totals -> entries of one workgroup per list, and its instructions: a lane owns W keys next
+// to each other, so that a run takes one prefix sum whatever the row's length. Lists with
+// the decode behind them, us, two launches / this: 8 sequences at 20000, merged lists of 32 heads 29.5 / 28.0, 2 at 32700 32.5 / 23.0,
+// 4 at 8000 (16 heads) 19.6 / 15.7; a list per head 4 fp32 sequences at 4096, 16 heads 12.2 / 10.6, 2 at 30000, 32 heads 20.4 / 18.0.
+constexpr int kOneLists = 64, kOnePolls = 64;
+
+// m[x]: bit k is key W * lane of the workgroup + k of the map x of group kv, of row i >= L whose patterns all exist (i < P, P >= W).
+// All flags are under way together, none of them behind a test: a piece that the row's or the flags' end cuts is read from inside
+// and shifted.
+template <int W, int GM>
+__device__ __forceinline__ void keys_of_list(const Geom &g, const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int kv, int G,
+                                             int i, unsigned (&m)[GM]) {
+  constexpr int kWords = W / 8;
+  uint64_t v[GM][kWords], d[GM][kWords];
+  const int key0 = (int)threadIdx.x * W, left = i - key0;  // (keys behind the row's own: left < 0)
+  const int at_v = min(key0, g.P - W), at_d = max(left - (W - 1), 0);  // offset of key k: left - k
+#pragma unroll
+  for (int x = 0; x < GM; ++x) {
+    const int64_t row = (int64_t)(kv * G + min(x, G - 1)) * g.P;
+    __builtin_memcpy(v[x], vflag + row + at_v, W);
+    __builtin_memcpy(d[x], dflag + row + at_d, W);
+  }
+  const unsigned all = W == 32 ? ~0u : (1u << (W & 31)) - 1, causal = left >= W - 1 ? all : left < 0 ? 0u : (2u << left) - 1;
+  const int cut_v = min(key0 - at_v, 31), cut_d = left < 0 ? 0 : max(W - 1 - left, 0);
+  auto gather = [&](auto ones) {  // ones: no flag is above 1, so its byte is its bit
+    constexpr bool ONES = decltype(ones)::value;
+    auto eight = [](uint64_t y) -> unsigned {
+      const unsigned lo = (unsigned)y, hi = (unsigned)(y >> 32);
+      if (ONES) return __builtin_amdgcn_udot4(hi, 0x80402010u, __builtin_amdgcn_udot4(lo, 0x08040201u, 0, false), false);
+      return bits_of_8(lo, hi);
+    };
+#pragma unroll
+    for (int x = 0; x < GM; ++x) {
+      unsigned vb = 0, db = 0;
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) {
+        vb |= eight(v[x][w]) << (8 * w);
+        db |= eight(d[x][w]) << (8 * w);
+      }
+      m[x] = x < G ? (vb >> cut_v | __brev(db) >> (32 - W) >> cut_d) & causal : 0;
+    }
+  };
+  uint64_t high = 0;
+#pragma unroll
+  for (int x = 0; x < GM; ++x)
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) high |= v[x][w] | d[x][w];
+  if (__ballot((high & 0xFEFEFEFEFEFEFEFEull) != 0) == 0) gather(std::true_type{});
+  else gather(std::false_type{});
+}
+
+template <int W, int GM>
+__global__ __launch_bounds__(1024) void k_list_one(Geom g, const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int row, int G,
+                                                   uint64_t number, int polls, uint64_t *__restrict__ said, int *__restrict__ kept_ptr,
+                                                   int64_t *__restrict__ kept_total, int *__restrict__ kept_idx,
+                                                   uint8_t *__restrict__ kept_member, int64_t capacity) {
+  __shared__ int part[GM + 1][16], run_total[GM + 1];
+  __shared__ int s_before, s_again;
+  __shared__ uint64_t s_missing;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kv = blockIdx.x, lists = gridDim.x;
+  unsigned m[GM], more = 0, any = 0;  // more: keys of two maps or more
+  keys_of_list<W, GM>(g, dflag, vflag, kv, G, row, m);
+#pragma unroll
+  for (int x = 0; x < GM; ++x) {
+    more |= any & m[x];
+    any |= m[x];
+  }
+  auto run = [&](int r) { return r == 0 ? more : m[r > 0 ? r - 1 : 0] & ~more; };
+  // a run's entries in front of the lane's, in its wave; two runs to a sum (a wave has at most 2048 keys)
+  int in_wave[GM + 1];
+#pragma unroll
+  for (int r = 0; r <= GM; r += 2)
+    if (r <= G) {
+      const int both = __popc(run(r)) | (r < GM ? __popc(run(r + 1)) << 16 : 0), incl = wave_prefix(both);
+      in_wave[r] = (incl & 0xFFFF) - (both & 0xFFFF);
+      if (lane == 63) part[r][wave] = incl & 0xFFFF;
+      if (r < GM) {
+        in_wave[r + 1] = (int)((unsigned)incl >> 16) - (both >> 16);
+        if (lane == 63) part[r + 1][wave] = (int)((unsigned)incl >> 16);
+      }
+    }
+  __syncthreads();
+  if (wave <= G) {
+    const int v = lane < 16 ? part[wave][lane] : 0, incl = wave_prefix(v);
+    if (lane < 16) part[wave][lane] = incl - v;
+    if (lane == 63) run_total[wave] = incl;
+  }
+  __syncthreads();
+  int total = 0;
+#pragma unroll
+  for (int r = 0; r <= GM; ++r)
+    if (r <= G) total += run_total[r];
+  if (wave == 0) {
+    // (two words: one alone would be taken for a total with a probability of 2^-33 whatever it holds)
+    const uint64_t second = number ^ (uint64_t)(unsigned)total;
+    if (lane == 0)
+      store_through(said + 2 * kv, __uint_as_float((unsigned)number), __uint_as_float((unsigned)(number >> 32)),
+                    __uint_as_float((unsigned)second), __uint_as_float((unsigned)(second >> 32)));
+    int theirs = 0;
+    bool there = lane >= kv;
+    for (int look = 0; look < polls && __ballot(!there) != 0; ++look)
+      if (!there) {
+        const uint64_t a = __hip_atomic_load(said + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t b = __hip_atomic_load(said + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ^ number;
+        if (a == number && b >> 31 == 0) {
+          theirs = (int)b;
+          there = true;
+        }
+      }
+    const uint64_t missing = __ballot(!there);
+    const int before = wave_total(theirs);
+    if (lane == 0) {
+      s_before = before;
+      s_missing = missing;
+      s_again = 0;
+    }
+  }
+  __syncthreads();
+  uint64_t missing = s_missing;
+  while (missing) {  // uniform
+    const int x = __ffsll((unsigned long long)missing) - 1;
+    missing &= missing - 1;
+    unsigned other[GM], keys = 0;
+    keys_of_list<W, GM>(g, dflag, vflag, x, G, row, other);
+#pragma unroll
+    for (int y = 0; y < GM; ++y) keys |= other[y];
+    int n = __popc(keys);
+    n = wave_total(n);
+    if (lane == 0) atomicAdd(&s_again, n);
+  }
+  __syncthreads();
+  const int64_t first = (int64_t)s_before + s_again;
+  if (threadIdx.x == 0) {  // (offsets past the capacity of the list buffers are cut to it, like the block index')
+    const int64_t clamp = kept_idx ? capacity : INT64_MAX;
+    kept_ptr[kv] = (int)min(first, clamp);
+    if (kv == lists - 1) {
+      kept_ptr[lists] = (int)min(first + total, clamp);
+      if (kept_total) *kept_total = first + total;
+    }
+  }
+  if (!kept_idx) return;
+  // Windows and sinks fill the pieces of a few lanes next to each other: wide pieces are dealt out again for the writing, one to
+  // every wave in turn. (Written where they were counted, one wave of the sixteen took 4 us longer than the others.)
+  constexpr bool kSpread = W > 8;
+  constexpr int kPitch = kSpread ? 17 * 64 : 1;
+  __shared__ unsigned piece[GM][kPitch];
+  __shared__ unsigned short place[GM + 1][kPitch];
+  int my = threadIdx.x, at_run[GM + 1];  // the piece this lane writes, and its places in the runs
+#pragma unroll
+  for (int r = 0; r <= GM; ++r) at_run[r] = r <= G ? part[r][wave] + in_wave[r] : 0;
+  if constexpr (kSpread) {
+    const int to = my + (my >> 4);  // (17 words for 16 pieces: no two lanes of a wave on one bank)
+#pragma unroll
+    for (int x = 0; x < GM; ++x)
+      if (x < G) piece[x][to] = m[x];
+#pragma unroll
+    for (int r = 0; r <= GM; ++r)
+      if (r <= G) place[r][to] = (unsigned short)at_run[r];
+    __syncthreads();
+    my = lane * 16 + wave;
+    const int from = my + (my >> 4);
+    more = any = 0;
+#pragma unroll
+    for (int x = 0; x < GM; ++x) {
+      m[x] = x < G ? piece[x][from] : 0;
+      more |= any & m[x];
+      any |= m[x];
+    }
+#pragma unroll
+    for (int r = 0; r <= GM; ++r)
+      if (r <= G) at_run[r] = place[r][from];
+  }
+  auto put = [&](int at, int key, unsigned who) {  // at: place in the list
+    if (first + at < capacity) {
+      kept_idx[first + at] = key;
+      if (kept_member) kept_member[first + at] = (uint8_t)who;
+    }
+  };
+  int base = 0;
+#pragma unroll
+  for (int r = 0; r <= GM; ++r) {
+    if (r <= G) {
+      unsigned left = run(r);
+      int at = base + at_run[r];
+      // Lanes with many keys (windows, sinks): 64 / W of them at a time, a lane of the wave per key, so that the stores of
+      // neighbours lie side by side. (Key by key in their own lane the launch above took 2 us more.)
+      constexpr int kFew = 4, kAtOnce = 64 / W;
+      if (W > 8) {
+        for (uint64_t many = __ballot(__popc(left) > kFew); many;) {
+          int from = 64;
+#pragma unroll
+          for (int y = 0; y < kAtOnce; ++y) {
+            const int next = many ? __ffsll((unsigned long long)many) - 1 : 64;
+            if (lane / W == y) from = next;
+            many &= many - 1;
+          }
+          const int src = from & 63, bit = lane & (W - 1);
+          const unsigned mask = (unsigned)__shfl((int)left, src);
+          const int their_at = __shfl(at, src);
+          unsigned who = r == 0 ? 0u : 1u << (r - 1);
+          if (r == 0) {
+#pragma unroll
+            for (int y = 0; y < GM; ++y)
+              if (y < G) who |= (((unsigned)__shfl((int)m[y], src) >> bit) & 1u) << y;
+          }
+          if (from < 64 && ((mask >> bit) & 1)) put(their_at + __popc(mask & ((1u << bit) - 1)), (kSpread ? from * 16 + wave : wave * 64 + from) * W + bit, who);
+        }
+        if (__popc(left) > kFew) left = 0;
+      }
+      while (left) {
+        const int bit = __ffs(left) - 1;
+        left &= left - 1;
+        unsigned who = r == 0 ? 0u : 1u << (r - 1);
+        if (r == 0) {
+#pragma unroll
+          for (int y = 0; y < GM; ++y) who |= ((m[y] >> bit) & 1u) << y;
+        }
+        put(at++, my * W + bit, who);
+      }
+      base += run_total[r];
     }
   }
 }
@@ -2456,6 +2680,33 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   return CountArgs{};
 }
 
+// Whether the lists of one row take the one launch of k_list_one. (A stream whose state cannot be told counts as captured.)
+bool lists_in_one(const dam_mask_params *p, const Geom &g, hipStream_t stream) {
+  const int lists = g.H / list_group(p);
+  if (lists > kOneLists || p->row_begin >= 1024 * 32 || (int64_t)g.H * g.pw < 2 * lists) return false;
+  if (p->row_begin < g.L || p->row_begin >= g.P || g.P < 8) return false;  // (rows of 8192 keys and more: g.P >= 16, 32)
+  if (list_group(p) > 4 && p->row_begin >= 1024 * 16) return false;         // (eight maps' pieces of 32 keys spill registers)
+  hipStreamCaptureStatus state = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &state) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return state == hipStreamCaptureStatusNone;
+}
+
+// (the totals lie where the column sets would: nothing reads those behind this launch)
+void launch_list_one(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o, const uint8_t *dflag,
+                     const uint8_t *vflag, int polls, hipStream_t stream) {
+  const int G = list_group(p), w_at = p->row_begin < 1024 * 8 ? 0 : p->row_begin < 1024 * 16 ? 1 : 2;
+  using Kernel = decltype(&k_list_one<8, 1>);
+  static const Kernel kernels[3][3] = {{k_list_one<8, 1>, k_list_one<8, 4>, k_list_one<8, 8>},
+                                       {k_list_one<16, 1>, k_list_one<16, 4>, k_list_one<16, 8>},
+                                       {k_list_one<32, 1>, k_list_one<32, 4>, nullptr}};
+  kernels[w_at][G > 4 ? 2 : G > 1 ? 1 : 0]<<<g.H / G, 1024, 0, stream>>>(
+      g, dflag, vflag, p->row_begin, G, fresh_flag(), polls, w.cbits, o->kept_ptr, o->kept_total,
+      o->kept_capacity > 0 ? o->kept_idx : nullptr, o->kept_member, o->kept_capacity);
+}
+
 // a4 + a5 and the kept lists: everything downstream of the stored artefact.
 void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w, const dam_mask_out *o,
                      const uint64_t *true_bits, const uint8_t *dflag, const uint8_t *vflag, const CountArgs &count,
@@ -2528,6 +2779,10 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
       const dim3 grid(p->row_begin / kListSpan + 1, g.H / G);
       const int64_t counts = list_counts(p);
       const bool scan = counts > kAddedCounts;
+      if (lists_in_one(p, g, stream)) {
+        launch_list_one(p, g, w, o, dflag, vflag, kOnePolls, stream);
+        return;
+      }
       k_list_count<<<grid, 256, 0, stream>>>(g, true_bits, dflag, vflag, p->row_begin, G, w.row_cnt);
       if (scan) k_exclusive_scan<<<1, 1024, 0, stream>>>(w.row_cnt, counts, 0, w.group_first, o->kept_total, INT32_MAX);
       auto fill = scan ? k_list_fill<true> : k_list_fill<false>;
@@ -2632,5 +2887,20 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
                                                 counts_in_prep(p, g, o) ? nullptr : w.vslices, w.dslices, stream);
   const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, counted);
   stage_extension(p, g, w, o, o->true_bits, dflag, vflag, count, stream);
+  return launch_status();
+}
+
+// The lists of one row as dam_mask_build makes them in one launch, without a look at the other workgroups' totals.
+extern "C" int dam_probe_row_lists(const dam_mask_params *p, const uint8_t *diag_in, const uint8_t *vert_in, const dam_mask_out *o, void *ws,
+                                   size_t ws_bytes, void *stream_v) {
+  const int bad = validate(p, nullptr, diag_in, vert_in, o);
+  if (bad != DAM_OK) return bad;
+  if (!ws || ws_bytes < dam_mask_build_workspace(p)) return DAM_ERR_WORKSPACE;
+  hipStream_t stream = static_cast<hipStream_t>(stream_v);
+  const Geom g = geometry(p);
+  if (p->mode != DAM_FROM_PATTERNS || !o->kept_ptr || (p->flags & DAM_MASK_PATTERN_PLAN) || p->row_end != p->row_begin + 1 ||
+      !lists_in_one(p, g, stream))
+    return DAM_ERR_UNSUPPORTED;
+  launch_list_one(p, g, carve(p, ws), o, diag_in, vert_in, 0, stream);
   return launch_status();
 }

@@ -1,5 +1,7 @@
 """Lists of one row straight from the pattern flags: rows around the pieces of eight keys and the spans of 2048 keys that the
 kernels work in, flag rows of odd length (so of every alignment), rows inside and below a true-mask block."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -45,3 +47,62 @@ def test_lists_on_both_sides_of_the_scan(H, G, spans):
         ptr.append(sum(x.numel() for x in idx))
     assert m.n_kept == ptr[-1] and m.kept_ptr.tolist() == ptr
     assert torch.equal(m.kept_idx[:ptr[-1]].long(), torch.cat(idx)) and torch.equal(m.kept_member[:ptr[-1]].long(), torch.cat(mem))
+
+
+def patterns_of(H, S, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    d, v = ((torch.rand((H, S), generator=gen, device="cuda") < 0.02).to(torch.uint8) for _ in range(2))
+    for h in range(H):
+        d[h, : 37 * (h % 9)] = 1
+        v[h, S // 2:S // 2 + 11 * (h % 5)] = 1 + h  # (any value but zero is a match)
+    return d, v
+
+
+def lists_of(d, v, row, G):
+    """kept_ptr, kept_idx, kept_member of a row from the flags: runs of keys of two maps or more, then of each map alone."""
+    bits = 1 << torch.arange(G, device="cuda")
+    idx, mem, ptr = [], [], [0]
+    for g in range(d.shape[0] // G):
+        keep = (d[g * G:(g + 1) * G, :row + 1].flip(1) | v[g * G:(g + 1) * G, :row + 1]) != 0
+        n = keep.sum(0)
+        for run in ([n >= 2] if G > 1 else []) + [keep[x] & (n == 1) for x in range(G)]:
+            at = run.nonzero().flatten()
+            idx.append(at)
+            mem.append((keep[:, at] * bits[:, None]).sum(0))
+        ptr.append(sum(x.numel() for x in idx))
+    return ptr, torch.cat(idx), torch.cat(mem)
+
+
+# a workgroup per list: rows at the edges of 8, 16 and 32 keys per lane, of the flags and of what one launch takes (32768 keys, 64
+# lists, 16384 keys of eight maps); built by the entry point, and with every total counted again instead of learned
+@pytest.mark.parametrize("H,G,S,rows", [
+    (3, 1, 8, (0, 3, 6, 7)), (16, 1, 4160, (4095, 4096, 4159)), (8, 4, 8200, (8190, 8191, 8192, 8199)), (6, 3, 16390, (16383, 16384, 16389)),
+    (8, 4, 32800, (32759, 32767, 32768)), (64, 1, 20000, (19999,)), (65, 1, 300, (299,)), (16, 8, 16500, (16383, 16384)), (5, 1, 33, (7, 31, 32)),
+])
+def test_lists_in_one_launch(H, G, S, rows):
+    d, v = patterns_of(H, S, S)
+    for row in rows:
+        m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=H, L=0, S=S, diag_in=d, vert_in=v, blocks=False, group=G if G > 1 else 0, rows=(row, row + 1))
+        torch.cuda.synchronize()
+        ptr, idx, mem = lists_of(d, v, row, G)
+        n = ptr[-1]
+        assert m.kept_ptr.tolist() == ptr and m.n_kept == n
+        assert torch.equal(m.kept_idx[:n].long(), idx) and (G == 1 or torch.equal(m.kept_member[:n].long(), mem))
+        p = B.MaskParams(B.DAM_FROM_PATTERNS, H, 0, S, 128, 128, row, row + 1, 0.5, 1e-8, 0.3, 0.8, float("nan"),
+                         B.DAM_MASK_GROUP_LISTS if G > 1 else 0, 0, G if G > 1 else 0)
+        again = {k: torch.full((n + 5,), 7, dtype=t, device="cuda") for k, t in (("idx", torch.int32), ("mem", torch.uint8))}
+        kept_ptr, total = torch.full((H // G + 1,), -7, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+        o = B.MaskOut()
+        o.kept_ptr, o.kept_idx, o.kept_total, o.kept_capacity = kept_ptr.data_ptr(), again["idx"].data_ptr(), total.data_ptr(), n - 1
+        if G > 1:
+            o.kept_member = again["mem"].data_ptr()
+        ws = B.mask_workspace(p, "cuda")
+        st = B.lib().dam_probe_row_lists(ctypes.byref(p), d.data_ptr(), v.data_ptr(), ctypes.byref(o), ws.data_ptr(), ws.numel(),
+                                         torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        if H // G > 64 or row >= 32768 or (G > 4 and row >= 16384) or (S <= 64 and G == 1):
+            assert st == -2  # DAM_ERR_UNSUPPORTED: the other way
+            continue
+        assert st == 0 and int(total) == n and kept_ptr.tolist() == [min(x, n - 1) for x in ptr]
+        assert torch.equal(again["idx"][:n - 1].long(), idx[:n - 1]) and bool((again["idx"][n - 1:] == 7).all())
+        assert G == 1 or torch.equal(again["mem"][:n - 1].long(), mem[:n - 1])
