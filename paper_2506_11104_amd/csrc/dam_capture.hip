@@ -236,36 +236,40 @@ __device__ __forceinline__ float row_lse(const CapArgs &a, const float *__restri
 // 128-byte line across the lanes, whatever the row length. A row tile per workgroup with K staged through LDS had one
 // block of A and C in flight and as many workgroups as row tiles (256 at 32 heads x 1000 tokens): 208 -> 81 us there
 // with its first pass (3.8 TB/s of A and C without it), 64 heads x 4096 tokens 2150 -> 1740 us (5.3 TB/s).
-constexpr int kSumKeys = 64;
-constexpr int kSumSpan = 4 * kSumKeys;  // keys of a workgroup's waves side by side: 1 KiB of every row
-// Workgroups of a head: rows come in groups of 32, and the 8 groups of block R of kSumSpan rows need R + 1 of them each.
-__host__ __device__ constexpr int sum_items_before(int R) { return 4 * R * (R + 1); }
+// BLOCKS: 32-key blocks of a wave, two or one. Waves of 64 keys move more bytes for what they fetch besides, waves of 32 fit the
+// chip three to a SIMD instead of two and come out more even where there are few (64 keys / 32, us, whole calls): 16 heads x 400
+// tokens 22.7 / 17.7, 16 x 900 47.0 / 44.2, 32 x 1000 83.1 / 81.7, 32 x 1472 153.5 / 152.8, 64 x 2000 491 / 520.
+constexpr int kSumNarrow = 6144;  // workgroups of 64 keys per wave up to which they get 32
+constexpr int sum_span(int blocks) { return 4 * 32 * blocks; }  // keys of a workgroup's waves side by side: 1 KiB or 512 bytes of every row
+// Workgroups of a head: rows come in groups of 32, and the groups of block R of a span's rows need R + 1 of them each.
+__host__ __device__ constexpr int sum_items_before(int blocks, int R) { return 2 * blocks * R * (R + 1); }
 // STREAM: non-temporal loads and stores. 5 to 10 % faster where a wave's 256 bytes of a row are whole 128-byte lines (A and
 // C pass through once), twice as slow where they are not (the neighbour's half of a line then does not meet it in L2).
-template <bool STREAM>
-__global__ __launch_bounds__(256, 2) void k_capture_sum(CapArgs a, const __hip_bfloat16 *__restrict__ q,
+template <bool STREAM, int BLOCKS>
+__global__ __launch_bounds__(256, BLOCKS == 1 ? 3 : 2) void k_capture_sum(CapArgs a, const __hip_bfloat16 *__restrict__ q,
                                                         const __hip_bfloat16 *__restrict__ k,
                                                         const float *__restrict__ lse2, float *__restrict__ attn_sum,
                                                         float *__restrict__ attn_cnt) {
-  const int blocks = (a.n + kSumSpan - 1) / kSumSpan;
+  constexpr int kSpan = 4 * 32 * BLOCKS;
+  auto before = [](int R) { return sum_items_before(BLOCKS, R); };
   int h, t;
-  cap_numbering(a, sum_items_before(blocks), h, t);
-  int R = (int)((sqrtf((float)t + 1.0f) - 1.0f) * 0.5f);  // sum_items_before(R) <= t
-  while (sum_items_before(R) > t) --R;
-  while (sum_items_before(R + 1) <= t) ++R;
+  cap_numbering(a, before((a.n + kSpan - 1) / kSpan), h, t);
+  int R = (int)((sqrtf((float)t * (2.0f / BLOCKS) + 1.0f) - 1.0f) * 0.5f);  // before(R) <= t
+  while (before(R) > t) --R;
+  while (before(R + 1) <= t) ++R;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, hf = lane >> 5;
-  const int within = t - sum_items_before(R);
-  const int row0 = R * kSumSpan + within / (R + 1) * 32, key0 = within % (R + 1) * kSumSpan + wave * kSumKeys;
+  const int within = t - before(R);
+  const int row0 = R * kSpan + within / (R + 1) * 32, key0 = within % (R + 1) * kSpan + wave * 32 * BLOCKS;
   if (row0 >= a.n || key0 > row0 + 31) return;  // (whole waves) no row, or every key above the diagonal
-  const int n_blk = key0 + 32 <= row0 + 31 ? 2 : 1;  // blocks of 32 keys that reach below the diagonal
+  const int n_blk = min(BLOCKS, (row0 + 31 - key0) / 32 + 1);  // blocks of 32 keys that reach below the diagonal
 
-  bf16x8 qf[8], kf[2][8];
+  bf16x8 qf[8], kf[BLOCKS][8];
   const __hip_bfloat16 *qp = q + (int64_t)h * a.q_sh + (int64_t)min(row0 + n, a.n - 1) * a.q_ss + 8 * hf;
 #pragma unroll
   for (int c = 0; c < 8; ++c) qf[c] = *reinterpret_cast<const bf16x8 *>(qp + 16 * c);
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
+  for (int b = 0; b < BLOCKS; ++b) {
     const __hip_bfloat16 *kp =
         k + (int64_t)(h / (a.Hq / a.Hkv)) * a.k_sh + (int64_t)min(key0 + 32 * b + n, a.n - 1) * a.k_ss + 8 * hf;
     if (b < n_blk) {
@@ -289,13 +293,13 @@ __global__ __launch_bounds__(256, 2) void k_capture_sum(CapArgs a, const __hip_b
   };
   // (inside: every pair of the tile is causal and exists, so nothing is tested)
   auto body = [&](auto inside) {
-    float av[2][16], cv[2][16];
+    float av[BLOCKS][16], cv[BLOCKS][16];
     auto wanted = [&](int b, int e) {
       return decltype(inside)::value || (row0 + row_of(e) < a.n && key0 + 32 * b + n <= row0 + row_of(e));
     };
     auto each = [&](auto f) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < BLOCKS; ++b)
         if (b < n_blk) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) f(b, e, at0 + (int64_t)(8 * (e >> 2) + (e & 3)) * a.L + 32 * b);
@@ -304,7 +308,7 @@ __global__ __launch_bounds__(256, 2) void k_capture_sum(CapArgs a, const __hip_b
     each([&](int b, int e, int64_t at) { av[b][e] = wanted(b, e) ? take(attn_sum + at + lane_at) : 0.0f; });
     if (attn_cnt) each([&](int b, int e, int64_t at) { cv[b][e] = wanted(b, e) ? take(attn_cnt + at + lane_at) : 0.0f; });
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < BLOCKS; ++b)
       if (b < n_blk) {
         f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void k_capture_sum(CapArgs a, const __hip_b
         if (wanted(b, e)) put(cv[b][e] + 1.0f, attn_cnt + at + lane_at);
       });
   };
-  if (row0 + 31 < a.n && key0 + kSumKeys - 1 <= row0) body(std::true_type{});
+  if (row0 + 31 < a.n && key0 + 32 * BLOCKS - 1 <= row0) body(std::true_type{});
   else body(std::false_type{});
 }
 
@@ -663,8 +667,11 @@ void launch(const dam_capture_params *p, const CapArgs &a, const void *q, const 
     if (MODE == kEmitBits) k_capture_pipe<1><<<grid, 256, 0, st>>>(a, qb, kb, lse2, true_bits);
     else {
       const bool whole_lines = ((a.L * 4) | (int)(reinterpret_cast<uintptr_t>(attn_sum) | reinterpret_cast<uintptr_t>(attn_cnt))) % 128 == 0;
-      auto kern = whole_lines ? k_capture_sum<true> : k_capture_sum<false>;
-      kern<<<a.Hq * sum_items_before((a.n + kSumSpan - 1) / kSumSpan), 256, 0, st>>>(a, qb, kb, lse2, attn_sum, attn_cnt);
+      auto groups = [&](int blocks) { return a.Hq * sum_items_before(blocks, (a.n + sum_span(blocks) - 1) / sum_span(blocks)); };
+      const int blocks = groups(2) <= kSumNarrow ? 1 : 2;
+      auto kern = blocks == 1 ? (whole_lines ? k_capture_sum<true, 1> : k_capture_sum<false, 1>)
+                              : (whole_lines ? k_capture_sum<true, 2> : k_capture_sum<false, 2>);
+      kern<<<groups(blocks), 256, 0, st>>>(a, qb, kb, lse2, attn_sum, attn_cnt);
     }
     return;
   }

@@ -85,3 +85,25 @@ def test_a_part_without_a_number_is_not_left_out(copies, first, last):
         assert np.array_equal(np.isnan(got), lower & (np.arange(n) >= first)[:, None])
     got = a_dev[0, :first].cpu().numpy()
     assert (np.abs(got - A[0, :first]) <= ATOL + RTOL * A[0, :first]).all()
+
+
+# 32 keys per wave up to 6144 workgroups of 64 keys, 64 beyond: the same four heads alone and among enough others, around the
+# spans of 128 and 256 keys, rows of whole lines and not
+@pytest.mark.parametrize("n,L", [(127, 128), (129, 130), (255, 256), (257, 288), (385, 385), (513, 515), (900, 900)])
+def test_narrow_and_wide_tiles_of_the_sum(n, L):
+    R = (n + 255) // 256
+    copies = 6144 // (4 * 4 * R * (R + 1)) + 1
+    q, k = (dev(x, "bf16") for x in seq_pair(47 + n, 4, 2, n, 128, "bf16", std=1.2))
+    s = (q.double().reshape(2, 2 * n, 128) @ k.double().transpose(1, 2).contiguous()).reshape(4, n, n) / 128 ** 0.5
+    want = s.masked_fill(torch.ones((n, n), dtype=torch.bool, device="cuda").triu(1), float("-inf")).softmax(-1)
+    for c in (1, copies):
+        A, C = (torch.full((4 * c, L, L), 0.25, device="cuda") for _ in range(2))
+        B.dam_capture_accumulate(q.repeat(c, 1, 1), k.repeat(c, 1, 1), A, C)
+        torch.cuda.synchronize()
+        lower = torch.ones((L, L), dtype=torch.bool, device="cuda").tril_()
+        lower[n:] = False
+        assert bool((C == torch.where(lower, 1.25, 0.25)).all())
+        assert bool((A[:, ~lower] == 0.25).all())
+        got = A[[*range(4), *range(4 * c - 4, 4 * c)], :n, :n].double() - 0.25
+        # (a quarter takes the probability's last bits: half an ulp of 0.5 and of 1)
+        assert bool(((got - want.repeat(2, 1, 1)).abs().tril() <= 2.0 ** -24 + ATOL + RTOL * want.repeat(2, 1, 1)).all())
