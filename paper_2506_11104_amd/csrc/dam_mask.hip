@@ -526,87 +526,88 @@ __global__ __launch_bounds__(256) void k_pattern_slices(const uint64_t *__restri
   count_chunk(true_bits + ((int64_t)h * L + i0) * tbw, min(kChunkRows, L - i0), tbw, chunk, sm, vslices + at, dslices + at);
 }
 
-// gamma = count / size >= mu for pattern p of head h (Sec. 4.2.4), counts summed over the row chunks.
-// The chunk counts stay bit-sliced while they are added: a thread owns one word of 64 patterns and a
-// sixteenth of the chunks, ripple-adds their 8-slice counts into a wider bit-sliced sum (a full adder is
-// five logic operations on 64 patterns at once), the sixteen sums of a word are added pairwise, and only
-// then every thread extracts the integer counts of its patterns.
-// blockIdx.z: 0 vertical, 1 diagonal patterns; blockIdx.x: group of 16 words.
-constexpr int kAccSlices = 17;  // counts below 2^17: pcl is limited accordingly
-
-template <int NIN>
-__device__ __forceinline__ void sliced_add(uint64_t (&acc)[kAccSlices], const uint64_t (&in)[NIN], int nb) {
-  uint64_t carry = 0;
+// Transpose of the 64 x 64 bit matrix whose row l is the word x of lane l: lane r returns the word whose
+// bit l is bit r of lane l's x. Six exchange steps on blocks of 32, 16, ... 1 bits, all in the vector registers (lane
+// swaps, row rotations, byte permutes: some 45 instructions; exchanges through LDS waited for it six times).
+__device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  // blocks of 32: the upper halves of lanes 0 .. 31 against the lower halves of lanes 32 .. 63
+  u32x2 v = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)(x >> 32), false, false);
+  const unsigned sel16 = lane & 16 ? 0x07060302u : 0x05040100u, sel8 = lane & 8 ? 0x03070105u : 0x06020400u;
 #pragma unroll
-  for (int k = 0; k < kAccSlices; ++k) {
-    if (k < nb) {  // wave-uniform
-      const uint64_t x = k < NIN ? in[k < NIN ? k : 0] : 0;
-      const uint64_t u = acc[k] ^ x;
-      const uint64_t c = (acc[k] & x) | (u & carry);
-      acc[k] = u ^ carry;
-      carry = c;
-    }
+  for (int k = 0; k < 2; ++k) {
+    unsigned w = v[k];
+    // 16: even rows' values and odd rows' values, in all lanes
+    const u32x2 rows = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+    w = __builtin_amdgcn_perm(rows[1], rows[0], sel16);
+    // 8: lane ^ 8 is the row turned by eight
+    unsigned other = __builtin_amdgcn_update_dpp(0, w, 0x128, 0xF, 0xF, false);
+    w = __builtin_amdgcn_perm(other, w, sel8);
+    auto step = [&](unsigned from, int j, unsigned low) {  // low: the lower j bits of every 2 j
+      const bool up = (lane & j) != 0;
+      const unsigned turned = __builtin_amdgcn_alignbit(from, from, up ? j : 32 - j), take = up ? low : ~low;
+      return (turned & take) | (w & ~take);
+    };
+    other = __builtin_amdgcn_update_dpp(0, w, 0x141, 0xF, 0xF, false);      // lane ^ 7, and
+    other = __builtin_amdgcn_update_dpp(0, other, 0x1B, 0xF, 0xF, false);   // ^ 3: lane ^ 4
+    w = step(other, 4, 0x0F0F0F0Fu);
+    w = step(__builtin_amdgcn_update_dpp(0, w, 0x4E, 0xF, 0xF, false), 2, 0x33333333u);
+    v[k] = step(__builtin_amdgcn_update_dpp(0, w, 0xB1, 0xF, 0xF, false), 1, 0x55555555u);
   }
+  return (uint64_t)v[1] << 32 | v[0];
 }
 
-constexpr int kFinWords = 16;  // words (of 64 patterns) per workgroup of k_pattern_finish
-
+// gamma = count / size >= mu for pattern p of head h (Sec. 4.2.4), counts summed over the row chunks: a wave per word of 64
+// patterns. A lane fetches one slice of one chunk, eight chunks to a fetch; the fetches of a batch, whose lanes hold slices of the
+// same weight, are added up bit by bit (seven to three words), and each of the three turned around is, in the lane of a pattern,
+// eight counts of a byte. blockIdx.z: 0 vertical, 1 diagonal patterns.
+// (Thread by thread through bit-sliced sums of 17 slices and a tree of sixteen in LDS this
+// launch took 12 us at 64 heads x 4096, now 6.6; capture of 4096 tokens 332 -> 326 us, 64 x 2048 103.4 -> 99.1, 32 x 1024 37.1 -> 32.1.)
+constexpr int kMaxCountBits = 17;  // counts below 2^17: pcl is limited accordingly
 __global__ __launch_bounds__(256) void k_pattern_finish(const uint64_t *__restrict__ vslices,
                                                         const uint64_t *__restrict__ dslices, int L, int tbw,
-                                                        int n_chunks, int nb, float mu, int *__restrict__ vert_cnt,
+                                                        int n_chunks, float mu, int *__restrict__ vert_cnt,
                                                         int *__restrict__ diag_cnt, uint8_t *__restrict__ vert_flag,
                                                         uint8_t *__restrict__ diag_flag) {
-  // thread t: word t % 16 of the group, chunks t / 16, t / 16 + 16, ...; the 16 partial sums of a word are
-  // then added pairwise through LDS
-  __shared__ uint64_t part[16][kAccSlices][kFinWords];
-  const int wi = threadIdx.x & (kFinWords - 1), sub = threadIdx.x / kFinWords;
-  const int h = blockIdx.y, word0 = blockIdx.x * kFinWords;
+  static_assert(kSlices == 8, "a count is a byte");
+  constexpr int kEach = 7;
+  const int lane = threadIdx.x & 63, word = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = blockIdx.y;
+  if (word >= tbw) return;
   const bool diag = blockIdx.z == 1;
-  const uint64_t *slices = diag ? dslices : vslices;
-  int *cnt_out = diag ? diag_cnt : vert_cnt;
-  uint8_t *flag_out = diag ? diag_flag : vert_flag;
-  const int wl = word0 + wi;
-  uint64_t acc[kAccSlices];
+  const uint64_t *slices = (diag ? dslices : vslices) + ((int64_t)h * n_chunks * tbw + word) * kSlices + (lane & 7);
+  int n = 0;
+  // rows above pattern p hold nothing of it: start at the chunk of the word's first
+  for (int c0 = word * 64 / kChunkRows; c0 < n_chunks; c0 += 8 * kEach) {
+    uint64_t w[kEach];
 #pragma unroll
-  for (int k = 0; k < kAccSlices; ++k) acc[k] = 0;
-  // rows above pattern p hold nothing of it: start at the chunk of the group's first pattern
-  for (int chunk = word0 * 64 / kChunkRows + sub; chunk < n_chunks; chunk += 16) {
-    uint64_t in[kSlices];
-    const int64_t at = (((int64_t)h * n_chunks + chunk) * tbw + wl) * kSlices;
-#pragma unroll
-    for (int k = 0; k < kSlices; ++k) in[k] = wl < tbw ? slices[at + k] : 0;
-    sliced_add(acc, in, nb);
-  }
-  for (int half = 8; half >= 1; half >>= 1) {
-    if (sub >= half && sub < 2 * half) {
-#pragma unroll
-      for (int k = 0; k < kAccSlices; ++k) part[sub][k][wi] = acc[k];
+    for (int u = 0; u < kEach; ++u) {
+      const int chunk = c0 + 8 * u + (lane >> 3);
+      w[u] = 0;
+      if (c0 + 8 * u < n_chunks) {  // wave-uniform
+        const uint64_t v = slices[(int64_t)min(chunk, n_chunks - 1) * tbw * kSlices];
+        w[u] = chunk < n_chunks ? v : 0;
+      }
     }
-    __syncthreads();
-    if (sub < half) {
-      uint64_t in[kAccSlices];
+    uint64_t s[3], t0, t1;
+    csa(t0, s[0], w[0], w[1], w[2]);
+    csa(t1, s[0], s[0], w[3], w[4]);
+    uint64_t t2;
+    csa(t2, s[0], s[0], w[5], w[6]);
+    csa(s[2], s[1], t0, t1, t2);
 #pragma unroll
-      for (int k = 0; k < kAccSlices; ++k) in[k] = part[sub + half][k][wi];
-      sliced_add(acc, in, nb);
-    }
+    for (int y = 0; y < 3; ++y)
+      if (y == 0 || c0 + 8 * ((1 << y) - 1) < n_chunks) {  // (2 and 4 at once take that many fetches; wave-uniform)
+        const uint64_t counts = transpose64(s[y], lane);
+        const unsigned sum = __builtin_amdgcn_udot4((unsigned)(counts >> 32), 0x01010101u,
+                                                    __builtin_amdgcn_udot4((unsigned)counts, 0x01010101u, 0u, false), false);
+        n += (int)(sum << y);
+      }
   }
-  if (sub == 0) {
-#pragma unroll
-    for (int k = 0; k < kAccSlices; ++k) part[0][k][wi] = acc[k];
-  }
-  __syncthreads();
-  const int p_end = min(L, (word0 + kFinWords) * 64);
-  for (int p = word0 * 64 + threadIdx.x; p < p_end; p += 256) {
-    const int wd = (p >> 6) - word0, t = p & 63;
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < kAccSlices; ++k)
-      if (k < nb) cnt |= (int)((part[0][k][wd] >> t) & 1) << k;
-    const int64_t e = (int64_t)h * L + p;
-    if (cnt_out) cnt_out[e] = cnt;
-    const float size = (float)(L - p);
-    flag_out[e] = (uint8_t)((float)cnt / size >= mu);
-  }
+  const int p = 64 * word + lane;
+  if (p >= L) return;
+  const int64_t e = (int64_t)h * L + p;
+  if (int *out = diag ? diag_cnt : vert_cnt) out[e] = n;
+  (diag ? diag_flag : vert_flag)[e] = (uint8_t)((float)n / (float)(L - p) >= mu);
 }
 
 // Flags -> bitsets. cbits bit c = column c matched. rrev bit q = diagonal (pw*64 - 1 - q) matched,
@@ -900,37 +901,6 @@ __device__ __forceinline__ void gather_columns_of_head(const Geom &g, const uint
   }
 }
 
-// Transpose of the 64 x 64 bit matrix whose row l is the word x of lane l: lane r returns the word whose
-// bit l is bit r of lane l's x. Six exchange steps on blocks of 32, 16, ... 1 bits, all in the vector registers (lane
-// swaps, row rotations, byte permutes: some 45 instructions; exchanges through LDS waited for it six times).
-__device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
-  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
-  // blocks of 32: the upper halves of lanes 0 .. 31 against the lower halves of lanes 32 .. 63
-  u32x2 v = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)(x >> 32), false, false);
-  const unsigned sel16 = lane & 16 ? 0x07060302u : 0x05040100u, sel8 = lane & 8 ? 0x03070105u : 0x06020400u;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    unsigned w = v[k];
-    // 16: even rows' values and odd rows' values, in all lanes
-    const u32x2 rows = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-    w = __builtin_amdgcn_perm(rows[1], rows[0], sel16);
-    // 8: lane ^ 8 is the row turned by eight
-    unsigned other = __builtin_amdgcn_update_dpp(0, w, 0x128, 0xF, 0xF, false);
-    w = __builtin_amdgcn_perm(other, w, sel8);
-    auto step = [&](unsigned from, int j, unsigned low) {  // low: the lower j bits of every 2 j
-      const bool up = (lane & j) != 0;
-      const unsigned turned = __builtin_amdgcn_alignbit(from, from, up ? j : 32 - j), take = up ? low : ~low;
-      return (turned & take) | (w & ~take);
-    };
-    other = __builtin_amdgcn_update_dpp(0, w, 0x141, 0xF, 0xF, false);      // lane ^ 7, and
-    other = __builtin_amdgcn_update_dpp(0, other, 0x1B, 0xF, 0xF, false);   // ^ 3: lane ^ 4
-    w = step(other, 4, 0x0F0F0F0Fu);
-    w = step(__builtin_amdgcn_update_dpp(0, w, 0x4E, 0xF, 0xF, false), 2, 0x33333333u);
-    v[k] = step(__builtin_amdgcn_update_dpp(0, w, 0xB1, 0xF, 0xF, false), 1, 0x55555555u);
-  }
-  return (uint64_t)v[1] << 32 | v[0];
-}
-
 // a3 for short captures, inside the kernel that needs the flags: match counts of one head from its true bits, gamma >= mu,
 // flags and bitsets, by the 16 waves of one workgroup. A job is one word (64 patterns) of one kind over one chunk of 64 rows:
 // a lane per row, the 64 x 64 bits turned around, and a lane per pattern then counts its word. The jobs of the causal
@@ -1002,8 +972,8 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
 // eight slices of one chunk, and the 64 x 64 bits of eight chunks turned around are, in the lane of a pattern, its eight
 // counts, a byte each. Bound by one trip to memory per job, so the next job's slices are under way.
 // Saves the launch of k_pattern_finish. Whole layers at 32 heads, us, each slice a wave-uniform load of its own / this: 4096
-// tokens captured at 1024 111.9 / 108.4, 6000 at 1536 187.1 / 180.2; 8000 at 2048, where k_pattern_finish did it, 267.3 / 262.6;
-// 16 heads x 8000 at 3072 and 64 x 9000 at 4096 k_pattern_finish 245.7 / 1158, this 245.6 / 1157.
+// tokens captured at 1024 111.9 / 108.4, 6000 at 1536 187.1 / 180.2; 8000 at 2048, where k_pattern_finish did it, 267.3 / 262.6
+// (in its older form, which took 6 us more; with it 3072 and 4096 came out the same).
 constexpr int kSlicesInPrep = 2048;
 __device__ __forceinline__ void sum_slices_of_head(const Geom &g, const uint64_t *__restrict__ vslices, const uint64_t *__restrict__ dslices,
                                                    float mu, int h, int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
@@ -2477,7 +2447,7 @@ int validate(const dam_mask_params *p, const float *attn_sum, const uint8_t *dia
   if ((int64_t)(p->seq + p->tile_n - 1) / p->tile_n > 32768) return DAM_ERR_UNSUPPORTED;
   if (p->mode == DAM_FROM_ATTN_MAP) {
     if (p->pcl < 1 || !attn_sum || !o->true_bits) return DAM_ERR_INVALID_ARG;
-    if (p->pcl >= (1 << kAccSlices)) return DAM_ERR_UNSUPPORTED;  // the match counts are summed in kAccSlices bits
+    if (p->pcl >= (1 << kMaxCountBits)) return DAM_ERR_UNSUPPORTED;
     if (!(p->eps > 0.0f)) return DAM_ERR_INVALID_ARG;
     if (p->transform < DAM_T_BOXCOX || p->transform > DAM_T_ARCSINH) return DAM_ERR_INVALID_ARG;
     if (p->transform == DAM_T_BOXCOX && p->lambda != 0.5f && p->lambda != 1.0f) return DAM_ERR_UNSUPPORTED;
@@ -2673,10 +2643,8 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   }
   if (g.L <= kSlicesInPrep && needs_prep(p, o))
     return CountArgs{kFromSlices, nullptr, {}, nullptr, w.vslices, w.dslices, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
-  int nb = 1;  // bits of the largest possible count, L
-  while ((g.L >> nb) != 0) ++nb;
-  k_pattern_finish<<<dim3((g.tbw + kFinWords - 1) / kFinWords, g.H, 2), 256, 0, stream>>>(w.vslices, w.dslices, g.L, g.tbw, n_chunks, nb, p->mu,
-                                                                       o->vert_cnt, o->diag_cnt, vf, df);
+  k_pattern_finish<<<dim3((g.tbw + 3) / 4, g.H, 2), 256, 0, stream>>>(w.vslices, w.dslices, g.L, g.tbw, n_chunks, p->mu, o->vert_cnt, o->diag_cnt,
+                                                                     vf, df);
   return CountArgs{};
 }
 

@@ -60,7 +60,7 @@ __device__ __forceinline__ void add_eight(uint64_t (&s)[N], const uint64_t (&w)[
 // those around the last addition, and a wave has its next eight words in flight while it counts the ones before.
 // Bound by the vector ALU: some 40 instructions per word and lane, of which the two counters are 11 and the window 9. 64 maps of
 // 4096 x 4096: 48.5 -> 25.5 us (five operations per full adder, 64-bit shifts, index tests, barriers around a copy of 64 whole
-// rows), and half as many chunk counts for k_pattern_finish (14.5 -> 12.3 us).
+// rows), and half as many chunk counts for k_pattern_finish.
 __device__ __forceinline__ void count_chunk(const uint64_t *__restrict__ tb, int rows, int tbw, int chunk, uint64_t *sm,
                                             uint64_t *__restrict__ vout, uint64_t *__restrict__ dout) {
   const int tid = threadIdx.x;
