@@ -51,6 +51,8 @@ __device__ __forceinline__ int wave_prefix(int v) {
   return v;
 }
 
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_prefix(v), 63); }
+
 // 16 bytes to memory past this XCD's L2, for readers on other XCDs; not complete before stores_done()
 __device__ __forceinline__ void store_through(void *p, float x, float y, float z, float w) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;

@@ -1564,24 +1564,25 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   // where this query tile's entries start: the listed tiles of the heads before h and of the query tiles before
   // qt (no scan kernel between the two passes: the counts are few enough for every wave to add up its own prefix)
   int64_t part = 0;
-  // (Both as one list, in batches of loads that travel together, the last of them with the places past the end repeated and
-  // left out: one trip for up to 512 counts. In whole batches of eight, four and one and each list by itself the waits were up
-  // to nine, at 32 heads x 32 query tiles 2.6 us of the kernel's 11.)
-  const int n_head = h * kHeadSub, n_before = n_head + qt;
+  // (Both as one list, dealt out over the workgroup's waves, which share all of it but the query tiles of the workgroup itself; a
+  // wave's loads travel together, places past the end repeated and left out. Each wave by itself, in batches of eight, four and
+  // one and list by list, the waits were up to nine, at 32 heads x 32 query tiles 2.6 us of the kernel's 11.)
+  __shared__ int64_t s_before[4];
+  const int each = share == 4 ? 1 : 4, at0 = my.at * each;  // the workgroup's first query tile
+  const int n_head = h * kHeadSub, n_before = n_head + at0;
   const int *cnt_h = tile_cnt + (int64_t)h * g.nQt;
-  auto count_at = [&](int x) { return x < n_head ? head_cnt + x : cnt_h + (x - n_head); };
-  auto batch = [&](int x0, auto k) {
-    constexpr int K = decltype(k)::value;
-    int v[K];
+  for (int x0 = wave * 64; x0 < n_before; x0 += 1024) {
+    int v[4];
 #pragma unroll
-    for (int y = 0; y < K; ++y) v[y] = *count_at(min(x0 + 64 * y + lane, n_before - 1));
+    for (int y = 0; y < 4; ++y) {
+      const int x = min(x0 + 256 * y + lane, n_before - 1);
+      v[y] = *(x < n_head ? head_cnt + x : cnt_h + (x - n_head));
+    }
 #pragma unroll
-    for (int y = 0; y < K; ++y) part += x0 + 64 * y + lane < n_before ? v[y] : 0;
-  };
-  int x0 = 0;
-  for (; x0 + 128 < n_before; x0 += 512) batch(x0, std::integral_constant<int, 8>{});
-  if (x0 < n_before) batch(x0, std::integral_constant<int, 2>{});
-  const int my_cnt = cnt_h[qt];
+    for (int y = 0; y < 4; ++y) part += x0 + 256 * y + lane < n_before ? v[y] : 0;
+  }
+  const int mine4 = cnt_h[min(at0 + min(lane, each - 1), g.nQt - 1)];  // the workgroup's own counts, one per lane
+  const int my_cnt = __builtin_amdgcn_readlane(mine4, qt - at0);
   // the walk's index words, a word of 64 tiles per lane, the first 64 of them before the sets are staged
   uint64_t ow_mine = lane < n_words ? oc[lane] : 0, fw_mine = lane < n_words ? fl[lane] : 0;
   // gathered columns: the ordinary tiles of a query tile of the pattern region hold the diagonal part only
@@ -1595,10 +1596,15 @@ __global__ __launch_bounds__(256) void k_tile_fill(Geom g, const uint64_t *__res
   if (split && tile_m == tile_n && (qt + 1) * tile_m <= g.S)
     r_bound = farthest_tile(classes + ((int64_t)h * 4 + kOffAny) * g.occw, g.occw, lane) * tile_n + tile_n - 1;
   const uint64_t vow0 = split ? voc[0] : 0, vfw0 = split ? vfl[0] : 0;  // (not written where there is no gathered tile)
+  {
+    const int low = wave_total((int)(part & 0xFFFFFF)), high = wave_total((int)(part >> 24));  // (64 lanes' sums fit 32 bits each)
+    if (lane == 0) s_before[wave] = ((int64_t)high << 24) + low;
+  }
   if (STAGED) stage_sets(lds_sets, g.pw, cb, rr);
+  else __syncthreads();
   if (!live) return;
-  for (int off = 32; off; off >>= 1) part += __shfl_xor(part, off);
-  const int64_t first = part;
+  int64_t first = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+  for (int y = 0; y < qt - at0; ++y) first += __builtin_amdgcn_readlane(mine4, y);
   if (lane == 0 && my_turn == 0) {  // the CSR offsets, cut to the capacity like everything they point into
     int *rp = row_ptr + (int64_t)h * (g.nQt + 1);
     rp[qt] = (int)min(first, capacity);
@@ -1996,8 +2002,6 @@ __device__ __forceinline__ void row_pieces(const Geom &g, const uint64_t *__rest
     any |= m[x];
   }
 }
-
-__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_prefix(v), 63); }
 
 // cnt[(kv * (G + 1) + run) * spans + span]
 __global__ __launch_bounds__(256) void k_list_count(Geom g, const uint64_t *__restrict__ true_bits,
