@@ -72,24 +72,31 @@ struct AttnArgs {
 // A wave has three blocks on average in the size below, so the time is as much the list in front of them (4 us, a chain of
 // loads) and the first block's loads as the products: the matrix rate (64 flop per cycle and SIMD) is used to about 30 % on the
 // blocks that are issued, each of which brings 16 KiB of K and V from L2 however few of its entries are kept. 2 sequences x 8
-// heads x 1500 keys, d 128, windows and stripes (46 % of the issued entries kept) 51.5 us, 55.7 with V fetched in front of its
-// own block's Q K products; 4 x 16 heads x 2000 351 -> 336, d 64 186 -> 183; 1 x 4 x 300 12.8 -> 11.7. With the older form: 391 -> 60 us against a row per d / 4
-// plain lanes, each visiting its kept keys only (Q in LDS for a third workgroup per CU spilled: 154 us). At the same size
+// heads x 1500 keys, d 128, windows and stripes (46 % of the issued entries kept) 46.2 us; 55.7 with V fetched in front of its
+// own block's Q K products and two workgroups on a CU, 51.4 with the fetches as they are (1 x 4 x 300 12.8 -> 11.7). That form
+// before it: 391 -> 60 us against a row per d / 4 plain lanes, each visiting its kept keys only. At the same size
 // a window of 64 101 -> 34 us; where nothing but isolated diagonals is kept (9 to 14 entries per block) the plain lanes
 // were faster, 1 % of the diagonals 50 -> 63 us, 4 % 92 -> 114, 10 % 176 -> 130.
 constexpr int kF32Seg = 64;  // listed tiles expanded at a time
 
 // GATHER: the block index may hold gathered column tiles, whose key rows are looked up in gather_idx. (A template
 // argument, because the look-up in front of every row's address makes the loads of a block wait for each other.)
-template <int D, bool GATHER>
-__global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float *__restrict__ q, const float *__restrict__ k,
-                                                        const float *__restrict__ v, const int *__restrict__ row_ptr,
-                                                        const int *__restrict__ blk_col, const uint8_t *__restrict__ blk_kind,
-                                                        const uint64_t *__restrict__ tile_bits,
-                                                        const int *__restrict__ gather_idx, float *__restrict__ out,
-                                                        float *__restrict__ lse) {
-  constexpr int CK = D / 16, HV = D / 64, kPad = D + 4;  // (rows of the merge area padded: 16 rows, 16 different banks)
-  typedef __attribute__((ext_vector_type(4))) float f32x4;
+//
+// ODD: for row groups whose V holds an infinity or a NaN in a block that they visit. It must reach the rows that keep that key and
+// no others, and a product would multiply it with the others' zero weights, so such a block's kept entries are added one by one.
+// The first form (ODD = false) only notices; the workgroup then takes its rows again through the second, a function of its own:
+// with both ways behind a branch of the loop the kernel holds 242 registers instead of 168, two workgroups on a CU instead of three.
+struct F32Args {
+  AttnArgs a;
+  const float *q, *k, *v;
+  const int *row_ptr, *blk_col;
+  const uint8_t *blk_kind;
+  const uint64_t *tile_bits;
+  const int *gather_idx;
+  float *out, *lse;
+};
+template <int D>
+struct F32Lds {
   // one LDS area, two lives: mask words, columns and block list of a segment of tiles; then the waves' partial results
   struct Lists {
     unsigned words[kF32Seg][64];  // [tile][32-key word g * 16 + row]
@@ -98,12 +105,25 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
     unsigned short blk[kF32Seg * 8];
   };
   struct Parts {
-    float o[4][16 * kPad];
+    float o[4][16 * (D + 4)];  // (rows padded: 16 rows, 16 different banks)
     float m[4][16], l[4][16];
     unsigned any[4][16];
+    int odd[4];
   };
-  constexpr size_t kLds = sizeof(Lists) > sizeof(Parts) ? sizeof(Lists) : sizeof(Parts);
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  static constexpr size_t kBytes = sizeof(Lists) > sizeof(Parts) ? sizeof(Lists) : sizeof(Parts);
+};
+
+// Whether the rows have to be taken again (ODD = false).
+template <int D, bool GATHER, bool ODD>
+__device__ __forceinline__ bool prefill_f32_rows(const AttnArgs &a, const float *__restrict__ q, const float *__restrict__ k,
+                                                 const float *__restrict__ v, const int *__restrict__ row_ptr,
+                                                 const int *__restrict__ blk_col, const uint8_t *__restrict__ blk_kind,
+                                                 const uint64_t *__restrict__ tile_bits, const int *__restrict__ gather_idx,
+                                                 float *__restrict__ out, float *__restrict__ lse, unsigned char *lds) {
+  constexpr int CK = D / 16, HV = D / 64, kPad = D + 4;
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  using Lists = typename F32Lds<D>::Lists;
+  using Parts = typename F32Lds<D>::Parts;
   Lists &L = *reinterpret_cast<Lists *>(lds);
   Parts &P = *reinterpret_cast<Parts *>(lds);
 
@@ -116,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
   const int pair = even ? blockIdx.x / kXcd / per_pair * kXcd + blockIdx.x % kXcd : blockIdx.x % n_pairs;
   const int wb = pair / a.Hkv, whkv = pair % a.Hkv, whq = whkv * G + within % G;
   const int wqt = a.nQt - 1 - within / (G * RG), rg = RG - 1 - within / G % RG, row0 = wqt * a.tile_m + rg * 16;
-  if (row0 >= a.S) return;
+  if (row0 >= a.S) return false;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int i = row0 + r16;
@@ -137,6 +157,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
   for (int x = 0; x < HV * 4; ++x) o[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.0f;  // of the lane's row; l is this lane's part
   unsigned any = 0;               // bits of kept keys
+  float odd_any = 0.0f;           // 0, or NaN when a V entry was infinite or NaN
 
   for (int seg = t0; seg < t1; seg += kF32Seg) {
     const int n_seg = min(kF32Seg, t1 - seg);
@@ -220,7 +241,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      float p[4], mx = m, odd = 0.0f;
+      float p[4], mx = m, odd = ODD ? 0.0f : odd_any;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         p[r] = (kept >> (4 * g + r)) & 1 ? (s0[r] + s1[r]) * a.scale : -INFINITY;
@@ -250,7 +271,8 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
           odd = fmaf(vf[r][h].z, 0.0f, fmaf(vf[r][h].w, 0.0f, odd));
         }
       }
-      if (__ballot(odd != 0.0f) == 0) {
+      if (!ODD) odd_any = odd;
+      if (!ODD || __ballot(odd != 0.0f) == 0) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -265,8 +287,6 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
             }
           }
       } else {
-        // a V row of the block holds an infinity or a NaN: it must reach the rows that keep that key and no others
-        // (a product would multiply it with the others' zero weights), so the kept entries are added one by one
 #pragma unroll 1
         for (int key = 0; key < 16; ++key) {
           const float pk = __shfl(key & 2 ? (key & 1 ? p[3] : p[2]) : (key & 1 ? p[1] : p[0]), r16 + 16 * (key >> 2));
@@ -317,6 +337,10 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
     P.l[wave][r16] = l;
     P.any[wave][r16] = any;
   }
+  if (!ODD) {
+    const bool odd = __ballot(odd_any != 0.0f) != 0;
+    if (lane == 0) P.odd[wave] = odd;
+  }
 #pragma unroll
   for (int h = 0; h < HV; ++h)
 #pragma unroll
@@ -324,8 +348,9 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
       *reinterpret_cast<float4 *>(&P.o[wave][r16 * kPad + 64 * h + 16 * g + 4 * r]) =
           make_float4(o[4 * h][r], o[4 * h + 1][r], o[4 * h + 2][r], o[4 * h + 3][r]);
   __syncthreads();
+  if (!ODD && (P.odd[0] | P.odd[1] | P.odd[2] | P.odd[3])) return true;
   const int row = threadIdx.x >> 4, part = threadIdx.x & 15;
-  if (row0 + row >= a.S) return;
+  if (row0 + row >= a.S) return false;
   float M = fmaxf(fmaxf(P.m[0][row], P.m[1][row]), fmaxf(P.m[2][row], P.m[3][row])), sum = 0.0f, wt[4];
 #pragma unroll
   for (int y = 0; y < 4; ++y) {
@@ -350,6 +375,40 @@ __global__ __launch_bounds__(256, 2) void k_prefill_f32(AttnArgs a, const float 
         make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
   }
   if (lse && part == 0) lse[((int64_t)wb * a.Hq + whq) * a.S + row0 + row] = sum > 0.0f ? M + logf(sum) : -INFINITY;
+  return false;
+}
+
+template <int D, bool GATHER>
+__device__ __attribute__((noinline)) void prefill_f32_odd_rows(uint64_t args_at, __attribute__((address_space(3))) unsigned char *lds) {
+  // (an argument in vector registers, the same in every lane)
+  const uint64_t at = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(args_at >> 32)) << 32 |
+                      (unsigned)__builtin_amdgcn_readfirstlane((int)args_at);
+  const F32Args &t = *(const F32Args *)(const __attribute__((address_space(4))) F32Args *)at;
+  prefill_f32_rows<D, GATHER, true>(t.a, t.q, t.k, t.v, t.row_ptr, t.blk_col, t.blk_kind, t.tile_bits, t.gather_idx, t.out, t.lse,
+                                    (unsigned char *)lds);
+}
+
+template <int D, bool GATHER>
+__global__ __launch_bounds__(256, D == 128 ? 3 : 4) void k_prefill_f32(F32Args t) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[F32Lds<D>::kBytes];
+  if (!prefill_f32_rows<D, GATHER, false>(t.a, t.q, t.k, t.v, t.row_ptr, t.blk_col, t.blk_kind, t.tile_bits, t.gather_idx, t.out, t.lse, lds))
+    return;
+  __syncthreads();
+  prefill_f32_odd_rows<D, GATHER>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), (__attribute__((address_space(3))) unsigned char *)lds);
+}
+
+// No more workgroups than the chip takes two to a CU: they are all there at once then, and the second form alone is the faster one
+// (no private memory to set up: 1 x 4 heads x 300 tokens 11.85 us against 12.0; 11.75 before there were two forms). From there on the first: 2 x 8 x 1500, d 128, 51.4 -> 46.2 us, 4 x 16 x 2000 336 -> 292, d 64 183 -> 166, 3 x 8 x 700
+// 23.0 -> 20.5.
+constexpr int kF32Few = 512;
+template <int D, bool GATHER>
+__global__ __launch_bounds__(256, 2) void k_prefill_f32_few(AttnArgs a, const float *__restrict__ q, const float *__restrict__ k,
+                                                            const float *__restrict__ v, const int *__restrict__ row_ptr,
+                                                            const int *__restrict__ blk_col, const uint8_t *__restrict__ blk_kind,
+                                                            const uint64_t *__restrict__ tile_bits, const int *__restrict__ gather_idx,
+                                                            float *__restrict__ out, float *__restrict__ lse) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[F32Lds<D>::kBytes];
+  prefill_f32_rows<D, GATHER, true>(a, q, k, v, row_ptr, blk_col, blk_kind, tile_bits, gather_idx, out, lse, lds);
 }
 
 // ================================================================================================
@@ -1408,10 +1467,19 @@ extern "C" int dam_sparse_attn_prefill(const dam_attn_params *p, const void *q, 
   }
   if (p->dtype == DAM_F32) {
     // (a list shorter than a tile's slots holds no gathered tile, and the kernel that looks slots up would read past it)
-    auto kern = mk->gather_idx && mk->gather_stride >= p->tile_n ? (p->head_dim == 64 ? k_prefill_f32<64, true> : k_prefill_f32<128, true>)
-                                                                     : (p->head_dim == 64 ? k_prefill_f32<64, false> : k_prefill_f32<128, false>);
-    kern<<<p->batch * p->hq * a.nQt * (p->tile_m / 16), 256, 0, st>>>(a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr, mk->blk_col,
-                                                    mk->blk_kind, mk->tile_bits, mk->gather_idx, (float *)out, lse);
+    const bool looks_up = mk->gather_idx && mk->gather_stride >= p->tile_n;
+    const int groups = p->batch * p->hq * a.nQt * (p->tile_m / 16);
+    const F32Args t{a, (const float *)q, (const float *)k, (const float *)v, mk->blk_row_ptr, mk->blk_col, mk->blk_kind, mk->tile_bits,
+                    mk->gather_idx, (float *)out, lse};
+    if (groups <= kF32Few) {
+      auto kern = looks_up ? (p->head_dim == 64 ? k_prefill_f32_few<64, true> : k_prefill_f32_few<128, true>)
+                           : (p->head_dim == 64 ? k_prefill_f32_few<64, false> : k_prefill_f32_few<128, false>);
+      kern<<<groups, 256, 0, st>>>(a, t.q, t.k, t.v, t.row_ptr, t.blk_col, t.blk_kind, t.tile_bits, t.gather_idx, t.out, t.lse);
+    } else {
+      auto kern = looks_up ? (p->head_dim == 64 ? k_prefill_f32<64, true> : k_prefill_f32<128, true>)
+                           : (p->head_dim == 64 ? k_prefill_f32<64, false> : k_prefill_f32<128, false>);
+      kern<<<groups, 256, 0, st>>>(t);
+    }
     return launch_status();
   }
   const int blocks = p->batch * p->hq * a.nQt;  // work items

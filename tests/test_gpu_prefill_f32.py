@@ -33,6 +33,8 @@ def run(Q, K, V, mask):
 @pytest.mark.parametrize("Hq,Hkv,S,d,tile,flags", [
     (2, 1, 1, 64, 64, 0), (2, 2, 15, 128, 128, 0), (4, 2, 17, 64, 128, 0), (2, 1, 65, 128, 64, 0),
     (8, 8, 130, 64, 64, 0), (16, 8, 259, 128, 128, B.DAM_MASK_GATHER_COLUMNS), (3, 3, 640, 64, 64, B.DAM_MASK_GATHER_COLUMNS),
+    (12, 4, 700, 128, 64, 0), (12, 6, 690, 64, 128, B.DAM_MASK_GATHER_COLUMNS),  # more than 512 workgroups
+    (16, 2, 1021, 128, 128, B.DAM_MASK_GATHER_COLUMNS),
     (1, 1, 64 * 66 + 5, 64, 64, 0),                 # more listed tiles in a row than one segment holds
 ])
 def test_edges_of_groups_blocks_and_segments(Hq, Hkv, S, d, tile, flags):
@@ -44,16 +46,28 @@ def test_edges_of_groups_blocks_and_segments(Hq, Hkv, S, d, tile, flags):
     assert np.abs(lse - LSE).max() <= TOL
 
 
-def test_a_row_does_not_see_what_it_does_not_keep():
+# in few workgroups (one form of the kernel) and in more than 512 of them (whose second form takes such rows again)
+@pytest.mark.parametrize("copies,d", [(1, 128), (40, 128), (40, 64)])
+def test_a_row_does_not_see_what_it_does_not_keep(copies, d):
     """A NaN and an infinity in V rows reach exactly the query rows that keep those keys."""
-    S, d = 200, 128
+    S = 200
     Q, K, V, art = inputs(2, 1, S, d, 5)
-    V[0, 37, 3], V[0, 101, 70] = np.nan, np.inf
-    out, _ = run(Q, K, V, gpu_mask_from_art(art, S, 64, 64))
+    V[0, 37, 3], V[0, 101, 60] = np.nan, np.inf
+    mask = gpu_mask_from_art(art, S, 64, 64)
+    t = lambda x: torch.from_numpy(x)[None].cuda().repeat(copies, 1, 1, 1)
+    v = t(V)
+    v[1:, 0, 37, 3] = v[1:, 0, 101, 60] = 1.0  # (the other sequences' values are finite)
+    outs, lses = B.dam_sparse_attn_prefill(t(Q), t(K), v, mask, want_lse=True)
+    out = outs[0].cpu().numpy()
+    if copies > 1:
+        Vf = V.copy()
+        Vf[0, 37, 3] = Vf[0, 101, 60] = 1.0
+        O, LSE = oracle.attend_prefill(Q, K, Vf, art)
+        assert np.abs(outs[-1].cpu().numpy() - O).max() <= TOL and np.abs(lses.cpu().numpy() - LSE).max() <= TOL
     i = np.arange(S)
     for h, keeps in ((0, lambda j: i >= j), (1, lambda j: (i >= j) & ((i - j < 8) | (j % 20 == 0)))):
         assert np.array_equal(np.isnan(out[h, :, 3]), keeps(37))
-        assert np.array_equal(np.isinf(out[h, :, 70]), keeps(101))
+        assert np.array_equal(np.isinf(out[h, :, 60]), keeps(101))
         assert np.isfinite(out[h, :, 5]).all()
 
 
