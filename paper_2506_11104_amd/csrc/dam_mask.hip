@@ -610,10 +610,6 @@ __global__ __launch_bounds__(256) void k_pattern_finish(const uint64_t *__restri
   (diag ? diag_flag : vert_flag)[e] = (uint8_t)((float)n / (float)(L - p) >= mu);
 }
 
-// Flags -> bitsets. cbits bit c = column c matched. rrev bit q = diagonal (pw*64 - 1 - q) matched,
-// i.e. the diagonal set reversed, so that the 64 offsets i-j, i-j-1, ... of one mask word are 64
-// consecutive ascending bits. Four lanes build one word: each turns 16 flag bytes (one 16-byte
-// load when the row is aligned) into 16 bits.
 // Eight flag bytes, four to a word, as eight bits: each byte's top bit is set where the byte is not zero, and a dot product with
 // the bits' places adds them up (128 times the result). The multiplications that gather such bits otherwise run at a quarter of
 // the rate.
@@ -623,7 +619,10 @@ __device__ __forceinline__ unsigned bits_of_8(unsigned lo, unsigned hi) {
 }
 __device__ __forceinline__ unsigned bits_of_16(const uint4 &v) { return bits_of_8(v.x, v.y) | bits_of_8(v.z, v.w) << 8; }
 
-// (every thread of the workgroup calls this; 512 words per pass)
+// Flags -> bitsets. cbits bit c = column c matched. rrev bit q = diagonal (pw*64 - 1 - q) matched,
+// i.e. the diagonal set reversed, so that the 64 offsets i-j, i-j-1, ... of one mask word are 64
+// consecutive ascending bits. Four lanes build one word, 16 flag bytes each. (every thread of the workgroup calls this; 512 words
+// per pass)
 // A piece is read where it lies, at any alignment, and one that the row's end cuts from 16 bytes before that end and shifted:
 // no lane is asked, so all of a pass's loads are under way together. (Aligned rows by 16 bytes with a branch around the last
 // piece, others byte by byte: 4.2 us of the prep kernel at 32 heads x 32768 tokens, now 2.7.)
@@ -907,11 +906,11 @@ __device__ __forceinline__ void gather_columns_of_head(const Geom &g, const uint
 // triangle go round the waves and add into LDS.
 // In place of the launches that longer captures take (k_pattern_slices, and k_pattern_finish or sum_slices_of_head), which
 // cost 5 us each however short they are. The jobs grow with the square of the capture and run on one CU per head, so the line
-// lies where the gain ends; whole builds, the launches / this, us: 32 heads x 320 35.9 / 31.8, x 512 42.7 / 40.0, x 768 52.1 /
-// 52.4, x 1024 63.1 / 68.0, 16 x 640 38.8 / 37.8, 64 x 768 72.8 / 72.2, 64 x 1024 98.3 / 102.7, 8 x 1024 42.0 / 47.8. A word
-// further where nothing follows the counts, so that the launches are two where this is one: 1 head x 832 17.8 / 17.1, 8 x 832
-// 19.8 / 18.9, 96 x 832 57.9 / 56.1, 96 x 769 60.6 / 58.9; 1 x 896 18.1 / 18.8, 32 x 896 30.4 / 31.6, 96 x 896 61.8 / 61.6.
-constexpr int kDirectL = 768, kDirectAloneL = 832;
+// lies where the gain ends; whole layers of 4000 tokens, the launches / this, us: 8 heads captured at 576 61.0 / 57.3, 768 61.5 / 60.0,
+// 832 70.3 / 69.5, 1024 68.7 / 72.2; 32 heads 85.2 / 81.3, 93.3 / 91.2, 101.1 / 100.0, 105.4 / 108.6; 64 heads 131.3 / 127.2, 138.7 / 136.7,
+// 157.2 / 155.1, 170.2 / 172.2. Patterns alone, where the launches are two and this is one: 1 head x 832 17.8 / 17.1, 96 x 832
+// 57.9 / 56.1; 1 x 896 18.1 / 18.8, 32 x 896 30.4 / 31.6, 96 x 896 61.8 / 61.6.
+constexpr int kDirectL = 832;
 template <int MOST>
 __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint64_t *__restrict__ tb,  // the head's true bits
                                                        float mu, int h, int *cnt,                       // LDS [2][MOST]
@@ -1354,11 +1353,11 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   const int h = blockIdx.x;
   if (threadIdx.x < kHeadSub) head_cnt[h * kHeadSub + threadIdx.x] = 0;  // the head's number of listed tiles: summed by k_tile_scan
   uint64_t *copy = in_lds && want_classes ? prep_sets : nullptr;
-  __shared__ int cnt[SOURCE == kFromTrueBits ? 2 * kDirectAloneL : SOURCE == kFromMap ? 2 * kMapInPrep : 1];
+  __shared__ int cnt[SOURCE == kFromTrueBits ? 2 * kDirectL : SOURCE == kFromMap ? 2 * kMapInPrep : 1];
   __shared__ uint64_t true_words[SOURCE == kFromMap ? kMapInPrep * kMapInPrep / 64 : 1];
   if constexpr (SOURCE == kFromTrueBits) {
-    count_patterns_of_head<kDirectAloneL>(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
-                                          ca.diag_flag, cbits, rrev, copy);
+    count_patterns_of_head<kDirectL>(g, ca.true_bits + (int64_t)h * g.L * g.tbw, ca.mu, h, cnt, ca.vert_cnt, ca.diag_cnt, ca.vert_flag,
+                                     ca.diag_flag, cbits, rrev, copy);
   } else if constexpr (SOURCE == kFromMap) {
     true_mask_of_head(g, ca.map + (int64_t)h * g.L * g.L, take_threshold(ca.thr), true_words, ca.true_bits + (int64_t)h * g.L * g.tbw);
     __syncthreads();
@@ -2630,9 +2629,7 @@ size_t prep_lds_bytes(const Geom &g) {
 bool scans_in_prep(const Geom &g, const dam_mask_out *o) { return o->blk_row_ptr && prep_lds_bytes(g) > 0 && g.nQt <= kScanInPrep; }
 
 // Whether k_pattern_prep counts the patterns itself (short captures, see count_patterns_of_head).
-bool counts_in_prep(const dam_mask_params *p, const Geom &g, const dam_mask_out *o) {
-  return g.L <= kDirectL || (g.L <= kDirectAloneL && !needs_prep(p, o));
-}
+bool counts_in_prep(const Geom &g) { return g.L <= kDirectL; }
 
 // a3: match scores of the true mask in o->true_bits; says where the flags are written, and (short captures) what
 // k_pattern_prep has to count for that. counted: the chunks' slices are there already. map: k_pattern_prep makes the true mask
@@ -2645,7 +2642,7 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   *dflag = df;
   *vflag = vf;
   if (o->bmin && !bmin_written) k_copy_f32<<<1, 64, 0, stream>>>(o->bmin, w.bmin);
-  if (counts_in_prep(p, g, o))
+  if (counts_in_prep(g))
     return CountArgs{map ? kFromMap : kFromTrueBits, map, thr, o->true_bits, nullptr, nullptr, p->mu, o->vert_cnt, o->diag_cnt, vf, df};
   const int n_chunks = (g.L + kChunkRows - 1) / kChunkRows;
   if (counted) {
@@ -2864,7 +2861,7 @@ extern "C" int dam_mask_build_from_qk(const dam_mask_params *p, const dam_captur
   // (one causal capture of two tokens or more: the minimum, and so the threshold, is known on the host)
   const Threshold thr = stage_threshold(p, g, w, nullptr, nullptr, stream, o->bmin, &bmin_written);
   const bool counted = launch_capture_true_bits(cp, q, k, lse2, thr.theta_val, thr.bmin_val, thr.bmin_out, o->true_bits,
-                                                counts_in_prep(p, g, o) ? nullptr : w.vslices, w.dslices, stream);
+                                                counts_in_prep(g) ? nullptr : w.vslices, w.dslices, stream);
   const CountArgs count = stage_patterns(p, g, w, o, stream, &dflag, &vflag, bmin_written, counted);
   stage_extension(p, g, w, o, o->true_bits, dflag, vflag, count, stream);
   return launch_status();

@@ -1,4 +1,4 @@
-"""Short captures: pattern counts taken inside the prep kernel (up to 768 tokens, 832 where nothing follows them), and query tiles inside the true-mask
+"""Short captures: pattern counts taken inside the prep kernel (up to 832 tokens), and query tiles inside the true-mask
 block, whose tiles the scan looks at four at a time. Bit for bit against the oracle."""
 import numpy as np
 import pytest
