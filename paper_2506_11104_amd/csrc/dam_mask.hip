@@ -366,9 +366,12 @@ __global__ __launch_bounds__(256) void k_true_mask(const float *__restrict__ A, 
 }
 
 // The same for the common case (no count matrix, L a multiple of 4) at streaming speed: one wave per
-// row, 16-byte loads, the live 256-key segments of a 2048-key span in flight at once, and the row's
-// words gathered into lanes so that they leave as one coalesced store (single 8-byte stores from one
+// row, 16-byte loads, the live 256-key segments of a 2048-key span in flight at once (of the last one what lies up to the
+// diagonal), and the row's bits gathered into lanes so that they leave as one coalesced store (single 8-byte stores from one
 // lane made the store path the bottleneck).
+// Bound by the reads where the maps are long, by instructions too where they are short; us, with the last segment read whole and
+// its bits gathered by a ballot for each component and word / this: 32 maps of 1024 21.8 / 16.8, 64 of 4096 437 / 411 (5.2 TB/s);
+// layers of 4000 tokens captured at 512 73.4 / 69.9, 64 heads x 2000 at 256 65.6 / 62.7.
 __device__ __forceinline__ float4 load_once(const float4 *p) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
@@ -384,45 +387,45 @@ __device__ __forceinline__ void true_mask_row(const float *__restrict__ A, int L
                                               uint64_t *__restrict__ true_bits, int lane) {
   const int i = __builtin_amdgcn_readfirstlane(i_any);
   const float4 *row = reinterpret_cast<const float4 *>(A + ((int64_t)h * L + i) * L);
-  uint64_t *out = true_bits + ((int64_t)h * L + i) * tbw;
+  unsigned *out = reinterpret_cast<unsigned *>(true_bits + ((int64_t)h * L + i) * tbw);
   const int nseg = i / 256 + 1;  // segments with a key <= i
-  const int c = lane & 3;
   const float theta_f = value_of(theta);
+  const unsigned place = 1u << (4 * (lane & 7));  // of the lane's first key among those of its eight lanes
   constexpr int kSeg = 8;  // 256-key segments in flight per pass
   for (int s0 = 0; s0 * 4 < tbw; s0 += kSeg) {
     float4 v[kSeg];
 #pragma unroll
     for (int u = 0; u < kSeg; ++u) {
       const int j0 = (s0 + u) * 256 + lane * 4;
-      v[u] = (s0 + u < nseg && j0 < L) ? load_once(row + (s0 + u) * 64 + lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[u] = (s0 + u < nseg && j0 <= i) ? load_once(row + (s0 + u) * 64 + lane) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    uint64_t mine = 0;  // word s0 * 4 + lane of the row
+    // Eight lanes' 32 keys are 32 bits next to each other: put together by their places, OR over the eight lanes. Of the eight
+    // lanes, lane u keeps segment u's.
+    unsigned mine = 0;
 #pragma unroll
     for (int u = 0; u < kSeg; ++u) {
       if (s0 + u < nseg) {  // wave-uniform
         const int j0 = (s0 + u) * 256 + lane * 4;
-        float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        uint64_t b[4];
+        const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        unsigned bits = 0;
         if (FAST && s0 + u < nseg - 1) {  // every key of the segment is <= i
 #pragma unroll
-          for (int e = 0; e < 4; ++e) b[e] = __ballot(x[e] >= theta_f);
+          for (int e = 0; e < 4; ++e) bits |= x[e] >= theta_f ? place << e : 0u;
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float val = x[e] != x[e] ? -INFINITY : x[e];
-            b[e] = __ballot(j0 + e <= i && key_of(val) >= theta);  // bit l: key 4 l + e of the segment
+            bits |= j0 + e <= i && key_of(val) >= theta ? place << e : 0u;
           }
         }
-        // lane l of word w is key 64 w + l = component l % 4 of lane 16 w + l / 4
-        const uint64_t sel = c == 0 ? b[0] : c == 1 ? b[1] : c == 2 ? b[2] : b[3];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint64_t word = __ballot((sel >> (16 * w + (lane >> 2))) & 1);
-          if (lane == u * 4 + w) mine = word;
-        }
+        bits |= __builtin_amdgcn_update_dpp(0, bits, 0xB1, 0xF, 0xF, false);   // the other lane of two
+        bits |= __builtin_amdgcn_update_dpp(0, bits, 0x4E, 0xF, 0xF, false);   // the other two of four
+        bits |= __builtin_amdgcn_update_dpp(0, bits, 0x141, 0xF, 0xF, false);  // the other four of eight
+        if ((lane & 7) == u) mine = bits;
       }
     }
-    if (lane < 4 * kSeg && s0 * 4 + lane < tbw) out[s0 * 4 + lane] = mine;
+    mine = __builtin_amdgcn_ds_bpermute(4 * ((lane & 7) * 8 + (lane >> 3)), mine);  // lane 8 u + d: 32 keys d of segment u
+    if (s0 * 8 + lane < 2 * tbw) out[s0 * 8 + lane] = mine;
   }
 }
 

@@ -56,6 +56,19 @@ def test_pattern_counts_alone_on_both_sides_of_the_line(L, copies):
         assert np.array_equal(getattr(mask, name).cpu().numpy(), np.tile(getattr(art, name), (copies, 1))), name
 
 
+# rows read 256 keys to a segment and eight segments to a pass: captures around both, rows that end within a lane's four keys
+@pytest.mark.parametrize("L", [132, 252, 256, 260, 508, 516, 2044, 2048, 2052, 2308])
+@pytest.mark.parametrize("tau", [0.02, -1.0])
+def test_true_mask_of_rows(L, tau):
+    A = synth_map(np.random.default_rng(L), 2, L)
+    A[0, L // 2, ::3] = np.nan
+    A[1, L - 1, ::5] = np.inf
+    m = B.build_mask(mode=B.DAM_FROM_ATTN_MAP, H=2, L=L, S=L, lam=0.5, eps=1e-8, tau=tau, mu=0.3, attn_sum=torch.from_numpy(A).cuda(),
+                     blocks=False)
+    art = oracle.derive(A, None, 0.5, 1e-8, tau, 0.3)
+    assert np.array_equal(u64(m.true_bits), pack_rows_u64(art.true_mask))
+
+
 # captures whose true mask the prep kernel makes itself (up to 128 tokens), maps of any alignment, values that no threshold takes
 @pytest.mark.parametrize("L", [1, 3, 62, 64, 65, 127, 128, 129])
 @pytest.mark.parametrize("shift", [0, 1])
