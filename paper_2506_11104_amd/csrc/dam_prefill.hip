@@ -1332,6 +1332,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if constexpr (FAST) {
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sh.redo) < 0) return;
+    __syncthreads();  // (wave 0 takes the first entry off the list at once: every wave has seen that there is one)
     prefill_with_reference<RAGGED, GATHER>((uint64_t)args_at, (__attribute__((address_space(3))) unsigned char *)lds,
                                            (__attribute__((address_space(3))) Shared *)&sh);
   }

@@ -73,3 +73,21 @@ def test_workgroups_redo_several_items(Hq, Hkv, S, odd_only, flags):
     torch.cuda.synchronize()
     against_oracle(out[0], lse[0], Q, K, V, art, 0.0)
     assert float((out[1].float() - 2 * out[0].float()).abs().max()) <= 2.0 ** -126 and torch.equal(lse[1], lse[0])
+
+
+@pytest.mark.parametrize("B_,Hq,Hkv,S,flags", [
+    (1, 8, 2, 2048, 0), (1, 4, 4, 1000, B.DAM_MASK_GATHER_COLUMNS), (2, 16, 8, 2048, B.DAM_MASK_GATHER_COLUMNS), (1, 6, 3, 257, 0),
+])
+def test_workgroups_redo_their_only_item(B_, Hq, Hkv, S, flags):
+    """18 to 512 items, one to a workgroup, all of them beyond the plain exponential: every list has exactly one entry, so that it
+    is empty again as soon as wave 0 has taken it, and every wave's rows have to be those of the second variant all the same."""
+    Q, K, V = qkv(11 + S, Hq, S)
+    K, V = K[:Hkv], V[:Hkv]
+    Q *= 64.0
+    art = patterns(Hq, S)
+    mask = gpu_mask_from_art(art, S, 128, 128, flags=flags)
+    q, k, v = (torch.stack([dev(x, "bf16")] * B_) for x in (Q, K, V))
+    out, lse = B.dam_sparse_attn_prefill(q, k, v, mask, want_lse=True)
+    torch.cuda.synchronize()
+    for b in range(B_):
+        against_oracle(out[b], lse[b], Q, K, V, art, 0.0)
