@@ -766,6 +766,16 @@ __device__ __forceinline__ bool pattern_row_full(const uint64_t *__restrict__ cb
   return all == ~0ull;
 }
 
+// Every column of the tile of row i0 and words [w0, w0 + wpr) is matched, or every offset that it meets. (Tiles begin at multiples of
+// 64: the offsets are (tile_m + tile_n) / 64 whole words but for the last bit, as in the classes below.)
+__device__ __forceinline__ bool pattern_tile_all(const Geom &g, const uint64_t *__restrict__ cb, const uint64_t *__restrict__ rr, int i0, int w0) {
+  uint64_t columns = cb ? ~0ull : 0, offsets = ~0ull;
+  for (int y = 0; cb && y < g.wpr; ++y) columns &= set_word(cb, w0 + y, g.pw);
+  const int end = g.pw - i0 / 64 + w0 + g.wpr;
+  for (int y = 1; y <= (g.tile_m + g.tile_n) / 64; ++y) offsets &= set_word(rr, end - y, g.pw) | (y == 1 ? 1ull << 63 : 0);
+  return columns == ~0ull || offsets == ~0ull;
+}
+
 // Classes of whole tiles for square tiles of width T, per head (pattern region, tile strictly below
 // the diagonal): the entries of tile (qt, kt) have the columns of key tile kt and exactly the offsets
 // T d - (T - 1) .. T d + (T - 1), d = qt - kt. So "some column matched" / "all columns matched" is a
@@ -1092,7 +1102,9 @@ __device__ __forceinline__ RowColumns fetch_columns(const Geom &g, const int *__
   }
   return c;
 }
-template <bool TRUE_BLOCK>  // there is a true-mask block (L > 0)
+// TRUE_BLOCK: there is a true-mask block (L > 0). SQUARE: tile_m == tile_n, so that there are classes; tiles of other shapes are a
+// form of their own, which costs the square ones no registers.
+template <bool TRUE_BLOCK, bool SQUARE>
 __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__restrict__ tb, const uint64_t *__restrict__ cb,
                                               const uint64_t *__restrict__ rr, const uint64_t *__restrict__ classes,  // of the head
                                               uint64_t *__restrict__ occ,
@@ -1105,7 +1117,7 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   // Square tiles, a whole row of tiles in the pattern region: 64 tiles at a time from the per-head
   // class bitsets. Only a tile that has matched and unmatched columns AND matched and unmatched
   // offsets needs the exact one-lane test for "full".
-  const bool by_class = g.tile_m == g.tile_n && i0 >= g.L && i0 + g.tile_m <= g.S;
+  const bool by_class = SQUARE && i0 >= g.L && i0 + g.tile_m <= g.S;
   // gathered columns: in a query tile of the pattern region the ordinary tiles hold the diagonal part only
   const bool split = gidx != nullptr && i0 >= g.L;
   const int n_cols = columns.n_cols, g_first = columns.first, g_last = columns.last;
@@ -1170,9 +1182,19 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
             // itself, each with the columns it meets, held the wave for as long as the longest took: 6 heads x 1000 tokens,
             // captured at 256, in the plain layout, whole layer 50.9 -> 36.5 us; builds of 32 heads of patterns there, 1024 tokens 29.7 ->
             // 14.3, 8000 57.4 -> 36.5, 32768 140 -> 121.
-            if (f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S && pattern_row_full(cbw, rr, g.pw, i0, kt * g.wpr, g.wpr) &&
-                pattern_row_full(cbw, rr, g.pw, i_last, kt * g.wpr, g.wpr))
-              f = 4;
+            // Tiles that are not square have no classes: those of matched columns or offsets alone, all of a dense mask and of a
+            // window, are looked for here, and tall ones are asked for the last row of every tile_n (an unmatched offset meets
+            // one of those or the first). Builds of 32 heads with windows of 4096 at 32768 tokens, 64 x 128 / 128 x 64 / 256 x 128
+            // tiles, 200 / 205 / 204 us with their full tiles evaluated by the whole wave, 69 / 64 / 56 so.
+            bool rows = f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S;
+            if (!SQUARE && rows && pattern_tile_all(g, cbw, rr, i0, kt * g.wpr)) {
+              f = 3;
+              rows = false;
+            }
+            rows = rows && pattern_row_full(cbw, rr, g.pw, i0, kt * g.wpr, g.wpr) && pattern_row_full(cbw, rr, g.pw, i_last, kt * g.wpr, g.wpr);
+            for (int i = i0 + g.tile_n - 1; !SQUARE && rows && i < i_last; i += g.tile_n)
+              rows = pattern_row_full(cbw, rr, g.pw, i, kt * g.wpr, g.wpr);
+            if (rows) f = 4;
           }
         } else if (by_class && kt == qt) {
           // the diagonal tile of a row of the pattern region, never full: it meets the offsets 0 .. T - 1, each in its last
@@ -1223,6 +1245,9 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
           const uint64_t m = mask_word(g, tb, cbw, rr, i0 + x / g.wpr, (w * 64 + b) * g.wpr + x % g.wpr);
           any |= m != 0;
           all &= m == ~0ull;
+          // (listed and not full, which the first words mostly tell: wave-uniform. 32 heads x 4096 tokens, 256 x 128 tiles with an
+          // unmatched offset here and there 45.2 -> 38.6 us)
+          if (__ballot(any) != 0 && __ballot(!all) != 0) break;
         }
         if (__ballot(any) != 0) ow |= 1ull << b;
         if (__ballot(!all) == 0) fw |= 1ull << b;
@@ -1346,7 +1371,7 @@ struct ScanArgs {
   int *cnt;
   const uint64_t *true_bits;
 };
-template <PrepSource SOURCE>
+template <PrepSource SOURCE, bool SQUARE>  // (SQUARE: of tile_scan_row)
 __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, ScanArgs scan, const uint8_t *__restrict__ diag_flag,
                                                        const uint8_t *__restrict__ vert_flag, uint64_t *__restrict__ cbits,
                                                        uint64_t *__restrict__ rrev, bool want_classes, uint64_t *__restrict__ classes,
@@ -1388,7 +1413,7 @@ __global__ __launch_bounds__(1024) void k_pattern_prep(Geom g, CountArgs ca, Sca
   const uint64_t *tb = SOURCE == kFromMap ? true_words : scan.true_bits ? scan.true_bits + (int64_t)h * g.L * g.tbw : nullptr;
   int mine = 0;
   for (int qt = wave; qt < g.nQt; qt += blockDim.x >> 6)
-    mine += tile_scan_row<true>(g, tb, prep_sets, prep_sets + g.pw, prep_sets + 2 * g.pw, scan.occ, scan.full, scan.cnt, gidx,
+    mine += tile_scan_row<true, SQUARE>(g, tb, prep_sets, prep_sets + g.pw, prep_sets + 2 * g.pw, scan.occ, scan.full, scan.cnt, gidx,
                           fetch_columns(g, gidx, gcnt, gstride, h, qt, lane), gstride, scan.vocc, scan.vfull, h, qt, lane);
   if (lane == 0) head_cnt[h * kHeadSub + wave] = mine;
 }
@@ -1486,7 +1511,7 @@ __device__ __forceinline__ QueryTiles my_query_tiles(const Geom &g, int each, bo
 // counts of the query tiles before its own. (Folding a scan into the last workgroup to finish was measured and
 // dropped: it needs a device-wide release fence in every workgroup, which on this chip writes back the L2 of its
 // XCD each time: 20 -> 190 us at S = 32768.)
-template <bool TRUE_BLOCK, bool STAGED>
+template <bool TRUE_BLOCK, bool STAGED, bool SQUARE>
 __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__restrict__ true_bits,
                                                    const uint64_t *__restrict__ cbits,
                                                    const uint64_t *__restrict__ rrev,
@@ -1510,10 +1535,10 @@ __global__ __launch_bounds__(256) void k_tile_scan(Geom g, const uint64_t *__res
   if constexpr (STAGED) {
     stage_sets(lds_sets, g.pw, cb, rr, classes_h, 4 * g.occw);
     if (qt < g.nQt)
-      mine = tile_scan_row<TRUE_BLOCK>(g, tb, lds_sets, lds_sets + g.pw + kGuardFront, lds_sets + 2 * g.pw + kGuardFront + kGuardBack, occ, full, cnt,
+      mine = tile_scan_row<TRUE_BLOCK, SQUARE>(g, tb, lds_sets, lds_sets + g.pw + kGuardFront, lds_sets + 2 * g.pw + kGuardFront + kGuardBack, occ, full, cnt,
                            gidx, columns, gstride, vocc, vfull, h, qt, lane);
   } else if (qt < g.nQt) {
-    mine = tile_scan_row<TRUE_BLOCK>(g, tb, cb, rr, classes_h, occ, full, cnt, gidx, columns, gstride, vocc, vfull, h, qt, lane);
+    mine = tile_scan_row<TRUE_BLOCK, SQUARE>(g, tb, cb, rr, classes_h, occ, full, cnt, gidx, columns, gstride, vocc, vfull, h, qt, lane);
   }
   // the head's total, for the offsets that the fill kernel derives itself (plain atomics, read by the next kernel
   // only; spread over kHeadSub words per head, because atomics on one address are served one after the other)
@@ -2703,8 +2728,14 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
   if (needs_prep(p, o) || count.source != kFlagsGiven) {
     const size_t prep_lds = want_blocks ? prep_lds_bytes(g) : 0;
     const ScanArgs scan{scans_in_prep(g, o), w.occ, w.full, w.vocc, w.vfull, w.tile_cnt, true_bits};
-    auto prep = count.source == kFromMap ? k_pattern_prep<kFromMap> : count.source == kFromTrueBits ? k_pattern_prep<kFromTrueBits>
-                : count.source == kFromSlices ? k_pattern_prep<kFromSlices> : k_pattern_prep<kFlagsGiven>;
+    auto form = [&](auto square) {
+      constexpr bool SQUARE = decltype(square)::value;
+      return count.source == kFromMap        ? k_pattern_prep<kFromMap, SQUARE>
+             : count.source == kFromTrueBits ? k_pattern_prep<kFromTrueBits, SQUARE>
+             : count.source == kFromSlices   ? k_pattern_prep<kFromSlices, SQUARE>
+                                             : k_pattern_prep<kFlagsGiven, SQUARE>;
+    };
+    auto prep = g.tile_m == g.tile_n ? form(std::true_type{}) : form(std::false_type{});
     prep<<<g.H, 1024, prep_lds, stream>>>(g, count, scan, dflag, vflag, w.cbits, w.rrev, want_blocks, w.classes, gstride, gather ? o->gather_idx : nullptr,
                                                    gather ? o->gather_cnt : nullptr, w.head_cnt, prep_lds > 0);
   }
@@ -2718,8 +2749,12 @@ void stage_extension(const dam_mask_params *p, const Geom &g, const Workspace &w
     };
     if (!scans_in_prep(g, o)) {
       const size_t lds = lds_sets > 0 && lds_sets + class_bytes(g) <= kMaxWithClasses ? lds_sets + class_bytes(g) : 0;
-      auto scan = g.L > 0 ? (lds > 0 ? k_tile_scan<true, true> : k_tile_scan<true, false>)
-                          : (lds > 0 ? k_tile_scan<false, true> : k_tile_scan<false, false>);
+      auto form = [&](auto square) {
+        constexpr bool SQUARE = decltype(square)::value;
+        return g.L > 0 ? (lds > 0 ? k_tile_scan<true, true, SQUARE> : k_tile_scan<true, false, SQUARE>)
+                       : (lds > 0 ? k_tile_scan<false, true, SQUARE> : k_tile_scan<false, false, SQUARE>);
+      };
+      auto scan = g.tile_m == g.tile_n ? form(std::true_type{}) : form(std::false_type{});
       scan<<<grid_of(4), 256, lds, stream>>>(g, true_bits, w.cbits, w.rrev, w.classes, w.occ, w.full, w.tile_cnt, gidx, gcnt, gstride, w.vocc, w.vfull, w.head_cnt);
     }
     if (fill) {

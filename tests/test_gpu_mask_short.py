@@ -110,6 +110,39 @@ def test_full_tiles_of_columns_and_diagonals(S, T):
     assert (2, 0) in full[0] and (2, 0) not in full[1] and (2, 0) in full[2] and (5, 0) in full[2] and (6, 1) not in full[2]
 
 
+# tiles that are not square have no classes: full by their offsets alone, by their columns alone, by both together, and not for one
+# unmatched offset in the middle of a tall tile, which its first and last rows do not meet; in the prep kernel and by a launch
+@pytest.mark.parametrize("S,tm,tn", [(1024, 64, 128), (1000, 128, 64), (1024, 256, 64), (2500, 64, 128), (2500, 128, 64), (2500, 64, 256),
+                                     (3500, 192, 128), (4500, 256, 128), (4500, 256, 64)])
+@pytest.mark.parametrize("L", [0, 100])
+def test_full_tiles_that_are_not_square(S, tm, tn, L):
+    d, v = (np.zeros((6, S), np.uint8) for _ in range(2))
+    d[0] = 1
+    d[1, :700] = 1
+    d[2] = 1
+    d[2, [tm + 31, 2 * tm + tn + 3]] = 0  # their columns all matched ...
+    v[2, :S // 2] = 1
+    d[3] = d[2]                           # ... but one
+    v[3] = v[2]
+    v[3, 2 * tn + 5] = 0
+    d[4] = 1
+    d[4, 70::400] = 0
+    v[4, ::7] = 1
+    d[5, ::90] = 1
+    v[5, 64:600] = 1
+    tb, true = None, None
+    if L:
+        true = np.tril(np.random.default_rng(S).random((6, L, L)) < 0.5)
+        tb = torch.from_numpy(pack_rows_u64(true).view(np.int64)).cuda()
+    art = oracle.from_patterns(d, v, true)
+    m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=6, L=L, S=S, tile_m=tm, tile_n=tn, diag_in=torch.from_numpy(d).cuda(),
+                     vert_in=torch.from_numpy(v).cuda(), true_bits=tb)
+    torch.cuda.synchronize()
+    test_gpu_mask.check_against_oracle(art, S, tm, tn, m, dense=False)
+    n_full = [int((m.blk_kind[m.blk_row_ptr[h, 0]:m.blk_row_ptr[h, -1]] & 1).sum()) for h in range(6)]
+    assert n_full[0] > n_full[2] > n_full[3] > 0 and n_full[1] > 0 and n_full[5] > 0
+
+
 # one query tile, the most and one more than the prep kernel scans itself; ragged, inside and beyond the true-mask block
 @pytest.mark.parametrize("S,tm,tn,L", [(60, 64, 64, 200), (500, 64, 64, 130), (512, 64, 64, 512), (513, 64, 64, 200), (1000, 128, 64, 300),
                                        (1024, 128, 128, 200), (1025, 128, 128, 200), (700, 256, 64, 64), (1024, 64, 64, 128),
