@@ -530,7 +530,8 @@ int dam_kv_remap_lists(const dam_evict_params *params, const int32_t *window, co
  * Both only enqueue on `stream`; the caller times them.
  * dam_probe_row_lists: the kept lists of one row from patterns, as dam_mask_build makes them where one launch does, with every
  *   list's workgroup counting all lists in front of its own itself instead of learning their totals from the others (what
- *   dam_mask_build does for a total that is late). DAM_ERR_UNSUPPORTED where dam_mask_build takes another way. */
+ *   dam_mask_build does for a total that is late). DAM_ERR_UNSUPPORTED where there is no single launch for them: more than 64
+ *   lists, rows from 32768 on (16384 with more than four maps to a list), rows inside a true-mask block. */
 int dam_probe_mfma(const void *operands, float *sink, int32_t workgroups, int32_t iters, void *stream);
 int dam_probe_stream_read(const void *src, size_t bytes, uint32_t *sink, int32_t workgroups, void *stream);
 int dam_probe_row_lists(const dam_mask_params *params, const uint8_t *diag_in, const uint8_t *vert_in,

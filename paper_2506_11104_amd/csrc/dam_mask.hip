@@ -1984,47 +1984,59 @@ constexpr int kListSpan = 256 * kPieceBits;       // keys per workgroup
 // 44.6; 64 maps at 2^20 one by one (65536) 377 / 156.
 constexpr int64_t kAddedCounts = 12288;
 
-__device__ __forceinline__ unsigned flags8(const uint8_t *p) {  // (p of any alignment)
-  uint64_t v;
-  __builtin_memcpy(&v, p, 8);
-  return bits_of_8((unsigned)v, (unsigned)(v >> 32));
-}
-
-// The mask bits of row i, keys [key0, key0 + 8) of one map; key0 a multiple of 8.
-__device__ __forceinline__ unsigned row_piece(const Geom &g, const uint64_t *__restrict__ true_bits,
-                                              const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int h, int i,
-                                              int key0) {
-  if (key0 > i) return 0;
-  unsigned bits;
-  if (i < g.L) {
-    bits = (unsigned)(true_bits[((int64_t)h * g.L + i) * g.tbw + (key0 >> 6)] >> (key0 & 63)) & 0xFFu;
-    if (key0 + 8 > g.L) bits &= (1u << (g.L - key0)) - 1;
-  } else {
-    const uint8_t *d = dflag + (int64_t)h * g.P, *v = vflag + (int64_t)h * g.P;
-    const int u = i - key0;  // offset of the first key; key k of the piece has offset u - k
-    if (key0 + 8 <= g.P && u >= 7 && u < g.P) {
-      bits = flags8(v + key0) | __brev(flags8(d + u - 7)) >> 24;
-    } else {
-      bits = 0;
-      for (int k = 0; k < 8; ++k) {
-        const bool col = key0 + k < g.P && v[key0 + k] != 0;
-        const bool off = u - k >= 0 && u - k < g.P && d[u - k] != 0;
-        bits |= (col || off ? 1u : 0u) << k;
-      }
-    }
-  }
-  return i - key0 >= 7 ? bits : bits & ((2u << (i - key0)) - 1);  // keys up to the row's own
-}
-
-// This lane's pieces for the maps of group kv (m[x], zero for x >= G), and the bits set in at least two of them.
+// This lane's pieces of row i, keys [key0, key0 + 8), for the maps of group kv (m[x], zero for x >= G), and the bits set in at least
+// two of them. Flags are read eight at a time, all maps' together and none behind a test: a piece that the row's or the flags' end
+// cuts is read from inside and shifted. (Flag by flag, the one piece at the row's end held both launches unless the row ends with a
+// whole one, seven in eight do not: 8 lists of four maps at 20004 18.2 -> 9.0 us, at 20007 9.9 -> 9.0; of eight at 17000 27.2 -> 11.4.)
 __device__ __forceinline__ void row_pieces(const Geom &g, const uint64_t *__restrict__ true_bits,
                                            const uint8_t *__restrict__ dflag, const uint8_t *__restrict__ vflag, int kv, int G, int i,
                                            int key0, unsigned (&m)[kMaxGroup], unsigned &shared) {
+  const int u = i - key0;  // offset of the first key; key k of the piece has offset u - k
+  const unsigned causal = u >= 7 ? 0xFFu : u < 0 ? 0u : (2u << u) - 1;
+  if (i < g.L) {  // uniform
+#pragma unroll
+    for (int x = 0; x < kMaxGroup; ++x) {
+      m[x] = 0;
+      if (x < G && u >= 0) {
+        m[x] = (unsigned)(true_bits[((int64_t)(kv * G + x) * g.L + i) * g.tbw + (key0 >> 6)] >> (key0 & 63)) & causal;
+        if (key0 + 8 > g.L) m[x] &= (1u << (g.L - key0)) - 1;
+      }
+    }
+  } else if (g.P >= 8) {  // uniform
+    const int at_v = min(key0, g.P - 8), at_d = min(max(u - 7, 0), g.P - 8);
+    const int cut_v = min(key0 - at_v, 8), cut_d = 7 - u + at_d;  // (cut_d < 0: offsets past the flags' end)
+    uint64_t v[kMaxGroup], d[kMaxGroup];
+#pragma unroll
+    for (int x = 0; x < kMaxGroup; ++x)
+      if (x < G) {  // uniform
+        const int64_t row = (int64_t)(kv * G + x) * g.P;
+        __builtin_memcpy(&v[x], vflag + row + at_v, 8);
+        __builtin_memcpy(&d[x], dflag + row + at_d, 8);
+      }
+#pragma unroll
+    for (int x = 0; x < kMaxGroup; ++x) {
+      m[x] = 0;
+      if (x < G) {
+        const unsigned off = __brev(bits_of_8((unsigned)d[x], (unsigned)(d[x] >> 32))) >> 24;
+        m[x] = (bits_of_8((unsigned)v[x], (unsigned)(v[x] >> 32)) >> cut_v | (cut_d >= 0 ? off >> min(cut_d, 8) : off << min(-cut_d, 8))) & causal;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < kMaxGroup; ++x) {
+      m[x] = 0;
+      for (int k = 0; k < 8 && x < G; ++k) {
+        const int64_t row = (int64_t)(kv * G + x) * g.P;
+        const bool col = key0 + k < g.P && vflag[row + key0 + k] != 0;
+        const bool off = u - k >= 0 && u - k < g.P && dflag[row + u - k] != 0;
+        m[x] |= ((col || off) && k <= u ? 1u : 0u) << k;
+      }
+    }
+  }
   unsigned any = 0;
   shared = 0;
 #pragma unroll
   for (int x = 0; x < kMaxGroup; ++x) {
-    m[x] = x < G ? row_piece(g, true_bits, dflag, vflag, kv * G + x, i, key0) : 0u;
     shared |= any & m[x];
     any |= m[x];
   }
@@ -2138,6 +2150,13 @@ __global__ __launch_bounds__(256) void k_list_fill(Geom g, const uint64_t *__res
 // the decode behind them, us, two launches / this: 8 sequences at 20000, merged lists of 32 heads 29.5 / 28.0, 2 at 32700 32.5 / 23.0,
 // 4 at 8000 (16 heads) 19.6 / 15.7; a list per head 4 fp32 sequences at 4096, 16 heads 12.2 / 10.6, 2 at 30000, 32 heads 20.4 / 18.0.
 constexpr int kOneLists = 64, kOnePolls = 64;
+// Where a lane owns 128 bytes of flags of either kind (four maps above 16384 keys, eight above 8192), flags off a multiple of
+// eight bytes cost this launch 2 us and the other two nothing, so up to 32 lists of such rows take those; lists alone, two
+// launches / this, us: 8 lists of four maps at 24575, windows, 9.1 / 11.3, in place 9.1 / 7.5, 5 % of the keys one by one 9.7 /
+// 13.4, in place 10.4 / 9.8; 64 lists 13.6 / 12.1. 8 of four maps at 16383, 64 bytes, off 9.1 / 8.1. (Bound by its instructions, it
+// grows with the keys that it lists, the two launches hardly do: with a fifth of the keys kept one by one they are faster from
+// some 16000 keys on, 8 lists of one map at 20007 6.7 / 8.0, of four at 16383 9.9 / 14.3. The host does not know that.)
+constexpr int kOneWide = 128, kOneWideLists = 32;
 
 // m[x]: bit k is key W * lane of the workgroup + k of the map x of group kv, of row i >= L whose patterns all exist (i < P, P >= W).
 // All flags are under way together, none of them behind a test: a piece that the row's or the flags' end cuts is read from inside
@@ -2687,12 +2706,19 @@ CountArgs stage_patterns(const dam_mask_params *p, const Geom &g, const Workspac
   return CountArgs{};
 }
 
-// Whether the lists of one row take the one launch of k_list_one. (A stream whose state cannot be told counts as captured.)
-bool lists_in_one(const dam_mask_params *p, const Geom &g, hipStream_t stream) {
+// Whether there is a form of k_list_one for the lists of one row.
+bool one_launch_lists(const dam_mask_params *p, const Geom &g) {
   const int lists = g.H / list_group(p);
   if (lists > kOneLists || p->row_begin >= 1024 * 32 || (int64_t)g.H * g.pw < 2 * lists) return false;
   if (p->row_begin < g.L || p->row_begin >= g.P || g.P < 8) return false;  // (rows of 8192 keys and more: g.P >= 16, 32)
-  if (list_group(p) > 4 && p->row_begin >= 1024 * 16) return false;         // (eight maps' pieces of 32 keys spill registers)
+  return list_group(p) <= 4 || p->row_begin < 1024 * 16;                    // (eight maps' pieces of 32 keys spill registers)
+}
+
+// Whether they take it. (A stream whose state cannot be told counts as captured.)
+bool lists_in_one(const dam_mask_params *p, const Geom &g, hipStream_t stream) {
+  if (!one_launch_lists(p, g)) return false;
+  const int keys = p->row_begin < 1024 * 8 ? 8 : p->row_begin < 1024 * 16 ? 16 : 32, G = list_group(p), maps = G > 4 ? 8 : G > 1 ? 4 : 1;
+  if (maps * keys >= kOneWide && g.P % 8 != 0 && g.H / G <= kOneWideLists) return false;
   hipStreamCaptureStatus state = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &state) != hipSuccess) {
     (void)hipGetLastError();
@@ -2914,7 +2940,7 @@ extern "C" int dam_probe_row_lists(const dam_mask_params *p, const uint8_t *diag
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   const Geom g = geometry(p);
   if (p->mode != DAM_FROM_PATTERNS || !o->kept_ptr || (p->flags & DAM_MASK_PATTERN_PLAN) || p->row_end != p->row_begin + 1 ||
-      !lists_in_one(p, g, stream))
+      !one_launch_lists(p, g))
     return DAM_ERR_UNSUPPORTED;
   launch_list_one(p, g, carve(p, ws), o, diag_in, vert_in, 0, stream);
   return launch_status();

@@ -54,7 +54,7 @@ def patterns_of(H, S, seed):
     d, v = ((torch.rand((H, S), generator=gen, device="cuda") < 0.02).to(torch.uint8) for _ in range(2))
     for h in range(H):
         d[h, : 37 * (h % 9)] = 1
-        v[h, S // 2:S // 2 + 11 * (h % 5)] = 1 + h  # (any value but zero is a match)
+        v[h, S // 2:S // 2 + 11 * (h % 5)] = 1 + h % 255  # (any value but zero is a match)
     return d, v
 
 
@@ -106,3 +106,42 @@ def test_lists_in_one_launch(H, G, S, rows):
         assert st == 0 and int(total) == n and kept_ptr.tolist() == [min(x, n - 1) for x in ptr]
         assert torch.equal(again["idx"][:n - 1].long(), idx[:n - 1]) and bool((again["idx"][n - 1:] == 7).all())
         assert G == 1 or torch.equal(again["mem"][:n - 1].long(), mem[:n - 1])
+
+
+# the two launches: more lists than one launch takes, or flags off a multiple of eight bytes where a lane would read 128 of them.
+# The piece at the row's end with one to eight keys, maps of fewer flags than a piece has
+@pytest.mark.parametrize("H,G,S,rows", [
+    (66, 1, 2061, range(2040, 2061)), (132, 2, 45, range(0, 45, 3)), (264, 4, 4099, range(4090, 4099)), (528, 8, 77, range(60, 77)),
+    (66, 1, 5, range(5)), (132, 2, 8, range(8)), (8, 4, 20011, range(20000, 20011, 3)), (16, 8, 9003, (9000, 9002)),
+])
+def test_pieces_at_the_end_of_a_row(H, G, S, rows):
+    d, v = patterns_of(H, S, S)
+    for row in rows:
+        m = B.build_mask(mode=B.DAM_FROM_PATTERNS, H=H, L=0, S=S, diag_in=d, vert_in=v, blocks=False, group=G if G > 1 else 0, rows=(row, row + 1))
+        torch.cuda.synchronize()
+        ptr, idx, mem = lists_of(d, v, row, G)
+        n = ptr[-1]
+        assert m.kept_ptr.tolist() == ptr and m.n_kept == n
+        if n:
+            assert torch.equal(m.kept_idx[:n].long(), idx) and (G == 1 or torch.equal(m.kept_member[:n].long(), mem))
+
+
+# rows behind the flags' end: offsets and columns up to the capture's length only
+@pytest.mark.parametrize("L", [5, 8, 9, 100, 2050])
+@pytest.mark.parametrize("G", [1, 4])
+def test_rows_past_the_flags(L, G):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    A = torch.rand((8, L, L), generator=gen, device="cuda").pow(6).tril()
+    listed = 0
+    for row in (*range(L, L + 18), 2 * L + 1, 4500):
+        m = B.build_mask(mode=B.DAM_FROM_ATTN_MAP, H=8, L=L, S=4600, tau=0.5, mu=0.4, attn_sum=A, blocks=False, group=G if G > 1 else 0,
+                         rows=(row, row + 1))
+        torch.cuda.synchronize()
+        d, v = (torch.nn.functional.pad(x, (0, row + 1 - L)) for x in (m.diag_flag, m.vert_flag))
+        ptr, idx, mem = lists_of(d, v, row, G)
+        n = ptr[-1]
+        listed += n
+        assert m.kept_ptr.tolist() == ptr and m.n_kept == n
+        if n:
+            assert torch.equal(m.kept_idx[:n].long(), idx) and (G == 1 or torch.equal(m.kept_member[:n].long(), mem))
+    assert listed > 0
