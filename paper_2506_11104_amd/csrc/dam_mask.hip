@@ -983,10 +983,13 @@ __device__ __forceinline__ void count_patterns_of_head(const Geom &g, const uint
 // The same from the chunk counts of k_pattern_slices (kSlicesInPrep), a wave per word of patterns: a lane fetches one of the
 // eight slices of one chunk, and the 64 x 64 bits of eight chunks turned around are, in the lane of a pattern, its eight
 // counts, a byte each. Bound by one trip to memory per job, so the next job's slices are under way.
-// Saves the launch of k_pattern_finish. Whole layers at 32 heads, us, each slice a wave-uniform load of its own / this: 4096
-// tokens captured at 1024 111.9 / 108.4, 6000 at 1536 187.1 / 180.2; 8000 at 2048, where k_pattern_finish did it, 267.3 / 262.6
-// (in its older form, which took 6 us more; with it 3072 and 4096 came out the same).
-constexpr int kSlicesInPrep = 2048;
+// Saves the launch of k_pattern_finish, but on one CU per head, so the line lies where the two meet. Whole builds of twice the
+// captured length, the launch / this, us: 2 heads captured at 1792 42.6 / 42.8, 1984 60.3 / 61.1, 2048 44.5 / 45.3; 8 heads at 1600 57.8 /
+// 57.5, 2048 52.1 / 52.9; 32 heads at 1600 86.5 / 86.2, 1792 83.3 / 83.2, 2048 97.3 / 98.1; 64 heads at 1600 132.0 / 131.6, 1792 137.2 /
+// 136.8, 2048 176.5 / 177.1.
+// (Each slice a wave-uniform load of its own / this, layers of 32 heads: 4096 tokens captured at 1024 111.9 / 108.4, 6000 at 1536
+// 187.1 / 180.2.)
+constexpr int kSlicesInPrep = 1792;
 __device__ __forceinline__ void sum_slices_of_head(const Geom &g, const uint64_t *__restrict__ vslices, const uint64_t *__restrict__ dslices,
                                                    float mu, int h, int *__restrict__ vert_cnt, int *__restrict__ diag_cnt,
                                                    uint8_t *__restrict__ vert_flag, uint8_t *__restrict__ diag_flag,

@@ -30,7 +30,7 @@ def check_counts(mask, L, mu):
 # both sides of the line at which captures are counted in chunks (832 tokens), 16 / 32 / 64 / 128 words
 # per row, more than that (two waves per chunk: a last chunk of one row, one of 65, a whole one); a block index or none
 @pytest.mark.parametrize("L,blocks", [(768, False), (769, False), (769, True), (832, False), (832, True), (833, False), (833, True), (1024, True), (1500, False), (1536, True), (1537, True), (2048, False),
-                                      (1920, True), (2048, True), (2049, True),  # added up in the prep kernel, and by a launch
+                                      (1792, True), (1793, True), (1920, True), (2048, True), (2049, True),  # added up in the prep kernel, and by a launch
                                       (2049, False), (4096, False), (4097, False), (8192, False), (8193, False),
                                       (8257, False), (8320, True), (12300, False)])
 def test_counts_in_chunks(L, blocks):
