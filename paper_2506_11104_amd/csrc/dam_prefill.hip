@@ -399,7 +399,10 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void k_prefill_f32(F32Args t
 
 // No more workgroups than the chip takes two to a CU: they are all there at once then, and the second form alone is the faster one
 // (no private memory to set up: 1 x 4 heads x 300 tokens 11.85 us against 12.0; 11.75 before there were two forms). From there on the first: 2 x 8 x 1500, d 128, 51.4 -> 46.2 us, 4 x 16 x 2000 336 -> 292, d 64 183 -> 166, 3 x 8 x 700
-// 23.0 -> 20.5.
+// 23.0 -> 20.5. What that costs is paid where V does hold an infinity or a NaN, by the row groups that meet one, which are taken twice
+// and the second time with registers in private memory: 4 x 16 x 2000, d 128, one NaN row in the middle of each sequence 332 -> 637 us,
+// one in 50 525 -> 1096, the last quarter of the rows infinite 407 -> 545; d 64 one in 50 259 -> 428. (Leaving the first pass at the
+// first odd value saves 1 to 11 % of that, and costs the others 0.2 %.)
 constexpr int kF32Few = 512;
 template <int D, bool GATHER>
 __global__ __launch_bounds__(256, 2) void k_prefill_f32_few(AttnArgs a, const float *__restrict__ q, const float *__restrict__ k,

@@ -50,25 +50,43 @@ def test_edges_of_groups_blocks_and_segments(Hq, Hkv, S, d, tile, flags):
 @pytest.mark.parametrize("copies,d", [(1, 128), (40, 128), (40, 64)])
 def test_a_row_does_not_see_what_it_does_not_keep(copies, d):
     """A NaN and an infinity in V rows reach exactly the query rows that keep those keys."""
-    S = 200
+    S, far = 200, 70 if d == 128 else 60  # (of 128 dims, one in either half)
     Q, K, V, art = inputs(2, 1, S, d, 5)
-    V[0, 37, 3], V[0, 101, 60] = np.nan, np.inf
+    V[0, 37, 3], V[0, 101, far] = np.nan, np.inf
     mask = gpu_mask_from_art(art, S, 64, 64)
     t = lambda x: torch.from_numpy(x)[None].cuda().repeat(copies, 1, 1, 1)
     v = t(V)
-    v[1:, 0, 37, 3] = v[1:, 0, 101, 60] = 1.0  # (the other sequences' values are finite)
+    v[1:, 0, 37, 3] = v[1:, 0, 101, far] = 1.0  # (the other sequences' values are finite)
     outs, lses = B.dam_sparse_attn_prefill(t(Q), t(K), v, mask, want_lse=True)
     out = outs[0].cpu().numpy()
     if copies > 1:
         Vf = V.copy()
-        Vf[0, 37, 3] = Vf[0, 101, 60] = 1.0
+        Vf[0, 37, 3] = Vf[0, 101, far] = 1.0
         O, LSE = oracle.attend_prefill(Q, K, Vf, art)
         assert np.abs(outs[-1].cpu().numpy() - O).max() <= TOL and np.abs(lses.cpu().numpy() - LSE).max() <= TOL
     i = np.arange(S)
     for h, keeps in ((0, lambda j: i >= j), (1, lambda j: (i >= j) & ((i - j < 8) | (j % 20 == 0)))):
         assert np.array_equal(np.isnan(out[h, :, 3]), keeps(37))
-        assert np.array_equal(np.isinf(out[h, :, 60]), keeps(101))
+        assert np.array_equal(np.isinf(out[h, :, far]), keeps(101))
         assert np.isfinite(out[h, :, 5]).all()
+
+
+# the only odd value in one dim, in each quarter of the dims and at their ends: the first form of more than 512 workgroups has to
+# notice it wherever it is (a row that does not keep the key would get a NaN from the product with its zero weight)
+@pytest.mark.parametrize("d,dim", [(128, 0), (128, 35), (128, 64), (128, 95), (128, 96), (128, 127), (64, 0), (64, 31), (64, 63)])
+@pytest.mark.parametrize("value", [np.nan, -np.inf])
+def test_one_odd_value_is_noticed_in_any_dim(d, dim, value):
+    S = 200
+    Q, K, V, art = inputs(2, 1, S, d, 5)
+    V[0, 101, dim] = value
+    mask = gpu_mask_from_art(art, S, 64, 64)
+    t = lambda x: torch.from_numpy(x)[None].cuda().repeat(40, 1, 1, 1)
+    out = B.dam_sparse_attn_prefill(t(Q), t(K), t(V), mask)
+    i = np.arange(S)
+    for h, keeps in ((0, lambda j: i >= j), (1, lambda j: (i >= j) & ((i - j < 8) | (j % 20 == 0)))):
+        want = np.zeros((S, d), bool)
+        want[:, dim] = keeps(101)
+        assert bool((torch.isfinite(out[:, h]) == torch.from_numpy(~want).cuda()).all())
 
 
 @pytest.mark.parametrize("d", [64, 128])
