@@ -1106,7 +1106,8 @@ __device__ __forceinline__ RowColumns fetch_columns(const Geom &g, const int *__
   return c;
 }
 // TRUE_BLOCK: there is a true-mask block (L > 0). SQUARE: tile_m == tile_n, so that there are classes; tiles of other shapes are a
-// form of their own, which costs the square ones no registers.
+// form of their own, which leaves the square ones' code as it was (with what they need in one form, and with the test of the two
+// widths left out, the compiler's choice of registers cost layers of 4096 tokens up to 0.5 %).
 template <bool TRUE_BLOCK, bool SQUARE>
 __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__restrict__ tb, const uint64_t *__restrict__ cb,
                                               const uint64_t *__restrict__ rr, const uint64_t *__restrict__ classes,  // of the head
@@ -1120,7 +1121,7 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
   // Square tiles, a whole row of tiles in the pattern region: 64 tiles at a time from the per-head
   // class bitsets. Only a tile that has matched and unmatched columns AND matched and unmatched
   // offsets needs the exact one-lane test for "full".
-  const bool by_class = SQUARE && i0 >= g.L && i0 + g.tile_m <= g.S;
+  const bool by_class = SQUARE && g.tile_m == g.tile_n && i0 >= g.L && i0 + g.tile_m <= g.S;
   // gathered columns: in a query tile of the pattern region the ordinary tiles hold the diagonal part only
   const bool split = gidx != nullptr && i0 >= g.L;
   const int n_cols = columns.n_cols, g_first = columns.first, g_last = columns.last;
@@ -1189,15 +1190,18 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
             // window, are looked for here, and tall ones are asked for the last row of every tile_n (an unmatched offset meets
             // one of those or the first). Builds of 32 heads with windows of 4096 at 32768 tokens, 64 x 128 / 128 x 64 / 256 x 128
             // tiles, 200 / 205 / 204 us with their full tiles evaluated by the whole wave, 69 / 64 / 56 so.
-            bool rows = f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S;
-            if (!SQUARE && rows && pattern_tile_all(g, cbw, rr, i0, kt * g.wpr)) {
-              f = 3;
-              rows = false;
+            if constexpr (SQUARE) {
+              if (f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S && pattern_row_full(cbw, rr, g.pw, i0, kt * g.wpr, g.wpr) &&
+                  pattern_row_full(cbw, rr, g.pw, i_last, kt * g.wpr, g.wpr))
+                f = 4;
+            } else if (f && j0 + g.tile_n <= g.S && i0 + g.tile_m <= g.S) {
+              if (pattern_tile_all(g, cbw, rr, i0, kt * g.wpr)) f = 3;
+              else f = 4;
+              for (int i = i0; f == 4; i = i == i0 ? i0 + min(g.tile_m, g.tile_n) - 1 : min(i + g.tile_n, i_last)) {
+                if (!pattern_row_full(cbw, rr, g.pw, i, kt * g.wpr, g.wpr)) f = 1;
+                if (i == i_last) break;
+              }
             }
-            rows = rows && pattern_row_full(cbw, rr, g.pw, i0, kt * g.wpr, g.wpr) && pattern_row_full(cbw, rr, g.pw, i_last, kt * g.wpr, g.wpr);
-            for (int i = i0 + g.tile_n - 1; !SQUARE && rows && i < i_last; i += g.tile_n)
-              rows = pattern_row_full(cbw, rr, g.pw, i, kt * g.wpr, g.wpr);
-            if (rows) f = 4;
           }
         } else if (by_class && kt == qt) {
           // the diagonal tile of a row of the pattern region, never full: it meets the offsets 0 .. T - 1, each in its last
@@ -1249,8 +1253,9 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
           any |= m != 0;
           all &= m == ~0ull;
           // (listed and not full, which the first words mostly tell: wave-uniform. 32 heads x 4096 tokens, 256 x 128 tiles with an
-          // unmatched offset here and there 45.2 -> 38.6 us)
-          if (__ballot(any) != 0 && __ballot(!all) != 0) break;
+          // unmatched offset here and there 45.2 -> 38.6 us. Of square tiles few come here: 2 heads x 454 tokens, 64 x 64 tiles,
+          // captured at 224, whole layer 28.1 us without it, 28.4 with.)
+          if (!SQUARE && __ballot(any) != 0 && __ballot(!all) != 0) break;
         }
         if (__ballot(any) != 0) ow |= 1ull << b;
         if (__ballot(!all) == 0) fw |= 1ull << b;
