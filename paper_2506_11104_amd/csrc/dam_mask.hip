@@ -1325,7 +1325,8 @@ __device__ __forceinline__ int tile_scan_row(const Geom &g, const uint64_t *__re
 // per head: the three steps are short chains of dependent work, and as separate kernels each paid a launch):
 // the two bitsets, the tile classes, the gathered column list.
 // SOURCE says where the flags come from: they are given; the patterns are counted here, from the true mask, or from the
-// attention map itself, whose true mask is made first; or the chunks' counts are added up.
+// attention map itself, whose true mask is made first; or the chunks' counts are added up. (A kernel for each, because their LDS
+// arrays differ, up to 6.5 KiB; all hold the registers of the scan, 126 or 127.)
 enum PrepSource { kFlagsGiven, kFromTrueBits, kFromMap, kFromSlices };
 struct CountArgs {
   PrepSource source = kFlagsGiven;

@@ -840,7 +840,7 @@ struct Operands {
 
 // The kernel's arguments, read where they arrive at every item's start and end (opaque to the compiler, so that it does not keep
 // them). Held in scalar registers through the items, 54 to 102 of those were spilled to vector lanes and taken back lane by lane,
-// how many by the allocator's chance: an argument more had cost every ragged length 1 to 2 %. Now one is at most. 2 x 32 heads x 1017
+// how many by the allocator's chance: an argument more had cost every ragged length 1 to 2 %. Now none is. 2 x 32 heads x 1017
 // tokens 35.2 -> 34.6 us, 8 x 700 20.3 -> 19.5, 32 x 2048 38.5 -> 37.8, 8 x 16 x 2000 94 -> 91; 16k tokens and more as before.
 struct KernelArgs {
   AttnArgs a;
